@@ -11,10 +11,10 @@
 //      streams its rows of one 32-channel block through LDS and accumulates the
 //      32x32 moment on the FP64 MFMA, each wave every fourth group of 4 rows; partial
 //      sums go to the workspace (fixed split -> fixed summation order, no atomics).
-//   2. wush_block_kernel: one wavefront per block: reduce the partials, damp,
-//      Cholesky of both moments side by side (lanes 0..31 / 32..63), A = W'^T X',
+//   2. wush_block_kernel: one workgroup of four wavefronts per block (two for 16 x 16
+//      blocks): reduce the partials, damp, Cholesky of both moments side by side, A = W'^T X',
 //      one-sided Jacobi SVD on the columns of A (16 disjoint column pairs per
-//      round, 4 lanes per pair; V is never needed), sort, sign convention
+//      round, 16 lanes per pair; V is never needed), sort, sign convention
 //      (largest-magnitude entry of each column of U positive), then
 //      T = H diag(s^-1/2) U^T W'^T, rounded to BF16 (nearest even, straight from
 //      FP64).
@@ -36,7 +36,9 @@ __device__ __forceinline__ int mfma_f64_row(int lane, int v) { return (lane >> 4
 
 __global__ __launch_bounds__(256) void second_moment_kernel(
     const uint16_t* __restrict__ W, int64_t ldw, int N, const uint16_t* __restrict__ X, int64_t ldx, int Mc,
-    int rows_per_split_w, int rows_per_split_x, int S, int C, double* __restrict__ partial) {
+    int rows_per_split_w, int rows_per_split_x, int S, int C, double* __restrict__ partial, int* __restrict__ status) {
+  // the kernel behind this one may set the status word
+  if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x < 4) status[threadIdx.x] = 0;
   // 2 * 1024 FP64 flop per row and block against 64 bytes read: arithmetic bound, so the products run
   // on the FP64 MFMA (16 x 16 x 4: four rows of the block at a time).  With A[i][k] = x[row k][channel i]
   // and B[k][j] = x[row k][channel j] a lane feeds both operands from the element (row lane / 16,
@@ -116,35 +118,31 @@ __global__ __launch_bounds__(256) void second_moment_kernel(
   }
 }
 
-__global__ __launch_bounds__(64) void wush_block_kernel(const double* __restrict__ partial, int S, int C, int N,
-                                                        int Mc, double lambda, uint16_t* __restrict__ T_out,
-                                                        double* __restrict__ T_f64, int* __restrict__ status) {
+__global__ __launch_bounds__(256) void wush_block_kernel(const double* __restrict__ partial, int S, int C, int N,
+                                                         int Mc, double lambda, uint16_t* __restrict__ T_out,
+                                                         double* __restrict__ T_f64, int* __restrict__ status) {
   const int b = blockIdx.x;
-  // reduce the partial moments in a fixed order and normalize
-  auto moment = [&](int half, int r, int c) {
-    const double* p = partial + ((int64_t)half * S * C + b) * 1024;
-    return ordered_sum(p + r * 32 + c, (int64_t)C * 1024, S) * (1.0 / (double)(half ? Mc : N));
+  // the partial moments are added in a fixed order and normalized
+  auto load = [&](int half, int r, int c, int s) {
+    return partial[(((int64_t)half * S + s) * C + b) * 1024 + r * 32 + c];
   };
-  wush_block_wave<32>(moment, lambda, T_out + (int64_t)b * 1024, T_f64 ? T_f64 + (int64_t)b * 1024 : nullptr, nullptr,
-                      status);
+  auto finish = [&](int half, double sum) { return sum * (1.0 / (double)(half ? Mc : N)); };
+  wush_block_group<32>(load, finish, S, S, lambda, T_out + (int64_t)b * 1024, T_f64 ? T_f64 + (int64_t)b * 1024 : nullptr,
+                       nullptr, status);
 }
 
 // The same for 16 x 16 blocks (the NVFP4 variant: transform block = quantization group of 16).  The
 // moments of block b are the diagonal 16 x 16 sub-block (b & 1) of the 32-channel moments of block b / 2.
-__global__ __launch_bounds__(64) void wush_block16_kernel(const double* __restrict__ partial, int S, int C, int N,
-                                                          int Mc, double lambda, uint16_t* __restrict__ T_out,
-                                                          double* __restrict__ T_f64, int* __restrict__ status) {
+__global__ __launch_bounds__(128) void wush_block16_kernel(const double* __restrict__ partial, int S, int C, int N,
+                                                           int Mc, double lambda, uint16_t* __restrict__ T_out,
+                                                           double* __restrict__ T_f64, int* __restrict__ status) {
   const int b = blockIdx.x, b32 = b >> 1, off = 16 * (b & 1);
-  auto moment = [&](int half, int r, int c) {
-    const double* p = partial + ((int64_t)half * S * C + b32) * 1024;
-    return ordered_sum(p + (off + r) * 32 + off + c, (int64_t)C * 1024, S) * (1.0 / (double)(half ? Mc : N));
+  auto load = [&](int half, int r, int c, int s) {
+    return partial[(((int64_t)half * S + s) * C + b32) * 1024 + (off + r) * 32 + off + c];
   };
-  wush_block_wave<16>(moment, lambda, T_out + (int64_t)b * 256, T_f64 ? T_f64 + (int64_t)b * 256 : nullptr, nullptr,
-                      status);
-}
-
-__global__ void reset_bt_status_kernel(int* status) {
-  if (threadIdx.x < 4) status[threadIdx.x] = 0;
+  auto finish = [&](int half, double sum) { return sum * (1.0 / (double)(half ? Mc : N)); };
+  wush_block_group<16>(load, finish, S, S, lambda, T_out + (int64_t)b * 256, T_f64 ? T_f64 + (int64_t)b * 256 : nullptr,
+                       nullptr, status);
 }
 
 int splits_for(int64_t C) {
@@ -170,19 +168,16 @@ hipError_t launch_build_transforms(const void* W, int64_t N, int64_t ldw, const 
   const int S = splits_for(C);
   double* partial = reinterpret_cast<double*>(workspace);
   int* status = reinterpret_cast<int*>(reinterpret_cast<char*>(workspace) + build_transforms_status_offset(K));
-  reset_bt_status_kernel<<<dim3(1), dim3(64), 0, stream>>>(status);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   auto per = [&](int64_t rows) { return (int)(((rows + S - 1) / S + kRowsPerStep - 1) / kRowsPerStep * kRowsPerStep); };
   second_moment_kernel<<<dim3(C, S, 2), dim3(256), 0, stream>>>((const uint16_t*)W, ldw, (int)N, (const uint16_t*)X,
-                                                               ldx, (int)Mc, per(N), per(Mc), S, C, partial);
-  e = hipGetLastError();
+                                                               ldx, (int)Mc, per(N), per(Mc), S, C, partial, status);
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (block == 16)
-    wush_block16_kernel<<<dim3(2 * C), dim3(64), 0, stream>>>(partial, S, C, (int)N, (int)Mc, lambda, (uint16_t*)T_out,
+    wush_block16_kernel<<<dim3(2 * C), dim3(128), 0, stream>>>(partial, S, C, (int)N, (int)Mc, lambda, (uint16_t*)T_out,
                                                               T_f64, status);
   else
-    wush_block_kernel<<<dim3(C), dim3(64), 0, stream>>>(partial, S, C, (int)N, (int)Mc, lambda, (uint16_t*)T_out, T_f64,
+    wush_block_kernel<<<dim3(C), dim3(256), 0, stream>>>(partial, S, C, (int)N, (int)Mc, lambda, (uint16_t*)T_out, T_f64,
                                                         status);
   return hipGetLastError();
 }

@@ -26,8 +26,6 @@ namespace wush {
 
 namespace {
 
-constexpr double kPivotFloor = 1e-290;
-
 // ------------------------------------------------------------------ Hessian
 // H = Xc^T Xc / M, 64 x 64 output tile per workgroup (tiles on or above the
 // diagonal; the mirror image is written too).  Products of BF16 values are exact.
@@ -319,15 +317,13 @@ __global__ __launch_bounds__(256) void gptq_moment_kernel(const double* __restri
 }
 
 // Alg. 1 on (M_W of the updated block, M_X = diagonal block of H): T_i
-__global__ __launch_bounds__(64) void gptq_wush_kernel(const double* __restrict__ partial, int S, int N,
-                                                       const double* __restrict__ MX_i, double lambda,
-                                                       uint16_t* __restrict__ T_bits_i, double* __restrict__ Tb,
-                                                       int* __restrict__ status) {
-  auto moment = [&](int half, int r, int c) {
-    if (half) return MX_i[r * 32 + c];
-    return ordered_sum(partial + r * 32 + c, 1024, S) / (double)N;
-  };
-  wush_block_wave<32>(moment, lambda, T_bits_i, nullptr, Tb, status);
+__global__ __launch_bounds__(256) void gptq_wush_kernel(const double* __restrict__ partial, int S, int N,
+                                                        const double* __restrict__ MX_i, double lambda,
+                                                        uint16_t* __restrict__ T_bits_i, double* __restrict__ Tb,
+                                                        int* __restrict__ status) {
+  auto load = [&](int half, int r, int c, int s) { return half ? MX_i[r * 32 + c] : partial[s * 1024 + r * 32 + c]; };
+  auto finish = [&](int half, double sum) { return half ? sum : sum / (double)N; };
+  wush_block_group<32>(load, finish, S, 1, lambda, T_bits_i, nullptr, Tb, status);
 }
 
 // identity / fixed transforms for comparisons: T_i given, only widen it
@@ -357,7 +353,7 @@ __global__ __launch_bounds__(64) void gptq_block_mats_kernel(const double* __res
       const int oidx = __shfl_xor(idx, off, 64);
       if (omag > mag || (omag == mag && oidx < idx)) { mag = omag; idx = oidx; }
     }
-    if (!(mag > kPivotFloor)) { singular = true; break; }   // uniform across the wave
+    if (!(mag > 1e-290)) { singular = true; break; }   // uniform across the wave
     if (idx != p) {
       const double t0 = a[p][lane];
       a[p][lane] = a[idx][lane];
@@ -627,7 +623,7 @@ hipError_t launch_gptq_prep(const void* W, int64_t N, int64_t K, int64_t ldw, co
     } else {
       gptq_moment_kernel<<<kMomentSplits, 256, 0, st>>>(Wf, Ni, Ki, i, rows_per_split, partial);
       WUSH_GPTQ_CHECK()
-      gptq_wush_kernel<<<1, 64, 0, st>>>(partial, kMomentSplits, Ni, MX + (int64_t)i * 1024, lambda,
+      gptq_wush_kernel<<<1, 256, 0, st>>>(partial, kMomentSplits, Ni, MX + (int64_t)i * 1024, lambda,
                                          Tbits + (int64_t)i * 1024, Tb, status);
     }
     WUSH_GPTQ_CHECK()

@@ -1,23 +1,9 @@
-// Wave-level FP64 pieces of the transform construction shared by the RTN-case
-// and the GPTQ-case kernels: Alg. 1 on one block.
+// FP64 pieces of the offline path shared by the RTN-case and the GPTQ-case kernels: Alg. 1 on one
+// block and the inverse of one block, each by a workgroup.
 #pragma once
 #include "wush_device.hpp"
 
 namespace wush {
-
-// Sum of the S values p[0], p[stride], ..., in ascending order (a fixed summation order), with the loads
-// of eight terms in flight at a time: one at a time, each waits out a full memory latency.
-__device__ __forceinline__ double ordered_sum(const double* __restrict__ p, int64_t stride, int S) {
-  double acc = 0.0;
-  for (int s0 = 0; s0 < S; s0 += 8) {
-    double v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = s0 + u < S ? p[(int64_t)(s0 + u) * stride] : 0.0;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) acc += v[u];
-  }
-  return acc;
-}
 
 // 1 / sqrt(x) for a positive normal x: the hardware estimate and two Newton steps (relative error of a
 // few 2^-53; not correctly rounded, which the Jacobi rotations below do not need).
@@ -29,6 +15,13 @@ __device__ __forceinline__ double rsqrt_newton(double x) {
   return y;
 }
 
+// 1 / x for a positive normal x: the hardware estimate and two Newton steps (a few 2^-53).
+__device__ __forceinline__ double rcp_newton(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(y, fma(-x, y, 1.0), y);
+  return fma(y, fma(-x, y, 1.0), y);
+}
+
 // The value of x in another lane of the same row of 16, chosen by a DPP control word (no LDS round trip).
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double x) {
@@ -37,204 +30,384 @@ __device__ __forceinline__ double dpp_f64(double x) {
   const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
-// Sum of x over the LANES adjacent lanes (4 or 8, aligned) that share a column pair, the same in each of
-// them: partner lane ^ 1, then lane ^ 2 (quad permutes), then the mirrored lane of the other quad.
-template <int LANES>
-__device__ __forceinline__ double group_sum(double x) {
-  static_assert(LANES == 4 || LANES == 8, "lanes per column pair");
+// Sum / maximum of x over the 16 lanes of a DPP row, the same in each of them: partner lane ^ 1, lane ^ 2
+// (quad permutes), the mirrored lane of the other quad, the mirrored lane of the other half row.
+__device__ __forceinline__ double row_sum(double x) {
   x += dpp_f64<0xB1>(x);    // quad_perm [1, 0, 3, 2]
   x += dpp_f64<0x4E>(x);    // quad_perm [2, 3, 0, 1]
-  if (LANES == 8) x += dpp_f64<0x141>(x);   // row_half_mirror: lane i <-> 7 - i
+  x += dpp_f64<0x141>(x);   // row_half_mirror: lane i <-> 7 - i
+  x += dpp_f64<0x140>(x);   // row_mirror: lane i <-> 15 - i
   return x;
 }
+__device__ __forceinline__ double row_max(double x) {
+  x = fmax(x, dpp_f64<0xB1>(x));
+  x = fmax(x, dpp_f64<0x4E>(x));
+  x = fmax(x, dpp_f64<0x141>(x));
+  return fmax(x, dpp_f64<0x140>(x));
+}
+__device__ __forceinline__ int row_min(int x) {
+  x = min(x, __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, true));
+  x = min(x, __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, true));
+  x = min(x, __builtin_amdgcn_update_dpp(0, x, 0x141, 0xF, 0xF, true));
+  return min(x, __builtin_amdgcn_update_dpp(0, x, 0x140, 0xF, 0xF, true));
+}
+__device__ __forceinline__ double readlane_f64(double x, int lane) {
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
 
-// Alg. 1 for one D x D block (D = 32, or 16 for the NVFP4 variant), by ONE wavefront (64 lanes, all active):
+typedef double v2d __attribute__((ext_vector_type(2)));
+
+// Largest of the keys of the D lanes that hold the rows of a block (the upper lanes repeat them), uniform.
+template <int D>
+__device__ __forceinline__ uint32_t row_group_max(uint32_t x) {
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, true));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, true));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, true));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x140, 0xF, 0xF, true));
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)x, 0);
+  return D == 16 ? lo : max(lo, (uint32_t)__builtin_amdgcn_readlane((int)x, 16));
+}
+
+// A pivot below 1e-290 makes a block singular (the upper word of that FP64 number).
+constexpr uint32_t kPivotKey = 0x03B8F2B1u;
+
+// Inverse of one D x D block (D = 32 or 16) by Gauss-Jordan elimination with partial pivoting on [T | I], by a
+// group of D * D / 4 threads (256 or 64; all of the workgroup).  Thread t owns row t / (D / 4), columns
+// 8 (t % (D / 4)) ... + 7 of the 2 D, in registers.  entry(r, c): element of T; store(r, c, v): element of the
+// inverse (zeros if the block is singular; the result says whether it is regular).
+// What bounds it is the chain of D dependent steps, so a step is one barrier: every thread publishes its
+// elements (two LDS buffers in turn), and behind the barrier reads the pivot column, the pivot row and its own
+// factor.  Magnitudes are compared by their upper words (20 fraction bits: enough for a pivot).  Rows are not swapped: pos = the position the row would have after the swaps, which decides ties.
+// 32 x 32: 20 us against 91 us for one wavefront that swapped rows in LDS and synchronized per row.
+template <int D, class EntryFn, class StoreFn>
+__device__ __forceinline__ bool invert_block_group(EntryFn entry, StoreFn store) {
+  static_assert(D == 32 || D == 16, "block size");
+  constexpr int kTpr = D / 4;                      // threads per row
+  __shared__ __attribute__((aligned(16))) double buf[2][D][2 * D + 2];
+  const int t = threadIdx.x, r = t / kTpr, c0 = 8 * (t % kTpr);
+  const int lane = t & 63, row = lane % D;         // the row whose pivot candidate this lane looks at
+  double a[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] = c0 < D ? entry(r, c0 + i) : (c0 - D + i == r ? 1.0 : 0.0);
+  int pos = row;
+  bool singular = false;
+  for (int p = 0; p < D; ++p) {
+    double (*b)[2 * D + 2] = buf[p & 1];
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) *reinterpret_cast<v2d*>(&b[r][c0 + i]) = (v2d){a[i], a[i + 1]};
+    __syncthreads();
+    const uint32_t key = pos >= p ? (uint32_t)((uint64_t)__double_as_longlong(b[row][p]) >> 32) & 0x7FFFFFFFu : 0u;
+    const uint32_t best = row_group_max<D>(key);
+    if (best < kPivotKey || best >= 0x7FF00000u) { singular = true; break; }   // the same in every wave
+    uint64_t ties = __ballot(key == best) & ((1ull << D) - 1);
+    int idx = __builtin_ctzll(ties);
+    int ipos = __builtin_amdgcn_readlane(pos, idx);
+    for (ties &= ties - 1; ties; ties &= ties - 1) {         // equal keys: the row first in position
+      const int k = __builtin_ctzll(ties), kpos = __builtin_amdgcn_readlane(pos, k);
+      if (kpos < ipos) { ipos = kpos; idx = k; }
+    }
+    if (row == idx) pos = p;
+    else if (pos == p) pos = ipos;
+    const double inv_piv = rcp_newton(b[idx][p]);
+    const double f = b[r][p];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const double prow = b[idx][c0 + i] * inv_piv;
+      a[i] = r == idx ? prow : a[i] - f * prow;
+    }
+  }
+  const int rpos = singular ? r : __shfl(pos, r, 64);
+  if (c0 >= D) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) store(rpos, c0 - D + i, singular ? 0.0 : a[i]);
+  }
+  return !singular;
+}
+
+// Alg. 1 for one D x D block (D = 32, or 16 for the NVFP4 variant), by a workgroup of 8 D threads:
 //   W' W'^T = M_W + lambda d^-1 tr(M_W) I,  X' X'^T likewise  (Cholesky, side by side)
 //   U S V^T = W'^T X'  (one-sided Jacobi on the columns; V never needed)
 //   T = H S^(-1/2) U^T W'^T, singular values descending, the entry of largest
 //   magnitude of every column of U positive.
-// moment(h, r, c): entry (r, c) of the normalized, undamped second moment, h = 0
-// for M_W, 1 for M_X.  T goes out as BF16 bits (T_bits) and, where the pointers
-// are non-null, as FP64 before rounding (T_f64) and as the FP64 value of the
-// rounded matrix (T_rounded), each [D][D] row-major.  A moment that is not
-// positive definite sets *status.
-template <int D, class MomentFn>
-__device__ __forceinline__ void wush_block_wave(MomentFn moment, double lambda, uint16_t* __restrict__ T_bits,
-                                                double* __restrict__ T_f64, double* __restrict__ T_rounded,
-                                                int* __restrict__ status) {
+// load(h, r, c, s): partial sum s (of S_W for h = 0, S_X for h = 1) of entry (r, c) of the second moment,
+// finish(h, sum): the normalized, undamped entry, h = 0 for M_W, 1 for M_X.  T goes out as BF16 bits
+// (T_bits) and, where the pointers are non-null, as FP64 before rounding (T_f64) and as the FP64 value of
+// the rounded matrix (T_rounded), each [D][D] row-major.  A moment that is not positive definite sets *status.
+//
+// A block is one chain of dependent steps (2 x D columns of the factors, 6 to 8 sweeps of D - 1 Jacobi
+// rounds), so what counts is the latency of a step, and the threads are there to shorten it: a column pair is
+// shared by the 16 lanes of a DPP row (two LDS loads and stores per lane, the three dot products summed by
+// four DPP steps), the factors are taken column by column out of registers with one barrier per column, and the
+// products are spread over the whole workgroup.  c2 layer (128 blocks): 201 -> 107 us; a Jacobi round is 850 cycles, of
+// which some 30 dependent FP64 operations and the LDS round trip are nearly all.
+template <int D, class LoadFn, class FinishFn>
+__device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, int S_W, int S_X, double lambda,
+                                                 uint16_t* __restrict__ T_bits, double* __restrict__ T_f64,
+                                                 double* __restrict__ T_rounded, int* __restrict__ status) {
   static_assert(D == 32 || D == 16, "block size");
-  constexpr int kPairs = D / 2;          // disjoint column pairs per Jacobi round
-  constexpr int kLpp = 64 / kPairs;      // lanes per pair
-  constexpr int kRpl = D / kLpp;         // rows of a column pair per lane
-  __shared__ double LW[D][D + 1];   // M_W, then W' (lower triangle)
-  __shared__ double LX[D][D + 1];   // M_X, then X'
-  __shared__ double A[D][D + 1];    // W'^T X', then U S (columns), then B
-  __shared__ double U[D][D + 1];
-  __shared__ double sv[D];
+  constexpr int NT = 8 * D;
+  constexpr int kRpl = D / 16;           // rows of a column pair per lane
+  constexpr int kOut = D * D / NT;       // entries of a D x D product per thread
+  __shared__ double LW[D][D + 1];        // M_W, then W' (lower triangle)
+  __shared__ double LX[D][D + 1];        // M_X, then X'
+  __shared__ __attribute__((aligned(16))) double A[D][D + 2];   // columns of W'^T X', then of U S: A[column][row]
+  __shared__ double U[D][D + 1];         // sorted, sign-normalized: U[row][column]; then B
+  __shared__ double colb[2][2][D];       // the factors' current column, two buffers in turn
+  __shared__ double norm2[D], sv[D], ssort[D];
   __shared__ int order[D];
-  __shared__ int conv;
-  const int lane = threadIdx.x & 63;
-  // lanes 0..D-1 own the rows of M_W, the next D those of M_X; with D = 16 the upper 32 lanes
-  // repeat the lower ones (same values to the same addresses)
-  const int half = (lane / D) & 1, r = lane % D;
-  double (*L)[D + 1] = half ? LX : LW;
+  __shared__ int again[2];
+  const int t = threadIdx.x;
   {
-    // consecutive lanes fetch consecutive entries of a row (the moments come from global memory),
-    // four entries per lane at a time so that their loads overlap
-    constexpr int kPerLane = 2 * D * D / 64;
-#pragma unroll 1
-    for (int i0 = 0; i0 < kPerLane; i0 += 4) {
-      double v[4];
+    // consecutive threads fetch consecutive entries of a row; all of a thread's entries and four of their
+    // partial sums are in flight at a time, added in ascending order
+    constexpr int kPer = 2 * D * D / NT;
+    double acc[kPer];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int e = lane + 64 * (i0 + u);
-        v[u] = moment(e / (D * D), (e % (D * D)) / D, e % D);
+    for (int i = 0; i < kPer; ++i) acc[i] = 0.0;
+    const int smax = max(S_W, S_X);
+    for (int s0 = 0; s0 < smax; s0 += 4) {
+      double v[kPer][4];
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        const int e = t + NT * i, h = e / (D * D);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          v[i][u] = s0 + u < (h ? S_X : S_W) ? load(h, (e % (D * D)) / D, e % D, s0 + u) : 0.0;
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int e = lane + 64 * (i0 + u);
-        (e / (D * D) ? LX : LW)[(e % (D * D)) / D][e % D] = v[u];
-      }
+      for (int i = 0; i < kPer; ++i)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc[i] += v[i][u];
     }
-    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int e = t + NT * i, h = e / (D * D);
+      (h ? LX : LW)[(e % (D * D)) / D][e % D] = finish(h, acc[i]);
+    }
+  }
+  if (t < 2) again[t] = 0;
+  __syncthreads();
+  // ---- damping and Cholesky (lower): the first half of the threads works on M_W, the second on M_X.
+  // Thread q of a half owns row q / 4, columns kCpt (q % 4) ... of its matrix in registers.  Step j publishes
+  // column j of what is left; with d its diagonal entry, entry (r, c) loses col[r] col[c] / d, and column j of
+  // the factor is col / sqrt(d), formed at the end by the threads that published it.
+  {
+    constexpr int kCpt = D / 4;
+    const int h = t / (NT / 2), q = t % (NT / 2), r = q / 4, c0 = kCpt * (q % 4);
+    double (*L)[D + 1] = h ? LX : LW;
     double tr = 0.0;
     for (int c = 0; c < D; ++c) tr += L[c][c];
-    const double damped = L[r][r] + lambda * tr / (double)D;
-    __syncthreads();
-    L[r][r] = damped;
-    __syncthreads();
-  }
-  // ---- Cholesky (lower), both matrices at once: lane r owns row r of its matrix
-  bool bad = false;
-  for (int j = 0; j < D; ++j) {
-    double d = L[j][j];
-#pragma unroll 4
-    for (int k = 0; k < j; ++k) d -= L[j][k] * L[j][k];
-    if (!(d > 0.0)) { bad = true; d = 1.0; }
-    const double dj = sqrt(d);
-    double v = 0.0;
-    if (r > j) {
-      v = L[r][j];
-#pragma unroll 4
-      for (int k = 0; k < j; ++k) v -= L[r][k] * L[j][k];
-      v /= dj;
+    const double add = lambda * tr / (double)D;
+    double a[kCpt], raw[kCpt], diag[kCpt];             // column c0 + i as published, and its d
+#pragma unroll
+    for (int i = 0; i < kCpt; ++i) {
+      a[i] = L[r][c0 + i] + (c0 + i == r ? add : 0.0);
+      raw[i] = 0.0;
+      diag[i] = 1.0;
+    }
+    bool bad = false;
+    for (int jb = 0; jb < 4; ++jb) {
+#pragma unroll
+      for (int ji = 0; ji < kCpt; ++ji) {
+        const int j = kCpt * jb + ji;
+        double* col = colb[ji & 1][h];
+        if ((q & 3) == jb) col[r] = a[ji];
+        __syncthreads();
+        double d = col[j];
+        if (!(d > 0.0)) { bad = true; d = 1.0; }
+        const double f = col[r] * rcp_newton(d);
+        if ((q & 3) == jb) {
+          raw[ji] = a[ji];
+          diag[ji] = d;
+        }
+#pragma unroll
+        for (int i = 0; i < kCpt; ++i) a[i] = fma(-f, col[c0 + i], a[i]);
+      }
     }
     __syncthreads();
-    if (r == j) L[j][j] = dj;
-    else if (r > j) L[r][j] = v;
-    else L[r][j] = 0.0;                                // zero the upper triangle
-    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kCpt; ++i) {
+      const double root = sqrt(diag[i]);
+      L[r][c0 + i] = r > c0 + i ? raw[i] / root : (r == c0 + i ? root : 0.0);
+    }
+    if (__any(bad) && (t & 63) == 0) atomicExch(status, 1);
   }
-  if (__any(bad)) {
-    if (lane == 0) atomicExch(status, 1);
-  }
-  // ---- A = W'^T X':  A[i][j] = sum_k W'[k][i] X'[k][j]   (16 outputs per lane)
-  for (int o = lane; o < D * D; o += 64) {
-    const int i = o / D, j = o % D;
-    double acc = 0.0;
+  __syncthreads();
+  // ---- A = W'^T X':  A[i][j] = sum_k W'[k][i] X'[k][j], stored by columns
+  {
+    double acc[kOut];
+#pragma unroll
+    for (int u = 0; u < kOut; ++u) acc[u] = 0.0;
 #pragma unroll 4
-    for (int k = max(i, j); k < D; ++k) acc = fma(LW[k][i], LX[k][j], acc);
-    A[i][j] = acc;
+    for (int k = 0; k < D; ++k) {
+#pragma unroll
+      for (int u = 0; u < kOut; ++u) {
+        const int o = t + NT * u;
+        acc[u] = fma(LW[k][o % D], LX[k][o / D], acc[u]);   // zeros above the diagonals
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kOut; ++u) A[(t + NT * u) / D][(t + NT * u) % D] = acc[u];
   }
   __syncthreads();
   // ---- one-sided Jacobi on the columns of A (right rotations): A V = U S
-  const int pr = lane / kLpp, sub = lane % kLpp;       // pair slot, kRpl rows per lane
+  const int pr = t / 16, sub = t % 16;                 // pair slot; rows kRpl sub ... of its two columns
   for (int sweep = 0; sweep < 40; ++sweep) {
-    if (lane == 0) conv = 1;
+    // squared norms of the columns: computed once a sweep, updated by the rotations in between (they only
+    // decide angles, so the updates' cancellation costs no accuracy of U)
+    for (int c = pr; c < D; c += NT / 16) {
+      double n2 = 0.0;
+#pragma unroll
+      for (int i = 0; i < kRpl; ++i) n2 = fma(A[c][kRpl * sub + i], A[c][kRpl * sub + i], n2);
+      n2 = row_sum(n2);
+      if (sub == 0) norm2[c] = n2;
+    }
     __syncthreads();
+    bool large = false;
+    // circle method: position 0 fixed, the other D - 1 rotate
+    int p = pr, q = D - 1 - pr;
     for (int rnd = 0; rnd < D - 1; ++rnd) {
-      // circle method: position 0 fixed, the other D - 1 rotate
-      const int pos_p = pr, pos_q = D - 1 - pr;
-      const int p = pos_p == 0 ? 0 : 1 + (pos_p - 1 + rnd) % (D - 1);
-      const int q = 1 + (pos_q - 1 + rnd) % (D - 1);
-      double al = 0.0, be = 0.0, ga = 0.0;
+      double *cp = &A[p][kRpl * sub], *cq = &A[q][kRpl * sub];
       double ap[kRpl], aq[kRpl];
+      if constexpr (kRpl == 2) {
+        const v2d vp = *reinterpret_cast<const v2d*>(cp), vq = *reinterpret_cast<const v2d*>(cq);
+        ap[0] = vp[0]; ap[1] = vp[1]; aq[0] = vq[0]; aq[1] = vq[1];
+      } else {
+        ap[0] = *cp; aq[0] = *cq;
+      }
+      const double al = norm2[p], be = norm2[q];
+      double ga = ap[0] * aq[0];
+#pragma unroll
+      for (int i = 1; i < kRpl; ++i) ga = fma(ap[i], aq[i], ga);
+      ga = row_sum(ga);
+      const double ab = al * be, gg = ga * ga;
+      large |= gg > 1e-20 * ab;
+      // The rotation by the angle of smaller magnitude that makes the two columns orthogonal:
+      // tan(2 theta) = 2 ga / (be - al), |theta| <= pi / 4.  With h = hypot(be - al, 2 ga):
+      // cos^2 = (1 + |be - al| / h) / 2 and tan = (|ga| / h) / cos^2.  The tangent only has to be about
+      // right (the hardware's estimates, some 2^-24: the next sweep sees what is left); that cos and sin form a
+      // rotation to FP64 accuracy is the last reciprocal square root's business, refined by a cubic step.
+      const double dd = be - al;
+      const double ih = __builtin_amdgcn_rsq(fma(dd, dd, 4.0 * gg));
+      const double c2 = fma(0.5 * fabs(dd), ih, 0.5);
+      double tn = fabs(ga) * ih * __builtin_amdgcn_rcp(c2);
+      tn = dd == 0.0 || (dd > 0.0) == (ga > 0.0) ? tn : -tn;
+      tn = gg > 1e-30 * ab ? tn : 0.0;                 // |ga| <= 1e-15 sqrt(al be): left alone
+      const double x = fma(tn, tn, 1.0);
+      const double y = __builtin_amdgcn_rsq(x);
+      const double e = fma(-x * y, y, 1.0);
+      const double cs = fma(y * e, fma(e, 0.375, 0.5), y);
+      const double sn = tn * cs;
 #pragma unroll
       for (int i = 0; i < kRpl; ++i) {
-        ap[i] = A[kRpl * sub + i][p];
-        aq[i] = A[kRpl * sub + i][q];
-        al = fma(ap[i], ap[i], al);
-        be = fma(aq[i], aq[i], be);
-        ga = fma(ap[i], aq[i], ga);
+        const double np = fma(-sn, aq[i], cs * ap[i]);
+        aq[i] = fma(sn, ap[i], cs * aq[i]);
+        ap[i] = np;
       }
-      al = group_sum<kLpp>(al);
-      be = group_sum<kLpp>(be);
-      ga = group_sum<kLpp>(ga);
-      if (ga * ga > 1e-30 * (al * be)) {             // |ga| > 1e-15 sqrt(al be)
-        // The rotation by the angle of smaller magnitude that makes the two columns orthogonal:
-        // tan(2 theta) = 2 ga / (be - al), |theta| <= pi / 4.  From cos(2 theta) = |be - al| / h and
-        // sin(2 theta) = |2 ga| / h, h = hypot(be - al, 2 ga):  c^2 = (1 + cos 2 theta) / 2,
-        // |s| = sin 2 theta / (2 c) -- two reciprocal square roots, no division, no cancellation.
-        const double dd = be - al, g2 = 2.0 * ga;
-        const double ih = rsqrt_newton(fma(dd, dd, g2 * g2));
-        const double c2 = fma(0.5 * fabs(dd), ih, 0.5);
-        const double ic = rsqrt_newton(c2);
-        const double c = c2 * ic;
-        const bool pos = dd == 0.0 || (dd > 0.0) == (g2 > 0.0);
-        const double sa = 0.5 * fabs(g2) * ih * ic;
-        const double s = pos ? sa : -sa;
-#pragma unroll
-        for (int i = 0; i < kRpl; ++i) {
-          A[kRpl * sub + i][p] = c * ap[i] - s * aq[i];
-          A[kRpl * sub + i][q] = s * ap[i] + c * aq[i];
-        }
-        conv = 0;
+      if constexpr (kRpl == 2) {
+        *reinterpret_cast<v2d*>(cp) = (v2d){ap[0], ap[1]};
+        *reinterpret_cast<v2d*>(cq) = (v2d){aq[0], aq[1]};
+      } else {
+        *cp = ap[0]; *cq = aq[0];
       }
+      if (sub == 0) {
+        norm2[p] = fma(-tn, ga, al);
+        norm2[q] = fma(tn, ga, be);
+      }
+      p = pr == 0 ? 0 : (p == D - 1 ? 1 : p + 1);
+      q = q == D - 1 ? 1 : q + 1;
       __syncthreads();
     }
-    if (conv) break;
+    // A sweep whose rotations all met cosines below 1e-10 leaves cosines of that squared over the relative
+    // gap of the singular values (quadratic convergence): below FP64's resolution, no further sweep is needed.
+    if (large) again[sweep & 1] = 1;
     __syncthreads();
+    const int more = again[sweep & 1];
+    if (t == 0) again[(sweep + 1) & 1] = 0;            // read last a sweep ago, set next a sweep from now
+    if (!more) break;
   }
-  // ---- singular values, descending order, U with the sign convention
-  if (lane < D) {
+  // ---- singular values, descending order, U with the sign convention (16 lanes per column)
+  for (int c = pr; c < D; c += NT / 16) {
     double n2 = 0.0;
-    for (int i = 0; i < D; ++i) n2 = fma(A[i][lane], A[i][lane], n2);
-    sv[lane] = sqrt(n2);
+#pragma unroll
+    for (int i = 0; i < kRpl; ++i) n2 = fma(A[c][kRpl * sub + i], A[c][kRpl * sub + i], n2);
+    n2 = row_sum(n2);
+    if (sub == 0) sv[c] = sqrt(n2);
   }
   __syncthreads();
-  if (lane < D) {
+  if (t < D) {
+    const double mine = sv[t];
     int rank = 0;
-    for (int k = 0; k < D; ++k) rank += (sv[k] > sv[lane]) || (sv[k] == sv[lane] && k < lane);
-    order[rank] = lane;
+    for (int k = 0; k < D; ++k) rank += (sv[k] > mine) || (sv[k] == mine && k < t);
+    order[rank] = t;
+    ssort[rank] = mine;
   }
   __syncthreads();
-  double s_mine = 0.0;
-  if (lane < D) {
-    const int src = order[lane];
-    s_mine = sv[src];
-    double best = -1.0, bestv = 1.0;
-    for (int i = 0; i < D; ++i) {
-      const double v = A[i][src] / s_mine;
-      U[i][lane] = v;
-      if (fabs(v) > best) { best = fabs(v); bestv = v; }
+  for (int c = pr; c < D; c += NT / 16) {
+    const int src = order[c];
+    const double s = ssort[c];
+    double v[kRpl], best = 0.0;
+#pragma unroll
+    for (int i = 0; i < kRpl; ++i) {
+      v[i] = A[src][kRpl * sub + i] / s;
+      best = fmax(best, fabs(v[i]));
     }
-    if (bestv < 0.0)
-      for (int i = 0; i < D; ++i) U[i][lane] = -U[i][lane];
+    best = row_max(best);
+    int first = 1 << 20;                               // 2 row + sign bit of the first row of largest magnitude
+#pragma unroll
+    for (int i = kRpl - 1; i >= 0; --i)
+      if (fabs(v[i]) == best) first = 2 * (kRpl * sub + i) + (v[i] < 0.0);
+    first = row_min(first);
+#pragma unroll
+    for (int i = 0; i < kRpl; ++i) U[kRpl * sub + i][c] = (first & 1) ? -v[i] : v[i];
   }
-  __syncthreads();
-  if (lane < D) sv[lane] = s_mine;
   __syncthreads();
   // ---- B = diag(s^-1/2) U^T W'^T :  B[i][k] = s_i^-1/2 sum_m U[m][i] W'[k][m]
-  for (int o = lane; o < D * D; o += 64) {
-    const int i = o / D, k = o % D;
-    double acc = 0.0;
-    for (int m = 0; m <= k; ++m) acc = fma(U[m][i], LW[k][m], acc);
-    A[i][k] = acc / sqrt(sv[i]);
+  {
+    double acc[kOut];
+#pragma unroll
+    for (int u = 0; u < kOut; ++u) acc[u] = 0.0;
+#pragma unroll 4
+    for (int m = 0; m < D; ++m) {                      // W' is zero past its diagonal
+#pragma unroll
+      for (int u = 0; u < kOut; ++u) {
+        const int o = t + NT * u;
+        acc[u] = fma(U[m][o / D], LW[o % D][m], acc[u]);
+      }
+    }
+    // A's columns are read no more: B[i][k] goes to A[i][k]
+#pragma unroll
+    for (int u = 0; u < kOut; ++u) {
+      const int o = t + NT * u;
+      A[o / D][o % D] = acc[u] / sqrt(ssort[o / D]);
+    }
   }
   __syncthreads();
   // ---- T = H B with the normalized Sylvester matrix H[j][i] = (-1)^popcount(j & i) / sqrt(D)
   const double hn = 1.0 / sqrt((double)D);
-  for (int o = lane; o < D * D; o += 64) {
-    const int j = o / D, k = o % D;
-    double acc = 0.0;
-    for (int i = 0; i < D; ++i) acc += (__popc(j & i) & 1) ? -A[i][k] : A[i][k];
-    acc *= hn;
-    const uint16_t bits = f64_to_bf16_bits(acc);
+  double acc[kOut];
+#pragma unroll
+  for (int u = 0; u < kOut; ++u) acc[u] = 0.0;
+#pragma unroll 4
+  for (int i = 0; i < D; ++i) {
+#pragma unroll
+    for (int u = 0; u < kOut; ++u) {
+      const int o = t + NT * u;
+      const double b = A[i][o % D];
+      acc[u] += (__popc((o / D) & i) & 1) ? -b : b;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kOut; ++u) {
+    const int o = t + NT * u;
+    const double v = acc[u] * hn;
+    const uint16_t bits = f64_to_bf16_bits(v);
     T_bits[o] = bits;
-    if (T_f64) T_f64[o] = acc;
+    if (T_f64) T_f64[o] = v;
     if (T_rounded) T_rounded[o] = (double)bf16_bits_to_f32(bits);
   }
 }
 
 }  // namespace wush
-
