@@ -20,6 +20,8 @@
 // traffic, and the accumulator layout then gives every lane exactly one group of 16).
 #include "nvfp4_layout.hpp"
 #include "transform_quant_core.hpp"
+#include "weight_mfma.hpp"
+#include "wush_block.hpp"
 #include "wush_kernels.hpp"
 
 namespace wush {
@@ -309,144 +311,128 @@ __global__ __launch_bounds__(256) void nvfp4_quantize_f32_kernel(const float* __
 // ---------------------------------------------------------------------------
 // Weight side
 // ---------------------------------------------------------------------------
-constexpr double kPivotFloor = 1e-290;
-
-// One wavefront per 16 x 16 block: FP64 Gauss-Jordan with partial pivoting on
-// [T | I] (16 x 32) in LDS; lanes 0..31 each own one column.
+// inv(T_b) of every 16 x 16 block, one wavefront each; also clears the AbsMax and status words, which the
+// kernel behind this one raises and sets.
 __global__ __launch_bounds__(64) void invert16_kernel(const uint16_t* __restrict__ T16, double* __restrict__ Tinv,
+                                                      unsigned long long* __restrict__ amax_bits,
                                                       int* __restrict__ status) {
-  __shared__ double a[16][33];
   const int b = blockIdx.x;
-  const int lane = threadIdx.x;
-  const int col = lane & 31;
-  for (int r = 0; r < 16; ++r) {
-    double v;
-    if (col < 16) v = (double)bf16_bits_to_f32(T16[((int64_t)b * 16 + r) * 16 + col]);
-    else v = (col - 16 == r) ? 1.0 : 0.0;
-    if (lane < 32) a[r][col] = v;
+  if (b == 0 && threadIdx.x == 0) { *amax_bits = 0ull; *status = 0; }
+  auto entry = [&](int r, int c) { return (double)bf16_bits_to_f32(T16[((int64_t)b * 16 + r) * 16 + c]); };
+  auto store = [&](int r, int c, double v) { Tinv[((int64_t)b * 16 + r) * 16 + c] = v; };
+  invert_block_group<16>(entry, store);
+}
+
+// The products W_blk inv(T_b) of both passes run on the FP64 MFMA (weight_mfma.hpp): a wavefront keeps the inverses
+// of two adjacent blocks (32 channels) in registers and walks tiles of 16 rows.
+struct RowWalk {
+  wm::Block16x2 inv;
+  v2u raw[2];
+  const uint16_t* base;
+  int64_t ldw;
+  int tiles, N, l16;
+  __device__ __forceinline__ RowWalk(const uint16_t* W, int64_t ldw_, const double* Tinv, int b32, int N_, int lane)
+      : base(W + 32 * b32 + 4 * (lane >> 4)), ldw(ldw_), tiles((N_ + 15) / 16), N(N_), l16(lane & 15) {
+    wm::load_block16x2(inv, Tinv + (int64_t)b32 * 512, lane);
+    fetch(blockIdx.x);
   }
+  __device__ __forceinline__ void fetch(int t) {
+    const uint16_t* p = base + (int64_t)min(16 * t + l16, N - 1) * ldw;
+    raw[0] = *reinterpret_cast<const v2u*>(p);
+    raw[1] = *reinterpret_cast<const v2u*>(p + 16);
+  }
+  // transformed channels of tile t: y[a][v] = channel 4 (lane / 16) + v of block a, row l16; fetches the next tile
+  __device__ __forceinline__ void tile(int t, double (&y)[2][4]) {
+    const v2u cur[2] = {raw[0], raw[1]};
+    fetch(min(t + (int)gridDim.x, tiles - 1));
+    wm::multiply16x2(inv, cur, y);
+  }
+};
+
+// Pass 1: AbsMax of the transformed weights (positive doubles order like their bit patterns; rows past N repeat
+// row N - 1).  A workgroup ends in one atomic on the one word, about 10 ns each: with a workgroup per 256 rows and
+// block they were the whole pass (8192 -> 28672: 695 us, now 198).
+__global__ __launch_bounds__(256) void nvfp4_weight_absmax_kernel(const uint16_t* __restrict__ W, int64_t ldw,
+                                                                  const double* __restrict__ Tinv,
+                                                                  unsigned long long* __restrict__ amax_bits,
+                                                                  int* __restrict__ status, int N, int C32) {
+  __shared__ double wave_max[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int b = 4 * blockIdx.y + wave;
+  double amax = 0.0;
+  if (b < C32) {   // wave-uniform
+    const double* ti = Tinv + (int64_t)b * 512;
+    // row 0 of a block's inverse is zero only if the block was singular (the lower half looks at the first block)
+    const uint64_t nonzero = __ballot(ti[256 * (lane >> 5) + (lane & 15)] != 0.0);
+    if (blockIdx.x == 0 && lane == 0 && (!(uint32_t)nonzero || !(uint32_t)(nonzero >> 32))) atomicExch(status, 1);
+    RowWalk walk(W, ldw, Tinv, b, N, lane);
+    for (int t = blockIdx.x; t < walk.tiles; t += gridDim.x) {
+      double y[2][4];
+      walk.tile(t, y);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) amax = fmax(amax, fmax(fabs(y[0][v]), fabs(y[1][v])));
+    }
+  }
+  amax = row_max(amax);
+  amax = fmax(fmax(readlane_f64(amax, 0), readlane_f64(amax, 16)), fmax(readlane_f64(amax, 32), readlane_f64(amax, 48)));
+  if (lane == 0) wave_max[wave] = amax;
   __syncthreads();
-  bool singular = false;
-  for (int p = 0; p < 16; ++p) {
-    const int r = lane & 15;
-    double mag = (r >= p) ? fabs(a[r][p]) : -1.0;
-    int idx = r;
-    for (int off = 8; off >= 1; off >>= 1) {
-      const double omag = __shfl_xor(mag, off, 64);
-      const int oidx = __shfl_xor(idx, off, 64);
-      if (omag > mag || (omag == mag && oidx < idx)) { mag = omag; idx = oidx; }
-    }
-    if (!(mag > kPivotFloor)) { singular = true; break; }  // uniform across the wave
-    if (idx != p && lane < 32) {
-      const double t0 = a[p][col];
-      a[p][col] = a[idx][col];
-      a[idx][col] = t0;
-    }
-    __syncthreads();
-    const double inv_piv = 1.0 / a[p][p];
-    __syncthreads();
-    const double prow = a[p][col] * inv_piv;
-    if (lane < 32) a[p][col] = prow;
-    __syncthreads();
-    for (int rr = 0; rr < 16; ++rr) {
-      if (rr == p) continue;
-      const double f = a[rr][p];
-      __syncthreads();
-      if (lane < 32) a[rr][col] -= f * prow;
-    }
-    __syncthreads();
-  }
-  if (singular) {
-    if (lane == 0) atomicExch(status, 1);
-    for (int r = 0; r < 16; ++r)
-      if (lane < 16) Tinv[((int64_t)b * 16 + r) * 16 + lane] = 0.0;
-    return;
-  }
-  for (int r = 0; r < 16; ++r)
-    if (lane >= 16 && lane < 32) Tinv[((int64_t)b * 16 + r) * 16 + (lane - 16)] = a[r][lane];
-}
-
-__global__ void reset_words_kernel(unsigned long long* amax_bits, int* status) {
-  if (threadIdx.x == 0) { *amax_bits = 0ull; *status = 0; }
-}
-
-// y[j] = sum_k W[n, 16b+k] inv(T_b)[k][j] in FP64 (k ascending, fused multiply-add).
-__device__ __forceinline__ void apply_block16(const uint16_t* __restrict__ wp, const double (*ti)[16], double (&y)[16]) {
-  double w[16];
-#pragma unroll
-  for (int k = 0; k < 16; k += 8) {
-    const v4u raw = *reinterpret_cast<const v4u*>(wp + k);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      w[k + 2 * i] = (double)__uint_as_float(raw[i] << 16);
-      w[k + 2 * i + 1] = (double)__uint_as_float(raw[i] & 0xFFFF0000u);
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    double acc = 0.0;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) acc = fma(w[k], ti[k][j], acc);
-    y[j] = acc;
+  if (threadIdx.x == 0) {
+    amax = fmax(fmax(wave_max[0], wave_max[1]), fmax(wave_max[2], wave_max[3]));
+    atomicMax(amax_bits, (unsigned long long)__double_as_longlong(amax));
   }
 }
 
-// Pass 1 (QUANT = false): AbsMax of the transformed weights (positive doubles
-// order like their bit patterns).  Pass 2 (QUANT = true): quantize with the
-// tensor scale derived from it.  grid = (rows / 256, K / 16).
-template <bool QUANT>
+// Pass 2: quantize with the tensor scale derived from it (8192 -> 28672: 369 us with one thread per row and block, now
+// 331).
 __global__ __launch_bounds__(256) void nvfp4_weight_kernel(const uint16_t* __restrict__ W, int64_t ldw,
                                                            const double* __restrict__ Tinv,
-                                                           unsigned long long* __restrict__ amax_bits,
+                                                           const unsigned long long* __restrict__ amax_bits,
                                                            uint8_t* __restrict__ Wq, uint8_t* __restrict__ Ws,
                                                            float* __restrict__ ts_out, int N, int K, int tiled) {
-  __shared__ double ti[16][16];
-  __shared__ unsigned long long wg_max;
-  const int b = blockIdx.y;
-  if (threadIdx.x < 256) ti[threadIdx.x >> 4][threadIdx.x & 15] = Tinv[(int64_t)b * 256 + threadIdx.x];
-  if (threadIdx.x == 0) wg_max = 0ull;
-  __syncthreads();
-  const int n = blockIdx.x * 256 + threadIdx.x;
-  double y[16];
-  double amax = 0.0;
-  if (n < N) {
-    apply_block16(W + (int64_t)n * ldw + 16 * b, ti, y);
-#pragma unroll
-    for (int j = 0; j < 16; ++j) amax = fmax(amax, fabs(y[j]));
-  }
-  if (!QUANT) {
-    atomicMax(&wg_max, (unsigned long long)__double_as_longlong(amax));
-    __syncthreads();
-    if (threadIdx.x == 0) atomicMax(amax_bits, wg_max);
-    return;
-  }
+  const int lane = threadIdx.x & 63, C32 = K >> 5;
+  const int b = 4 * blockIdx.y + (threadIdx.x >> 6);
   const float tsf = (float)(__longlong_as_double((long long)*amax_bits) / 2688.0);  // AbsMax / (6 * 448)
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *ts_out = tsf;
-  if (n >= N) return;
+  if (b >= C32) return;   // wave-uniform
   const double ts = (double)tsf;
   const double c = ts == 0.0 ? 0.0 : 1.0 / (6.0 * ts);
-  int byte;
-  const double d = round_e4m3_f64(amax * c, byte) * ts;
-  const double rcp = byte == 0 ? 0.0 : 1.0 / d;
-  uint32_t words[2];
+  RowWalk walk(W, ldw, Tinv, b, N, lane);
+  for (int t = blockIdx.x; t < walk.tiles; t += gridDim.x) {
+    double y2[2][4], y[8];
+    walk.tile(t, y2);
+    // an even row of 16 lanes takes 8 consecutive channels of block 0 (its own four and the odd row's), an odd one
+    // those of block 1; lane ^ 32 has the block's other 8
 #pragma unroll
-  for (int g = 0; g < 2; ++g) {
-    uint32_t wd = 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const double v = y[8 * g + i];
-      const uint32_t sign = (uint32_t)(((uint64_t)__double_as_longlong(v)) >> 63);
-      wd |= ((sign << 3) | e2m1_code_f64(fabs(v * rcp))) << (4 * i);
+    for (int v = 0; v < 4; ++v) {
+      const wm::PairF64 p = wm::pair16(y2[0][v], y2[1][v]);
+      y[v] = p.first;
+      y[4 + v] = p.second;
     }
-    words[g] = wd;
-  }
-  if (tiled) {
-    const int kt = b >> 2, gi = b & 3, KT = K >> 6;
-    *reinterpret_cast<v2u*>(Wq + nv_tiled_chunk_offset(n, kt, gi >> 1, KT) + 8 * (gi & 1)) = (v2u){words[0], words[1]};
-    Ws[nv_tiled_scale_offset(n, kt, KT) + gi] = (uint8_t)byte;
-  } else {
-    *reinterpret_cast<v2u*>(Wq + (int64_t)n * (K / 2) + 8 * b) = (v2u){words[0], words[1]};
-    Ws[(int64_t)n * (K / 16) + b] = (uint8_t)byte;
+    double amax = 0.0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) amax = fmax(amax, fabs(y[i]));
+    const wm::PairF64 m = wm::pair32(amax);
+    int byte;
+    const double d = round_e4m3_f64(fmax(m.first, m.second) * c, byte) * ts;
+    const double rcp = byte == 0 ? 0.0 : 1.0 / d;
+    // v rcp is at most about 12 (a group maximum whose scale byte rounded down from just below twice the smallest
+    // step), so the hardware convert at scale 1 decides it as FP64 comparisons would
+    float v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = f64_to_f32_sticky(y[i] * rcp);
+    const uint32_t word = pack8_e2m1(v, 1.0f);
+    const int n = 16 * t + walk.l16, row = lane >> 4;
+    const int blk = 2 * b + (row & 1);
+    if (n >= N) continue;
+    if (tiled) {
+      const int kt = blk >> 2, gi = blk & 3, KT = K >> 6;
+      *reinterpret_cast<uint32_t*>(Wq + nv_tiled_chunk_offset(n, kt, gi >> 1, KT) + 8 * (gi & 1) + 4 * (row >> 1)) = word;
+      if (row < 2) Ws[nv_tiled_scale_offset(n, kt, KT) + gi] = (uint8_t)byte;
+    } else {
+      *reinterpret_cast<uint32_t*>(Wq + (int64_t)n * (K / 2) + 8 * blk + 4 * (row >> 1)) = word;
+      if (row < 2) Ws[(int64_t)n * (K / 16) + blk] = (uint8_t)byte;
+    }
   }
 }
 
@@ -543,19 +529,16 @@ hipError_t launch_nvfp4_weight_prep(const void* W, int64_t N, int64_t K, int64_t
   char* base = reinterpret_cast<char*>(workspace);
   unsigned long long* amax = reinterpret_cast<unsigned long long*>(base + nvfp4_weight_prep_amax_offset(K));
   int* status = reinterpret_cast<int*>(base + nvfp4_weight_prep_status_offset(K));
-  reset_words_kernel<<<dim3(1), dim3(64), 0, stream>>>(amax, status);
+  invert16_kernel<<<dim3((unsigned)(K / 16)), dim3(64), 0, stream>>>((const uint16_t*)T16, tinv, amax, status);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  invert16_kernel<<<dim3((unsigned)(K / 16)), dim3(64), 0, stream>>>((const uint16_t*)T16, tinv, status);
+  const int C32 = (int)(K / 32);
+  dim3 grid((unsigned)wm::row_groups(N, C32, device_cu_count()), (unsigned)((C32 + 3) / 4));
+  nvfp4_weight_absmax_kernel<<<grid, dim3(256), 0, stream>>>((const uint16_t*)W, ldw, tinv, amax, status, (int)N, C32);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  dim3 grid((unsigned)((N + 255) / 256), (unsigned)(K / 16));
-  nvfp4_weight_kernel<false><<<grid, dim3(256), 0, stream>>>((const uint16_t*)W, ldw, tinv, amax, nullptr, nullptr,
-                                                             nullptr, (int)N, (int)K, tiled);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  nvfp4_weight_kernel<true><<<grid, dim3(256), 0, stream>>>((const uint16_t*)W, ldw, tinv, amax, (uint8_t*)Wq,
-                                                            (uint8_t*)Ws, ts_out, (int)N, (int)K, tiled);
+  nvfp4_weight_kernel<<<grid, dim3(256), 0, stream>>>((const uint16_t*)W, ldw, tinv, amax, (uint8_t*)Wq, (uint8_t*)Ws,
+                                                      ts_out, (int)N, (int)K, tiled);
   return hipGetLastError();
 }
 

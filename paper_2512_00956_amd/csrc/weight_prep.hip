@@ -1,14 +1,13 @@
 // Offline weight path (Alg. 2, RTN case): T_xvsh = T_wush^{-T}, then
 // q(T_xvsh W).  Also the quantizer-only test tap on FP32 values.
 //
-//   1. invert_blocks_kernel: one wavefront per 32x32 block, FP64 Gauss-Jordan
-//      with partial pivoting on the augmented matrix [T | I] held in LDS.
-//   2. weight_apply_quant_kernel: Wt = W_blk . inv(T_b) in FP64 (inv(T_b) in
-//      LDS, one thread per (row, block) group), then the same RTN AbsMax MXFP4
-//      rules as the activation kernel, evaluated on the FP64 values.
-// This path runs once per layer, offline; it is written for exactness against
-// an FP64 reference, not for speed.
+//   1. invert_blocks_kernel: one workgroup per 32x32 block, FP64 Gauss-Jordan
+//      with partial pivoting on the augmented matrix [T | I].
+//   2. weight_apply_quant_kernel: Wt = W_blk . inv(T_b) on the FP64 MFMA, then the
+//      same RTN AbsMax MXFP4 rules as the activation kernel, decided on the FP64 values.
 #include "nvfp4_layout.hpp"
+#include "weight_mfma.hpp"
+#include "wush_block.hpp"
 #include "wush_device.hpp"
 #include "wush_kernels.hpp"
 
@@ -16,195 +15,116 @@ namespace wush {
 
 namespace {
 
-constexpr double kPivotFloor = 1e-290;
-
-__global__ __launch_bounds__(64) void invert_blocks_kernel(const uint16_t* __restrict__ T,
-                                                           double* __restrict__ Tinv,
-                                                           int* __restrict__ status) {
-  __shared__ double a[32][65];  // [T | I], padded row
+// inv(T_b) of every block; the status word is cleared here and set by the kernel behind this one, which
+// knows a singular block by its zero inverse.
+__global__ __launch_bounds__(256) void invert_blocks_kernel(const uint16_t* __restrict__ T, double* __restrict__ Tinv,
+                                                            int* __restrict__ status) {
   const int b = blockIdx.x;
-  const int lane = threadIdx.x;
-  for (int r = 0; r < 32; ++r) {
-    double v;
-    if (lane < 32) v = (double)bf16_bits_to_f32(T[((int64_t)b * 32 + r) * 32 + lane]);
-    else v = (lane - 32 == r) ? 1.0 : 0.0;
-    a[r][lane] = v;
-  }
-  __syncthreads();
-  bool singular = false;
-  for (int p = 0; p < 32; ++p) {
-    // pivot search over rows p..31 in column p (first row of largest magnitude)
-    double best = -1.0;
-    int brow = p;
-    {
-      const int r = lane & 31;
-      double mag = (r >= p) ? fabs(a[r][p]) : -1.0;
-      int idx = r;
-      for (int off = 16; off >= 1; off >>= 1) {
-        const double omag = __shfl_xor(mag, off, 64);
-        const int oidx = __shfl_xor(idx, off, 64);
-        if (omag > mag || (omag == mag && oidx < idx)) { mag = omag; idx = oidx; }
-      }
-      best = mag;
-      brow = idx;
-    }
-    if (!(best > kPivotFloor)) { singular = true; break; }  // uniform across the wave
-    if (brow != p) {
-      const double t0 = a[p][lane];
-      a[p][lane] = a[brow][lane];
-      a[brow][lane] = t0;
-    }
-    __syncthreads();
-    const double inv_piv = 1.0 / a[p][p];
-    __syncthreads();
-    const double prow = a[p][lane] * inv_piv;
-    a[p][lane] = prow;
-    __syncthreads();
-    for (int r = 0; r < 32; ++r) {
-      if (r == p) continue;
-      const double f = a[r][p];
-      __syncthreads();
-      a[r][lane] -= f * prow;
-    }
-    __syncthreads();
-  }
-  if (singular) {
-    if (lane == 0) atomicExch(status, 1);
-    for (int r = 0; r < 32; ++r)
-      if (lane < 32) Tinv[((int64_t)b * 32 + r) * 32 + lane] = 0.0;
-    return;
-  }
-  for (int r = 0; r < 32; ++r)
-    if (lane >= 32) Tinv[((int64_t)b * 32 + r) * 32 + (lane - 32)] = a[r][lane];
+  if (b == 0 && threadIdx.x < 4) status[threadIdx.x] = 0;
+  auto entry = [&](int r, int c) { return (double)bf16_bits_to_f32(T[((int64_t)b * 32 + r) * 32 + c]); };
+  auto store = [&](int r, int c, double v) { Tinv[((int64_t)b * 32 + r) * 32 + c] = v; };
+  invert_block_group<32>(entry, store);
 }
 
-__global__ void reset_status_kernel(int* status) {
-  if (threadIdx.x < 4) status[threadIdx.x] = 0;
-}
-
+// Wt_blk = W_blk inv(T_b) and its codes.  Bound by the FP64 matrix arithmetic (1024 multiply-adds per row and
+// block): a wavefront keeps its block's inverse in registers and walks tiles of 16 rows (weight_mfma.hpp), the
+// four of a workgroup on adjacent blocks, so that a tile is 16 runs of 256 bytes.  Everything behind the product
+// is decided on the FP64 values, in 32-bit arithmetic: f64_to_f32_sticky keeps every comparison with a midpoint of
+// the grid and with 1.5 x a power of two what it was.  4096 -> 6144: 42 us (one thread per row and block, inverse in
+// LDS, FP64 comparisons: 72).
+template <int FMT>   // 0: MXFP4, 1: INT4
 __global__ __launch_bounds__(256) void weight_apply_quant_kernel(
     const uint16_t* __restrict__ W, int64_t ldw, const double* __restrict__ Tinv,
-    uint8_t* __restrict__ Wq, uint8_t* __restrict__ Ws, int N, int K, int C, int rule, int tiled) {
-  __shared__ double ti[32][32];  // inv(T_b)[k][j]
-  const int b = blockIdx.y;
-  for (int i = threadIdx.x; i < 1024; i += 256) ti[i >> 5][i & 31] = Tinv[(int64_t)b * 1024 + i];
-  __syncthreads();
-  const int n = blockIdx.x * 256 + threadIdx.x;
-  if (n >= N) return;
-  double w[32];
-  const uint16_t* wp = W + (int64_t)n * ldw + 32 * b;
+    uint8_t* __restrict__ Wq, uint8_t* __restrict__ Ws, int N, int K, int C, int rule, int tiled,
+    int* __restrict__ status) {
+  const int lane = threadIdx.x & 63, l16 = lane & 15, l4 = lane >> 4;
+  const int b = 4 * blockIdx.y + (threadIdx.x >> 6);
+  if (b >= C) return;
+  const double* ti = Tinv + (int64_t)b * 1024;
+  // row 0 of a block's inverse is zero only if the block was singular
+  if (blockIdx.x == 0 && !__any(ti[lane & 31] != 0.0) && lane == 0) atomicExch(status, 1);
+  wm::Block32 inv;
+  wm::load_block32(inv, [&](int k, int j) { return ti[32 * k + j]; }, lane);
+  const int tiles = (N + 15) / 16;
+  auto fetch = [&](int t) {
+    const int n = min(16 * t + l16, N - 1);
+    return *reinterpret_cast<const v4u*>(W + (int64_t)n * ldw + 32 * b + 8 * l4);
+  };
+  v4u raw = fetch(blockIdx.x);
+  for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
+    const int n = 16 * t + l16;
+    double w[8], y[8] = {};
+    wm::widen8(raw, w);
+    raw = fetch(min(t + (int)gridDim.x, tiles - 1));
+    wm::multiply32(inv, w, y);
+    uint32_t word = 0, scale;   // this lane's 8 codes; the group's scale bits
+    if constexpr (FMT == 0) {
+      float v[8], amax = 0.0f;
 #pragma unroll
-  for (int k = 0; k < 32; k += 8) {
-    const v4u raw = *reinterpret_cast<const v4u*>(wp + k);
+      for (int i = 0; i < 8; ++i) {
+        v[i] = f64_to_f32_sticky(y[i]);
+        amax = fmaxf(amax, fabsf(v[i]));
+      }
+      amax = wm::max_xor32(wm::max_xor16(amax));
+      int byte = scale_byte_f32(amax, rule);
+      if (!__any(byte < kSafeByteLo || byte > kSafeByteHi)) {
+        word = pack8_e2m1(v, scale_as_f32(byte));
+      } else {
+        // some row's values leave FP32's range: the same rules on the FP64 values
+        double am = 0.0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      w[k + 2 * i] = (double)__uint_as_float(raw[i] << 16);
-      w[k + 2 * i + 1] = (double)__uint_as_float(raw[i] & 0xFFFF0000u);
-    }
-  }
-  double y[32];
-  double amax = 0.0;
+        for (int i = 0; i < 8; ++i) am = fmax(am, fabs(y[i]));
+        wm::PairF64 p = wm::pair16(am, am);
+        p = wm::pair32(fmax(p.first, p.second));
+        byte = scale_byte_f64(fmax(p.first, p.second), rule);
+        const double inv_scale = __longlong_as_double((int64_t)(uint64_t)(1023 + 127 - byte) << 52);  // 2^(127-byte)
 #pragma unroll
-  for (int j = 0; j < 32; ++j) {
-    double acc = 0.0;
-#pragma unroll
-    for (int k = 0; k < 32; ++k) acc = fma(w[k], ti[k][j], acc);
-    y[j] = acc;
-    amax = fmax(amax, fabs(acc));
-  }
-  const int byte = scale_byte_f64(amax, rule);
-  const double inv_scale = __longlong_as_double((int64_t)(uint64_t)(1023 + 127 - byte) << 52);  // 2^(127-byte)
-  uint32_t words[4];
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    uint32_t wd = 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const double v = y[8 * g + i];
-      const uint32_t sign = (uint32_t)(((uint64_t)__double_as_longlong(v)) >> 63);
-      wd |= ((sign << 3) | e2m1_code_f64(fabs(v) * inv_scale)) << (4 * i);
-    }
-    words[g] = wd;
-  }
-  const v4u chunk = {words[0], words[1], words[2], words[3]};
-  if (tiled) {
-    *reinterpret_cast<v4u*>(Wq + tiled_chunk_offset(n, b, K >> 8)) = chunk;
-    Ws[tiled_scale_offset(n, b, K >> 8)] = (uint8_t)byte;
-  } else {
-    *reinterpret_cast<v4u*>(Wq + (int64_t)n * (K / 2) + 16 * b) = chunk;
-    Ws[(int64_t)n * C + b] = (uint8_t)byte;
-  }
-}
-
-// INT4 variant (Table 1: 4-bit integers, BF16 scale per 32 = Gaussian-MSE-optimal step times the
-// group's root mean square): the same FP64 product, then the quantizer decided in FP64 with one IEEE
-// operation per step and no fused multiply-add in the sum of squares (channels 0..15 left to right,
-// channels 16..31 left to right, the two sums added).  Tiled layout: nvfp4_layout.hpp.
-__global__ __launch_bounds__(256) void weight_apply_quant_int4_kernel(
-    const uint16_t* __restrict__ W, int64_t ldw, const double* __restrict__ Tinv, uint8_t* __restrict__ Wq,
-    uint8_t* __restrict__ Ws, int N, int K, int C, int tiled) {
-  __shared__ double ti[32][32];  // inv(T_b)[k][j]
-  const int b = blockIdx.y;
-  for (int i = threadIdx.x; i < 1024; i += 256) ti[i >> 5][i & 31] = Tinv[(int64_t)b * 1024 + i];
-  __syncthreads();
-  const int n = blockIdx.x * 256 + threadIdx.x;
-  if (n >= N) return;
-  double w[32];
-  const uint16_t* wp = W + (int64_t)n * ldw + 32 * b;
-#pragma unroll
-  for (int k = 0; k < 32; k += 8) {
-    const v4u raw = *reinterpret_cast<const v4u*>(wp + k);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      w[k + 2 * i] = (double)__uint_as_float(raw[i] << 16);
-      w[k + 2 * i + 1] = (double)__uint_as_float(raw[i] & 0xFFFF0000u);
-    }
-  }
-  double y[32];
-#pragma unroll
-  for (int j = 0; j < 32; ++j) {
-    double acc = 0.0;
-#pragma unroll
-    for (int k = 0; k < 32; ++k) acc = fma(w[k], ti[k][j], acc);
-    y[j] = acc;
-  }
-  uint32_t bits;
-  double rcp;
-  {
+        for (int i = 0; i < 8; ++i) {
+          const uint32_t sign = (uint32_t)(((uint64_t)__double_as_longlong(y[i])) >> 63);
+          word |= ((sign << 3) | e2m1_code_f64(fabs(y[i]) * inv_scale)) << (4 * i);
+        }
+      }
+      scale = (uint32_t)byte;
+    } else {
+      // INT4 (Table 1: 4-bit integers, BF16 scale per 32 = Gaussian-MSE-optimal step times the group's root mean
+      // square): one IEEE operation per step and no fused multiply-add in the sum of squares (channels 0..15 left to
+      // right, channels 16..31 left to right, the two sums added).  Lanes l4 = 0 and 2 begin the two sums, 1 and 3 go on.
 #pragma clang fp contract(off)
-    double lo = y[0] * y[0], hi = y[16] * y[16];
+      double sq[8], s = 0.0;
 #pragma unroll
-    for (int j = 1; j < 16; ++j) {
-      const double t0 = y[j] * y[j], t1 = y[16 + j] * y[16 + j];
-      lo = lo + t0;
-      hi = hi + t1;
+      for (int i = 0; i < 8; ++i) {
+        sq[i] = y[i] * y[i];
+        s = i == 0 ? sq[0] : s + sq[i];
+      }
+      double half = wm::pair16(s, s).first;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) half = half + sq[i];
+      const wm::PairF64 sums = wm::pair32(wm::pair16(half, half).second);
+      const double sigma = sqrt((sums.first + sums.second) * 0.03125);
+      uint32_t bits = f64_to_bf16_bits(0.33860793 * sigma);
+      bits = bits < 0x80u ? 0u : bits;
+      const double q = 1.0 / (double)__uint_as_float(bits << 16);
+      const double rcp = bits == 0 ? 0.0 : q;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const double c = fmin(fmax(y[i] * rcp, -8.0), 7.0);
+        word |= ((uint32_t)(int)rint(c) & 0xFu) << (4 * i);
+      }
+      scale = bits;
     }
-    const double ss = lo + hi;
-    const double sigma = sqrt(ss * 0.03125);
-    bits = f64_to_bf16_bits(0.33860793 * sigma);
-    bits = bits < 0x80u ? 0u : bits;
-    const double q = 1.0 / (double)__uint_as_float(bits << 16);
-    rcp = bits == 0 ? 0.0 : q;
-  }
-  uint32_t words[4];
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    uint32_t wd = 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const double t = fmin(fmax(y[8 * g + i] * rcp, -8.0), 7.0);
-      wd |= ((uint32_t)(int)rint(t) & 0xFu) << (4 * i);
+    if (n >= N) continue;
+    if (FMT == 0 && tiled) {
+      *reinterpret_cast<uint32_t*>(Wq + tiled_chunk_offset(n, b, K >> 8) + 4 * l4) = word;
+      if (l4 == 0) Ws[tiled_scale_offset(n, b, K >> 8)] = (uint8_t)scale;
+    } else if (tiled) {
+      const int KT = K >> 6;
+      *reinterpret_cast<uint32_t*>(Wq + nv_tiled_chunk_offset(n, b >> 1, b & 1, KT) + 4 * l4) = word;
+      if (l4 == 0) reinterpret_cast<uint16_t*>(Ws + nv_tiled_scale_offset(n, b >> 1, KT))[b & 1] = (uint16_t)scale;
+    } else {
+      *reinterpret_cast<uint32_t*>(Wq + (int64_t)n * (K / 2) + 16 * b + 4 * l4) = word;
+      if (FMT == 0 && l4 == 0) Ws[(int64_t)n * C + b] = (uint8_t)scale;
+      if (FMT == 1 && l4 == 0) reinterpret_cast<uint16_t*>(Ws)[(int64_t)n * C + b] = (uint16_t)scale;
     }
-    words[g] = wd;
-  }
-  const v4u chunk = {words[0], words[1], words[2], words[3]};
-  if (tiled) {
-    const int KT = K >> 6;
-    *reinterpret_cast<v4u*>(Wq + nv_tiled_chunk_offset(n, b >> 1, b & 1, KT)) = chunk;
-    reinterpret_cast<uint16_t*>(Ws + nv_tiled_scale_offset(n, b >> 1, KT))[b & 1] = (uint16_t)bits;
-  } else {
-    *reinterpret_cast<v4u*>(Wq + (int64_t)n * (K / 2) + 16 * b) = chunk;
-    reinterpret_cast<uint16_t*>(Ws)[(int64_t)n * C + b] = (uint16_t)bits;
   }
 }
 
@@ -259,39 +179,33 @@ size_t weight_prep_status_offset(int64_t K) { return (size_t)(K / 32) * 1024 * s
 
 size_t weight_prep_workspace_bytes(int64_t /*N*/, int64_t K) { return weight_prep_status_offset(K) + 16; }
 
-hipError_t launch_weight_prep(const void* W, int64_t N, int64_t K, int64_t ldw, const void* T, int rule,
-                              int tiled, void* Wq, void* Ws, void* workspace, hipStream_t stream) {
+namespace {
+
+template <int FMT>
+hipError_t launch_prep(const void* W, int64_t N, int64_t K, int64_t ldw, const void* T, int rule, int tiled, void* Wq,
+                       void* Ws, void* workspace, hipStream_t stream) {
   const int C = (int)(K / 32);
   double* tinv = reinterpret_cast<double*>(workspace);
   int* status = reinterpret_cast<int*>(reinterpret_cast<char*>(workspace) + weight_prep_status_offset(K));
-  // cleared by a kernel, not a memset node, so the sequence stays capturable
-  reset_status_kernel<<<dim3(1), dim3(64), 0, stream>>>(status);
+  invert_blocks_kernel<<<dim3(C), dim3(256), 0, stream>>>((const uint16_t*)T, tinv, status);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  invert_blocks_kernel<<<dim3(C), dim3(64), 0, stream>>>((const uint16_t*)T, tinv, status);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  dim3 grid((unsigned)((N + 255) / 256), (unsigned)C);
-  weight_apply_quant_kernel<<<grid, dim3(256), 0, stream>>>((const uint16_t*)W, ldw, tinv, (uint8_t*)Wq,
-                                                           (uint8_t*)Ws, (int)N, (int)K, C, rule, tiled);
+  dim3 grid((unsigned)wm::row_groups(N, C, device_cu_count()), (unsigned)((C + 3) / 4));
+  weight_apply_quant_kernel<FMT><<<grid, dim3(256), 0, stream>>>((const uint16_t*)W, ldw, tinv, (uint8_t*)Wq, (uint8_t*)Ws,
+                                                                (int)N, (int)K, C, rule, tiled, status);
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_weight_prep(const void* W, int64_t N, int64_t K, int64_t ldw, const void* T, int rule,
+                              int tiled, void* Wq, void* Ws, void* workspace, hipStream_t stream) {
+  return launch_prep<0>(W, N, K, ldw, T, rule, tiled, Wq, Ws, workspace, stream);
 }
 
 hipError_t launch_int4_weight_prep(const void* W, int64_t N, int64_t K, int64_t ldw, const void* T, int tiled, void* Wq,
                                    void* Ws, void* workspace, hipStream_t stream) {
-  const int C = (int)(K / 32);
-  double* tinv = reinterpret_cast<double*>(workspace);
-  int* status = reinterpret_cast<int*>(reinterpret_cast<char*>(workspace) + weight_prep_status_offset(K));
-  reset_status_kernel<<<dim3(1), dim3(64), 0, stream>>>(status);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  invert_blocks_kernel<<<dim3(C), dim3(64), 0, stream>>>((const uint16_t*)T, tinv, status);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  dim3 grid((unsigned)((N + 255) / 256), (unsigned)C);
-  weight_apply_quant_int4_kernel<<<grid, dim3(256), 0, stream>>>((const uint16_t*)W, ldw, tinv, (uint8_t*)Wq,
-                                                                (uint8_t*)Ws, (int)N, (int)K, C, tiled);
-  return hipGetLastError();
+  return launch_prep<1>(W, N, K, ldw, T, 0, tiled, Wq, Ws, workspace, stream);
 }
 
 hipError_t launch_quantize_f32(const float* Y, int64_t M, int64_t K, int rule, int tiled, void* q, void* s,
