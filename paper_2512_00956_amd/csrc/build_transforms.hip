@@ -127,8 +127,8 @@ __global__ __launch_bounds__(256) void wush_block_kernel(const double* __restric
     return partial[(((int64_t)half * S + s) * C + b) * 1024 + r * 32 + c];
   };
   auto finish = [&](int half, double sum) { return sum * (1.0 / (double)(half ? Mc : N)); };
-  wush_block_group<32>(load, finish, S, S, lambda, T_out + (int64_t)b * 1024, T_f64 ? T_f64 + (int64_t)b * 1024 : nullptr,
-                       nullptr, status);
+  wush_block_group<32, 0>(load, finish, S, S, lambda, nullptr, T_out + (int64_t)b * 1024,
+                          T_f64 ? T_f64 + (int64_t)b * 1024 : nullptr, nullptr, status);
 }
 
 // The same for 16 x 16 blocks (the NVFP4 variant: transform block = quantization group of 16).  The
@@ -141,8 +141,8 @@ __global__ __launch_bounds__(128) void wush_block16_kernel(const double* __restr
     return partial[(((int64_t)half * S + s) * C + b32) * 1024 + (off + r) * 32 + off + c];
   };
   auto finish = [&](int half, double sum) { return sum * (1.0 / (double)(half ? Mc : N)); };
-  wush_block_group<16>(load, finish, S, S, lambda, T_out + (int64_t)b * 256, T_f64 ? T_f64 + (int64_t)b * 256 : nullptr,
-                       nullptr, status);
+  wush_block_group<16, 0>(load, finish, S, S, lambda, nullptr, T_out + (int64_t)b * 256,
+                          T_f64 ? T_f64 + (int64_t)b * 256 : nullptr, nullptr, status);
 }
 
 int splits_for(int64_t C) {

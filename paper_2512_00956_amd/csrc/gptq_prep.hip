@@ -1,24 +1,28 @@
 // Offline weight path, GPTQ case of Alg. 2: WUSH transforms interleaved with
 // GPTQ's intra-block and inter-block error propagation.  Everything is FP64; the
-// path runs once per layer and is written for agreement with an FP64 reference.
+// path runs once per layer.
 //
 // The paper's schedule uses L, the lower Cholesky factor of the inverse of the
 // damped Hessian Hd = H + lambda tr(H)/d_in I, through three quantities per
 // block i: (L_ii L_ii^T)^-1, and L_ji L_ii^-1 for j > i.  This file never
 // inverts Hd.  With the reverse Cholesky factorization Hd = U U^T (U upper
-// triangular) one has L = U^-T, hence
+// triangular) and V = U^-1 one has L = V^T, hence
 //     (L_ii L_ii^T)^-1       = U_ii U_ii^T
-//     (L_ji L_ii^-1)^T       = U_ii (U^-1)_ij          (j > i)
-// so the work is: H, its reverse Cholesky factor in place (blocked, right-
-// looking from the last block), V = U^-1 (blocked, one workgroup per block row),
-// and then the sequential loop over blocks:
-//     M_W of the UPDATED weight block, Alg. 1 -> T_i (rounded to BF16),
-//     Wbar = W_i inv(T_i),  Hbar = (T_i U_ii)(T_i U_ii)^T,
-//     R = inverse of the reverse Cholesky factor of Hbar (R^T R = inv(Hbar)),
-//     GPTQ subroutine on Wbar with R: per output channel, 32 steps of
-//       quantize (static group scale), err = (w - q)/R[r][r], w[r'] -= err R[r][r'],
-//     E = deq T_i - W_i,  W_rest += E (U_ii V_i,rest).
+//     (L_ji L_ii^-1)^T       = U_ii V_ij                (j > i),
+// so block j enters its step as W_j + D_j with D_j = sum_{i<j} E_i U_ii V_ij, E_i the error of block i against what it
+// entered with.  With F_i = E_i U_ii the D_j + E_j are the blocks of F V, and (F V) U = F gives, block by block,
+//     D_j = -(sum_{i<j} G_i U_ij) V_jj,   G_i = E_i + D_i = (deq T)_i - W_i (the ORIGINAL weights):
+// the propagation needs the factor U and the inverses of its diagonal blocks, no other part of U^-1 (whose
+// computation, a triangular inverse, took 5.6 ms of the c2 layer's 70).
+//
+// Steps: H; its factor (one launch per 32 columns); then the sequential loop over blocks, three launches each:
+//     M_W of block i's current weights, Alg. 1 -> T_i (rounded to BF16);   beside it errors G U onto later S
+//     inv(T_i);  Hbar = (T_i U_ii)(T_i U_ii)^T, R = inverse of its reverse Cholesky factor (R^T R = inv(Hbar))
+//     per output channel: transformed weights, GPTQ subroutine (32 steps of quantize at a static group scale,
+//     err = (w - q)/R[r][r], w[r'] -= err R[r][r']), G_i, and block i + 1: S += G_i U, current weights, M_W.
+// c2 (4096 calibration tokens, 4096 -> 6144): 70.4 -> 18.4 ms, of which the loop 128 x 104 us, the factor 3.1 ms and H 1.8.
 // Summation orders are fixed (no atomics), so the result is reproducible.
+#include "weight_mfma.hpp"
 #include "wush_block.hpp"
 #include "wush_kernels.hpp"
 
@@ -26,53 +30,83 @@ namespace wush {
 
 namespace {
 
+using wm::Block32;
+using wm::v4d;
+
+// Eight consecutive doubles (64 bytes, 16-byte aligned).
+__device__ __forceinline__ void load8(const double* __restrict__ p, double (&x)[8]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const v2d v = reinterpret_cast<const v2d*>(p)[i];
+    x[2 * i] = v[0];
+    x[2 * i + 1] = v[1];
+  }
+}
+__device__ __forceinline__ void store8(double* __restrict__ p, const double (&x)[8]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) reinterpret_cast<v2d*>(p)[i] = (v2d){x[2 * i], x[2 * i + 1]};
+}
+
 // ------------------------------------------------------------------ Hessian
-// H = Xc^T Xc / M, 64 x 64 output tile per workgroup (tiles on or above the
-// diagonal; the mirror image is written too).  Products of BF16 values are exact.
+// H = Xc^T Xc / M, 64 x 64 tile per workgroup, tiles on or above the diagonal (the factorization reads no other).
+// Products of BF16 values are exact.  Arithmetic bound (K^2 M multiply-adds): FP64 MFMA, a wavefront per 32 x 32
+// quarter, operands widened as they come out of LDS; row pitch 80 floats: the four rows of an operand read hit
+// distinct banks.  c2: 1.8 ms = 39 TFLOP/s (2.6 on the vector unit).
 __global__ __launch_bounds__(256) void gptq_hessian_kernel(const uint16_t* __restrict__ X, int64_t ldx, int Mc, int K,
-                                                           double* __restrict__ H) {
+                                                           double* __restrict__ H, int* __restrict__ status) {
   const int ti = blockIdx.y, tj = blockIdx.x;
+  if (ti == 0 && tj == 0 && threadIdx.x < 4) status[threadIdx.x] = 0;   // later kernels set it
   if (tj < ti) return;
-  __shared__ float a[32][65], b[32][65];
-  const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
-  double acc[4][4] = {};
+  __shared__ __attribute__((aligned(16))) float side_a[32][80], side_b[32][80];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, l4 = lane >> 4;
+  const int wr = 32 * (wave >> 1), wc = 32 * (wave & 1);
+  v4d acc[2][2] = {};
   const int lr = threadIdx.x >> 3, lc = (threadIdx.x & 7) * 8;   // one 16-byte chunk per thread and side
+  const int ca = 64 * ti + lc, cb = 64 * tj + lc;
+  v4u ra, rb;
+  auto fetch = [&](int m0) {
+    const v4u zero = {0, 0, 0, 0};
+    const bool row = m0 + lr < Mc;
+    ra = row && ca < K ? *reinterpret_cast<const v4u*>(X + (int64_t)(m0 + lr) * ldx + ca) : zero;
+    rb = row && cb < K ? *reinterpret_cast<const v4u*>(X + (int64_t)(m0 + lr) * ldx + cb) : zero;
+  };
+  auto widen = [&](const v4u& raw, float* dst) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      dst[2 * i] = __uint_as_float(raw[i] << 16);
+      dst[2 * i + 1] = __uint_as_float(raw[i] & 0xFFFF0000u);
+    }
+  };
+  fetch(0);
   for (int m0 = 0; m0 < Mc; m0 += 32) {
     __syncthreads();
-#pragma unroll
-    for (int side = 0; side < 2; ++side) {
-      const int col = 64 * (side ? tj : ti) + lc;
-      v4u raw = {0, 0, 0, 0};
-      if (m0 + lr < Mc && col < K) raw = *reinterpret_cast<const v4u*>(X + (int64_t)(m0 + lr) * ldx + col);
-      float (*dst)[65] = side ? b : a;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        dst[lr][lc + 2 * i] = __uint_as_float(raw[i] << 16);
-        dst[lr][lc + 2 * i + 1] = __uint_as_float(raw[i] & 0xFFFF0000u);
-      }
-    }
+    widen(ra, &side_a[lr][lc]);
+    widen(rb, &side_b[lr][lc]);
     __syncthreads();
-    for (int r = 0; r < 32; ++r) {
-      double av[4], bv[4];
+    if (m0 + 32 < Mc) fetch(m0 + 32);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) { av[i] = a[r][4 * ty + i]; bv[i] = b[r][4 * tx + i]; }
+    for (int kk = 0; kk < 8; ++kk) {
+      double a[2], b[2];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int u = 0; u < 2; ++u) {
+        a[u] = (double)side_a[4 * kk + l4][wr + 16 * u + l16];
+        b[u] = (double)side_b[4 * kk + l4][wc + 16 * u + l16];
+      }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fma(av[i], bv[j], acc[i][j]);
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[v], acc[u][v], 0, 0, 0);
     }
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int r = 64 * ti + 4 * ty + i, c = 64 * tj + 4 * tx + j;
-      if (r < K && c < K) {
-        const double v = acc[i][j] / (double)Mc;
-        H[(int64_t)r * K + c] = v;
-        H[(int64_t)c * K + r] = v;
+    for (int v = 0; v < 2; ++v)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = 64 * ti + wr + 16 * u + l4 + 4 * e, c = 64 * tj + wc + 16 * v + l16;
+        if (r < K && c < K) H[(int64_t)r * K + c] = acc[u][v][e] / (double)Mc;
       }
-    }
 }
 
 // tr(H) in a fixed order, then: keep the undamped diagonal blocks (the M_X of
@@ -103,447 +137,470 @@ __global__ __launch_bounds__(256) void gptq_damp_kernel(double* __restrict__ H, 
   }
 }
 
-// ------------------------------------------------- 32 x 32 building blocks
-// (one wavefront; matrices in LDS with a padded row)
-
-// U upper triangular with U U^T = S (S symmetric positive definite, overwritten:
-// upper triangle = U, strict lower triangle = 0).  Lane r < 32 owns row r.
-__device__ __forceinline__ bool reverse_cholesky32(double (*S)[33], int lane) {
-  bool bad = false;
-  const int r = lane & 31;
-  for (int j = 31; j >= 0; --j) {
-    double d = S[j][j];
-#pragma unroll 4
-    for (int l = j + 1; l < 32; ++l) d -= S[j][l] * S[j][l];
-    if (!(d > 0.0)) { bad = true; d = 1.0; }
-    const double dj = sqrt(d);
-    double v = 0.0;
-    if (r < j) {
-      v = S[r][j];
-#pragma unroll 4
-      for (int l = j + 1; l < 32; ++l) v -= S[r][l] * S[j][l];
-      v /= dj;
-    }
-    __syncthreads();
-    if (lane < 32) {
-      if (r == j) S[j][j] = dj;
-      else if (r < j) S[r][j] = v;
-      else S[r][j] = 0.0;
-    }
-    __syncthreads();
-  }
-  return bad;
-}
-
-// Vout = inverse of the upper triangular U (both [32][33] in LDS); lane c < 32
-// computes column c by back substitution.
-__device__ __forceinline__ void upper_inverse32(const double (*U)[33], double (*Vout)[33], int lane) {
-  if (lane < 32) {
-    const int c = lane;
-    double x[32];
-#pragma unroll
-    for (int r = 31; r >= 0; --r) {
-      double acc = (r == c) ? 1.0 : 0.0;
-#pragma unroll
-      for (int l = r + 1; l < 32; ++l) acc -= U[r][l] * x[l];
-      x[r] = (r <= c) ? acc / U[r][r] : 0.0;
-    }
-#pragma unroll
-    for (int r = 0; r < 32; ++r) Vout[r][c] = x[r];
-  }
-  __syncthreads();
-}
-
 // ------------------------------------------------ reverse Cholesky of Hd
-__global__ __launch_bounds__(64) void gptq_rchol_diag_kernel(double* __restrict__ H, int K, int i, int* __restrict__ status) {
-  __shared__ double S[32][33];
-  const int lane = threadIdx.x;
-  for (int o = lane; o < 1024; o += 64) S[o >> 5][o & 31] = H[(int64_t)(32 * i + (o >> 5)) * K + 32 * i + (o & 31)];
-  __syncthreads();
-  const bool bad = reverse_cholesky32(S, lane);
-  if (__any(bad) && lane == 0) atomicExch(status, 1);
-  for (int o = lane; o < 1024; o += 64) H[(int64_t)(32 * i + (o >> 5)) * K + 32 * i + (o & 31)] = S[o >> 5][o & 31];
-}
-
-// rows above block i: U_ki = S_ki U_ii^-T, one thread per row (x U_ii^T = s by back substitution)
-__global__ __launch_bounds__(256) void gptq_rchol_panel_kernel(double* __restrict__ H, int K, int i) {
-  __shared__ double U[32][33];
-  for (int o = threadIdx.x; o < 1024; o += 256) U[o >> 5][o & 31] = H[(int64_t)(32 * i + (o >> 5)) * K + 32 * i + (o & 31)];
-  __syncthreads();
-  const int row = blockIdx.x * 256 + threadIdx.x;
-  if (row >= 32 * i) return;
-  double* p = H + (int64_t)row * K + 32 * i;
-  double x[32];
-#pragma unroll
-  for (int j = 0; j < 32; ++j) x[j] = p[j];
-#pragma unroll
-  for (int j = 31; j >= 0; --j) {
-    double acc = x[j];
-#pragma unroll
-    for (int l = j + 1; l < 32; ++l) acc -= x[l] * U[j][l];
-    x[j] = acc / U[j][j];
+// Step i (C, C - 1, ..., 1) takes block column i out of what is left of Hd: U_ki = H_ki V_ii^T and
+// H_kl -= U_ki U_li^T for all k <= l < i, and, in workgroup 0, the factor U_dd, V_dd of the next diagonal block
+// d = i - 1 right behind that block's update -- the chain of diagonal factors never waits for the rest, and a step is
+// one launch (c2: 62 us on average as three kernels that waited for each other, now 24).  Step C only factors block C - 1.  A
+// wavefront per pair (k, l); the panel products U_ki, U_li are repeated by every pair rather than fetched from
+// another launch.  U goes to its own buffer: other wavefronts of the step still read H_ki.
+__global__ __launch_bounds__(256) void gptq_rchol_kernel(double* __restrict__ H, double* __restrict__ U,
+                                                         double* __restrict__ Vd, int K, int i, int* __restrict__ status) {
+  __shared__ double Sd[32][33];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, l4 = lane >> 4;
+  const int d = i - 1;
+  int k = d, l = d, a_begin = wave, a_end = wave < 2 ? wave + 1 : wave;   // workgroup 0: one 16-row half per wavefront
+  if (blockIdx.x > 0) {
+    const int64_t idx = ((int64_t)blockIdx.x - 1) * 4 + wave;
+    if (idx >= (int64_t)i * (i + 1) / 2 - 1) return;   // wave-uniform; no barrier follows in these workgroups
+    l = (int)((sqrt(8.0 * (double)idx + 1.0) - 1.0) * 0.5);
+    while ((int64_t)l * (l + 1) / 2 > idx) --l;
+    while ((int64_t)(l + 1) * (l + 2) / 2 <= idx) ++l;
+    k = (int)(idx - (int64_t)l * (l + 1) / 2);
+    a_begin = 0;
+    a_end = 2;
   }
+  const bool update = 32 * i < K;
+  if (update && a_begin < a_end) {
+    Block32 v, ul;
+    wm::load_block32(v, [&](int kk, int j) { return Vd[(int64_t)i * 1024 + 32 * j + kk]; }, lane);
+    // U_li with its rows where the next product wants its first operand's (weight_mfma.hpp)
 #pragma unroll
-  for (int j = 0; j < 32; ++j) p[j] = x[j];
-}
-
-// trailing update: S_kl -= U_ki U_li^T for block pairs k <= l < i (one 32 x 32 block per workgroup)
-__global__ __launch_bounds__(256) void gptq_rchol_update_kernel(double* __restrict__ H, int K, int i) {
-  const int k = blockIdx.y, l = blockIdx.x;
-  if (k > l) return;
-  __shared__ double pk[32][33], pl[32][33];
-  for (int o = threadIdx.x; o < 1024; o += 256) {
-    pk[o >> 5][o & 31] = H[(int64_t)(32 * k + (o >> 5)) * K + 32 * i + (o & 31)];
-    pl[o >> 5][o & 31] = H[(int64_t)(32 * l + (o >> 5)) * K + 32 * i + (o & 31)];
-  }
-  __syncthreads();
-  const int r = threadIdx.x >> 3, c0 = (threadIdx.x & 7) * 4;
-  double acc[4] = {0, 0, 0, 0};
-  for (int m = 0; m < 32; ++m) {
-    const double a = pk[r][m];
+    for (int t = 0; t < 2; ++t) {
+      double w[8], y[8] = {};
+      load8(H + (int64_t)(32 * l + 8 * (l16 & 3) + 4 * t + (l16 >> 2)) * K + 32 * i + 8 * l4, w);
+      wm::multiply32(v, w, y);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = fma(a, pl[c0 + t][m], acc[t]);
-  }
-  double* out = H + (int64_t)(32 * k + r) * K + 32 * l + c0;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) out[t] -= acc[t];
-}
-
-// ------------------------------------------------------------ V = U^-1
-__global__ __launch_bounds__(64) void gptq_triinv_diag_kernel(const double* __restrict__ H, int K, double* __restrict__ V) {
-  __shared__ double U[32][33], Vi[32][33];
-  const int i = blockIdx.x, lane = threadIdx.x;
-  for (int o = lane; o < 1024; o += 64) U[o >> 5][o & 31] = H[(int64_t)(32 * i + (o >> 5)) * K + 32 * i + (o & 31)];
-  __syncthreads();
-  upper_inverse32(U, Vi, lane);
-  for (int o = lane; o < 1024; o += 64) V[(int64_t)(32 * i + (o >> 5)) * K + 32 * i + (o & 31)] = Vi[o >> 5][o & 31];
-}
-
-// block row i of V: V_ij = -(sum_{k=i}^{j-1} V_ik U_kj) V_jj for j = i+1 .. C-1.
-// The workgroup reads back what it wrote for smaller j; the workgroup barrier orders that.
-// The 32 x 32 block products run on the FP64 MFMA (16 x 16 x 4), one 16 x 16 output tile per wave:
-// with scalar FMAs the kernel was bound by its LDS reads (five per four FMAs), and its longest chain
-// (block row 0: C^2 / 2 products one after the other) is the whole kernel's duration.
-typedef double v4d_t __attribute__((ext_vector_type(4)));
-__global__ __launch_bounds__(256) void gptq_triinv_rows_kernel(const double* __restrict__ H, int K, int C,
-                                                               double* __restrict__ V) {
-  __shared__ double va[32][33], ub[32][33], acc_s[32][33];
-  const int i = blockIdx.x;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int tr = 16 * (wave >> 1), tc = 16 * (wave & 1);      // this wave's output tile
-  const int l16 = lane & 15, l4 = lane >> 4;
-  // A[row l16][k l4] and B[k l4][column l16] of the MFMA; accumulator element v is (row l4 + 4 v, column l16)
-  auto product = [&](const double (*a)[33], const double (*b)[33], v4d_t acc) {
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk)
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[tr + l16][4 * kk + l4], b[4 * kk + l4][tc + l16], acc, 0, 0, 0);
-    return acc;
-  };
-  // the blocks of step k + 1 travel from memory into registers while step k is multiplied
-  double rv[4], ru[4];
-  auto fetch = [&](int k, int j) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int o = threadIdx.x + 256 * u;
-      rv[u] = V[(int64_t)(32 * i + (o >> 5)) * K + 32 * k + (o & 31)];
-      ru[u] = H[(int64_t)(32 * k + (o >> 5)) * K + 32 * j + (o & 31)];
+      for (int q = 0; q < 8; ++q) ul.m[t][q] = -y[q];
     }
-  };
-  for (int j = i + 1; j < C; ++j) {
-    v4d_t acc = {0, 0, 0, 0};
-    fetch(i, j);
-    for (int k = i; k < j; ++k) {
-      __syncthreads();
+    for (int a = a_begin; a < a_end; ++a) {
+      const int64_t row = (int64_t)(32 * k + 16 * a + l16) * K;
+      double w[8], uk[8] = {}, y[8];
+      load8(H + row + 32 * i + 8 * l4, w);
+      load8(H + row + 32 * l + 8 * l4, y);
+      wm::multiply32(v, w, uk);
+      if (k == l) store8(U + row + 32 * i + 8 * l4, uk);
+      wm::multiply32(ul, uk, y);
+      if (blockIdx.x > 0) {
+        store8(H + row + 32 * l + 8 * l4, y);
+      } else {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int o = threadIdx.x + 256 * u;
-        va[o >> 5][o & 31] = rv[u];
-        ub[o >> 5][o & 31] = ru[u];
+        for (int q = 0; q < 8; ++q) Sd[16 * a + l16][8 * l4 + q] = y[q];
       }
-      __syncthreads();
-      if (k + 1 < j) fetch(k + 1, j);
-      acc = product(va, ub, acc);
     }
-    __syncthreads();
-#pragma unroll
-    for (int v = 0; v < 4; ++v) acc_s[tr + l4 + 4 * v][tc + l16] = acc[v];
-    for (int o = threadIdx.x; o < 1024; o += 256)
-      ub[o >> 5][o & 31] = V[(int64_t)(32 * j + (o >> 5)) * K + 32 * j + (o & 31)];   // V_jj
-    __syncthreads();
-    const v4d_t out = product(acc_s, ub, (v4d_t){0, 0, 0, 0});
-#pragma unroll
-    for (int v = 0; v < 4; ++v) V[(int64_t)(32 * i + tr + l4 + 4 * v) * K + 32 * j + tc + l16] = -out[v];
-    __threadfence_block();
   }
+  if (blockIdx.x > 0) return;
+  if (!update)
+    for (int o = threadIdx.x; o < 1024; o += 256) Sd[o >> 5][o & 31] = H[(int64_t)(32 * d + (o >> 5)) * K + 32 * d + (o & 31)];
+  __syncthreads();
+  const bool good = reverse_factor_group([&](int r, int c) { return Sd[r][c]; },
+                                         [&](int r, int c, double x) { U[(int64_t)(32 * d + r) * K + 32 * d + c] = x; },
+                                         [&](int r, int c, double x) { Vd[(int64_t)d * 1024 + 32 * r + c] = x; });
+  if (!good && threadIdx.x == 0) atomicExch(status, 1);
 }
 
 // ------------------------------------------------------ per-block kernels
-__global__ __launch_bounds__(256) void gptq_widen_kernel(const uint16_t* __restrict__ W, int64_t ldw, int N, int K,
-                                                         double* __restrict__ Wf) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (int64_t)N * K) return;
-  const int n = (int)(idx / K), k = (int)(idx % K);
-  Wf[idx] = (double)bf16_bits_to_f32(W[(int64_t)n * ldw + k]);
-}
-
-// partial second moments of the current weight block: split s sums its rows
-__global__ __launch_bounds__(256) void gptq_moment_kernel(const double* __restrict__ Wf, int N, int K, int i,
-                                                          int rows_per_split, double* __restrict__ partial) {
-  __shared__ double tile[64][33];
-  const int s = blockIdx.x;
-  const int r_begin = min(s * rows_per_split, N), r_end = min(r_begin + rows_per_split, N);
-  const int ti = threadIdx.x >> 4, tj = threadIdx.x & 15;
-  double a00 = 0, a01 = 0, a10 = 0, a11 = 0;
-  for (int r0 = r_begin; r0 < r_end; r0 += 64) {
+// Second moment of 32 channels over tiles of 16 rows, by the wavefronts of a workgroup: a lane brings channels
+// 8 l4 ... + 7 of row l16, the tile is turned through the wavefront's own LDS area into operands whose contraction
+// runs over the rows, and the three distinct 16 x 16 blocks are accumulated on the FP64 MFMA.
+constexpr int kAreaDoubles = 768;    // LDS per wavefront: a 16 x 34 tile and 16 x 8 errors, at the end its three sums
+struct Moment {
+  v4d acc00 = {0, 0, 0, 0}, acc01 = {0, 0, 0, 0}, acc11 = {0, 0, 0, 0};
+  __device__ __forceinline__ void add(const double (&x)[8], double* area, int l16, int l4) {
+    store8(area + 34 * l16 + 8 * l4, x);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      const double x0 = area[34 * (4 * kk + l4) + l16], x1 = area[34 * (4 * kk + l4) + 16 + l16];
+      acc00 = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, x0, acc00, 0, 0, 0);
+      acc01 = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, x1, acc01, 0, 0, 0);
+      acc11 = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, x1, acc11, 0, 0, 0);
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  // sums of the workgroup's WAVES wavefronts in wave order -> out [32][32]
+  template <int WAVES>
+  __device__ __forceinline__ void reduce(double* areas, int wave, int lane, double* __restrict__ out) {
     __syncthreads();
-    for (int o = threadIdx.x; o < 64 * 32; o += 256) {
-      const int rr = o >> 5, c = o & 31;
-      tile[rr][c] = (r0 + rr < r_end) ? Wf[(int64_t)(r0 + rr) * K + 32 * i + c] : 0.0;
+    double* mine = areas + wave * kAreaDoubles;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      mine[4 * lane + v] = acc00[v];
+      mine[256 + 4 * lane + v] = acc01[v];
+      mine[512 + 4 * lane + v] = acc11[v];
     }
     __syncthreads();
-    for (int rr = 0; rr < 64; ++rr) {
-      const double ax = tile[rr][2 * ti], ay = tile[rr][2 * ti + 1], cx = tile[rr][2 * tj], cy = tile[rr][2 * tj + 1];
-      a00 = fma(ax, cx, a00);
-      a01 = fma(ax, cy, a01);
-      a10 = fma(ay, cx, a10);
-      a11 = fma(ay, cy, a11);
+    for (int e = threadIdx.x; e < 768; e += 64 * WAVES) {
+      double s = areas[e];
+#pragma unroll
+      for (int w = 1; w < WAVES; ++w) s += areas[w * kAreaDoubles + e];
+      const int el = (e & 255) >> 2, i = (el >> 4) + 4 * (e & 3), c = el & 15;   // row, column of the 16 x 16 block
+      if (e < 256) out[i * 32 + c] = s;
+      else if (e < 512) {
+        out[i * 32 + 16 + c] = s;
+        out[(16 + c) * 32 + i] = s;
+      } else out[(16 + i) * 32 + 16 + c] = s;
     }
   }
-  double* out = partial + (int64_t)s * 1024;
-  out[(2 * ti) * 32 + 2 * tj] = a00;
-  out[(2 * ti) * 32 + 2 * tj + 1] = a01;
-  out[(2 * ti + 1) * 32 + 2 * tj] = a10;
-  out[(2 * ti + 1) * 32 + 2 * tj + 1] = a11;
+};
+
+// Second moments of all blocks of the original weights (grid: splits of the rows x blocks), for the warm start.
+__global__ __launch_bounds__(256) void gptq_moment0_kernel(const uint16_t* __restrict__ W, int64_t ldw, int N,
+                                                           double* __restrict__ partial) {
+  __shared__ __attribute__((aligned(16))) double areas[4 * kAreaDoubles];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, l4 = lane >> 4;
+  const int b = blockIdx.y, tiles = (N + 15) / 16;
+  Moment m;
+  for (int t = 4 * blockIdx.x + wave; t < tiles; t += 4 * gridDim.x) {
+    const int n = 16 * t + l16;
+    double x[8];
+    wm::widen8(*reinterpret_cast<const v4u*>(W + (int64_t)min(n, N - 1) * ldw + 32 * b + 8 * l4), x);
+    if (n >= N)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) x[q] = 0.0;
+    m.add(x, areas + wave * kAreaDoubles, l16, l4);
+  }
+  m.reduce<4>(areas, wave, lane, partial + ((int64_t)b * gridDim.x + blockIdx.x) * 1024);
 }
 
-// Alg. 1 on (M_W of the updated block, M_X = diagonal block of H): T_i
-__global__ __launch_bounds__(256) void gptq_wush_kernel(const double* __restrict__ partial, int S, int N,
-                                                        const double* __restrict__ MX_i, double lambda,
-                                                        uint16_t* __restrict__ T_bits_i, double* __restrict__ Tb,
-                                                        int* __restrict__ status) {
-  auto load = [&](int half, int r, int c, int s) { return half ? MX_i[r * 32 + c] : partial[s * 1024 + r * 32 + c]; };
+// Right singular vectors of W'^T X' of every block of the ORIGINAL weights: what the SVD inside the loop starts from.
+// All blocks at once (they fill the chip), while inside the loop a block waits for its SVD alone: there the sweeps left
+// to do fall from 7..9 to about 5.
+__global__ __launch_bounds__(256) void gptq_warm_kernel(const double* __restrict__ partial, int splits, int N,
+                                                        const double* __restrict__ MX, double lambda, double* __restrict__ V0) {
+  const int b = blockIdx.x;
+  auto load = [&](int half, int r, int c, int s) {
+    return half ? MX[(int64_t)b * 1024 + r * 32 + c] : partial[((int64_t)b * splits + s) * 1024 + r * 32 + c];
+  };
   auto finish = [&](int half, double sum) { return half ? sum : sum / (double)N; };
-  wush_block_group<32>(load, finish, S, 1, lambda, T_bits_i, nullptr, Tb, status);
+  wush_block_group<32, 1>(load, finish, splits, 1, lambda, nullptr, nullptr, nullptr, V0 + (int64_t)b * 1024, nullptr);
 }
 
-// identity / fixed transforms for comparisons: T_i given, only widen it
-__global__ __launch_bounds__(64) void gptq_fixed_transform_kernel(const uint16_t* __restrict__ T_bits_i,
-                                                                  double* __restrict__ Tb) {
-  for (int o = threadIdx.x; o < 1024; o += 64) Tb[o] = (double)bf16_bits_to_f32(T_bits_i[o]);
+// What the sums S_l still lack travels in groups of kGroup blocks: S is N x K doubles, and adding every block's error to
+// all of it at once made that traffic the longest part of a step (190 us at the start of the c2 layer, against a chain of
+// 70).  Step i (i = kGroup q + s) brings
+//   block i + 1    up to date for its own step: the errors of group q so far, before them those of group q - 1;
+//   every kGroup-th later block, from kGroup (q + 1) + s on: the errors of group q - 1
+// so that each block has each group's errors added once, groups in order, and the steps share the work evenly.
+constexpr int kGroup = 4;
+struct Pending { int l, lo, hi; };    // block l takes the errors of blocks lo ... hi - 1
+__host__ __device__ inline int pending_columns(int i, int C) {
+  const int q = i / kGroup, s = i % kGroup, first = kGroup * (q + 1) + s;
+  const int far = q > 0 && first < C ? (C - first + kGroup - 1) / kGroup : 0;
+  return (i > 0 && i + 1 < C ? 1 : 0) + far;
+}
+__host__ __device__ inline Pending pending_of(int i, int C, int index) {
+  const int q = i / kGroup, s = i % kGroup;
+  if (i > 0 && i + 1 < C) {
+    if (index == 0) return {i + 1, s < kGroup - 1 && q > 0 ? kGroup * (q - 1) : kGroup * q, i};
+    --index;
+  }
+  return {kGroup * (q + 1) + s + kGroup * index, kGroup * (q - 1), kGroup * q};
+}
+constexpr int kMostPending = 2 * kGroup - 2;
+
+// Workgroup 0: Alg. 1 on (M_W of block i's current weights, M_X = diagonal block of H) -> T_i, a chain of some 70 us on
+// one compute unit (110 before).  The others meanwhile: S_l += sum_b G_b U_bl for the pending blocks l.  A workgroup holds its U_bl
+// in LDS in operand order, its wavefronts walk tiles of 16 rows (64 bytes per lane and operand, the next tile's
+// requested before this one's products); the panels G_b (the errors; block b's, whose S is used up) and S_l are [N][32].
+__global__ __launch_bounds__(256) void gptq_chain_kernel(const double* __restrict__ partial, int splits, int N, int K, int i,
+                                                         const double* __restrict__ MX_i, double lambda,
+                                                         const double* __restrict__ V0_i, uint16_t* __restrict__ T_bits_i,
+                                                         int given, const double* __restrict__ U, double* __restrict__ S,
+                                                         int row_groups, int* __restrict__ status) {
+  if (blockIdx.x == 0) {
+    if (given) return;
+    __builtin_amdgcn_s_setprio(3);   // ahead of wavefronts that may share its compute unit
+    auto load = [&](int half, int r, int c, int s) { return half ? MX_i[r * 32 + c] : partial[(int64_t)s * 1024 + r * 32 + c]; };
+    auto finish = [&](int half, double sum) { return half ? sum : sum / (double)N; };
+    wush_block_group<32, 0>(load, finish, splits, 1, lambda, V0_i, T_bits_i, nullptr, nullptr, status);
+    return;
+  }
+  extern __shared__ __attribute__((aligned(16))) double smem[];   // [block][pair of operand registers][lane][2]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, l4 = lane >> 4;
+  const int g = ((int)blockIdx.x - 1) % row_groups;
+  const Pending job = pending_of(i, K >> 5, ((int)blockIdx.x - 1) / row_groups);
+  const int nb = job.hi - job.lo;
+  for (int b = wave; b < nb; b += 4) {
+    Block32 u;
+    wm::load_block32(u, [&](int k, int j) { return U[(int64_t)(32 * (job.lo + b) + k) * K + 32 * job.l + j]; }, lane);
+#pragma unroll
+    for (int p = 0; p < 8; ++p)
+      *reinterpret_cast<v2d*>(&smem[((b * 8 + p) * 64 + lane) * 2]) = (v2d){u.m[p >> 2][2 * (p & 3)], u.m[p >> 2][2 * (p & 3) + 1]};
+  }
+  __syncthreads();
+  const int64_t panel = (int64_t)N * 32;
+  double* sum = S + job.l * panel;
+  const double* err = S + job.lo * panel;
+  const int tiles = (N + 15) / 16, stride = 4 * row_groups;
+  const bool fresh = job.lo == 0;    // the block's first errors: nothing to add to
+  auto at = [&](int t) { return (int64_t)min(16 * t + l16, N - 1) * 32 + 8 * l4; };
+  int t = 4 * g + wave;
+  if (t >= tiles) return;
+  // fetched one product ahead: the next block's errors, behind the last the next tile's first errors and sums
+  double en[8], sn[8] = {};
+  load8(err + at(t), en);
+  if (!fresh) load8(sum + at(t), sn);
+  for (; t < tiles; t += stride) {
+    const int64_t here = at(t), next = at(min(t + stride, tiles - 1));
+    double s[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s[q] = sn[q];
+    if (!fresh) load8(sum + next, sn);   // other rows than this tile's, except behind the last one, where it is not used
+    for (int b = 0; b < nb; ++b) {
+      double e[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) e[q] = en[q];
+      load8(b + 1 < nb ? err + (b + 1) * panel + here : err + next, en);
+      Block32 u;
+#pragma unroll
+      for (int p = 0; p < 8; ++p) {
+        const v2d v = *reinterpret_cast<const v2d*>(&smem[((b * 8 + p) * 64 + lane) * 2]);
+        u.m[p >> 2][2 * (p & 3)] = v[0];
+        u.m[p >> 2][2 * (p & 3) + 1] = v[1];
+      }
+      wm::multiply32(u, e, s);
+    }
+    if (16 * t + l16 < N) store8(sum + here, s);
+  }
 }
 
-// From T_i (BF16-valued) and U_ii: inv(T_i) (Gauss-Jordan, partial pivoting) and
-// R = inverse of the reverse Cholesky factor of Hbar = (T_i U_ii)(T_i U_ii)^T.
-__global__ __launch_bounds__(64) void gptq_block_mats_kernel(const double* __restrict__ Tb, const double* __restrict__ H,
-                                                             int K, int i, double* __restrict__ Tinv,
-                                                             double* __restrict__ R, int* __restrict__ status) {
-  __shared__ double a[32][65];
-  __shared__ double B[32][33], Hb[32][33], Rm[32][33];
-  const int lane = threadIdx.x;
-  // ---- inverse of T_i
-  for (int r = 0; r < 32; ++r) a[r][lane] = lane < 32 ? Tb[r * 32 + lane] : ((lane - 32 == r) ? 1.0 : 0.0);
-  __syncthreads();
-  bool singular = false;
-  for (int p = 0; p < 32; ++p) {
-    const int rr = lane & 31;
-    double mag = (rr >= p) ? fabs(a[rr][p]) : -1.0;
-    int idx = rr;
-    for (int off = 16; off >= 1; off >>= 1) {
-      const double omag = __shfl_xor(mag, off, 64);
-      const int oidx = __shfl_xor(idx, off, 64);
-      if (omag > mag || (omag == mag && oidx < idx)) { mag = omag; idx = oidx; }
-    }
-    if (!(mag > 1e-290)) { singular = true; break; }   // uniform across the wave
-    if (idx != p) {
-      const double t0 = a[p][lane];
-      a[p][lane] = a[idx][lane];
-      a[idx][lane] = t0;
-    }
-    __syncthreads();
-    const double inv_piv = 1.0 / a[p][p];
-    __syncthreads();
-    const double prow = a[p][lane] * inv_piv;
-    a[p][lane] = prow;
-    __syncthreads();
-    // column p (the factors) is read whole before any lane touches it: lane p updates it below
-    double f[32];
-#pragma unroll
-    for (int r = 0; r < 32; ++r) f[r] = a[r][p];
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < 32; ++r)
-      if (r != p) a[r][lane] -= f[r] * prow;
-    __syncthreads();
+// From T_i (BF16) and U_ii: workgroup 0 inv(T_i), workgroup 1 R = inverse of the reverse Cholesky factor of
+// Hbar = (T_i U_ii)(T_i U_ii)^T.
+__global__ __launch_bounds__(256) void gptq_block_mats_kernel(const uint16_t* __restrict__ T, const double* __restrict__ U,
+                                                              int K, int i, double* __restrict__ Tinv,
+                                                              double* __restrict__ R, int* __restrict__ status) {
+  const int t = threadIdx.x;
+  if (blockIdx.x == 0) {
+    const bool good = invert_block_group<32>([&](int r, int c) { return (double)bf16_bits_to_f32(T[32 * r + c]); },
+                                             [&](int r, int c, double v) { Tinv[32 * r + c] = v; });
+    if (!good && t == 0) atomicExch(status, 1);
+    return;
   }
-  if (singular && lane == 0) atomicExch(status, 1);
-  for (int r = 0; r < 32; ++r)
-    if (lane >= 32) Tinv[r * 32 + (lane - 32)] = singular ? 0.0 : a[r][lane];
-  // ---- B = T_i U_ii (U_ii upper triangular), Hbar = B B^T
-  for (int o = lane; o < 1024; o += 64) {
-    Rm[o >> 5][o & 31] = H[(int64_t)(32 * i + (o >> 5)) * K + 32 * i + (o & 31)];
-    Hb[o >> 5][o & 31] = Tb[o];                       // T_i, until Hbar takes its place
+  __shared__ double Tm[32][33], Um[32][33], B[32][33];
+  for (int o = t; o < 1024; o += 256) {
+    Tm[o >> 5][o & 31] = (double)bf16_bits_to_f32(T[o]);
+    Um[o >> 5][o & 31] = U[(int64_t)(32 * i + (o >> 5)) * K + 32 * i + (o & 31)];
   }
   __syncthreads();
-  for (int o = lane; o < 1024; o += 64) {
-    const int r = o >> 5, c = o & 31;
-    double acc = 0.0;
+  double acc[4] = {};
 #pragma unroll 4
-    for (int m = 0; m <= c; ++m) acc = fma(Hb[r][m], Rm[m][c], acc);
-    B[r][c] = acc;
-  }
+  for (int m = 0; m < 32; ++m)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[u] = fma(Tm[(t >> 5) + 8 * u][m], Um[m][t & 31], acc[u]);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) B[(t >> 5) + 8 * u][t & 31] = acc[u];
   __syncthreads();
-  for (int o = lane; o < 1024; o += 64) {
-    const int r = o >> 5, c = o & 31;
-    double acc = 0.0;
-#pragma unroll 8
-    for (int m = 0; m < 32; ++m) acc = fma(B[r][m], B[c][m], acc);
-    Hb[r][c] = acc;
-  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) acc[u] = 0.0;
+#pragma unroll 4
+  for (int m = 0; m < 32; ++m)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[u] = fma(B[(t >> 5) + 8 * u][m], B[t & 31][m], acc[u]);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) Tm[(t >> 5) + 8 * u][t & 31] = acc[u];
   __syncthreads();
-  const bool bad = reverse_cholesky32(Hb, lane);
-  if (__any(bad) && lane == 0) atomicExch(status, 1);
-  upper_inverse32(Hb, Rm, lane);
-  for (int o = lane; o < 1024; o += 64) R[o] = Rm[o >> 5][o & 31];
+  const bool good = reverse_factor_group([&](int r, int c) { return Tm[r][c]; }, [](int, int, double) {},
+                                         [&](int r, int c, double v) { R[32 * r + c] = v; });
+  if (!good && t == 0) atomicExch(status, 1);
 }
 
-// P = U_ii V[block row i][columns past block i]: the inter-block propagation matrix, [32][K]
-__global__ __launch_bounds__(256) void gptq_pmat_kernel(const double* __restrict__ H, const double* __restrict__ V,
-                                                        int K, int i, double* __restrict__ P) {
-  __shared__ double U[32][33];
-  for (int o = threadIdx.x; o < 1024; o += 256) U[o >> 5][o & 31] = H[(int64_t)(32 * i + (o >> 5)) * K + 32 * i + (o & 31)];
-  __syncthreads();
-  const int c = 32 * (i + 1) + blockIdx.x * 256 + threadIdx.x;
-  if (c >= K) return;
-  double v[32];
-#pragma unroll
-  for (int m = 0; m < 32; ++m) v[m] = V[(int64_t)(32 * i + m) * K + c];
-#pragma unroll
-  for (int r = 0; r < 32; ++r) {
-    double acc = 0.0;
-#pragma unroll
-    for (int m = r; m < 32; ++m) acc = fma(U[r][m], v[m], acc);
-    P[(int64_t)r * K + c] = acc;
-  }
-}
-
-// The GPTQ subroutine on the transformed block, one thread per output channel,
-// the codes and scale of the block, and the error in the original space.
-__global__ __launch_bounds__(64) void gptq_quant_kernel(const double* __restrict__ Wf, int N, int K, int i,
-                                                         const double* __restrict__ Tb, const double* __restrict__ Tinv,
-                                                         const double* __restrict__ R, int rule, int tiled,
-                                                         uint8_t* __restrict__ Wq, uint8_t* __restrict__ Ws,
-                                                         double* __restrict__ E) {
-  __shared__ double ti[32][32], tb[32][32], rm[32][32];
-  for (int o = threadIdx.x; o < 1024; o += 64) {
-    ti[o >> 5][o & 31] = Tinv[o];
-    tb[o >> 5][o & 31] = Tb[o];
-    rm[o >> 5][o & 31] = R[o];
-  }
-  __syncthreads();
-  const int n = blockIdx.x * 64 + threadIdx.x;
-  if (n >= N) return;
-  double w[32], y[32];
-  const double* wp = Wf + (int64_t)n * K + 32 * i;
-#pragma unroll
-  for (int k = 0; k < 32; ++k) w[k] = wp[k];
-  double amax = 0.0;
-#pragma unroll
-  for (int j = 0; j < 32; ++j) {
-    double acc = 0.0;
-#pragma unroll
-    for (int k = 0; k < 32; ++k) acc = fma(w[k], ti[k][j], acc);
-    y[j] = acc;
-    amax = fmax(amax, fabs(acc));
-  }
-  const int byte = scale_byte_f64(amax, rule);   // static group scale: taken before any update
-  const double inv_scale = __longlong_as_double((int64_t)(uint64_t)(1023 + 127 - byte) << 52);   // 2^(127-byte)
-  const double scale = __longlong_as_double((int64_t)(uint64_t)(1023 - 127 + byte) << 52);       // 2^(byte-127)
-  double dq[32];
-  uint32_t words[4] = {0, 0, 0, 0};
-#pragma unroll
-  for (int r = 0; r < 32; ++r) {
-#pragma clang fp contract(off)   // the reference subtracts a rounded product: no fused multiply-add here
-    const double v = y[r];
+// One element of the GPTQ subroutine: code of v at the group's scale (in float range: through the hardware converts, which
+// agree with FP64 comparisons, f64_to_f32_sticky), its value.
+template <bool SAFE>
+__device__ __forceinline__ uint32_t gptq_code(double v, float sc, double inv_scale, double scale, double& value) {
+  if constexpr (SAFE) {
+    const uint32_t code = pack2_e2m1<0>(0, f64_to_f32_sticky(v), 0.0f, sc) & 0xFu;
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    const v2f q = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(code, sc, 0);
+    value = (double)q[0];
+    return code;
+  } else {
     const uint32_t sign = (uint32_t)(((uint64_t)__double_as_longlong(v)) >> 63);
     const uint32_t code = e2m1_code_f64(fabs(v) * inv_scale);
-    words[r >> 3] |= ((sign << 3) | code) << (4 * (r & 7));
     const double mag = (code < 4 ? 0.5 * (double)code : (code == 4 ? 2.0 : (code == 5 ? 3.0 : (code == 6 ? 4.0 : 6.0)))) * scale;
-    dq[r] = sign ? -mag : mag;
-    const double err = (v - dq[r]) / rm[r][r];
-#pragma unroll
-    for (int rp = r + 1; rp < 32; ++rp) y[rp] = y[rp] - err * rm[r][rp];
-  }
-  const v4u chunk = {words[0], words[1], words[2], words[3]};
-  if (tiled) {
-    *reinterpret_cast<v4u*>(Wq + tiled_chunk_offset(n, i, K >> 8)) = chunk;
-    Ws[tiled_scale_offset(n, i, K >> 8)] = (uint8_t)byte;
-  } else {
-    *reinterpret_cast<v4u*>(Wq + (int64_t)n * (K / 2) + 16 * i) = chunk;
-    Ws[(int64_t)n * (K / 32) + i] = (uint8_t)byte;
-  }
-  double* e = E + (int64_t)n * 32;
-#pragma unroll
-  for (int k = 0; k < 32; ++k) {
-    double acc = 0.0;
-#pragma unroll
-    for (int j = 0; j < 32; ++j) acc = fma(dq[j], tb[j][k], acc);
-    e[k] = acc - wp[k];   // read again rather than kept in registers through the recurrence
+    value = sign ? -mag : mag;
+    return (sign << 3) | code;
   }
 }
 
-// W[:, columns past block i] += E P, 64 x 64 tile per workgroup
-__global__ __launch_bounds__(256) void gptq_propagate_kernel(double* __restrict__ Wf, int N, int K, int i,
-                                                             const double* __restrict__ E, const double* __restrict__ P) {
-  __shared__ double es[64][33], ps[32][65];
-  const int n0 = blockIdx.y * 64, c0 = 32 * (i + 1) + blockIdx.x * 64;
-  for (int o = threadIdx.x; o < 64 * 32; o += 256) {
-    const int r = o >> 5, m = o & 31;
-    es[r][m] = (n0 + r < N) ? E[(int64_t)(n0 + r) * 32 + m] : 0.0;
-  }
-  for (int o = threadIdx.x; o < 32 * 64; o += 256) {
-    const int m = o >> 6, c = o & 63;
-    ps[m][c] = (c0 + c < K) ? P[(int64_t)m * K + c0 + c] : 0.0;
-  }
-  __syncthreads();
-  // rank-32 update on the FP64 MFMA (16 x 16 x 4): wave w owns rows 16 w .. 16 w + 15 of the tile and its
-  // four 16-column blocks; A[row l16][k l4] is shared by the four, B[k l4][column l16] differs
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int l16 = lane & 15, l4 = lane >> 4;
-  // accumulator element v of column block tc: row l4 + 4 v, column l16.  The weights it updates are
-  // requested before the products, so that the kernel runs at the rate of its memory traffic.
-  double w[4][4];
+struct RowOperands {            // in LDS, the same for the workgroup
+  double r[32][34];             // R
+  double rinv[32];              // 1 / R[r][r]
+};
+
+// The GPTQ subroutine on 16 rows: lane (l16, l4) holds channels 8 l4 ... + 7 of row l16 (y).  The channels go in index
+// order: the lanes l4 = g take their eight steps among themselves, hand the eight errors to the lanes with later channels
+// through LDS, and those subtract them in the same order.  The quotient (v - q) / R[r][r] from the correctly rounded
+// reciprocal, corrected once, is the correctly rounded one (Markstein).  err holds 16 x 8 doubles.
+template <bool SAFE>
+__device__ __forceinline__ uint32_t gptq_subroutine(double (&y)[8], double (&dq)[8], int byte, const RowOperands& op,
+                                                    double* err, int l16, int l4) {
+  const float sc = scale_as_f32(byte);
+  const double inv_scale = __longlong_as_double((int64_t)(uint64_t)(1023 + 127 - byte) << 52);   // 2^(127-byte)
+  const double scale = __longlong_as_double((int64_t)(uint64_t)(1023 - 127 + byte) << 52);       // 2^(byte-127)
+  uint32_t word = 0;
+  for (int g = 0; g < 4; ++g) {
+    if (l4 == g) {
 #pragma unroll
-  for (int tc = 0; tc < 4; ++tc)
+      for (int s = 0; s < 8; ++s) {
+#pragma clang fp contract(off)   // the reference subtracts a rounded product: no fused multiply-add here
+        const int r = 8 * g + s;
+        const double v = y[s];
+        word |= gptq_code<SAFE>(v, sc, inv_scale, scale, dq[s]) << (4 * s);
+        const double a = v - dq[s], q0 = a * op.rinv[r];
+        const double e = __builtin_fma(__builtin_fma(-op.r[r][r], q0, a), op.rinv[r], q0);
+        err[8 * l16 + s] = e;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int n = n0 + 16 * wave + l4 + 4 * v, c = c0 + 16 * tc + l16;
-      w[tc][v] = (n < N && c < K) ? Wf[(int64_t)n * K + c] : 0.0;
+        for (int q = s + 1; q < 8; ++q) {
+          const double p = e * op.r[r][8 * g + q];
+          y[q] = y[q] - p;
+        }
+      }
     }
-  double ev[8];
+    __builtin_amdgcn_wave_barrier();
+    if (l4 > g) {
+      double e[8];
+      load8(err + 8 * l16, e);
 #pragma unroll
-  for (int kk = 0; kk < 8; ++kk) ev[kk] = es[16 * wave + l16][4 * kk + l4];
+      for (int s = 0; s < 8; ++s) {
+#pragma clang fp contract(off)
+        double rr[8];
+        load8(&op.r[8 * g + s][8 * l4], rr);
 #pragma unroll
-  for (int tc = 0; tc < 4; ++tc) {
-    v4d_t acc = {0, 0, 0, 0};
+        for (int q = 0; q < 8; ++q) {
+          const double p = e[s] * rr[q];
+          y[q] = y[q] - p;
+        }
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  return word;
+}
+
+constexpr int kRowWaves = 8;
+struct RowShared {
+  double areas[kRowWaves * kAreaDoubles];
+  RowOperands op;
+  double inv[32][33], tm[32][33], u[32][33], v[32][33];   // inv(T_i), T_i, U_{i,i+1}, -V_{i+1,i+1}
+};
+
+// Block i of all rows (i = -1: none, the first block's moment only): from the current weights to codes, scale and G_i =
+// (deq T)_i - W_i, and on to block i + 1: S += G_i U_{i,i+1} (S_{i+1} is complete then), current weights W - S V, their
+// moment.  Everything of a row stays in the four lanes that hold it (weight_mfma.hpp); a wavefront takes 16 rows at a time.
+// A chain as well: 32 quantize-and-divide steps of some 170 cycles and five block products.  c2: 19 us; as three
+// kernels (moment, quantize with a thread per row, propagate) 90 us.
+// The errors G_i take the place of S_i, which block i has used up.
+__global__ __launch_bounds__(64 * kRowWaves) void gptq_rows_kernel(
+    const uint16_t* __restrict__ W, int64_t ldw, int N, int K, int i, double* __restrict__ S, const double* __restrict__ U,
+    const double* __restrict__ Vd, const uint16_t* __restrict__ T, const double* __restrict__ Tinv,
+    const double* __restrict__ R, int rule, int tiled, uint8_t* __restrict__ Wq, uint8_t* __restrict__ Ws,
+    double* __restrict__ current, double* __restrict__ partial) {
+  extern __shared__ __attribute__((aligned(16))) double smem[];
+  RowShared& sh = *reinterpret_cast<RowShared*>(smem);
+  RowOperands& op = sh.op;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, l4 = lane >> 4;
+  const int next = i + 1, C = K >> 5, tiles = (N + 15) / 16;
+  double* area = sh.areas + wave * kAreaDoubles;
+  if (i >= 0) {
+    for (int o = threadIdx.x; o < 1024; o += 64 * kRowWaves) {
+      const int k = o >> 5, j = o & 31;
+      op.r[k][j] = R[o];
+      sh.inv[k][j] = Tinv[o];
+      sh.tm[k][j] = (double)bf16_bits_to_f32(T[o]);
+      if (next < C) {
+        sh.u[k][j] = U[(int64_t)(32 * i + k) * K + 32 * next + j];
+        sh.v[k][j] = -Vd[(int64_t)next * 1024 + o];
+      }
+    }
+    if (threadIdx.x < 32) op.rinv[threadIdx.x] = 1.0 / R[33 * threadIdx.x];
+    __syncthreads();
+  }
+  // y += w M, M one of the four matrices in LDS (in registers they would take 128 of a lane's 256)
+  auto multiply = [&](const double (*m)[33], const double (&w)[8], double (&y)[8]) {
+    Block32 b;
+    wm::load_block32(b, [&](int k, int j) { return m[k][j]; }, lane);
+    wm::multiply32(b, w, y);
+  };
+  Moment m;
+  for (int t = kRowWaves * blockIdx.x + wave; t < tiles; t += kRowWaves * gridDim.x) {
+    const int n = 16 * t + l16, nc = min(n, N - 1);
+    const uint16_t* wrow = W + (int64_t)nc * ldw + 8 * l4;
+    const int64_t at = (int64_t)nc * 32 + 8 * l4;
+    double wn[8];   // current weights of block i + 1
+    if (i >= 0) {
+      v4u raw = *reinterpret_cast<const v4u*>(wrow + 32 * i), raw_next = {0, 0, 0, 0};
+      double s[8] = {};
+      if (next < C) {
+        raw_next = *reinterpret_cast<const v4u*>(wrow + 32 * next);
+        if (i > 0) load8(S + (int64_t)next * N * 32 + at, s);
+      }
+      double w[8], y[8] = {}, dq[8], g[8];
+      wm::widen8(raw, g);
+      if (i > 0) {
+        load8(current + at, w);
+      } else {
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk)
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ev[kk], ps[4 * kk + l4][16 * tc + l16], acc, 0, 0, 0);
+        for (int q = 0; q < 8; ++q) w[q] = g[q];
+      }
+      multiply(sh.inv, w, y);
+      // static group scale: taken before any update
+      float amax = 0.0f;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int n = n0 + 16 * wave + l4 + 4 * v, c = c0 + 16 * tc + l16;
-      if (n < N && c < K) Wf[(int64_t)n * K + c] = w[tc][v] + acc[v];
+      for (int q = 0; q < 8; ++q) amax = fmaxf(amax, fabsf(f64_to_f32_sticky(y[q])));
+      amax = wm::max_xor32(wm::max_xor16(amax));
+      int byte = scale_byte_f32(amax, rule);
+      uint32_t word;
+      if (!__any(byte < kSafeByteLo || byte > kSafeByteHi)) {
+        word = gptq_subroutine<true>(y, dq, byte, op, area + 16 * 34, l16, l4);
+      } else {
+        double am = 0.0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) am = fmax(am, fabs(y[q]));
+        wm::PairF64 p = wm::pair16(am, am);
+        p = wm::pair32(fmax(p.first, p.second));
+        byte = scale_byte_f64(fmax(p.first, p.second), rule);
+        word = gptq_subroutine<false>(y, dq, byte, op, area + 16 * 34, l16, l4);
+      }
+      if (n < N) {
+        const int KT = K >> 8;
+        uint8_t* cq = tiled ? Wq + tiled_chunk_offset(n, i, KT) : Wq + (int64_t)n * (K / 2) + 16 * i;
+        *reinterpret_cast<uint32_t*>(cq + 4 * l4) = word;
+        if (l4 == 0) Ws[tiled ? tiled_scale_offset(n, i, KT) : (int64_t)n * C + i] = (uint8_t)byte;
+      }
+      if (next < C) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) g[q] = -g[q];
+        multiply(sh.tm, dq, g);
+        if (n < N) store8(S + (int64_t)i * N * 32 + at, g);
+        multiply(sh.u, g, s);
+        wm::widen8(raw_next, wn);
+        multiply(sh.v, s, wn);
+        if (n < N) store8(current + at, wn);
+      }
+    } else {
+      wm::widen8(*reinterpret_cast<const v4u*>(wrow), wn);
+    }
+    if (next < C) {
+      if (n >= N)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) wn[q] = 0.0;
+      m.add(wn, area, l16, l4);
     }
   }
+  if (next < C) m.reduce<kRowWaves>(sh.areas, wave, lane, partial + (int64_t)blockIdx.x * 1024);
 }
 
-__global__ void gptq_reset_status_kernel(int* status) {
-  if (threadIdx.x < 4) status[threadIdx.x] = 0;
-}
-
-constexpr int kMomentSplits = 64;
+// Partial moments of a block: at most this many workgroups of gptq_rows_kernel.
+constexpr int kMomentSplits = 64, kMomentSplitsLarge = 128;
+constexpr int kWarmSplits = 8;
+// From this K on the Hessian's buffer, free behind the factorization, has room for the warm start (V0, its partial
+// moments) and for more partial moments: (32 + 8 * 32) K + 128 * 1024 <= K^2.
+constexpr int64_t kLargeK = 1024;
 
 struct Layout {
-  size_t H, V, Wf, MX, partial, Tb, Tinv, R, P, E, tr, status, total;
+  size_t H, U, S, MX, partial, spare, Tinv, R, Vd, current, tr, status, total;
 };
 
 Layout layout(int64_t N, int64_t K) {
@@ -552,15 +609,15 @@ Layout layout(int64_t N, int64_t K) {
   auto take = [&](size_t doubles) { const size_t o = off; off += (doubles * sizeof(double) + 255) / 256 * 256; return o; };
   const size_t C = (size_t)(K / 32);
   L.H = take((size_t)K * K);
-  L.V = take((size_t)K * K);
-  L.Wf = take((size_t)N * K);
+  L.U = take((size_t)K * K);
+  L.S = take((size_t)N * K);
   L.MX = take(C * 1024);
   L.partial = take((size_t)kMomentSplits * 1024);
-  L.Tb = take(1024);
+  L.spare = take(1024);
   L.Tinv = take(1024);
   L.R = take(1024);
-  L.P = take((size_t)32 * K);
-  L.E = take((size_t)N * 32);
+  L.Vd = take(C * 1024);
+  L.current = take((size_t)N * 32);
   L.tr = take(4);
   L.status = take(4);
   L.total = off;
@@ -584,61 +641,66 @@ hipError_t launch_gptq_prep(const void* W, int64_t N, int64_t K, int64_t ldw, co
   const Layout L = layout(N, K);
   char* base = static_cast<char*>(workspace);
   auto D = [&](size_t off) { return reinterpret_cast<double*>(base + off); };
-  double *H = D(L.H), *V = D(L.V), *Wf = D(L.Wf), *MX = D(L.MX), *partial = D(L.partial), *Tb = D(L.Tb),
-         *Tinv = D(L.Tinv), *R = D(L.R), *P = D(L.P), *E = D(L.E), *tr = D(L.tr);
+  double *H = D(L.H), *U = D(L.U), *S = D(L.S), *MX = D(L.MX), *partial = D(L.partial), *Tinv = D(L.Tinv), *R = D(L.R),
+         *Vd = D(L.Vd), *current = D(L.current), *tr = D(L.tr);
   int* status = reinterpret_cast<int*>(base + L.status);
   const int C = (int)(K / 32), Ki = (int)K, Ni = (int)N;
+  const uint16_t* Wb = static_cast<const uint16_t*>(W);
   uint16_t* Tbits = static_cast<uint16_t*>(T_blocks);
 
-  gptq_reset_status_kernel<<<1, 64, 0, st>>>(status);
-  WUSH_GPTQ_CHECK()
-  gptq_widen_kernel<<<(unsigned)(((int64_t)N * K + 255) / 256), 256, 0, st>>>((const uint16_t*)W, ldw, Ni, Ki, Wf);
-  WUSH_GPTQ_CHECK()
   const unsigned t64 = (unsigned)((K + 63) / 64);
-  gptq_hessian_kernel<<<dim3(t64, t64), 256, 0, st>>>((const uint16_t*)Xc, ldx, (int)Mc, Ki, H);
+  gptq_hessian_kernel<<<dim3(t64, t64), 256, 0, st>>>((const uint16_t*)Xc, ldx, (int)Mc, Ki, H, status);
   WUSH_GPTQ_CHECK()
   gptq_trace_kernel<<<1, 256, 0, st>>>(H, Ki, tr);
   WUSH_GPTQ_CHECK()
   gptq_damp_kernel<<<C, 256, 0, st>>>(H, Ki, lambda, tr, MX);
   WUSH_GPTQ_CHECK()
-  // reverse Cholesky, last block first
-  for (int i = C - 1; i >= 0; --i) {
-    gptq_rchol_diag_kernel<<<1, 64, 0, st>>>(H, Ki, i, status);
+  for (int i = C; i >= 1; --i) {
+    const int64_t pairs = i < C ? (int64_t)i * (i + 1) / 2 - 1 : 0;
+    gptq_rchol_kernel<<<(unsigned)(1 + (pairs + 3) / 4), 256, 0, st>>>(H, U, Vd, Ki, i, status);
     WUSH_GPTQ_CHECK()
-    if (i > 0) {
-      gptq_rchol_panel_kernel<<<(unsigned)((32 * i + 255) / 256), 256, 0, st>>>(H, Ki, i);
+  }
+  static DynamicLdsLimit rows_lds;
+  hipError_t attr = rows_lds.ensure(reinterpret_cast<const void*>(gptq_rows_kernel), (int)sizeof(RowShared));
+  if (attr != hipSuccess) return attr;
+  constexpr int kChainLds = kMostPending * 1024 * (int)sizeof(double);
+  static DynamicLdsLimit chain_lds;
+  attr = chain_lds.ensure(reinterpret_cast<const void*>(gptq_chain_kernel), kChainLds);
+  if (attr != hipSuccess) return attr;
+  const bool large = K >= kLargeK;
+  double* V0 = nullptr;
+  if (large) {
+    partial = H;
+    if (!transform_given) {
+      V0 = H + (size_t)kMomentSplitsLarge * 1024;
+      double* partial0 = V0 + (size_t)C * 1024;
+      gptq_moment0_kernel<<<dim3(kWarmSplits, C), 256, 0, st>>>(Wb, ldw, Ni, partial0);
       WUSH_GPTQ_CHECK()
-      gptq_rchol_update_kernel<<<dim3(i, i), 256, 0, st>>>(H, Ki, i);
+      gptq_warm_kernel<<<C, 256, 0, st>>>(partial0, kWarmSplits, Ni, MX, lambda, V0);
       WUSH_GPTQ_CHECK()
     }
   }
-  gptq_triinv_diag_kernel<<<C, 64, 0, st>>>(H, Ki, V);
-  WUSH_GPTQ_CHECK()
-  gptq_triinv_rows_kernel<<<C, 256, 0, st>>>(H, Ki, C, V);
-  WUSH_GPTQ_CHECK()
-  const int rows_per_split = (int)((N + kMomentSplits - 1) / kMomentSplits);
-  for (int i = 0; i < C; ++i) {
-    if (transform_given) {
-      gptq_fixed_transform_kernel<<<1, 64, 0, st>>>(Tbits + (int64_t)i * 1024, Tb);
-    } else {
-      gptq_moment_kernel<<<kMomentSplits, 256, 0, st>>>(Wf, Ni, Ki, i, rows_per_split, partial);
+  const int64_t tiles = (N + 15) / 16;
+  const int64_t groups = (tiles + kRowWaves - 1) / kRowWaves, most = large ? kMomentSplitsLarge : kMomentSplits;
+  const int splits = (int)(groups < most ? groups : most);
+  for (int i = -1; i < C; ++i) {
+    if (i >= 0) {
+      // workgroup 0: T_i; the others: pending errors, one round of workgroups (one per compute unit, by their LDS)
+      const int columns = pending_columns(i, C);
+      int row_groups = columns > 0 ? (device_cu_count() - 1) / columns : 0;
+      if (row_groups > (tiles + 3) / 4) row_groups = (int)((tiles + 3) / 4);
+      if (columns > 0 && row_groups < 1) row_groups = 1;
+      gptq_chain_kernel<<<(unsigned)(1 + columns * row_groups), 256, kChainLds, st>>>(
+          partial, splits, Ni, Ki, i, MX + (int64_t)i * 1024, lambda, V0 ? V0 + (int64_t)i * 1024 : nullptr,
+          Tbits + (int64_t)i * 1024, transform_given, U, S, row_groups, status);
       WUSH_GPTQ_CHECK()
-      gptq_wush_kernel<<<1, 256, 0, st>>>(partial, kMomentSplits, Ni, MX + (int64_t)i * 1024, lambda,
-                                         Tbits + (int64_t)i * 1024, Tb, status);
-    }
-    WUSH_GPTQ_CHECK()
-    gptq_block_mats_kernel<<<1, 64, 0, st>>>(Tb, H, Ki, i, Tinv, R, status);
-    WUSH_GPTQ_CHECK()
-    gptq_quant_kernel<<<(unsigned)((N + 63) / 64), 64, 0, st>>>(Wf, Ni, Ki, i, Tb, Tinv, R, rule, tiled,
-                                                                  (uint8_t*)Wq, (uint8_t*)Ws, E);
-    WUSH_GPTQ_CHECK()
-    if (i + 1 < C) {
-      const int rest = Ki - 32 * (i + 1);
-      gptq_pmat_kernel<<<(unsigned)((rest + 255) / 256), 256, 0, st>>>(H, V, Ki, i, P);
-      WUSH_GPTQ_CHECK()
-      gptq_propagate_kernel<<<dim3((unsigned)((rest + 63) / 64), (unsigned)((N + 63) / 64)), 256, 0, st>>>(Wf, Ni, Ki, i, E, P);
+      gptq_block_mats_kernel<<<2, 256, 0, st>>>(Tbits + (int64_t)i * 1024, U, Ki, i, Tinv, R, status);
       WUSH_GPTQ_CHECK()
     }
+    gptq_rows_kernel<<<(unsigned)splits, 64 * kRowWaves, sizeof(RowShared), st>>>(Wb, ldw, Ni, Ki, i, S, U, Vd,
+                                                                  Tbits + (int64_t)(i < 0 ? 0 : i) * 1024, Tinv, R, rule, tiled,
+                                                                  (uint8_t*)Wq, (uint8_t*)Ws, current, partial);
+    WUSH_GPTQ_CHECK()
   }
   return hipSuccess;
 }

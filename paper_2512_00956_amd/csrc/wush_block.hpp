@@ -5,21 +5,11 @@
 
 namespace wush {
 
-// 1 / sqrt(x) for a positive normal x: the hardware estimate and two Newton steps (relative error of a
-// few 2^-53; not correctly rounded, which the Jacobi rotations below do not need).
-__device__ __forceinline__ double rsqrt_newton(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  const double hx = 0.5 * x;
-  y = fma(y, fma(-hx * y, y, 0.5), y);
-  y = fma(y, fma(-hx * y, y, 0.5), y);
-  return y;
-}
-
-// 1 / x for a positive normal x: the hardware estimate and two Newton steps (a few 2^-53).
-__device__ __forceinline__ double rcp_newton(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-  y = fma(y, fma(-x, y, 1.0), y);
-  return fma(y, fma(-x, y, 1.0), y);
+// 1 / x for a normal x: the hardware estimate (some 2^-24) and one cubic step (a few 2^-53).
+__device__ __forceinline__ double rcp_refined(double x) {
+  const double y = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, y, 1.0);
+  return fma(y, fma(e, e, e), y);
 }
 
 // The value of x in another lane of the same row of 16, chosen by a DPP control word (no LDS round trip).
@@ -59,71 +49,116 @@ __device__ __forceinline__ double readlane_f64(double x, int lane) {
 
 typedef double v2d __attribute__((ext_vector_type(2)));
 
-// Largest of the keys of the D lanes that hold the rows of a block (the upper lanes repeat them), uniform.
+// Largest of the keys of the D lanes that hold the rows of a block (the upper lanes repeat them), in every lane.
 template <int D>
 __device__ __forceinline__ uint32_t row_group_max(uint32_t x) {
   x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, true));
   x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, true));
   x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, true));
   x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x140, 0xF, 0xF, true));
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)x, 0);
-  return D == 16 ? lo : max(lo, (uint32_t)__builtin_amdgcn_readlane((int)x, 16));
+  if constexpr (D == 32) {
+    const auto s = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = max(s[0], s[1]);
+  }
+  return x;
 }
 
 // A pivot below 1e-290 makes a block singular (the upper word of that FP64 number).
 constexpr uint32_t kPivotKey = 0x03B8F2B1u;
 
-// Inverse of one D x D block (D = 32 or 16) by Gauss-Jordan elimination with partial pivoting on [T | I], by a
+// Inverse of one D x D block (D = 32 or 16) by Gauss-Jordan elimination in place with partial pivoting, by a
 // group of D * D / 4 threads (256 or 64; all of the workgroup).  Thread t owns row t / (D / 4), columns
-// 8 (t % (D / 4)) ... + 7 of the 2 D, in registers.  entry(r, c): element of T; store(r, c, v): element of the
-// inverse (zeros if the block is singular; the result says whether it is regular).
+// 4 (t % (D / 4)) ... + 3, in registers.  entry(r, c): element of T; store(r, c, v): element of the inverse
+// (zeros if the block is singular; the result says whether it is regular).
 // What bounds it is the chain of D dependent steps, so a step is one barrier: every thread publishes its
 // elements (two LDS buffers in turn), and behind the barrier reads the pivot column, the pivot row and its own
-// factor.  Magnitudes are compared by their upper words (20 fraction bits: enough for a pivot).  Rows are not swapped: pos = the position the row would have after the swaps, which decides ties.
-// 32 x 32: 20 us against 91 us for one wavefront that swapped rows in LDS and synchronized per row.
+// factor.  Rows are not swapped: pos = the position the row would have after the swaps.  Pivot candidates are
+// compared by their upper words less 5 bits (15 fraction bits: enough for a pivot), which those 5 bits, the first position,
+// make unique; a singular block is found at the end.  32 x 32: 12 us against 91 us for one wavefront that swapped
+// rows in LDS and synchronized per row.
 template <int D, class EntryFn, class StoreFn>
 __device__ __forceinline__ bool invert_block_group(EntryFn entry, StoreFn store) {
   static_assert(D == 32 || D == 16, "block size");
   constexpr int kTpr = D / 4;                      // threads per row
-  __shared__ __attribute__((aligned(16))) double buf[2][D][2 * D + 2];
-  const int t = threadIdx.x, r = t / kTpr, c0 = 8 * (t % kTpr);
+  __shared__ __attribute__((aligned(16))) double buf[2][D][D + 2];
+  __shared__ int pivot_row[D];
+  const int t = threadIdx.x, r = t / kTpr, c0 = 4 * (t % kTpr);
   const int lane = t & 63, row = lane % D;         // the row whose pivot candidate this lane looks at
-  double a[8];
+  double a[4];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) a[i] = c0 < D ? entry(r, c0 + i) : (c0 - D + i == r ? 1.0 : 0.0);
+  for (int i = 0; i < 4; ++i) a[i] = entry(r, c0 + i);
   int pos = row;
-  bool singular = false;
+  uint32_t least = ~0u, most = 0;
   for (int p = 0; p < D; ++p) {
-    double (*b)[2 * D + 2] = buf[p & 1];
-#pragma unroll
-    for (int i = 0; i < 8; i += 2) *reinterpret_cast<v2d*>(&b[r][c0 + i]) = (v2d){a[i], a[i + 1]};
+    double (*b)[D + 2] = buf[p & 1];
+    *reinterpret_cast<v2d*>(&b[r][c0]) = (v2d){a[0], a[1]};
+    *reinterpret_cast<v2d*>(&b[r][c0 + 2]) = (v2d){a[2], a[3]};
     __syncthreads();
-    const uint32_t key = pos >= p ? (uint32_t)((uint64_t)__double_as_longlong(b[row][p]) >> 32) & 0x7FFFFFFFu : 0u;
+    const double cand = b[row][p], f = b[r][p];
+    const uint32_t mag = (uint32_t)((uint64_t)__double_as_longlong(cand) >> 32) & 0x7FFFFFFFu;
+    const uint32_t key = pos >= p ? (mag & ~31u) | (31u - (uint32_t)pos) : 0u;
     const uint32_t best = row_group_max<D>(key);
-    if (best < kPivotKey || best >= 0x7FF00000u) { singular = true; break; }   // the same in every wave
-    uint64_t ties = __ballot(key == best) & ((1ull << D) - 1);
-    int idx = __builtin_ctzll(ties);
-    int ipos = __builtin_amdgcn_readlane(pos, idx);
-    for (ties &= ties - 1; ties; ties &= ties - 1) {         // equal keys: the row first in position
-      const int k = __builtin_ctzll(ties), kpos = __builtin_amdgcn_readlane(pos, k);
-      if (kpos < ipos) { ipos = kpos; idx = k; }
-    }
+    const int idx = __builtin_ctzll(__ballot(key == best) | (1ull << (D - 1)));   // never past the rows
+    least = min(least, best);
+    most = max(most, best);
+    const double inv_piv = rcp_refined(readlane_f64(cand, idx));
+    const v2d r0 = *reinterpret_cast<const v2d*>(&b[idx][c0]), r1 = *reinterpret_cast<const v2d*>(&b[idx][c0 + 2]);
+    const int ipos = 31 - (int)(best & 31u);
     if (row == idx) pos = p;
     else if (pos == p) pos = ipos;
-    const double inv_piv = rcp_newton(b[idx][p]);
-    const double f = b[r][p];
+    if (t == 0) pivot_row[p] = idx;
+    const double prow[4] = {r0[0], r0[1], r1[0], r1[1]};
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const double prow = b[idx][c0 + i] * inv_piv;
-      a[i] = r == idx ? prow : a[i] - f * prow;
+    for (int i = 0; i < 4; ++i) {
+      // column p of what was T becomes the column of the inverse that the pivot row stands for
+      const double q = c0 + i == p ? inv_piv : prow[i] * inv_piv;
+      const double old = c0 + i == p ? 0.0 : a[i];
+      a[i] = r == idx ? q : old - f * q;
     }
   }
-  const int rpos = singular ? r : __shfl(pos, r, 64);
-  if (c0 >= D) {
+  __syncthreads();
+  const bool good = (least & ~31u) >= (kPivotKey & ~31u) && most < 0x7FF00000u;   // the same in every thread
+  const int rpos = good ? __shfl(pos, r, 64) : r;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) store(rpos, c0 - D + i, singular ? 0.0 : a[i]);
+  for (int i = 0; i < 4; ++i) store(rpos, good ? pivot_row[c0 + i] : c0 + i, good ? a[i] : 0.0);
+  return good;
+}
+
+// Reverse Cholesky factor of a symmetric positive definite 32 x 32 S and its inverse, by 256 threads: S = U U^T with
+// U upper triangular, V = U^-1, from the elimination of [S | I] row by row from the last: with d the diagonal entry
+// of row j of what is left, row j over sqrt(d) is column j of U (left half) and row j of V (right half), and a row
+// r < j loses row j times its own entry over d -- which is row j's entry r, S being symmetric.  Thread t owns row
+// t / 8, columns 8 (t % 8) ... + 7 of the 64; one barrier per row.  Returns false if S is not positive definite (the
+// same in every thread).
+template <class EntryFn, class StoreUFn, class StoreVFn>
+__device__ __forceinline__ bool reverse_factor_group(EntryFn entry, StoreUFn store_u, StoreVFn store_v) {
+  __shared__ __attribute__((aligned(16))) double rowb[2][64];
+  const int t = threadIdx.x, r = t >> 3, c0 = 8 * (t & 7);
+  double a[8], diag = 1.0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] = c0 < 32 ? entry(r, c0 + i) : (c0 - 32 + i == r ? 1.0 : 0.0);
+  bool good = true;
+  for (int j = 31; j >= 0; --j) {
+    double* row = rowb[j & 1];
+    if (r == j) {
+#pragma unroll
+      for (int i = 0; i < 8; i += 2) *reinterpret_cast<v2d*>(&row[c0 + i]) = (v2d){a[i], a[i + 1]};
+    }
+    __syncthreads();
+    double d = row[j];
+    if (!(d > 0.0)) { good = false; d = 1.0; }
+    if (r == j) diag = d;
+    const double f = r < j ? row[r] * rcp_refined(d) : 0.0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) a[i] = fma(-f, row[c0 + i], a[i]);
   }
-  return !singular;
+  const double root = sqrt(diag);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    if (c0 < 32) store_u(c0 + i, r, c0 + i <= r ? a[i] / root : 0.0);
+    else store_v(r, c0 - 32 + i, c0 - 32 + i >= r ? a[i] / root : 0.0);
+  }
+  return good;
 }
 
 // Alg. 1 for one D x D block (D = 32, or 16 for the NVFP4 variant), by a workgroup of 8 D threads:
@@ -133,8 +168,11 @@ __device__ __forceinline__ bool invert_block_group(EntryFn entry, StoreFn store)
 //   magnitude of every column of U positive.
 // load(h, r, c, s): partial sum s (of S_W for h = 0, S_X for h = 1) of entry (r, c) of the second moment,
 // finish(h, sum): the normalized, undamped entry, h = 0 for M_W, 1 for M_X.  T goes out as BF16 bits
-// (T_bits) and, where the pointers are non-null, as FP64 before rounding (T_f64) and as the FP64 value of
-// the rounded matrix (T_rounded), each [D][D] row-major.  A moment that is not positive definite sets *status.
+// (T_bits) and, where the pointer is non-null, as FP64 before rounding (T_f64), each [D][D] row-major.  A moment
+// that is not positive definite sets *status.
+// V0 (may be null): an orthogonal [D][D] the SVD starts from, A V0 in place of A; U and S are the same, and a V0 close
+// to the right singular vectors leaves little for the sweeps to do.  MODE 1 computes such a V0 in place of T (into
+// V_out; the identity where the moments give none) and leaves the status alone.
 //
 // A block is one chain of dependent steps (2 x D columns of the factors, 6 to 8 sweeps of D - 1 Jacobi
 // rounds), so what counts is the latency of a step, and the threads are there to shorten it: a column pair is
@@ -142,10 +180,11 @@ __device__ __forceinline__ bool invert_block_group(EntryFn entry, StoreFn store)
 // four DPP steps), the factors are taken column by column out of registers with one barrier per column, and the
 // products are spread over the whole workgroup.  c2 layer (128 blocks): 201 -> 107 us; a Jacobi round is 850 cycles, of
 // which some 30 dependent FP64 operations and the LDS round trip are nearly all.
-template <int D, class LoadFn, class FinishFn>
+template <int D, int MODE, class LoadFn, class FinishFn>
 __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, int S_W, int S_X, double lambda,
-                                                 uint16_t* __restrict__ T_bits, double* __restrict__ T_f64,
-                                                 double* __restrict__ T_rounded, int* __restrict__ status) {
+                                                 const double* __restrict__ V0, uint16_t* __restrict__ T_bits,
+                                                 double* __restrict__ T_f64, double* __restrict__ V_out,
+                                                 int* __restrict__ status) {
   static_assert(D == 32 || D == 16, "block size");
   constexpr int NT = 8 * D;
   constexpr int kRpl = D / 16;           // rows of a column pair per lane
@@ -160,31 +199,27 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
   __shared__ int again[2];
   const int t = threadIdx.x;
   {
-    // consecutive threads fetch consecutive entries of a row; all of a thread's entries and four of their
-    // partial sums are in flight at a time, added in ascending order
-    constexpr int kPer = 2 * D * D / NT;
-    double acc[kPer];
+    // consecutive threads fetch consecutive entries of a row; a thread's entries of one moment and eight of
+    // their partial sums are in flight at a time, added in ascending order
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) acc[i] = 0.0;
-    const int smax = max(S_W, S_X);
-    for (int s0 = 0; s0 < smax; s0 += 4) {
-      double v[kPer][4];
+    for (int h = 0; h < 2; ++h) {
+      const int splits = h ? S_X : S_W;
+      double acc[kOut];
 #pragma unroll
-      for (int i = 0; i < kPer; ++i) {
-        const int e = t + NT * i, h = e / (D * D);
+      for (int u = 0; u < kOut; ++u) acc[u] = 0.0;
+      for (int s0 = 0; s0 < splits; s0 += 8) {
+        double v[kOut][8];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-          v[i][u] = s0 + u < (h ? S_X : S_W) ? load(h, (e % (D * D)) / D, e % D, s0 + u) : 0.0;
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+          for (int u = 0; u < kOut; ++u) v[u][i] = s0 + i < splits ? load(h, (t + NT * u) / D, (t + NT * u) % D, s0 + i) : 0.0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+          for (int u = 0; u < kOut; ++u) acc[u] += v[u][i];
       }
 #pragma unroll
-      for (int i = 0; i < kPer; ++i)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc[i] += v[i][u];
-    }
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int e = t + NT * i, h = e / (D * D);
-      (h ? LX : LW)[(e % (D * D)) / D][e % D] = finish(h, acc[i]);
+      for (int u = 0; u < kOut; ++u) (h ? LX : LW)[(t + NT * u) / D][(t + NT * u) % D] = finish(h, acc[u]);
     }
   }
   if (t < 2) again[t] = 0;
@@ -217,7 +252,7 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
         __syncthreads();
         double d = col[j];
         if (!(d > 0.0)) { bad = true; d = 1.0; }
-        const double f = col[r] * rcp_newton(d);
+        const double f = col[r] * rcp_refined(d);
         if ((q & 3) == jb) {
           raw[ji] = a[ji];
           diag[ji] = d;
@@ -232,7 +267,7 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
       const double root = sqrt(diag[i]);
       L[r][c0 + i] = r > c0 + i ? raw[i] / root : (r == c0 + i ? root : 0.0);
     }
-    if (__any(bad) && (t & 63) == 0) atomicExch(status, 1);
+    if (MODE == 0 && __any(bad) && (t & 63) == 0) atomicExch(status, 1);
   }
   __syncthreads();
   // ---- A = W'^T X':  A[i][j] = sum_k W'[k][i] X'[k][j], stored by columns
@@ -248,6 +283,22 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
         acc[u] = fma(LW[k][o % D], LX[k][o / D], acc[u]);   // zeros above the diagonals
       }
     }
+#pragma unroll
+    for (int u = 0; u < kOut; ++u) A[(t + NT * u) / D][(t + NT * u) % D] = acc[u];
+  }
+  if (V0) {   // the same for the whole workgroup
+#pragma unroll
+    for (int u = 0; u < kOut; ++u) U[(t + NT * u) / D][(t + NT * u) % D] = V0[t + NT * u];
+    __syncthreads();
+    double acc[kOut];
+#pragma unroll
+    for (int u = 0; u < kOut; ++u) acc[u] = 0.0;
+#pragma unroll 4
+    for (int k = 0; k < D; ++k) {
+#pragma unroll
+      for (int u = 0; u < kOut; ++u) acc[u] = fma(A[k][(t + NT * u) % D], U[k][(t + NT * u) / D], acc[u]);
+    }
+    __syncthreads();
 #pragma unroll
     for (int u = 0; u < kOut; ++u) A[(t + NT * u) / D][(t + NT * u) % D] = acc[u];
   }
@@ -364,6 +415,46 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
     for (int i = 0; i < kRpl; ++i) U[kRpl * sub + i][c] = (first & 1) ? -v[i] : v[i];
   }
   __syncthreads();
+  if constexpr (MODE == 1) {
+    // V = A^T U S^-1 = X'^T (W' U) S^-1, made orthogonal to FP64 accuracy by one Newton-Schulz step
+    // V (3 I - V^T V) / 2; the identity if it is not close to orthogonal (a singular moment)
+    auto product = [&](auto left, auto right, double (&acc)[kOut]) {
+#pragma unroll
+      for (int u = 0; u < kOut; ++u) acc[u] = 0.0;
+#pragma unroll 4
+      for (int k = 0; k < D; ++k) {
+#pragma unroll
+        for (int u = 0; u < kOut; ++u) acc[u] = fma(left((t + NT * u) / D, k), right(k, (t + NT * u) % D), acc[u]);
+      }
+    };
+    double acc[kOut], v[kOut];
+    product([&](int r, int k) { return LW[r][k]; }, [&](int k, int c) { return U[k][c]; }, acc);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kOut; ++u) A[(t + NT * u) / D][(t + NT * u) % D] = acc[u] / ssort[(t + NT * u) % D];
+    __syncthreads();
+    product([&](int r, int k) { return LX[k][r]; }, [&](int k, int c) { return A[k][c]; }, v);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kOut; ++u) U[(t + NT * u) / D][(t + NT * u) % D] = v[u];
+    if (t == 0) again[0] = 0;
+    __syncthreads();
+    product([&](int r, int k) { return U[k][r]; }, [&](int k, int c) { return U[k][c]; }, acc);
+#pragma unroll
+    for (int u = 0; u < kOut; ++u) {
+      const int r = (t + NT * u) / D, c = (t + NT * u) % D;
+      if (!(fabs(acc[u] - (r == c ? 1.0 : 0.0)) < 1e-3)) again[0] = 1;
+      LW[r][c] = acc[u];
+    }
+    __syncthreads();
+    product([&](int r, int k) { return U[r][k]; }, [&](int k, int c) { return LW[k][c]; }, acc);
+#pragma unroll
+    for (int u = 0; u < kOut; ++u) {
+      const int r = (t + NT * u) / D, c = (t + NT * u) % D;
+      V_out[t + NT * u] = again[0] ? (r == c ? 1.0 : 0.0) : 1.5 * v[u] - 0.5 * acc[u];
+    }
+    return;
+  }
   // ---- B = diag(s^-1/2) U^T W'^T :  B[i][k] = s_i^-1/2 sum_m U[m][i] W'[k][m]
   {
     double acc[kOut];
@@ -406,7 +497,6 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
     const uint16_t bits = f64_to_bf16_bits(v);
     T_bits[o] = bits;
     if (T_f64) T_f64[o] = v;
-    if (T_rounded) T_rounded[o] = (double)bf16_bits_to_f32(bits);
   }
 }
 

@@ -171,3 +171,29 @@ def test_gptq_c2_full_size(P, G):
     t2 = time.perf_counter()
     print(f"c2 GPTQ case: GPU call incl. transfers {t1 - t0:.2f} s, oracle {t2 - t1:.1f} s")
     _compare(T_gpu, c_gpu, s_gpu, T_ref, c_ref, s_ref, W, X, "c2")
+
+
+# sizes at the edges of the kernels: one row and one block; more rows than one pass of the row workgroups takes (64 of
+# 128 rows below K = 1024); K from 1024 on (warm-started SVD, buffers inside the Hessian's) with an odd number of blocks and
+# fewer rows than a wavefront's tile; every position inside the groups of blocks whose errors travel together
+@pytest.mark.parametrize("N,K,Mc", [(1, 32, 64), (9000, 64, 128), (13, 1056, 300), (40, 32 * 11, 400)])
+def test_gptq_edge_sizes(P, G, N, K, Mc):
+    W, Xc, X = _layer(64, K, N, Mc)
+    T, c, s = _run_gpu(P, G, W, Xc, 1e-2)
+    Tr, cr, sr = Q.gptq_wush_layer(W, Xc, 1e-2)
+    _compare(T, c, s, Tr, cr, sr, W, X, f"N={N} K={K}")
+
+
+def test_gptq_scales_beyond_float_range(P, G):
+    """Rows whose group maxima lie outside the range the 32-bit decisions cover (scale bytes below 8), a zero row."""
+    rng = np.random.default_rng(11)
+    N, K = 48, 128
+    W = np.ldexp(rng.standard_normal((N, K)), np.round(np.linspace(-131, -100, N)).astype(int)[:, None])
+    W[7] = 0.0
+    W = O.round_to_bf16(W)
+    Xc = O.round_to_bf16(rng.standard_normal((400, K)))
+    T0 = np.broadcast_to(O.round_to_bf16(O.hadamard()), (K // 32, 32, 32)).copy()
+    T, c, s = _run_gpu(P, G, W, Xc, 1e-2, T_given=T0)
+    _, cr, sr = Q.gptq_wush_layer(W, Xc, 1e-2, transform="hadamard")
+    same = (c == cr) | (((c & 7) == 0) & ((cr & 7) == 0))      # +-0 have one magnitude
+    assert np.mean(s != sr) <= 1e-4 and np.mean(~same) <= 1e-4, (np.mean(s != sr), np.mean(~same))
