@@ -209,11 +209,10 @@ wush_status wush_prepare_weight_gptq_status(const void* workspace, int64_t N, in
  *   Wq, Ws   in   u8 [N][K/2], u8 [N][K/32]
  *   Y        out  [M][ldy], bf16 (fmt.out_dtype == WUSH_OUT_BF16, rounded to
  *                 nearest even from the FP32 accumulator) or f32
- * ldy >= N (elements); Y aligned to its element size.  The tiled kernel needs
- * Y 16-byte aligned and ldy a multiple of 8; other layouts take a slower
- * general kernel.  In the tiled layout M <= 64 (and M <= 128 unless the layer is
- * very large) takes a weight-streaming kernel
- * (one workgroup per 32 output channels) instead of 256 x 256 tiles.
+ * ldy >= N (elements); Y aligned to its element size.  Both layouts store 16 bytes at a time
+ * where Y is 16-byte aligned and its rows keep that alignment, element by element otherwise.
+ * In the tiled layout M <= 64 (and M <= 128 unless the layer is very large) takes a
+ * weight-streaming kernel (one workgroup per 32 output channels) instead of 256 x 256 tiles.
  */
 wush_status wush_linear(const void* Xq, const void* Xs, const void* Wq, const void* Ws,
                         int64_t M, int64_t N, int64_t K, wush_fmt fmt,
@@ -462,9 +461,10 @@ wush_status wush_unpack_tiled(const void* q_tiled, const void* s_tiled, int64_t 
  * library would otherwise choose by itself.  Process-wide, read by every later call on any
  * thread; value -1 restores the library's own choice.  Results do not depend on them beyond
  * the accumulation order of a GEMM; nothing reads the environment.
- *   WUSH_DEBUG_GEMM_TILE            wush_linear, tiled layout: 0..3 = 256x256, 128x384, 128x256, 128x128 tiles
+ *   WUSH_DEBUG_GEMM_TILE            wush_linear, tiled layout: 0..3 = 256x256, 128x384, 128x256, 128x128 tiles; canonical
+ *                                   layout: 0..4 = 256x256, 128x128, 128x128 with more steps in flight, 64x128, 64x64
  *   WUSH_DEBUG_GEMM_SKINNY          wush_linear up to 128 tokens: 1 = weight-streaming kernel, 0 = tiled kernel
- *   WUSH_DEBUG_GEMM_SIMPLE          wush_linear, canonical layout: 1 = the general one-wave-per-tile kernel
+ *   WUSH_DEBUG_GEMM_SIMPLE          wush_linear, canonical layout: 1 = the reference-grade one-wave-per-tile kernel
  *   WUSH_DEBUG_W4_WIDTH             wush_linear_nvfp4 / _int4: tile width 2..4 (x 64 output channels)
  *   WUSH_DEBUG_W4_SKINNY            wush_linear_nvfp4 / _int4 up to 128 tokens: 0 = tiled kernel; weight-streaming kernel with
  *                                   1 = K split over a workgroup's waves, 2 = activations shared through LDS (65..128 tokens;

@@ -167,10 +167,10 @@ __global__ __launch_bounds__(kWaves * TG * 64, (TG == 2 || DBG) ? 2 : 3) void in
         uint8_t* q = Xq + (int64_t)m * (K / 2) + 16 * bfirst + 32 * h;
         uint16_t* sp = reinterpret_cast<uint16_t*>(Xs) + (int64_t)m * C + bfirst;
         if (nb == kNB && (C & 3) == 0) {
-          __builtin_nontemporal_store(out[0], reinterpret_cast<v4u*>(q));
-          __builtin_nontemporal_store(out[1], reinterpret_cast<v4u*>(q + 16));
+          *reinterpret_cast<v4u*>(q) = out[0];
+          *reinterpret_cast<v4u*>(q + 16) = out[1];
           if (h == 0)
-            __builtin_nontemporal_store((v2u){sc[0] | sc[1] << 16, sc[2] | sc[3] << 16}, reinterpret_cast<v2u*>(sp));
+            *reinterpret_cast<v2u*>(sp) = (v2u){sc[0] | sc[1] << 16, sc[2] | sc[3] << 16};
         } else {
 #pragma unroll
           for (int p = 0; p < 2; ++p)

@@ -213,9 +213,9 @@ __global__ __launch_bounds__(kWaves * TG * 64, (TG == 2 || DBG) ? 2 : 3) void nv
         uint8_t* q = Xq + (int64_t)m * (K / 2) + 16 * bfirst + 32 * h;
         uint8_t* sp = Xs + (int64_t)m * (K / 16) + 2 * bfirst;
         if (nb == kNB && (C32 & 3) == 0) {
-          __builtin_nontemporal_store(out[0], reinterpret_cast<v4u*>(q));
-          __builtin_nontemporal_store(out[1], reinterpret_cast<v4u*>(q + 16));
-          if (h == 0) __builtin_nontemporal_store(scales, reinterpret_cast<v2u*>(sp));
+          *reinterpret_cast<v4u*>(q) = out[0];
+          *reinterpret_cast<v4u*>(q + 16) = out[1];
+          if (h == 0) *reinterpret_cast<v2u*>(sp) = scales;
         } else {
           // ragged tail of the channel dimension: chunks 2h and 2h+1 of this lane
 #pragma unroll

@@ -85,6 +85,9 @@ hipError_t launch_build_transforms(const void* W, int64_t N, int64_t ldw, const 
                                    hipStream_t stream);   // block = 32, or 16 for the NVFP4 variant
 
 // Operands in the fragment-order layout (K % 256 == 0).
+hipError_t launch_mxfp4_gemm_canon(const void* Xq, const void* Xs, const void* Wq, const void* Ws,
+                                   int64_t M, int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy,
+                                   hipStream_t stream);
 hipError_t launch_mxfp4_gemm_frag(const void* Xq, const void* Xs, const void* Wq, const void* Ws,
                                   int64_t M, int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy,
                                   hipStream_t stream);
