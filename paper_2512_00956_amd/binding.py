@@ -1,10 +1,11 @@
-"""ctypes binding of include/wush.h: argument marshalling only.
+"""Binding of include/wush.h: argument marshalling only.
 
 Tensor arguments are torch tensors on the GPU (torch is used for device memory
 and streams); each wrapper passes `data_ptr()`s, sizes and the current HIP
 stream to the C entry point of the same name and raises `WushError` on a
-non-zero status.  No fallback exists: if `libwush.so` is missing the first call
-raises.
+non-zero status.  The entry points a program calls every step go through the
+extension module `_wush_call` (csrc/py_call.cpp), the others through ctypes.  No
+fallback exists: if `libwush.so` or the module is missing the first call raises.
 """
 from __future__ import annotations
 
@@ -164,6 +165,18 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+_fast = None
+
+
+def _load_fast():
+    """The extension module of the per-step calls (loads it on first use; it links to the libwush.so beside it)."""
+    global _fast
+    lib()
+    from . import _wush_call
+    _fast = _wush_call
+    return _fast
+
+
 def default_fmt(scale_rule: int = WUSH_SCALE_NOSAT, out_dtype: int = WUSH_OUT_BF16,
                 layout: int = WUSH_LAYOUT_CANONICAL) -> WushFmt:
     f = lib().wush_default_fmt()
@@ -207,6 +220,33 @@ def _stream(stream):
     return c_void_p(stream if isinstance(stream, int) else stream.cuda_stream)
 
 
+_raw_stream = None
+
+
+def _current_stream() -> int:
+    """torch's current stream of the current device as an integer (torch.cuda.current_stream().cuda_stream, without
+    building the Stream object)."""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        torch.cuda.current_stream()              # initializes CUDA, or says why it cannot
+        device = getattr(torch._C, "_cuda_getDevice", None)
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if device is None or raw is None:
+            def _raw_stream():
+                return torch.cuda.current_stream().cuda_stream
+        else:
+            def _raw_stream():
+                return raw(device())
+    return _raw_stream()
+
+
+def _handle(stream) -> int:
+    if stream is None:
+        return _current_stream()
+    return stream if isinstance(stream, int) else stream.cuda_stream
+
+
 def _check(code: int, where: str):
     if code != 0:
         raise WushError(code, where)
@@ -215,9 +255,9 @@ def _check(code: int, where: str):
 def wush_quantize_act(X, T_blocks, Xq, Xs, fmt: WushFmt | None = None, dbg_Yt=None, stream=None):
     """X bf16 [M][K] (row stride X.stride(0)), T_blocks bf16 [K/32][32][32] ->
     Xq u8 [M][K/2], Xs u8 [M][K/32] (pre-allocated by the caller)."""
-    M, K = X.shape
-    _check(lib().wush_quantize_act(_ptr(X), M, K, X.stride(0), _ptr(T_blocks), fmt or default_fmt(),
-                                   _ptr(Xq), _ptr(Xs), _ptr(dbg_Yt), _stream(stream)), "wush_quantize_act")
+    code = (_fast or _load_fast()).quantize_act(X, T_blocks, Xq, Xs, fmt or None, dbg_Yt, _handle(stream))
+    if code:
+        raise WushError(code, "wush_quantize_act")
 
 
 def wush_prepare_weight_workspace(N: int, K: int) -> int:
@@ -242,11 +282,9 @@ def wush_linear(Xq, Xs, Wq, Ws, Y, fmt: WushFmt | None = None, stream=None, K: i
     """Y [M][N] (bf16 or f32 per fmt.out_dtype, row stride Y.stride(0)) =
     deq(Xq, Xs) . deq(Wq, Ws)^T.  M and N come from Y; K from the canonical
     shape of Xq unless given (the tiled layout has no 2-D shape to read it from)."""
-    M, N = Y.shape
-    if K is None:
-        K = 2 * Xq.shape[-1]
-    _check(lib().wush_linear(_ptr(Xq), _ptr(Xs), _ptr(Wq), _ptr(Ws), M, N, K, fmt or default_fmt(),
-                             _ptr(Y), Y.stride(0), _stream(stream)), "wush_linear")
+    code = (_fast or _load_fast()).linear(Xq, Xs, Wq, Ws, Y, fmt or None, _handle(stream), K)
+    if code:
+        raise WushError(code, "wush_linear")
 
 
 def wush_build_transforms_workspace(K: int) -> int:
@@ -302,21 +340,17 @@ def wush_layer_decode_init(workspace, K: int, stream=None):
 def wush_layer_decode(X, T_blocks, Wq, Ws, Y, workspace, fmt: WushFmt | None = None, stream=None):
     """One-launch layer forward for M <= 64 tokens: X bf16 [M][K], prepared tiled
     weights Wq/Ws -> Y [M][N] (N from Y)."""
-    M, K = X.shape
-    N = Y.shape[1]
-    _check(lib().wush_layer_decode(_ptr(X), M, K, X.stride(0), _ptr(T_blocks), _ptr(Wq), _ptr(Ws), N,
-                                   fmt or default_fmt(layout=WUSH_LAYOUT_TILED), _ptr(Y), Y.stride(0),
-                                   _ptr(workspace), _nbytes(workspace), _stream(stream)), "wush_layer_decode")
+    code = (_fast or _load_fast()).layer_decode(X, T_blocks, Wq, Ws, Y, workspace, fmt or None, _handle(stream))
+    if code:
+        raise WushError(code, "wush_layer_decode")
 
 
 def wush_layer_decode_static(X, T_blocks, Wq, Ws, Y, fmt: WushFmt | None = None, stream=None):
     """wush_layer_decode without a workspace (K <= 32768): the library's own fixed scratch holds the
     quantized activations; allocates nothing."""
-    M, K = X.shape
-    N = Y.shape[1]
-    _check(lib().wush_layer_decode_static(_ptr(X), M, K, X.stride(0), _ptr(T_blocks), _ptr(Wq), _ptr(Ws), N,
-                                          fmt or default_fmt(layout=WUSH_LAYOUT_TILED), _ptr(Y), Y.stride(0),
-                                          _stream(stream)), "wush_layer_decode_static")
+    code = (_fast or _load_fast()).layer_decode_static(X, T_blocks, Wq, Ws, Y, fmt or None, _handle(stream))
+    if code:
+        raise WushError(code, "wush_layer_decode_static")
 
 
 def wush_layer_decode_status(workspace, K: int, stream=None):
@@ -352,9 +386,9 @@ def wush_quantize_act_nvfp4(X, T16, tensor_scale, Xq, Xs, layout: int = WUSH_LAY
                             stream=None):
     """X bf16 [M][K] -> Xq u8 [M][K/2], Xs u8 [M][K/16] (canonical shapes); tensor_scale: float32 tensor
     (1 element, GPU)."""
-    M, K = X.shape
-    _check(lib().wush_quantize_act_nvfp4(_ptr(X), M, K, X.stride(0), _ptr(T16), _ptr(tensor_scale), layout, _ptr(Xq),
-                                         _ptr(Xs), _ptr(dbg_Yt), _stream(stream)), "wush_quantize_act_nvfp4")
+    code = (_fast or _load_fast()).quantize_act_nvfp4(X, T16, tensor_scale, Xq, Xs, layout, dbg_Yt, _handle(stream))
+    if code:
+        raise WushError(code, "wush_quantize_act_nvfp4")
 
 
 def wush_calibrate_act_nvfp4(X, T16, tensor_scale, stream=None):
@@ -386,11 +420,9 @@ def wush_prepare_weight_nvfp4_status(workspace, K: int, stream=None):
 def wush_linear_nvfp4(Xq, Xs, tsx, Wq, Ws, tsw, Y, layout: int = WUSH_LAYOUT_CANONICAL,
                       out_dtype: int = WUSH_OUT_BF16, stream=None, K: int | None = None):
     """Y [M][N] = tsx tsw deq(Xq, Xs) . deq(Wq, Ws)^T; K from the canonical shape of Xq unless given."""
-    M, N = Y.shape
-    if K is None:
-        K = 2 * Xq.shape[-1]
-    _check(lib().wush_linear_nvfp4(_ptr(Xq), _ptr(Xs), _ptr(tsx), _ptr(Wq), _ptr(Ws), _ptr(tsw), M, N, K, layout,
-                                   out_dtype, _ptr(Y), Y.stride(0), _stream(stream)), "wush_linear_nvfp4")
+    code = (_fast or _load_fast()).linear_nvfp4(Xq, Xs, tsx, Wq, Ws, tsw, Y, layout, out_dtype, _handle(stream), K)
+    if code:
+        raise WushError(code, "wush_linear_nvfp4")
 
 
 def wush_quantize_f32_nvfp4(Yt, tensor_scale, q, s, layout: int = WUSH_LAYOUT_CANONICAL, stream=None):
@@ -419,9 +451,9 @@ def wush_unpack_tiled_nvfp4(q_tiled, s_tiled, rows: int, K: int, q, s, stream=No
 # ---------------------------------------------------------------------------
 def wush_quantize_act_int4(X, T_blocks, Xq, Xs, layout: int = WUSH_LAYOUT_CANONICAL, dbg_Yt=None, stream=None):
     """X bf16 [M][K] -> Xq u8 [M][K/2], Xs: BF16 scales [M][K/32] (2 bytes each; canonical shapes)."""
-    M, K = X.shape
-    _check(lib().wush_quantize_act_int4(_ptr(X), M, K, X.stride(0), _ptr(T_blocks), layout, _ptr(Xq), _ptr(Xs),
-                                        _ptr(dbg_Yt), _stream(stream)), "wush_quantize_act_int4")
+    code = (_fast or _load_fast()).quantize_act_int4(X, T_blocks, Xq, Xs, layout, dbg_Yt, _handle(stream))
+    if code:
+        raise WushError(code, "wush_quantize_act_int4")
 
 
 def wush_prepare_weight_int4(W, T_blocks, Wq, Ws, workspace, layout: int = WUSH_LAYOUT_CANONICAL, stream=None):
@@ -436,11 +468,9 @@ def wush_prepare_weight_int4(W, T_blocks, Wq, Ws, workspace, layout: int = WUSH_
 def wush_linear_int4(Xq, Xs, Wq, Ws, Y, layout: int = WUSH_LAYOUT_CANONICAL, out_dtype: int = WUSH_OUT_BF16,
                      stream=None, K: int | None = None):
     """Y [M][N] = deq(Xq, Xs) . deq(Wq, Ws)^T; K from the canonical shape of Xq unless given."""
-    M, N = Y.shape
-    if K is None:
-        K = 2 * Xq.shape[-1]
-    _check(lib().wush_linear_int4(_ptr(Xq), _ptr(Xs), _ptr(Wq), _ptr(Ws), M, N, K, layout, out_dtype, _ptr(Y),
-                                  Y.stride(0), _stream(stream)), "wush_linear_int4")
+    code = (_fast or _load_fast()).linear_int4(Xq, Xs, Wq, Ws, Y, layout, out_dtype, _handle(stream), K)
+    if code:
+        raise WushError(code, "wush_linear_int4")
 
 
 def wush_quantize_f32_int4(Yt, q, s, layout: int = WUSH_LAYOUT_CANONICAL, stream=None):

@@ -1,5 +1,6 @@
 """Builds libwush.so (gfx950 only) in-tree with hipcc, and beside it libwush_probes.so, the
-benchmark's measurement aids (MFMA-only and streaming kernels: not part of the layer path).
+benchmark's measurement aids (MFMA-only and streaming kernels: not part of the layer path), and
+_wush_call.so, the Python module of the per-step calls.
 
 Usage: python -m paper_2512_00956_amd.build
 """
@@ -9,11 +10,14 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libwush.so")
+CALL_SRC = os.path.join(CSRC, "py_call.cpp")
+CALL_LIB = os.path.join(HERE, "_wush_call.so")
 PROBES_SRC = os.path.join(HERE, "probes", "probes.hip")
 PROBES_LIB = os.path.join(HERE, "libwush_probes.so")
 SOURCES = ["wush_api.hip", "transform_quant.hip", "weight_prep.hip", "mxfp4_gemm.hip", "mxfp4_gemm_frag.hip", "mxfp4_gemm_canon.hip", "build_transforms.hip", "layer_decode.hip", "gptq_prep.hip", "nvfp4_quant.hip", "nvfp4_gemm.hip", "int4_quant.hip", "w4_gemm_skinny.hip"]
@@ -77,6 +81,14 @@ def build(verbose: bool = False) -> str:
         if r.returncode != 0:
             raise RuntimeError(f"link failed:\n{r.stdout}")
         os.replace(tmp, lib)
+    # the Python module of the per-step calls: host code only, finds libwush.so beside itself
+    tmp = CALL_LIB + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"], "-I",
+           os.path.join(ROOT, "include"), CALL_SRC, "-o", tmp, "-L", HERE, "-lwush", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on py_call.cpp:\n{r.stdout}")
+    os.replace(tmp, CALL_LIB)
     return LIB
 
 

@@ -1,0 +1,59 @@
+"""The extension module of the per-step calls marshals as the ctypes binding does: every call with all arguments valid but
+an impossible size (no kernel is launched, so no GPU is needed) returns the C library's status; wrong argument
+kinds raise and leave nothing behind."""
+import pytest
+import torch
+
+import paper_2512_00956_amd.binding as P
+
+
+@pytest.fixture(scope="module")
+def F():
+    return P._load_fast()
+
+
+def _t(*shape, dtype=torch.uint8):
+    return torch.zeros(shape, dtype=dtype)
+
+
+X, Y, T, Q, S = _t(4, 40, dtype=torch.bfloat16), _t(4, 64, dtype=torch.bfloat16), _t(64), _t(4, 20), _t(64)
+CALLS = [
+    ("quantize_act", (X, T, Q, S, None, None, 0)),
+    ("linear", (Q, S, Q, S, Y, None, 0, None)),
+    ("linear", (Q, S, Q, S, Y, P.default_fmt(layout=1), 0, 40)),
+    ("layer_decode", (X, T, Q, S, Y, S, None, 0)),
+    ("layer_decode_static", (X, T, Q, S, Y, None, 0)),
+    ("quantize_act_nvfp4", (X, T, T, Q, S, 0, None, 0)),
+    ("linear_nvfp4", (Q, S, T, Q, S, T, Y, 0, 0, 0, None)),
+    ("quantize_act_int4", (X, T, Q, S, 0, None, 0)),
+    ("linear_int4", (Q, S, Q, S, Y, 0, 0, 0, None)),
+]
+
+
+@pytest.mark.parametrize("name,args", CALLS)
+def test_status_of_an_impossible_size(F, name, args):
+    assert getattr(F, name)(*args) == 2                       # K = 40: WUSH_ERR_SHAPE
+    null = (None,) + args[1:] if name.startswith("linear") and args[-1] is not None else None
+    if null:
+        assert getattr(F, name)(*null) == 1                   # WUSH_ERR_NULL
+
+
+@pytest.mark.parametrize("name,args", CALLS)
+def test_wrong_arguments_raise(F, name, args):
+    fn = getattr(F, name)
+    with pytest.raises(TypeError):
+        fn(*args[:-1])
+    with pytest.raises(AttributeError):
+        fn(*((object(),) + args[1:]))
+    with pytest.raises((TypeError, AttributeError)):
+        fn(*(args[:-1] + ("x",)))
+
+
+def test_format_descriptor_is_checked(F):
+    with pytest.raises((TypeError, BufferError)):
+        F.linear(Q, S, Q, S, Y, b"short", 0, 40)
+    bad = P.default_fmt()
+    bad.block = 16
+    assert F.linear(Q, S, Q, S, Y, bad, 0, 64) == 4           # WUSH_ERR_FMT
+    with pytest.raises(ValueError):
+        F.quantize_act(_t(4), T, Q, S, None, None, 0)
