@@ -123,6 +123,7 @@ __device__ __forceinline__ void accumulate_block(v16f (&acc)[RB], FragTile (&w)[
   }
 }
 
+// Row blocks RB blockIdx.y ... of the tokens.
 template <int RB, bool OUT_F32>
 __global__ __launch_bounds__(kWaves * 64) void gemm_skinny_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const uint8_t* __restrict__ Wq,
@@ -131,6 +132,11 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_skinny_kernel(
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int KT = K >> 8, NB = (N + 31) >> 5;
+  const int64_t row_block = (int64_t)RB * blockIdx.y;
+  Xq += row_block * KT * 4096;
+  Xs += row_block * KT * 256;
+  Y = static_cast<uint8_t*>(Y) + 32 * row_block * ldy * (OUT_F32 ? 4 : 2);
+  M -= 32 * (int)row_block;
   int kt0, kt1;
   wave_k_range(KT, wave, kt0, kt1);
   for (int j = blockIdx.x; j < NB; j += gridDim.x) {
@@ -272,18 +278,33 @@ hipError_t resident_limit(Kern kern, int* limit) {
 
 }  // namespace
 
+// Row blocks of 32 tokens a workgroup takes.  A workgroup reads all of its tokens' activations for every 32 output
+// channels, so beyond 32 tokens it is bound by that traffic into its compute unit: while the layer has too few blocks of
+// output channels for all of them, the tokens are dealt out as well, as finely as one workgroup per compute unit allows
+// (us, all tokens in one workgroup | two groups | one group per 32 tokens: 100 x 14336 -> 4096 16.4 | 12.8 | 15.2;
+// 64 x 14336 -> 4096 12.3 | - | 10.2; 128 x 4096 -> 4096 7.7 | 6.1 | 6.2; 100 x 8192 -> 1024 8.8 | 6.7 | 5.2; with more
+// groups than compute units the weights' second trip costs more than it saves: 128 x 28672 -> 8192 43.7 | 49.6 | 73.7).
+// Eight waves per workgroup instead of four (deeper split of K) gave nothing.
+int skinny_row_blocks(int64_t M, int64_t N) {
+  const int64_t blocks = (N + 31) / 32, tokens = (M + 31) / 32, cus = device_cu_count();
+  if (M <= 32 || blocks * tokens <= cus) return 1;
+  if (M <= 64 || blocks * ((tokens + 1) / 2) <= cus) return 2;
+  return 4;
+}
+
 hipError_t launch_mxfp4_gemm_skinny(const void* Xq, const void* Xs, const void* Wq, const void* Ws, int64_t M,
                                     int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy, hipStream_t stream) {
   const int NB = (int)((N + 31) / 32);
-  dim3 grid((unsigned)(NB < 4096 ? NB : 4096)), block(kWaves * 64);
   const int vec = decode_vec_store(Y, N, ldy, out_f32);
+  const int rb = skinny_row_blocks(M, N), groups = (int)((M + 32 * rb - 1) / (32 * rb));
+  dim3 grid((unsigned)(NB < 4096 ? NB : 4096), (unsigned)groups), block(kWaves * 64);
 #define WUSH_SKINNY_LAUNCH(RB, F32)                                                                         \
   gemm_skinny_kernel<RB, F32><<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs,           \
                                                           (const uint8_t*)Wq, (const uint8_t*)Ws, (int)M,   \
                                                           (int)N, (int)K, Y, ldy, vec)
-  if (M <= 32) {
+  if (rb == 1) {
     if (out_f32) WUSH_SKINNY_LAUNCH(1, true); else WUSH_SKINNY_LAUNCH(1, false);
-  } else if (M <= 64) {
+  } else if (rb == 2) {
     if (out_f32) WUSH_SKINNY_LAUNCH(2, true); else WUSH_SKINNY_LAUNCH(2, false);
   } else {
     if (out_f32) WUSH_SKINNY_LAUNCH(4, true); else WUSH_SKINNY_LAUNCH(4, false);

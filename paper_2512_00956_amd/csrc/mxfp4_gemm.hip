@@ -77,19 +77,21 @@ hipError_t launch_mxfp4_gemm(const void* Xq, const void* Xs, const void* Wq, con
     // the tiled kernel with one row of 128-row tiles.  Up to 32 tokens the streaming kernel always
     // wins or ties.  Beyond, whichever the timing models below put first; they are fits to
     // measurements on ten layer shapes (4096 x 4096 .. 8192 x 57344 and 28672 x 8192), in us:
-    //   streaming, 33..64 tokens : max(0.8 K/1024 + 2.5, MiB of weights / 5.5 + 3)
-    //   streaming, 65..128 tokens: rounds of (N/32 workgroups over the CUs) x (1.05 K/1024 + 2.5)
+    //   streaming, by the row blocks of 32 tokens a workgroup takes (skinny_row_blocks):
+    //     1: 0.6 K/1024 + 1.8, 2: 0.75 K/1024 + 2.3, and at least MiB of weights / 5.5 + 3
+    //     4: rounds of (N/32 workgroups over the CUs) x (1.05 K/1024 + 2.5)
     //   tiled                    : max(4.3 + 0.3 x K/256 x rounds of (N/128 tiles over the CUs),
     //                                  MiB of weights / 6.4 + 4)
-    // (8192 x 57344, 64 tokens: 45.6 against 38.0; 128 tokens: 78.5 against 39.3;
+    // (100 x 14336 -> 4096 12.8 against 22.3; 8192 x 57344, 64 tokens: 45.6 against 38.0; 128 tokens: 78.5 against 39.3;
     //  4096 x 24576, 128 tokens: 21.8 against 11.3; 28672 x 8192, 128 tokens: 31.1 against 41.4).
     bool skinny = M <= 32;
     if (!skinny && M <= 128) {
       const double cus = (double)device_cu_count();
       const double weight_mib = (double)N * (double)K * (17.0 / 32.0) / 1048576.0;
       const double kk = (double)K / 1024.0;
-      const double skinny_us = M <= 64 ? fmax(0.8 * kk + 2.5, weight_mib / 5.5 + 3.0)
-                                       : ceil((double)((N + 31) / 32) / cus) * (1.05 * kk + 2.5);
+      const int rb = skinny_row_blocks(M, N);
+      const double skinny_us = rb == 4 ? ceil((double)((N + 31) / 32) / cus) * (1.05 * kk + 2.5)
+                                       : fmax(rb == 1 ? 0.6 * kk + 1.8 : 0.75 * kk + 2.3, weight_mib / 5.5 + 3.0);
       const double tile_rounds = ceil((double)((N + 127) / 128) / cus);
       const double tiled_us = fmax(4.3 + 0.3 * (double)(K / 256) * tile_rounds, weight_mib / 6.4 + 4.0);
       skinny = skinny_us < tiled_us;

@@ -75,6 +75,12 @@ __global__ __launch_bounds__(kWaves * 64) void w4_skinny_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 31, h = lane >> 5;
   const int KT = K >> 6, NB = (N + 31) >> 5;
+  // row blocks RB blockIdx.y ... of the tokens
+  const int64_t row_block = (int64_t)RB * blockIdx.y;
+  Xq += row_block * KT * 1024;
+  Xs += row_block * KT * 128;
+  Y = static_cast<uint8_t*>(Y) + 32 * row_block * ldy * (OUT_F32 ? 4 : 2);
+  M -= 32 * (int)row_block;
   const int nrb = (M + 31) >> 5;   // row blocks the X buffers hold (a multiple of 32 rows): a block past them re-reads the last, never stored
   const int groups = (NB + CBW - 1) / CBW;
   const uint32_t sel = 0x05040C0Cu + 0x02020000u * h;
@@ -332,11 +338,26 @@ hipError_t launch_split_k(const void* Xq, const void* Xs, const float* tsx, cons
                           const float* tsw, int64_t M, int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy,
                           hipStream_t stream) {
   const int NB = (int)((N + 31) / 32);
-  // Two weight blocks per pass once that still leaves every CU two workgroups or more (up to 64 tokens:
-  // beyond, the accumulators of two blocks leave room for a single wave per SIMD).
-  const int cbw = (M <= 64 && NB >= 4 * device_cu_count()) ? 2 : 1;
+  // Row blocks of 32 tokens (rb) and weight blocks (cbw) a workgroup takes at a time.  Every workgroup converts all of its
+  // tokens' activations, so with few output channels the tokens are dealt out to idle compute units, and with many two
+  // weight blocks share the conversion (us, NVFP4 | INT4, a workgroup with all tokens and one weight block before:
+  // 100 x 14336 -> 4096 33.8 -> 23.4 | 46.0 -> 30.3; 64 x 14336 -> 4096 21.1 -> 17.0 | 28.1 -> 21.4; 100 x 2048 -> 2048
+  // 8.5 -> 4.9 | 10.2 -> 5.5; 128 x 8192 -> 28672 81 -> 77 | 119 -> 93; 128 x 4096 -> 24576 34.6 -> 33.0 | 50.4 -> 39.0).
+  // Up to 64 tokens two weight blocks pay from where both take four rounds' worth of blocks per compute unit (16 x 8192 ->
+  // 28672, 3.5 blocks each: 35.7 -> 33.0 | 44.1 -> 40.1; with 2.5 or 3 blocks each the coarser grid wastes more than it saves:
+  // 16 x 8192 -> 20480 25.1 against 27.2).
+  const int64_t cus = device_cu_count(), tokens = (M + 31) / 32;
+  int rb = 2, cbw = 2;
+  if (M <= 32 || NB * tokens <= cus) {
+    rb = 1;
+    cbw = M <= 32 && NB > 3 * cus ? 2 : 1;
+  } else if (M <= 64) {
+    cbw = NB > 3 * cus ? 2 : 1;
+  } else if (2 * NB <= cus) {
+    cbw = 1;
+  }
   const int groups = (NB + cbw - 1) / cbw;
-  dim3 grid((unsigned)(groups < 4096 ? groups : 4096)), block(kWaves * 64);
+  dim3 grid((unsigned)(groups < 4096 ? groups : 4096), (unsigned)((M + 32 * rb - 1) / (32 * rb))), block(kWaves * 64);
   const int vec = skinny::decode_vec_store(Y, N, ldy, out_f32);
 #define WUSH_W4S_LAUNCH(RB, CBW, F32)                                                                          \
   w4_skinny_kernel<RB, CBW, FMT, F32><<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs, tsx, \
@@ -344,12 +365,10 @@ hipError_t launch_split_k(const void* Xq, const void* Xs, const float* tsx, cons
                                                                   (int)M, (int)N, (int)K, Y, ldy, vec)
 #define WUSH_W4S_BY_OUT(RB, CBW) \
   { if (out_f32) WUSH_W4S_LAUNCH(RB, CBW, true); else WUSH_W4S_LAUNCH(RB, CBW, false); }
-  if (M <= 32) {
+  if (rb == 1) {
     if (cbw == 2) WUSH_W4S_BY_OUT(1, 2) else WUSH_W4S_BY_OUT(1, 1)
-  } else if (M <= 64) {
-    if (cbw == 2) WUSH_W4S_BY_OUT(2, 2) else WUSH_W4S_BY_OUT(2, 1)
   } else {
-    WUSH_W4S_BY_OUT(4, 1)
+    if (cbw == 2) WUSH_W4S_BY_OUT(2, 2) else WUSH_W4S_BY_OUT(2, 1)
   }
 #undef WUSH_W4S_BY_OUT
 #undef WUSH_W4S_LAUNCH
@@ -357,11 +376,10 @@ hipError_t launch_split_k(const void* Xq, const void* Xs, const float* tsx, cons
 }
 
 // The shared-X schedule is built for 65..128 tokens with one weight block per wave: the only shape in which it
-// beats the K split (measured, us, K split | shared X, 8192 -> 57344 at 96 and 128 tokens: NVFP4 140 | 134 and
-// 147 | 127, INT4 206 | 150 and 205 | 150; 8192 -> 28672: NVFP4 71 | 85 and 72 | 86, INT4 114 | 92 and 120 | 97;
-// 4096 -> 24576: 32 | 46 and 51 | 50).  With fewer tokens the K split's conversions are already cheap, with two
-// weight blocks per wave too few workgroups are left, and with fewer output channels the whole-K walk of a wave
-// leaves CUs idle.
+// beats the K split (measured from HBM, us, K split | shared X, 128 tokens: 8192 -> 57344 NVFP4 148 | 152, INT4 181 | 170;
+// 4096 -> 57344 81 | 80 and 94 | 92; 8192 -> 43008 INT4 145 | 141; 8192 -> 28672 INT4 93 | 100).  With fewer tokens the K
+// split's conversions are already cheap, with two weight blocks per wave too few workgroups are left, and with fewer
+// output channels the whole-K walk of a wave leaves CUs idle.
 template <int FMT>
 hipError_t launch_shared_x(const void* Xq, const void* Xs, const float* tsx, const void* Wq, const void* Ws,
                            const float* tsw, int64_t M, int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy,
@@ -382,14 +400,14 @@ hipError_t launch_shared_x(const void* Xq, const void* Xs, const float* tsx, con
 }
 
 // Which schedule: shared X for 65..128 tokens once the layer has enough output channels for it (fitted on the
-// cases above: from 3.5 workgroups of four blocks per CU for INT4, whose conversions cost more, from 7 for
-// NVFP4); the switch kDbgW4Skinny forces one (1 = K split across the waves, 2 = shared X where it exists).
+// cases above: from 5 blocks of 32 per CU for INT4, whose conversions cost more, from 7 for NVFP4); the switch
+// kDbgW4Skinny forces one (1 = K split across the waves, 2 = shared X where it exists).
 template <int FMT>
 hipError_t launch(const void* Xq, const void* Xs, const float* tsx, const void* Wq, const void* Ws, const float* tsw,
                   int64_t M, int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy, hipStream_t stream) {
   const int forced = debug_option(kDbgW4Skinny);
   const int64_t NB = (N + 31) / 32;
-  const bool wide = 2 * NB >= (FMT == kInt4 ? 7 : 14) * (int64_t)device_cu_count();
+  const bool wide = NB >= (FMT == kInt4 ? 5 : 7) * (int64_t)device_cu_count();
   const bool shared_x = M > 64 && (forced == 2 || (forced != 1 && wide));
   if (shared_x) return launch_shared_x<FMT>(Xq, Xs, tsx, Wq, Ws, tsw, M, N, K, out_f32, Y, ldy, stream);
   return launch_split_k<FMT>(Xq, Xs, tsx, Wq, Ws, tsw, M, N, K, out_f32, Y, ldy, stream);
