@@ -43,16 +43,19 @@ __global__ __launch_bounds__(256) void second_moment_kernel(
   // on the FP64 MFMA (16 x 16 x 4: four rows of the block at a time).  With A[i][k] = x[row k][channel i]
   // and B[k][j] = x[row k][channel j] a lane feeds both operands from the element (row lane / 16,
   // channel lane % 16) of a 16-channel half; the moment is symmetric, so the two diagonal 16 x 16
-  // blocks and one off-diagonal block are computed (3 MFMAs per 4 rows) and the fourth is its mirror.
+  // blocks and one off-diagonal block are computed (3 MFMAs per 4 rows) and the fourth is its mirror.  c2 layer: 42 us, the
+  // MFMAs alone 26 (47 with twice the splits and the waves' sums in LDS of their own: three workgroups per CU instead of six).
   // A wave takes every fourth group of 4 rows; the four waves' sums are added at the end in wave order.
   __shared__ __attribute__((aligned(16))) float tile[kRowsPerStep][48];   // row stride 48: the 4-row reads hit 32 distinct banks per half wave
-  __shared__ double red[3][768];
+  static_assert(sizeof(tile) >= 3 * 768 * sizeof(double), "the waves' sums fit the tile");
+  double (*red)[768] = reinterpret_cast<double (*)[768]>(tile);
   const int b = blockIdx.x, s = blockIdx.y, z = blockIdx.z;
   const uint16_t* A = z == 0 ? W : X;
   const int64_t ld = z == 0 ? ldw : ldx;
   const int rows = z == 0 ? N : Mc;
   const int per = z == 0 ? rows_per_split_w : rows_per_split_x;
   const int r_begin = min(s * per, rows), r_end = min(r_begin + per, rows);
+  if (r_begin == r_end) return;   // a split with no rows left: its partial moment is not read
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int k = lane >> 4, c = lane & 15;
   v4d acc00 = {0, 0, 0, 0}, acc01 = {0, 0, 0, 0}, acc11 = {0, 0, 0, 0};
@@ -92,6 +95,7 @@ __global__ __launch_bounds__(256) void second_moment_kernel(
       acc11 = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, x1, acc11, 0, 0, 0);
     }
   }
+  __syncthreads();
   // waves 1..3 hand their sums to wave 0, which adds them in wave order and writes the 32 x 32 partial
   if (wave > 0) {
 #pragma unroll
@@ -118,8 +122,9 @@ __global__ __launch_bounds__(256) void second_moment_kernel(
   }
 }
 
-__global__ __launch_bounds__(256) void wush_block_kernel(const double* __restrict__ partial, int S, int C, int N,
-                                                         int Mc, double lambda, uint16_t* __restrict__ T_out,
+// The first S_W splits of S hold rows of W, the first S_X rows of X.
+__global__ __launch_bounds__(256) void wush_block_kernel(const double* __restrict__ partial, int S, int S_W, int S_X,
+                                                         int C, int N, int Mc, double lambda, uint16_t* __restrict__ T_out,
                                                          double* __restrict__ T_f64, int* __restrict__ status) {
   const int b = blockIdx.x;
   // the partial moments are added in a fixed order and normalized
@@ -127,26 +132,30 @@ __global__ __launch_bounds__(256) void wush_block_kernel(const double* __restric
     return partial[(((int64_t)half * S + s) * C + b) * 1024 + r * 32 + c];
   };
   auto finish = [&](int half, double sum) { return sum * (1.0 / (double)(half ? Mc : N)); };
-  wush_block_group<32, 0>(load, finish, S, S, lambda, nullptr, T_out + (int64_t)b * 1024,
+  wush_block_group<32, 0>(load, finish, S_W, S_X, lambda, nullptr, T_out + (int64_t)b * 1024,
                           T_f64 ? T_f64 + (int64_t)b * 1024 : nullptr, nullptr, status);
 }
 
 // The same for 16 x 16 blocks (the NVFP4 variant: transform block = quantization group of 16).  The
 // moments of block b are the diagonal 16 x 16 sub-block (b & 1) of the 32-channel moments of block b / 2.
-__global__ __launch_bounds__(128) void wush_block16_kernel(const double* __restrict__ partial, int S, int C, int N,
-                                                           int Mc, double lambda, uint16_t* __restrict__ T_out,
+__global__ __launch_bounds__(128) void wush_block16_kernel(const double* __restrict__ partial, int S, int S_W, int S_X,
+                                                           int C, int N, int Mc, double lambda, uint16_t* __restrict__ T_out,
                                                            double* __restrict__ T_f64, int* __restrict__ status) {
   const int b = blockIdx.x, b32 = b >> 1, off = 16 * (b & 1);
   auto load = [&](int half, int r, int c, int s) {
     return partial[(((int64_t)half * S + s) * C + b32) * 1024 + (off + r) * 32 + off + c];
   };
   auto finish = [&](int half, double sum) { return sum * (1.0 / (double)(half ? Mc : N)); };
-  wush_block_group<16, 0>(load, finish, S, S, lambda, nullptr, T_out + (int64_t)b * 256,
+  wush_block_group<16, 0>(load, finish, S_W, S_X, lambda, nullptr, T_out + (int64_t)b * 256,
                           T_f64 ? T_f64 + (int64_t)b * 256 : nullptr, nullptr, status);
 }
 
+// Splits of the rows, for about four workgroups of each moment per compute unit.  Every split costs a partial moment of 8 KiB per
+// block, written and read back (both kernels together, us, 2048 / C | 1024 / C | 512 / C: c2 layer 168.6 | 164.6 | 163.4,
+// 8192 x 8192 -> 57344 626 | 616 | 640, 512 x 1024 -> 1024 146 | 132 | 126); partials of splits without rows are not read
+// (the last shape 132 -> 121).
 int splits_for(int64_t C) {
-  int64_t s = 2048 / C;
+  int64_t s = 1024 / C;
   if (s < 1) s = 1;
   if (s > 256) s = 256;
   return (int)s;
@@ -169,16 +178,17 @@ hipError_t launch_build_transforms(const void* W, int64_t N, int64_t ldw, const 
   double* partial = reinterpret_cast<double*>(workspace);
   int* status = reinterpret_cast<int*>(reinterpret_cast<char*>(workspace) + build_transforms_status_offset(K));
   auto per = [&](int64_t rows) { return (int)(((rows + S - 1) / S + kRowsPerStep - 1) / kRowsPerStep * kRowsPerStep); };
+  auto used = [&](int64_t rows) { return (int)((rows + per(rows) - 1) / per(rows)); };
   second_moment_kernel<<<dim3(C, S, 2), dim3(256), 0, stream>>>((const uint16_t*)W, ldw, (int)N, (const uint16_t*)X,
                                                                ldx, (int)Mc, per(N), per(Mc), S, C, partial, status);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (block == 16)
-    wush_block16_kernel<<<dim3(2 * C), dim3(128), 0, stream>>>(partial, S, C, (int)N, (int)Mc, lambda, (uint16_t*)T_out,
-                                                              T_f64, status);
+    wush_block16_kernel<<<dim3(2 * C), dim3(128), 0, stream>>>(partial, S, used(N), used(Mc), C, (int)N, (int)Mc, lambda,
+                                                              (uint16_t*)T_out, T_f64, status);
   else
-    wush_block_kernel<<<dim3(C), dim3(256), 0, stream>>>(partial, S, C, (int)N, (int)Mc, lambda, (uint16_t*)T_out, T_f64,
-                                                        status);
+    wush_block_kernel<<<dim3(C), dim3(256), 0, stream>>>(partial, S, used(N), used(Mc), C, (int)N, (int)Mc, lambda,
+                                                        (uint16_t*)T_out, T_f64, status);
   return hipGetLastError();
 }
 

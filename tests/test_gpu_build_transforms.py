@@ -153,3 +153,19 @@ def test_build_transforms_16_matches_oracle(P, G, name):
     eq = t64[b] @ O.damped(O.second_moment(Xc[:, sl]), lam) @ t64[b].T
     assert np.allclose(np.diag(eq), s.sum() / 16, rtol=1e-8)
     assert O.fp_model_objective(t64[b], Wp, Xp) == pytest.approx(s.sum() ** 2 / 16, rel=1e-8)
+
+
+@pytest.mark.parametrize("rows", [(33, 128), (129, 127), (128, 1025), (257, 33)])
+def test_row_splits_without_rows_are_not_read(P, G, rows):
+    """Row counts around the splits of 128 rows, a workspace full of NaN: partial moments of splits that hold no rows stay
+    unwritten and must not be read (the bar of the parity test above)."""
+    import torch
+    cfg = I.scaled(I.CONFIGS["c1"], K=96, N=rows[0], calib_tokens=rows[1], n_outlier=2)
+    L = I.make_layer(cfg)
+    T = torch.empty((3, 32, 32), dtype=torch.bfloat16, device="cuda")
+    T64 = torch.empty((3, 32, 32), dtype=torch.float64, device="cuda")
+    ws = torch.full((P.wush_build_transforms_workspace(96),), 255, dtype=torch.uint8, device="cuda")
+    P.wush_build_transforms(G.bf16_dev(L["W"]), G.bf16_dev(L["X_cal"]), 1e-2, T, ws, T_f64=T64)
+    P.wush_build_transforms_status(ws, 96)
+    T_ref = O.build_transforms(O.bf16_bits_to_f64(L["W"]), O.bf16_bits_to_f64(L["X_cal"]), 1e-2)
+    assert np.max(np.abs(T64.cpu().numpy() - T_ref) / np.max(np.abs(T_ref), axis=(1, 2), keepdims=True)) <= 1e-9
