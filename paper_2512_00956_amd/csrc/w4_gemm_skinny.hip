@@ -343,14 +343,15 @@ hipError_t launch_split_k(const void* Xq, const void* Xs, const float* tsx, cons
   // weight blocks share the conversion (us, NVFP4 | INT4, a workgroup with all tokens and one weight block before:
   // 100 x 14336 -> 4096 33.8 -> 23.4 | 46.0 -> 30.3; 64 x 14336 -> 4096 21.1 -> 17.0 | 28.1 -> 21.4; 100 x 2048 -> 2048
   // 8.5 -> 4.9 | 10.2 -> 5.5; 128 x 8192 -> 28672 81 -> 77 | 119 -> 93; 128 x 4096 -> 24576 34.6 -> 33.0 | 50.4 -> 39.0).
-  // Up to 64 tokens two weight blocks pay from where both take four rounds' worth of blocks per compute unit (16 x 8192 ->
-  // 28672, 3.5 blocks each: 35.7 -> 33.0 | 44.1 -> 40.1; with 2.5 or 3 blocks each the coarser grid wastes more than it saves:
-  // 16 x 8192 -> 20480 25.1 against 27.2).
+  // Up to 64 tokens two weight blocks pay from where the coarser grid takes no round more: 64 x 8192 -> 28672, 3.5 blocks per
+  // compute unit, 49.3 -> 43.1 | 61.9 -> 51.2, 16 tokens INT4 44.1 -> 40.1, but 16 x 8192 -> 20480 (2.5 blocks) NVFP4 25.1 against
+  // 27.2.  NVFP4 at 16 tokens and 3.5 blocks gains from HBM what it loses with its weights in the last-level cache
+  // (35.7 -> 33.0, 33.5 -> 34.0), so there it waits for four.
   const int64_t cus = device_cu_count(), tokens = (M + 31) / 32;
   int rb = 2, cbw = 2;
   if (M <= 32 || NB * tokens <= cus) {
     rb = 1;
-    cbw = M <= 32 && NB > 3 * cus ? 2 : 1;
+    cbw = M <= 32 && (FMT == kInt4 ? NB > 3 * cus : NB >= 4 * cus) ? 2 : 1;
   } else if (M <= 64) {
     cbw = NB > 3 * cus ? 2 : 1;
   } else if (2 * NB <= cus) {
