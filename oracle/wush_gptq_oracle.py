@@ -86,11 +86,11 @@ def gptq_block(Wbar: np.ndarray, Hbar: np.ndarray, rule: str = "nosat"):
 
 
 def gptq_wush_layer(W: np.ndarray, X_cal: np.ndarray, lam: float = 1e-2, rule: str = "nosat",
-                    transform: str = "wush"):
+                    transform="wush"):
     """Alg. 2, GPTQ case.  W [N][K], X_cal [M][K] (FP64 values).
 
     transform: "wush" (the algorithm), or "hadamard" / "identity" (the same
-    schedule with a fixed transform; used by pins and comparisons).
+    schedule with a fixed transform; used by pins and comparisons), or the transforms themselves [C][d][d].
     Returns (T [C][d][d] BF16-valued FP64, codes [N][K], scale bytes [N][C]).
     """
     W = np.array(W, dtype=np.float64)
@@ -103,7 +103,9 @@ def gptq_wush_layer(W: np.ndarray, X_cal: np.ndarray, lam: float = 1e-2, rule: s
     scales = np.empty((N, C), dtype=np.uint8)
     for i in range(C):
         bi = slice(D * i, D * i + D)
-        if transform == "wush":
+        if isinstance(transform, np.ndarray):
+            Ti = transform[i]
+        elif transform == "wush":
             M_W = O.second_moment(W[:, bi])                  # updated weight block
             M_X = Hs[bi, bi]                                 # diagonal block of the Hessian
             Ti = O.round_to_bf16(O.wush_block(M_W, M_X, lam))

@@ -85,16 +85,18 @@ __device__ __forceinline__ uint32_t e2m1_code_f64(double a) {
 // An FP64 value as an FP32 one that rounds to E2M1 (at any scale byte in the range below) exactly as the FP64
 // value would: 20 of its fraction bits with everything below them folded into the last fraction bit ("sticky"),
 // so that no midpoint of the grid, none of which needs more than 3 fraction bits, is reached or crossed.  The
-// hardware convert then decides an element in 5 integer operations and half a convert, where the seven FP64
-// comparisons of e2m1_code_f64 took 15.  Magnitudes below 2^-126 become zero and those from 2^128 on are wrong,
-// so the group's scale byte must be one whose midpoints (from 2^(byte - 129) on) and range (up to 2^(byte - 124))
-// lie between.
+// hardware convert then decides an element in 6 operations and half a convert, where the seven FP64
+// comparisons of e2m1_code_f64 took 15.  Magnitudes below 2^-126 become zero; those from 2^128 on, infinities and
+// NaNs become the largest finite FP32, so that a group maximum taken over these values has a scale byte beyond kSafeByteHi
+// whenever an element left the range.  The group's scale byte must be one whose midpoints (from 2^(byte - 129) on) and
+// range (up to 2^(byte - 124)) lie between.
 constexpr int kSafeByteLo = 8, kSafeByteHi = 250;
 __device__ __forceinline__ float f64_to_f32_sticky(double v) {
   const uint64_t b = (uint64_t)__double_as_longlong(v);
   const uint32_t hi = (uint32_t)(b >> 32), lo = (uint32_t)b;
-  const uint32_t mag = __builtin_elementwise_sub_sat(hi & 0x7FFFFFFFu, 896u << 20);   // rebias; small values become 0
-  return __uint_as_float((hi & 0x80000000u) | (mag << 3) | min(lo, 1u));
+  const uint32_t rebased = __builtin_elementwise_sub_sat(hi & 0x7FFFFFFFu, 896u << 20);   // small values become 0
+  const uint32_t mag = min(rebased, (255u << 20) - 1u) << 3 | min(lo, 1u);
+  return __uint_as_float((hi & 0x80000000u) | mag);
 }
 
 // ---------------------------------------------------------------------------
