@@ -334,7 +334,6 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
       for (int i = 1; i < kRpl; ++i) ga = fma(ap[i], aq[i], ga);
       ga = row_sum(ga);
       const double ab = al * be, gg = ga * ga;
-      large |= gg > 1e-20 * ab;
       // The rotation by the angle of smaller magnitude that makes the two columns orthogonal:
       // tan(2 theta) = 2 ga / (be - al), |theta| <= pi / 4.  With h = hypot(be - al, 2 ga):
       // cos^2 = (1 + |be - al| / h) / 2 and tan = (|ga| / h) / cos^2.  The tangent only has to be about
@@ -346,6 +345,7 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
       double tn = fabs(ga) * ih * __builtin_amdgcn_rcp(c2);
       tn = dd == 0.0 || (dd > 0.0) == (ga > 0.0) ? tn : -tn;
       tn = gg > 1e-30 * ab ? tn : 0.0;                 // |ga| <= 1e-15 sqrt(al be): left alone
+      large |= gg > 1e-20 * ab || fabs(tn) > 1e-7;
       const double x = fma(tn, tn, 1.0);
       const double y = __builtin_amdgcn_rsq(x);
       const double e = fma(-x * y, y, 1.0);
@@ -371,8 +371,11 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
       q = q == D - 1 ? 1 : q + 1;
       __syncthreads();
     }
-    // A sweep whose rotations all met cosines below 1e-10 leaves cosines of that squared over the relative
-    // gap of the singular values (quadratic convergence): below FP64's resolution, no further sweep is needed.
+    // A rotation by tan(theta) = tn undoes what earlier ones of its sweep zeroed by tn times the cosines it mixes in (the
+    // ratio of the two columns' norms is in tn), 2 D of them per pair at most.  So a sweep that met cosines up to 1e-10 and
+    // tangents up to 1e-7 only leaves cosines of some 1e-16, and the last ones' own, 2^-24 of what they were: no
+    // further sweep is needed.  Equal or nearly equal singular values turn by large angles at any cosine; there the sweeps go on until
+    // no cosine is above 1e-15.  (Stopping at cosines of 1e-10 alone left the columns of such a block orthogonal to 3e-11.)
     if (large) again[sweep & 1] = 1;
     __syncthreads();
     const int more = again[sweep & 1];

@@ -169,3 +169,32 @@ def test_row_splits_without_rows_are_not_read(P, G, rows):
     P.wush_build_transforms_status(ws, 96)
     T_ref = O.build_transforms(O.bf16_bits_to_f64(L["W"]), O.bf16_bits_to_f64(L["X_cal"]), 1e-2)
     assert np.max(np.abs(T64.cpu().numpy() - T_ref) / np.max(np.abs(T_ref), axis=(1, 2), keepdims=True)) <= 1e-9
+
+
+@pytest.mark.parametrize("block", [32])
+@pytest.mark.parametrize("clusters", [1, 2])
+@pytest.mark.parametrize("noise_exp", [None, -28, -22, -16])
+def test_repeated_singular_values(P, G, block, clusters, noise_exp):
+    """Blocks whose singular values repeat (one group, or two a factor of 2 apart) or nearly do, M_W = I exactly: the columns of
+    U stay orthogonal to FP64 accuracy however the rotations inside a group fall.  With W' = I, H T = S^(-1/2) U^T; the two
+    products with H sum `block` rounded terms each, 2 block^2 2^-53 in the Gram matrix at most."""
+    import torch
+    rng = np.random.default_rng(17)
+    Hs = O.hadamard(block) * np.sqrt(block)
+    X = Hs * (1.0 + (np.arange(block) >= block // 2) * (clusters - 1))
+    if noise_exp is not None:
+        X = np.concatenate([X, np.ldexp(rng.standard_normal((32, block)), noise_exp)])
+    reps = 32 // block
+    W, X = np.tile(Hs, (1, reps)), np.tile(X, (1, reps))
+    T = torch.empty((reps, block, block), dtype=torch.bfloat16, device="cuda")
+    T64 = torch.full((reps, block, block), float("nan"), dtype=torch.float64, device="cuda")
+    ws = G.empty_u8(P.wush_build_transforms_workspace(32))
+    build = P.wush_build_transforms if block == 32 else P.wush_build_transforms_nvfp4
+    bits = [G.bf16_dev(O.bf16_values_to_bits(O.round_to_bf16(a))) for a in (W, X)]
+    build(*bits, 0.0, T, ws, T_f64=T64)
+    P.wush_build_transforms_status(ws, 32)
+    for t in T64.cpu().numpy():
+        ut = O.hadamard(block) @ t
+        ut /= np.linalg.norm(ut, axis=1, keepdims=True)
+        err = np.max(np.abs(ut @ ut.T - np.eye(block)))
+        assert err <= 2 * block * block * 2.0 ** -53, err
