@@ -21,8 +21,11 @@ __device__ __forceinline__ double dpp_f64(double x) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 // Sum / maximum of x over the 16 lanes of a DPP row, the same in each of them: partner lane ^ 1, lane ^ 2
-// (quad permutes), the mirrored lane of the other quad, the mirrored lane of the other half row.
+// (quad permutes), the mirrored lane of the other quad, the mirrored lane of the other half row.  Every addition has the same two
+// operands in the lanes it joins; no multiplication of the caller's may be fused into the first one, or x stays unrounded on one
+// side of it and rounded on the other, and the lanes get different sums.
 __device__ __forceinline__ double row_sum(double x) {
+#pragma clang fp contract(off)
   x += dpp_f64<0xB1>(x);    // quad_perm [1, 0, 3, 2]
   x += dpp_f64<0x4E>(x);    // quad_perm [2, 3, 0, 1]
   x += dpp_f64<0x141>(x);   // row_half_mirror: lane i <-> 7 - i

@@ -171,7 +171,7 @@ def test_row_splits_without_rows_are_not_read(P, G, rows):
     assert np.max(np.abs(T64.cpu().numpy() - T_ref) / np.max(np.abs(T_ref), axis=(1, 2), keepdims=True)) <= 1e-9
 
 
-@pytest.mark.parametrize("block", [32])
+@pytest.mark.parametrize("block", [32, 16])
 @pytest.mark.parametrize("clusters", [1, 2])
 @pytest.mark.parametrize("noise_exp", [None, -28, -22, -16])
 def test_repeated_singular_values(P, G, block, clusters, noise_exp):
