@@ -38,17 +38,21 @@ def hipcc_path() -> str:
 
 
 def check_generated_code(hipcc: str, bdir: str) -> None:
-    """The tiled MXFP4 GEMM issues its main-loop loads from inline asm; what that relies on in the
+    """The MXFP4 GEMMs issue their main-loop loads from inline asm; what that relies on in the
     generated code (build_checks.py) is verified on every build, with the flags of the build."""
-    from .build_checks import check_gemm_frag_asm
-    asm = os.path.join(bdir, "mxfp4_gemm_frag.s")
-    cmd = [hipcc, *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-S", "--cuda-device-only",
-           os.path.join(CSRC, "mxfp4_gemm_frag.hip"), "-o", asm]
-    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"hipcc -S failed on mxfp4_gemm_frag.hip:\n{r.stdout}")
-    with open(asm) as f:
-        check_gemm_frag_asm(f.read())      # raises InvariantError
+    from .build_checks import check_gemm_frag_asm, check_lds_load_asm
+    for name, checks in (("mxfp4_gemm_frag", (check_gemm_frag_asm, check_lds_load_asm)),
+                         ("mxfp4_gemm_canon", (check_lds_load_asm,))):
+        asm = os.path.join(bdir, name + ".s")
+        cmd = [hipcc, *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-S", "--cuda-device-only",
+               os.path.join(CSRC, name + ".hip"), "-o", asm]
+        r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        if r.returncode != 0:
+            raise RuntimeError(f"hipcc -S failed on {name}.hip:\n{r.stdout}")
+        with open(asm) as f:
+            text = f.read()
+        for check in checks:
+            check(text)                    # raises InvariantError
 
 
 def build(verbose: bool = False) -> str:

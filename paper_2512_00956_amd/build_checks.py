@@ -30,6 +30,26 @@ def kernels(text: str) -> dict:
     return {parts[i]: parts[i + 1].split("s_endpgm")[0] for i in range(1, len(parts) - 1, 2)}
 
 
+def check_lds_load_asm(text: str) -> None:
+    """Direct-to-LDS loads issued from asm (csrc/mxfp4_gemm_frag.hip, csrc/mxfp4_gemm_canon.hip): each reads the m0 its own asm
+    block wrote, with a wait state in between, and m0 has no other writer; no scalar address of one comes straight from a
+    vector instruction (five wait states, which the compiler does not count for an asm)."""
+    ins = [s for s in (line.split(";")[0].strip() for line in text.split("\n")) if s and not s.startswith((".", "#"))]
+    loads = [k for k, s in enumerate(ins) if s.startswith("global_load_lds_")]
+    if not loads:
+        raise InvariantError("no direct-to-LDS load found")
+    for k in loads:
+        if not (ins[k - 2].startswith("s_mov_b32 m0,") and ins[k - 1].startswith("s_nop")):
+            raise InvariantError(f"no wait state between the write of m0 and {ins[k]!r}: {ins[k - 2:k + 1]}")
+        base = re.search(r"s\[(\d+):(\d+)\]", ins[k])
+        for s in ins[max(0, k - 7):k]:
+            m = re.match(r"v_read(?:first)?lane_b32 s(\d+),", s)
+            if m and int(base.group(1)) <= int(m.group(1)) <= int(base.group(2)):
+                raise InvariantError(f"{s!r} too close before {ins[k]!r}")
+    if sum("m0" in re.findall(r"\w+", s) for s in ins) != len(loads):
+        raise InvariantError("m0 is used outside the loads' asm blocks")
+
+
 def shape(name: str):
     """(RB, CB) from the mangled template arguments ...ILb<f32>ELi<RB>ELi<CB>E..."""
     m = re.search(r"ILb[01]ELi(\d+)ELi(\d+)E", name)

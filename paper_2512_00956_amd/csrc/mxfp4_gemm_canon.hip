@@ -103,7 +103,8 @@ __global__ __launch_bounds__(256) void gemm_canon_kernel(
       const int chunk = chunk_of(u);
       o -= 16u * (uint32_t)(chunk - min(chunk, rem - 1));
     }
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(o), "s"(src), "s"(dst));
+    // the wait state a load to LDS needs behind the write of m0; m0 itself: see mxfp4_gemm_frag.hip
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(o), "s"(src), "s"(dst));
   };
 
   // ---- scales: rows threadIdx.x + 256 i of [X tile; W tile], 16 bytes (two steps) at a time

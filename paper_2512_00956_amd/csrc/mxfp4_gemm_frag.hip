@@ -128,20 +128,22 @@ __global__ __launch_bounds__(256) void gemm_frag_kernel(
   // compiler never keeps a value of its own in it across statements: it is a reserved register of
   // this target (naming it in the clobber list is rejected with "clobber list contains reserved
   // registers"), written immediately before each instruction the compiler itself emits that reads it.
+  // A scalar write of m0 needs one wait state before a load to LDS that reads it.  The compiler fills it for its own
+  // instructions (with s_nop 0 if with nothing better) but does not look inside an asm, so it stands there.
   const uint32_t lds_base = (uint32_t)(uintptr_t)smem;   // LDS byte address of the ring
   // The four fragments (kk) of one (row block, K tile) are 4 KiB contiguous both in
   // memory and in the ring stage; the instruction's immediate offset is added to
   // the global AND to the LDS address, so they share one base and one m0 value.
   auto dma16 = [&](const uint8_t* src, uint32_t lds_addr, int kk) {
     switch (kk) {
-      case 0: asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(loff), "s"(src), "s"(lds_addr)); break;
-      case 1: asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 offset:1024" ::"v"(loff), "s"(src), "s"(lds_addr)); break;
-      case 2: asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 offset:2048" ::"v"(loff), "s"(src), "s"(lds_addr)); break;
-      default: asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 offset:3072" ::"v"(loff), "s"(src), "s"(lds_addr)); break;
+      case 0: asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(loff), "s"(src), "s"(lds_addr)); break;
+      case 1: asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:1024" ::"v"(loff), "s"(src), "s"(lds_addr)); break;
+      case 2: asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:2048" ::"v"(loff), "s"(src), "s"(lds_addr)); break;
+      default: asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:3072" ::"v"(loff), "s"(src), "s"(lds_addr)); break;
     }
   };
   auto dma4 = [&](const uint8_t* src, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1" ::"v"(soff), "s"(src), "s"(lds_addr));
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(soff), "s"(src), "s"(lds_addr));
   };
   auto dma_x_frag = [&](int kt, int f) {
     const int u = f >> 2, kk = f & 3;

@@ -59,6 +59,20 @@ def test_the_checks_catch_what_they_are_for(asm_text):
         check_gemm_frag_asm(drained)
 
 
+@pytest.mark.parametrize("src", ["mxfp4_gemm_frag.hip", "mxfp4_gemm_canon.hip"])
+def test_loads_to_lds_wait_for_m0(src):
+    """A wait state between every write of m0 and the load to LDS that reads it, and no other use of m0; planted faults in
+    the assembly text are caught."""
+    from paper_2512_00956_amd.build_checks import InvariantError, check_lds_load_asm
+    text = _compile(src)
+    check_lds_load_asm(text)
+    load = re.search(r"s_mov_b32 m0, s\d+\n\s*s_nop 0\n\s*global_load_lds_dwordx4 v\d+, s\[(\d+):\d+\]", text)
+    for planted in (load.group(0).replace("s_nop 0\n", "", 1), "s_mov_b32 m0, 0\n\t" + load.group(0),
+                    f"v_readfirstlane_b32 s{load.group(1)}, v0\n\t" + load.group(0)):
+        with pytest.raises(InvariantError):
+            check_lds_load_asm(text[:load.start()] + planted + text[load.end():])
+
+
 # ---------------------------------------------------------------------------
 # The FP16-dequantizing GEMM of the NVFP4 / INT4 variants and the three fused quantizers: performance
 # invariants of the generated code -- nothing spills to scratch (the GEMM keeps up to 256 accumulator
