@@ -208,7 +208,7 @@ struct Moment {
   v4d acc00 = {0, 0, 0, 0}, acc01 = {0, 0, 0, 0}, acc11 = {0, 0, 0, 0};
   __device__ __forceinline__ void add(const double (&x)[8], double* area, int l16, int l4) {
     store8(area + 34 * l16 + 8 * l4, x);
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       const double x0 = area[34 * (4 * kk + l4) + l16], x1 = area[34 * (4 * kk + l4) + 16 + l16];
@@ -216,7 +216,7 @@ struct Moment {
       acc01 = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, x1, acc01, 0, 0, 0);
       acc11 = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, x1, acc11, 0, 0, 0);
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
   }
   // sums of the workgroup's WAVES wavefronts in wave order -> out [32][32]
   template <int WAVES>
@@ -458,7 +458,7 @@ __device__ __forceinline__ uint32_t gptq_subroutine(double (&y)[8], double (&dq)
         }
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     if (l4 > g) {
       double e[8];
       load8(err + 8 * l16, e);
@@ -474,7 +474,7 @@ __device__ __forceinline__ uint32_t gptq_subroutine(double (&y)[8], double (&dq)
         }
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
   }
   return word;
 }

@@ -248,7 +248,7 @@ __global__ __launch_bounds__(256) void gemm_canon_kernel(
       for (int q = 0; q < 4; ++q)
         *reinterpret_cast<v4f*>(buf + r * kPitch + 8 * q + 4 * kh) =
             (v4f){acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_sync();
       if (vec_store && col0 + 32 <= N) {
         // rows of 16-byte aligned chunks: 8 lanes (FP32) or 4 (BF16) per row
         constexpr int kLanes = OUT_F32 ? 8 : 4, kPer = 32 / kLanes;
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(256) void gemm_canon_kernel(
           }
         }
       }
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_sync();
     }
   }
 }

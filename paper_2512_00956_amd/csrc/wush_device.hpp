@@ -130,6 +130,15 @@ __device__ __forceinline__ int xcd_contiguous_id(int id, int total) {
   return xcd * base + min(xcd, rem) + pos;
 }
 
+// Orders a wavefront's LDS accesses before this point against those behind it when its lanes exchange data through LDS.
+// The hardware does that by itself (one wavefront's LDS accesses take effect in order); the fences keep the compiler from moving or
+// forwarding across, which the barrier alone does not (to the compiler it touches no memory).  No instruction comes of it.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t b) {
   return __uint_as_float((uint32_t)b << 16);
 }

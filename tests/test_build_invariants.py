@@ -73,6 +73,18 @@ def test_loads_to_lds_wait_for_m0(src):
             check_lds_load_asm(text[:load.start()] + planted + text[load.end():])
 
 
+def test_lanes_that_exchange_through_lds_are_fenced():
+    """__builtin_amdgcn_wave_barrier touches no memory to the compiler: wherever it orders LDS accesses of one wavefront it stands
+    between wavefront fences, that is in wave_lds_sync (wush_device.hpp) and nowhere else."""
+    csrc = os.path.dirname(SRC)
+    uses = {name: open(os.path.join(csrc, name)).read().count("__builtin_amdgcn_wave_barrier(") for name in os.listdir(csrc)}
+    assert {name: n for name, n in uses.items() if n} == {"wush_device.hpp": 1}
+    body = re.search(r"void wave_lds_sync\(\) \{(.*?)\n\}", open(os.path.join(csrc, "wush_device.hpp")).read(), flags=re.S).group(1)
+    calls = re.findall(r"__builtin_amdgcn_\w+\([^)]*\)", body)
+    assert calls == ['__builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local")', "__builtin_amdgcn_wave_barrier()",
+                     '__builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local")']
+
+
 # ---------------------------------------------------------------------------
 # The FP16-dequantizing GEMM of the NVFP4 / INT4 variants and the three fused quantizers: performance
 # invariants of the generated code -- nothing spills to scratch (the GEMM keeps up to 256 accumulator
