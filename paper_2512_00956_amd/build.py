@@ -40,9 +40,9 @@ def hipcc_path() -> str:
 def check_generated_code(hipcc: str, bdir: str) -> None:
     """The MXFP4 GEMMs issue their main-loop loads from inline asm; what that relies on in the
     generated code (build_checks.py) is verified on every build, with the flags of the build."""
-    from .build_checks import check_gemm_frag_asm, check_lds_load_asm
+    from .build_checks import check_gemm_canon_asm, check_gemm_frag_asm, check_lds_load_asm
     for name, checks in (("mxfp4_gemm_frag", (check_gemm_frag_asm, check_lds_load_asm)),
-                         ("mxfp4_gemm_canon", (check_lds_load_asm,))):
+                         ("mxfp4_gemm_canon", (check_gemm_canon_asm, check_lds_load_asm))):
         asm = os.path.join(bdir, name + ".s")
         cmd = [hipcc, *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-S", "--cuda-device-only",
                os.path.join(CSRC, name + ".hip"), "-o", asm]

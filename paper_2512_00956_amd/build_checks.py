@@ -1,6 +1,6 @@
-"""Checks on the generated gfx950 assembly of the tiled MXFP4 GEMM (csrc/mxfp4_gemm_frag.hip).
+"""Checks on the generated gfx950 assembly of the MXFP4 GEMMs that issue loads from inline asm.
 
-Its main-loop global loads are issued from inline asm with explicit vmcnt waits, so the compiler
+The tiled one (csrc/mxfp4_gemm_frag.hip): its main-loop global loads are issued from inline asm with explicit vmcnt waits, so the compiler
 does not know that their destination registers are written asynchronously.  The kernel is only
 correct while
   (a) nothing in it spills to scratch,
@@ -13,6 +13,12 @@ correct while
 None of this can be said in the source, and a different compiler may break it silently, so the
 build runs these checks on every compile and fails when one does not hold; the test suite runs
 them again.
+
+The canonical one (csrc/mxfp4_gemm_canon.hip) has no register destination in its asm, but its LDS
+ring is filled behind the compiler's back.  It is only correct while every LDS read of a step stays
+between the step's barrier and the next, with the explicit count of outstanding loads in front of
+the barrier; it is only fast while nothing spills and nothing but the documented wait for the
+scale loads drains the ring.
 """
 from __future__ import annotations
 
@@ -84,3 +90,65 @@ def check_gemm_frag_asm(text: str, expected_kernels: int = 8) -> None:
             raise InvariantError(f"{name}: a full waitcnt drain inside the pipelined loop")
         if loop.count("s_barrier") != 2:
             raise InvariantError(f"{name}: {loop.count('s_barrier')} barriers in the loop (expected 2)")
+
+
+def _loops(body: str) -> dict:
+    """{loop header: [basic block, ...]} of the blocks the compiler annotates as belonging to a loop."""
+    blocks = re.split(r"^(\.LBB\d+_\d+:.*|; %bb\.\d+:.*)$", body, flags=re.M)
+    loops = {}
+    for label, block in zip(blocks[1::2], blocks[2::2]):
+        m = re.search(r"in Loop: Header=(BB\d+_\d+)", label)
+        if not m and "Loop Header" in label:
+            m = re.match(r"\.L(BB\d+_\d+):", label)
+        if m:
+            loops.setdefault(m.group(1), []).append(block)
+    return loops
+
+
+def check_gemm_canon_asm(text: str, expected_kernels: int = 20) -> None:
+    parts = re.split(r"^(_ZN4wush\S*gemm_canon_kernel\S*):.*$", text, flags=re.M)
+    ks = {parts[i]: parts[i + 1].split(".Lfunc_end")[0] for i in range(1, len(parts) - 1, 2)}
+    if len(ks) != expected_kernels:
+        raise InvariantError(f"expected {expected_kernels} gemm_canon_kernel instantiations, found {len(ks)}: {list(ks)}")
+    for name, body in ks.items():
+        WM, WN, RB, CB, ST = map(int, re.search(r"ILb[01]ELb[01]" + r"ELi(\d+)" * 5 + "E", name).groups())
+        loads = WM * RB + WN * CB                    # direct loads per wavefront and step
+        mma = RB * CB
+        if "scratch_" in body:
+            raise InvariantError(f"{name}: spills to scratch")
+        loops = {h: b for h, b in _loops(body).items() if any("v_mfma_scale" in x for x in b)}
+        if len(loops) != 2:
+            raise InvariantError(f"{name}: {len(loops)} pipelined loops (expected the filling and the draining one)")
+        for header, blocks in loops.items():
+            where = f"{name}, loop {header}"
+            whole = "".join(blocks)
+            dwords = len(re.findall(r"ds_read_b32", whole)) + 2 * len(re.findall(r"ds_read2\w*_b32", whole))
+            counts = (whole.count("v_mfma_scale"), whole.count("s_barrier"), whole.count("ds_read_b128"), dwords)
+            if counts != (4 * mma, 1, 4 * (RB + CB), RB + CB):
+                raise InvariantError(f"{where}: MFMAs, barriers, fragment and scale reads {counts} are not one step's")
+            n_loads = whole.count("global_load_lds_")
+            if n_loads not in (0, loads):
+                raise InvariantError(f"{where}: {n_loads} direct loads (expected {loads} or none)")
+            # the step's barrier: the explicit count right before it, the first issue's fragments and all scales right behind
+            block = next(b for b in blocks if "s_barrier" in b)
+            before, after = block.split("s_barrier")
+            waits = re.findall(r"s_waitcnt ([^\n;]*)", before)
+            count = (ST - 2) * loads if n_loads else 0
+            if not waits or waits[-1].split() != [f"vmcnt({count})", "lgkmcnt(0)"] or "ds_read" in before:
+                raise InvariantError(f"{where}: not vmcnt({count}) lgkmcnt(0), then the barrier: {waits}")
+            first = len(re.findall(r"ds_read_b128", after))
+            scales = len(re.findall(r"ds_read_b32", after)) + 2 * len(re.findall(r"ds_read2\w*_b32", after))
+            if first < RB + CB or scales != RB + CB:
+                raise InvariantError(f"{where}: a read of the step's first operands left its place behind the barrier")
+            # the MFMAs: one block, no wait for loads in it, no LDS read once the last issue has begun
+            multiply = [b for b in blocks if "v_mfma_scale" in b]
+            pieces = "".join(multiply).split("v_mfma_scale")
+            if len(multiply) != 1 or "vmcnt" in multiply[0]:
+                raise InvariantError(f"{where}: the MFMAs are not one block free of waits for loads")
+            if any("ds_read" in p for p in pieces[3 * mma + 1:]):
+                raise InvariantError(f"{where}: an LDS read behind the last issue: it may belong to the next step")
+            # full drains: with the scales' ds_write, and among the byte loads of a row's last scales
+            for b in blocks:
+                if "vmcnt(0)" in b and "s_barrier" not in b and "ds_write_b128" not in b and "global_load_ubyte" not in b \
+                        and re.search(r"ds_read|global_load_lds", b):
+                    raise InvariantError(f"{where}: a full drain of the ring")

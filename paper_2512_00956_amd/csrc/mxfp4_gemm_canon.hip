@@ -15,7 +15,7 @@
 //   * Scale rows are K / 32 bytes at any alignment.  Read where an MFMA needs them, they were as many cache-line lookups
 //     as the operands; instead each thread fetches the 16 bytes of one row's next two steps at a time and leaves them
 //     in LDS, where a lane picks its dword per step (its bytes are the four issues').
-// The direct loads are issued from inline asm (and the barrier is a bare s_barrier) for the reason given in
+// The direct loads are issued from inline asm (and the barrier's fences name LDS only) for the reason given in
 // mxfp4_gemm_frag.hip: the compiler would drain them at every LDS read.  They have no register destination; their
 // arrival is the explicit vmcnt's business.  The scale loads are ordinary ones; the compiler's wait for them, one in two
 // steps, drains the ring's loads as well.
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(256) void gemm_canon_kernel(
     else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     __builtin_amdgcn_s_waitcnt(kLgkm0);
     WUSH_FENCE
-    asm volatile("s_barrier");
+    lds_barrier();
     WUSH_FENCE
     asm volatile("" : "+s"(slot_off));        // LDS changes behind the compiler's back: no address may look like an old one
     int refill_off = slot_off - S::kSlotB;    // slot of step kt - 1 = of step kt + ST - 1

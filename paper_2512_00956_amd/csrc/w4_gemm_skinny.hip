@@ -168,12 +168,6 @@ __global__ __launch_bounds__(kWaves * 64) void w4_skinny_kernel(
 // It needs a workgroup per 4 CBW blocks of output channels, so few channels leave CUs idle, and every MFMA reads
 // its X fragment from LDS (with CBW = 1): the launcher takes it where it was measured faster (launch()).  The
 // kernel is written for any RB and CBW; only RB = 4, CBW = 1 is instantiated.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Accumulator e of lane (r, h), row block rb: token 32 rb + r, output channel 32 j + 8 (e / 4) + 4 h + e % 4.
 template <int RB, bool OUT_F32>
 __device__ __forceinline__ void store_block(const v16f (&acc)[RB], int j, int M, int N, void* __restrict__ Y,

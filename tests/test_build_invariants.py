@@ -73,6 +73,28 @@ def test_loads_to_lds_wait_for_m0(src):
             check_lds_load_asm(text[:load.start()] + planted + text[load.end():])
 
 
+def test_gemm_canon_generated_code():
+    """The canonical GEMM: one step's MFMAs and LDS reads between two barriers, the explicit count of loads in front of the
+    barrier, no spill, no drain beside the documented one; planted faults in the assembly text are caught."""
+    from paper_2512_00956_amd.build_checks import InvariantError, check_gemm_canon_asm
+    text = _compile("mxfp4_gemm_canon.hip")
+    check_gemm_canon_asm(text)
+    barrier = re.search(r"s_waitcnt vmcnt\(([1-9]\d*)\) lgkmcnt\(0\)\n(?:\s*;[^\n]*\n)*\s*s_barrier\n", text)        # a ring of three or four
+    start = text.rindex("v_mfma_scale", 0, barrier.start())
+    last = re.search(r"(?s).*(v_mfma_scale[^\n]*\n)", text[:barrier.start()]).end(1)
+    read = re.compile(r"\s*ds_read_b128 [^\n]*\n").search(text, barrier.end())
+    faults = [
+        text.replace("s_barrier", "scratch_store_dword off, v0, s0\n\ts_barrier", 1),
+        text[:barrier.start()] + barrier.group(0).replace(barrier.group(1), "0", 1) + text[barrier.end():],
+        text[:start] + "s_waitcnt vmcnt(0)\n\t" + text[start:],
+        text[:barrier.start()] + read.group(0).strip() + "\n\t" + barrier.group(0) + text[barrier.end():read.start()] + "\n" + text[read.end():],
+        text[:last] + read.group(0) + text[last:read.start()] + "\n" + text[read.end():],
+    ]
+    for planted in faults:
+        with pytest.raises(InvariantError):
+            check_gemm_canon_asm(planted)
+
+
 def test_lanes_that_exchange_through_lds_are_fenced():
     """__builtin_amdgcn_wave_barrier touches no memory to the compiler: wherever it orders LDS accesses of one wavefront it stands
     between wavefront fences, that is in wave_lds_sync (wush_device.hpp) and nowhere else."""
