@@ -223,6 +223,15 @@ def _stream(stream):
 _raw_stream = None
 
 
+def _forget_raw_stream():
+    global _raw_stream
+    _raw_stream = None
+
+
+# In a forked child the first call asks torch again, which refuses to use CUDA there.
+os.register_at_fork(after_in_child=_forget_raw_stream)
+
+
 def _current_stream() -> int:
     """torch's current stream of the current device as an integer (torch.cuda.current_stream().cuda_stream, without
     building the Stream object)."""

@@ -57,3 +57,26 @@ def test_format_descriptor_is_checked(F):
     assert F.linear(Q, S, Q, S, Y, bad, 0, 64) == 4           # WUSH_ERR_FMT
     with pytest.raises(ValueError):
         F.quantize_act(_t(4), T, Q, S, None, None, 0)
+
+
+def test_a_forked_child_asks_torch_for_its_stream(monkeypatch):
+    """A stream handle read past torch.cuda.current_stream() would not notice that CUDA cannot be used behind a fork: torch
+    refuses there, and so must a call made in the child of a process whose calls have run."""
+    import os
+
+    def refuse(*_):
+        raise RuntimeError("Cannot re-initialize CUDA in forked subprocess")
+    monkeypatch.setattr(torch.cuda, "current_stream", refuse)
+    monkeypatch.setattr(P, "_raw_stream", lambda: 0x1234)
+    assert P._current_stream() == 0x1234
+    pid = os.fork()
+    if pid == 0:
+        code = 1
+        try:
+            P._current_stream()
+        except RuntimeError:
+            code = 0
+        finally:
+            os._exit(code)
+    assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
+    assert P._current_stream() == 0x1234
