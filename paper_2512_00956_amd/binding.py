@@ -173,6 +173,7 @@ def _load_fast():
     global _fast
     lib()
     from . import _wush_call
+    _wush_call.use_format_type(WushFmt)
     _fast = _wush_call
     return _fast
 

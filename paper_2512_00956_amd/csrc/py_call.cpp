@@ -13,6 +13,7 @@
 namespace {
 
 PyObject *s_data_ptr, *s_shape, *s_stride, *s_numel, *s_element_size, *o_zero;
+PyObject* format_type;   // binding.WushFmt, set when binding loads this module
 
 // Conversions: false with an exception set on failure.
 bool to_i64(PyObject* o, int64_t* out) {
@@ -92,8 +93,14 @@ bool format(PyObject* f, int32_t default_layout, wush_fmt* out) {
     return true;
   }
   Py_buffer b;
+  const int type = format_type ? PyObject_IsInstance(f, format_type) : 0;
+  if (type < 0) return false;
+  if (!type) {
+    PyErr_SetString(PyExc_TypeError, "a WushFmt is expected");
+    return false;
+  }
   if (PyObject_GetBuffer(f, &b, PyBUF_SIMPLE) != 0) return false;
-  const bool ok = b.len == static_cast<Py_ssize_t>(sizeof(wush_fmt));
+  const bool ok = b.len >= static_cast<Py_ssize_t>(sizeof(wush_fmt));
   if (ok) *out = *static_cast<const wush_fmt*>(b.buf);
   else PyErr_SetString(PyExc_TypeError, "a WushFmt is expected");
   PyBuffer_Release(&b);
@@ -230,10 +237,18 @@ PyObject* linear_int4(PyObject*, PyObject* const* a, Py_ssize_t n) {
   WUSH_CALL(wush_linear_int4(Xq, Xs, Wq, Ws, M, N, K, layout, out, Y, ld, stream));
 }
 
+// (type): the class format descriptors are instances of
+PyObject* use_format_type(PyObject*, PyObject* type) {
+  Py_INCREF(type);
+  Py_XSETREF(format_type, type);
+  Py_RETURN_NONE;
+}
+
 #define WUSH_METHOD(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {WUSH_METHOD(quantize_act),       WUSH_METHOD(linear),       WUSH_METHOD(layer_decode),
                          WUSH_METHOD(layer_decode_static), WUSH_METHOD(quantize_act_nvfp4), WUSH_METHOD(linear_nvfp4),
-                         WUSH_METHOD(quantize_act_int4),  WUSH_METHOD(linear_int4),  {nullptr, nullptr, 0, nullptr}};
+                         WUSH_METHOD(quantize_act_int4),  WUSH_METHOD(linear_int4),
+                         {"use_format_type", use_format_type, METH_O, nullptr},            {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_wush_call", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

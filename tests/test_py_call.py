@@ -52,6 +52,9 @@ def test_wrong_arguments_raise(F, name, args):
 def test_format_descriptor_is_checked(F):
     with pytest.raises((TypeError, BufferError)):
         F.linear(Q, S, Q, S, Y, b"short", 0, 40)
+    for other in (bytes(P.default_fmt()), torch.zeros(6, dtype=torch.int32).numpy(), 24):
+        with pytest.raises(TypeError):
+            F.linear(Q, S, Q, S, Y, other, 0, 40)             # the right bytes are not the right type
     bad = P.default_fmt()
     bad.block = 16
     assert F.linear(Q, S, Q, S, Y, bad, 0, 64) == 4           # WUSH_ERR_FMT
