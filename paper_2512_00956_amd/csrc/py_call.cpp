@@ -76,7 +76,7 @@ bool k_of(PyObject* k, PyObject* codes, int64_t* out) {
   bool ok = PyTuple_Check(s) && PyTuple_GET_SIZE(s) > 0;
   if (!ok) PyErr_SetString(PyExc_IndexError, "codes without a shape");
   ok = ok && to_i64(PyTuple_GET_ITEM(s, PyTuple_GET_SIZE(s) - 1), out);
-  *out *= 2;
+  if (ok) *out *= 2;
   Py_DECREF(s);
   return ok;
 }
