@@ -4,8 +4,9 @@ Tensor arguments are torch tensors on the GPU (torch is used for device memory
 and streams); each wrapper passes `data_ptr()`s, sizes and the current HIP
 stream to the C entry point of the same name and raises `WushError` on a
 non-zero status.  The entry points a program calls every step go through the
-extension module `_wush_call` (csrc/py_call.cpp), the others through ctypes.  No
-fallback exists: if `libwush.so` or the module is missing the first call raises.
+extension module `_wush_call` (csrc/py_call.cpp) where it is built for the running
+Python, the others through ctypes.  Either way the C library does the work; it has
+no fallback: if `libwush.so` is missing the first call raises.
 """
 from __future__ import annotations
 
@@ -169,12 +170,16 @@ _fast = None
 
 
 def _load_fast():
-    """The extension module of the per-step calls (loads it on first use; it links to the libwush.so beside it)."""
+    """The extension module of the per-step calls (loads it on first use; it links to the libwush.so beside it), or the
+    same functions through ctypes where there is none for this Python."""
     global _fast
     lib()
-    from . import _wush_call
-    _wush_call.use_format_type(WushFmt)
-    _fast = _wush_call
+    try:
+        from . import _wush_call as calls
+        calls.use_format_type(WushFmt)
+    except ImportError:
+        from . import _ctypes_call as calls
+    _fast = calls
     return _fast
 
 

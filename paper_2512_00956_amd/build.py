@@ -1,6 +1,6 @@
 """Builds libwush.so (gfx950 only) in-tree with hipcc, and beside it libwush_probes.so, the
 benchmark's measurement aids (MFMA-only and streaming kernels: not part of the layer path), and
-_wush_call.so, the Python module of the per-step calls.
+_wush_call, the Python module of the per-step calls (where the running Python's headers are there).
 
 Usage: python -m paper_2512_00956_amd.build
 """
@@ -17,7 +17,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libwush.so")
 CALL_SRC = os.path.join(CSRC, "py_call.cpp")
-CALL_LIB = os.path.join(HERE, "_wush_call.so")
+# named for the Python it is built for: another one does not load it (and calls through ctypes)
+CALL_LIB = os.path.join(HERE, "_wush_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 PROBES_SRC = os.path.join(HERE, "probes", "probes.hip")
 PROBES_LIB = os.path.join(HERE, "libwush_probes.so")
 SOURCES = ["wush_api.hip", "transform_quant.hip", "weight_prep.hip", "mxfp4_gemm.hip", "mxfp4_gemm_frag.hip", "mxfp4_gemm_canon.hip", "build_transforms.hip", "layer_decode.hip", "gptq_prep.hip", "nvfp4_quant.hip", "nvfp4_gemm.hip", "int4_quant.hip", "w4_gemm_skinny.hip"]
@@ -55,6 +56,28 @@ def check_generated_code(hipcc: str, bdir: str) -> None:
             check(text)                    # raises InvariantError
 
 
+def build_call_module() -> str | None:
+    """The Python module of the per-step calls: host code only, finds libwush.so beside itself.  Needs the running Python's
+    headers and g++; without them the binding makes the same calls through ctypes.  Returns its path, or None."""
+    stale = os.path.join(HERE, "_wush_call.so")          # a module any Python would load
+    if os.path.exists(stale):
+        os.remove(stale)
+    include, compiler = sysconfig.get_paths()["include"], shutil.which("g++")
+    if compiler is None or not os.path.exists(os.path.join(include, "Python.h")):
+        print("_wush_call is not built (no g++ or no Python.h): the per-step calls go through ctypes", file=sys.stderr)
+        if os.path.exists(CALL_LIB):
+            os.remove(CALL_LIB)                          # it belongs to an earlier libwush.so
+        return None
+    tmp = CALL_LIB + ".tmp"
+    cmd = [compiler, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", include, "-I", os.path.join(ROOT, "include"),
+           CALL_SRC, "-o", tmp, "-L", HERE, "-lwush", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on py_call.cpp:\n{r.stdout}")
+    os.replace(tmp, CALL_LIB)
+    return CALL_LIB
+
+
 def build(verbose: bool = False) -> str:
     """Compile every kernel source and link libwush.so; returns its path."""
     hipcc = hipcc_path()
@@ -85,14 +108,7 @@ def build(verbose: bool = False) -> str:
         if r.returncode != 0:
             raise RuntimeError(f"link failed:\n{r.stdout}")
         os.replace(tmp, lib)
-    # the Python module of the per-step calls: host code only, finds libwush.so beside itself
-    tmp = CALL_LIB + ".tmp"
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"], "-I",
-           os.path.join(ROOT, "include"), CALL_SRC, "-o", tmp, "-L", HERE, "-lwush", "-Wl,-rpath,$ORIGIN"]
-    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"g++ failed on py_call.cpp:\n{r.stdout}")
-    os.replace(tmp, CALL_LIB)
+    build_call_module()
     return LIB
 
 

@@ -39,6 +39,28 @@ def test_status_of_an_impossible_size(F, name, args):
 
 
 @pytest.mark.parametrize("name,args", CALLS)
+def test_calls_without_the_module(monkeypatch, name, args):
+    """Where there is no module for the running Python, the same functions through ctypes return the same status."""
+    import sys
+    monkeypatch.setattr(P, "_fast", None)
+    monkeypatch.setitem(sys.modules, "paper_2512_00956_amd._wush_call", None)      # importing it raises ImportError
+    monkeypatch.delattr("paper_2512_00956_amd._wush_call", raising=False)
+    calls = P._load_fast()
+    assert calls.__name__.endswith("_ctypes_call")
+    test_status_of_an_impossible_size(calls, name, args)
+    with pytest.raises(P.WushError):
+        P.wush_linear(Q, S, Q, S, Y, stream=0)
+
+
+def test_the_build_does_without_a_host_compiler(monkeypatch, tmp_path):
+    from paper_2512_00956_amd import build
+    monkeypatch.setattr(build, "HERE", str(tmp_path))
+    monkeypatch.setattr(build, "CALL_LIB", str(tmp_path / "_wush_call.so"))
+    monkeypatch.setattr(build.shutil, "which", lambda name: None)
+    assert build.build_call_module() is None and not list(tmp_path.iterdir())
+
+
+@pytest.mark.parametrize("name,args", CALLS)
 def test_wrong_arguments_raise(F, name, args):
     fn = getattr(F, name)
     with pytest.raises(TypeError):
