@@ -371,10 +371,9 @@ hipError_t launch_split_k(const void* Xq, const void* Xs, const float* tsx, cons
 }
 
 // The shared-X schedule is built for 65..128 tokens with one weight block per wave: the only shape in which it
-// beats the K split (measured from HBM, us, K split | shared X, 128 tokens: 8192 -> 57344 NVFP4 148 | 152, INT4 181 | 170;
-// 4096 -> 57344 81 | 80 and 94 | 92; 8192 -> 43008 INT4 145 | 141; 8192 -> 28672 INT4 93 | 100).  With fewer tokens the K
-// split's conversions are already cheap, with two weight blocks per wave too few workgroups are left, and with fewer
-// output channels the whole-K walk of a wave leaves CUs idle.
+// beats the K split, and only on the layers shared_x_pays() names.  With fewer tokens the K split's conversions are
+// already cheap, with two weight blocks per wave too few workgroups are left, and with fewer output channels the whole-K
+// walk of a wave leaves CUs idle.
 template <int FMT>
 hipError_t launch_shared_x(const void* Xq, const void* Xs, const float* tsx, const void* Wq, const void* Ws,
                            const float* tsw, int64_t M, int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy,
@@ -394,16 +393,26 @@ hipError_t launch_shared_x(const void* Xq, const void* Xs, const float* tsx, con
   return hipGetLastError();
 }
 
-// Which schedule: shared X for 65..128 tokens once the layer has enough output channels for it (fitted on the
-// cases above: from 5 blocks of 32 per CU for INT4, whose conversions cost more, from 7 for NVFP4); the switch
-// kDbgW4Skinny forces one (1 = K split across the waves, 2 = shared X where it exists).
+// Whether the shared-X schedule is the faster one for 65..128 tokens.  Its time goes in rounds of two workgroups, eight blocks of 32
+// channels, per CU, while the K split's finer grid grows with the channels; so it pays where a round is nearly full, for INT4, whose
+// conversions cost more, from six blocks per CU, for NVFP4 from seven, but not where a second round has only begun.  Measured at
+// 100 tokens from HBM, us, K split | shared X, by blocks per CU:
+//   INT4  8192: 5 127 | 143, 6 150 | 148, 6.25 167 | 148, 7 179 | 154, 8 205 | 165, 9 234 | 228, 10 261 | 236, 12 302 | 254
+//         4096: 5  64 |  78, 6  77 |  80, 6.25  84 |  80, 7  89 |  83, 8 101 |  87, 9 121 | 122, 10 131 | 124, 12 152 | 131
+//   NVFP4 8192: 6 122 | 133, 6.5 139 | 137, 7 146 | 140, 8 171 | 147, 9 200 | 203, 10 220 | 211, 11 240 | 217
+//         4096: 6  64 |  74, 6.5  73 |  75, 7  76 |  76, 8  87 |  79, 9  97 | 112, 10 109 | 115, 11 119 | 117
+bool shared_x_pays(int fmt, int64_t N) {
+  const int64_t NB = (N + 31) / 32, cus = device_cu_count();
+  return fmt == kInt4 ? NB > 6 * cus && !(NB > 8 * cus && NB <= 9 * cus)
+                      : NB >= 7 * cus && !(NB > 8 * cus && NB <= 10 * cus);
+}
+
+// The switch kDbgW4Skinny forces a schedule (1 = K split across the waves, 2 = shared X where it exists).
 template <int FMT>
 hipError_t launch(const void* Xq, const void* Xs, const float* tsx, const void* Wq, const void* Ws, const float* tsw,
                   int64_t M, int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy, hipStream_t stream) {
   const int forced = debug_option(kDbgW4Skinny);
-  const int64_t NB = (N + 31) / 32;
-  const bool wide = NB >= (FMT == kInt4 ? 5 : 7) * (int64_t)device_cu_count();
-  const bool shared_x = M > 64 && (forced == 2 || (forced != 1 && wide));
+  const bool shared_x = M > 64 && (forced == 2 || (forced != 1 && shared_x_pays(FMT, N)));
   if (shared_x) return launch_shared_x<FMT>(Xq, Xs, tsx, Wq, Ws, tsw, M, N, K, out_f32, Y, ldy, stream);
   return launch_split_k<FMT>(Xq, Xs, tsx, Wq, Ws, tsw, M, N, K, out_f32, Y, ldy, stream);
 }

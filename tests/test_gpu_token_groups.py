@@ -81,3 +81,38 @@ def test_few_tokens(P, M, K, N, fmt):
     torch.cuda.synchronize()
     assert O.rel_fro(Y[:M].double().cpu().numpy(), ref) <= 1e-5
     assert (Y[M:] == 7.0).all()
+
+
+# blocks of 32 output channels per compute unit (256 of them) -> schedule (1: K split over a workgroup's waves, 2: activations
+# shared), on either side of every line of the rule
+SCHEDULES = [("int4", 5, 1), ("int4", 6, 1), ("int4", 6.125, 2), ("int4", 8, 2), ("int4", 8.125, 1), ("int4", 9, 1), ("int4", 9.125, 2),
+             ("nvfp4", 6.875, 1), ("nvfp4", 7, 2), ("nvfp4", 8, 2), ("nvfp4", 8.125, 1), ("nvfp4", 10, 1), ("nvfp4", 10.125, 2)]
+
+
+@pytest.mark.parametrize("fmt,blocks,schedule", SCHEDULES)
+def test_schedule_by_output_channels(P, fmt, blocks, schedule):
+    """65..128 tokens: the schedules add K in different orders, so the default's bits tell which one ran."""
+    import torch
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256
+    M, K, N = 70, 512, int(32 * 256 * blocks)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    size = lambda rows: P.wush_packed_sizes_nvfp4(rows, K, 1)
+    codes = lambda rows: torch.randint(0, 256, (size(rows)[0],), dtype=torch.uint8, device="cuda", generator=g)
+    if fmt == "nvfp4":
+        scales = lambda rows: torch.randint(30, 100, (size(rows)[1],), dtype=torch.uint8, device="cuda", generator=g)
+    else:
+        scales = lambda rows: (torch.rand(size(rows)[1] // 2, device="cuda", generator=g) + 0.5).bfloat16().view(torch.uint8)
+    X, W, ts = (codes(M), scales(M)), (codes(N), scales(N)), torch.ones(1, device="cuda")
+    y = {}
+    for forced in (-1, 1, 2):
+        Y = torch.empty(M, N, device="cuda")
+        P.wush_debug_set(P.WUSH_DEBUG_W4_SKINNY, forced)
+        try:
+            if fmt == "nvfp4":
+                P.wush_linear_nvfp4(*X, ts, *W, ts, Y, 1, 1, K=K)
+            else:
+                P.wush_linear_int4(*X, *W, Y, 1, 1, K=K)
+        finally:
+            P.wush_debug_set(P.WUSH_DEBUG_W4_SKINNY, -1)
+        y[forced] = Y
+    assert not torch.equal(y[1], y[2]) and torch.equal(y[-1], y[schedule])
