@@ -339,13 +339,14 @@ hipError_t launch_split_k(const void* Xq, const void* Xs, const float* tsx, cons
   // 8.5 -> 4.9 | 10.2 -> 5.5; 128 x 8192 -> 28672 81 -> 77 | 119 -> 93; 128 x 4096 -> 24576 34.6 -> 33.0 | 50.4 -> 39.0).
   // Up to 64 tokens two weight blocks pay from where the coarser grid takes no round more: 64 x 8192 -> 28672, 3.5 blocks per
   // compute unit, 49.3 -> 43.1 | 61.9 -> 51.2, 16 tokens INT4 44.1 -> 40.1, but 16 x 8192 -> 20480 (2.5 blocks) NVFP4 25.1 against
-  // 27.2.  NVFP4 at 16 tokens and 3.5 blocks gains from HBM what it loses with its weights in the last-level cache
-  // (35.7 -> 33.0, 33.5 -> 34.0), so there it waits for four.
+  // 27.2.  NVFP4 between three and four blocks (replayed graphs, from HBM | weights in the last-level cache, one -> two weight
+  // blocks): 16 x 8192 -> 28672 35.2 -> 33.7 | 28.8 -> 28.3, 16 x 8192 -> 25088 33.1 -> 31.4 | 27.9 -> 27.0, 32 x 4096 -> 28672 21.4 ->
+  // 21.2 | 17.9 -> 17.4, 1 x 16384 -> 28672 64.6 -> 60.3 | 53.9 -> 51.5.
   const int64_t cus = device_cu_count(), tokens = (M + 31) / 32;
   int rb = 2, cbw = 2;
   if (M <= 32 || NB * tokens <= cus) {
     rb = 1;
-    cbw = M <= 32 && (FMT == kInt4 ? NB > 3 * cus : NB >= 4 * cus) ? 2 : 1;
+    cbw = M <= 32 && NB > 3 * cus ? 2 : 1;
   } else if (M <= 64) {
     cbw = NB > 3 * cus ? 2 : 1;
   } else if (2 * NB <= cus) {
