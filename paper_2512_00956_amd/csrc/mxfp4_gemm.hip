@@ -22,8 +22,9 @@ __device__ __forceinline__ void store_out(void* Y, int64_t ldy, int row, int col
   else reinterpret_cast<uint16_t*>(Y)[(int64_t)row * ldy + col] = f32_to_bf16_bits(v);
 }
 
-// Reference-grade kernel: one wavefront per 32x32 output tile, operands straight
-// from global memory.  Handles every shape (ragged M, N, odd K/32).
+// One wavefront per 32x32 output tile, operands straight from global memory.  Handles every
+// shape (ragged M, N, odd K/32).  Runs where K is too short for a pipeline (short_k below), and, forced,
+// as an independent implementation in the tests.
 __global__ __launch_bounds__(256) void gemm_simple_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs,
     const uint8_t* __restrict__ Wq, const uint8_t* __restrict__ Ws,
@@ -67,6 +68,23 @@ __global__ __launch_bounds__(256) void gemm_simple_kernel(
   }
 }
 
+// Canonical layout: whether K is so short that the one-wave-per-tile kernel is the faster one.  The pipelined kernel
+// (mxfp4_gemm_canon.hip) spends a fixed part per tile on its prologue and on turning the outputs in LDS; with one or two steps of K
+// nothing hides that.  us, pipelined | one wave per tile:
+//   K <= 128: 2048 x 96 -> 32768 FP32 88 | 47, BF16 56 | 33, 2048 x 128 -> 4096 7.0 | 7.1
+//   K < 256:  2048 x 192 -> 32768 FP32 89 | 60; small BF16 outputs are up to 1.15 times faster pipelined; rows without 16-byte alignment
+//             1.1 to 1.5 times slower at any size
+//   K < 512, a partial second step: up to 16 tokens 1.0 to 1.25 times slower pipelined (288 -> 32768), at 200 and more tokens faster (352 ->
+//             8192 0.80); rows without 16-byte alignment 1.02 to 1.4 times slower up to some 4 M outputs, at 2048 x 416 -> 8192 0.90
+//   whole steps (256, 512): pipelined, 0.3 to 0.95 of the time
+bool short_k(int64_t M, int64_t N, int64_t K, int vec_store) {
+  if (M * N >= (int64_t)1 << 35) return false;   // its grid of 32 x 32 tiles
+  if (K <= 128) return true;
+  if (K < 256) return !vec_store || M * N >= (int64_t)1 << 24;
+  if (K % 256 != 0 && K < 512) return vec_store ? M <= 16 : M * N <= (int64_t)1 << 22;
+  return false;
+}
+
 }  // namespace
 
 hipError_t launch_mxfp4_gemm(const void* Xq, const void* Xs, const void* Wq, const void* Ws,
@@ -100,8 +118,10 @@ hipError_t launch_mxfp4_gemm(const void* Xq, const void* Xs, const void* Wq, con
     if (skinny) return launch_mxfp4_gemm_skinny(Xq, Xs, Wq, Ws, M, N, K, out_f32, Y, ldy, stream);
     return launch_mxfp4_gemm_frag(Xq, Xs, Wq, Ws, M, N, K, out_f32, Y, ldy, stream);
   }
-  const bool force_simple = debug_option(kDbgGemmSimple) == 1;   // tests: the general kernel
-  if (!force_simple) return launch_mxfp4_gemm_canon(Xq, Xs, Wq, Ws, M, N, K, out_f32, Y, ldy, stream);
+  bool simple = short_k(M, N, K, canon_vec_store(Y, ldy, out_f32));
+  if (debug_option(kDbgGemmTile) >= 0) simple = false;                                       // tests: a tile shape of the other kernel
+  if (const int forced = debug_option(kDbgGemmSimple); forced >= 0) simple = forced == 1;    // tests: either kernel
+  if (!simple) return launch_mxfp4_gemm_canon(Xq, Xs, Wq, Ws, M, N, K, out_f32, Y, ldy, stream);
   const int64_t tiles = ((M + 31) / 32) * ((N + 31) / 32);
   gemm_simple_kernel<<<dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, stream>>>(
       (const uint8_t*)Xq, (const uint8_t*)Xs, (const uint8_t*)Wq, (const uint8_t*)Ws,

@@ -293,7 +293,7 @@ hipError_t launch_shape(const void* Xq, const void* Xs, const void* Wq, const vo
   const hipError_t attr = lds_limit.ensure(reinterpret_cast<const void*>(kernel), S::kLds);
   if (attr != hipSuccess) return attr;
   const int tiles_m = (int)((M + S::kTM - 1) / S::kTM), tiles_n = (int)((N + S::kTN - 1) / S::kTN);
-  const int vec_store = ldy % (OUT_F32 ? 4 : 8) == 0 && (reinterpret_cast<uintptr_t>(Y) & 15) == 0;
+  const int vec_store = canon_vec_store(Y, ldy, OUT_F32);
   kernel<<<dim3((unsigned)((int64_t)tiles_m * tiles_n)), dim3(256), S::kLds, stream>>>(
       (const uint8_t*)Xq, (const uint8_t*)Xs, (const uint8_t*)Wq, (const uint8_t*)Ws, (int)M, (int)N, (int)K, Y, ldy, tiles_m,
       tiles_n, vec_store);
@@ -331,7 +331,7 @@ hipError_t launch_mxfp4_gemm_canon(const void* Xq, const void* Xs, const void* W
                                    int64_t K, int out_f32, void* Y, int64_t ldy, hipStream_t stream) {
   const int cus = device_cu_count();
   const bool one_each = ((M + 127) / 128) * ((N + 127) / 128) <= cus;   // 128 x 128: a compute unit's one workgroup gets four slots
-  const int vec = ldy % (out_f32 ? 4 : 8) == 0 && (reinterpret_cast<uintptr_t>(Y) & 15) == 0;
+  const int vec = canon_vec_store(Y, ldy, out_f32);
   const double cost[5] = {shape_cost_us(M, N, K, 256, 256, 1.0, 6.6, 1.95, 1.95, vec, cus),
                           shape_cost_us(M, N, K, 128, 128, 2.5, 1.8, 0.77, 0.64, vec, cus),
                           one_each ? shape_cost_us(M, N, K, 128, 128, 2.5, 1.8, 0.67, 0.67, vec, cus) : 1e30,

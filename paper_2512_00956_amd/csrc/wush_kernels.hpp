@@ -84,10 +84,14 @@ hipError_t launch_build_transforms(const void* W, int64_t N, int64_t ldw, const 
                                    int64_t K, double lambda, int block, void* T_out, double* T_f64, void* workspace,
                                    hipStream_t stream);   // block = 32, or 16 for the NVFP4 variant
 
-// Operands in the fragment-order layout (K % 256 == 0).
+// Row-major operands, any K % 32 == 0.  canon_vec_store: whether every row of Y takes 16-byte stores.
+inline int canon_vec_store(const void* Y, int64_t ldy, int out_f32) {
+  return ldy % (out_f32 ? 4 : 8) == 0 && (reinterpret_cast<uintptr_t>(Y) & 15) == 0;
+}
 hipError_t launch_mxfp4_gemm_canon(const void* Xq, const void* Xs, const void* Wq, const void* Ws,
                                    int64_t M, int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy,
                                    hipStream_t stream);
+// Operands in the fragment-order layout (K % 256 == 0).
 hipError_t launch_mxfp4_gemm_frag(const void* Xq, const void* Xs, const void* Wq, const void* Ws,
                                   int64_t M, int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy,
                                   hipStream_t stream);

@@ -52,3 +52,38 @@ def test_every_tile_shape(P, G, M, K, N, tile):
             assert torch.equal(y[0], y[1].bfloat16()), pad
     finally:
         P.wush_debug_set(P.WUSH_DEBUG_GEMM_TILE, -1)
+
+
+# (tokens, K, output channels, row stride past them) -> the kernel with one wavefront per tile (True) or the pipelined one, on
+# either side of the rule's lines
+SHORT_K = [(64, 128, 520, 0, True), (64, 160, 520, 0, False), (64, 224, 520, 3, True), (64, 256, 520, 3, False),
+           (16, 288, 520, 0, True), (17, 288, 520, 0, False), (17, 480, 520, 3, True), (17, 512, 520, 3, False), (16, 512, 520, 0, False),
+           (16, 544, 520, 3, False), (2048, 480, 2056, 3, False), (2047, 480, 2048, 3, True), (2048, 160, 8192, 0, True),
+           (2047, 160, 8192, 0, False)]
+
+
+@pytest.mark.parametrize("M,K,N,pad,one_wave", SHORT_K)
+def test_short_k_dispatch(P, G, M, K, N, pad, one_wave):
+    """Both kernels against the FP64 product where the default changes from one to the other, and the default's bits."""
+    import torch
+    rng = np.random.default_rng(M + K + N)
+    xc, wc = rng.integers(0, 16, (M, K), dtype=np.uint8), rng.integers(0, 16, (N, K), dtype=np.uint8)
+    xs, ws = rng.integers(110, 140, (M, K // 32), dtype=np.uint8), rng.integers(110, 140, (N, K // 32), dtype=np.uint8)
+    args = (G.u8_dev(O.pack_codes(xc)), G.u8_dev(xs), G.u8_dev(O.pack_codes(wc)), G.u8_dev(ws))
+    y = {}
+    for forced in (-1, 0, 1):
+        Y = torch.full((M + 1, N + pad), 7.0, dtype=torch.float32, device="cuda")
+        P.wush_debug_set(P.WUSH_DEBUG_GEMM_SIMPLE, forced)
+        try:
+            P.wush_linear(*args, Y[:M, :N], P.default_fmt(out_dtype=1))
+        finally:
+            P.wush_debug_set(P.WUSH_DEBUG_GEMM_SIMPLE, -1)
+        assert (Y[M:] == 7.0).all() and (Y[:, N:] == 7.0).all()
+        y[forced] = Y[:M, :N].cpu()
+    rows = np.unique(np.linspace(0, M - 1, 64).astype(int))
+    ref = O.linear_dequant(xc[rows], xs[rows], wc, ws)
+    for forced in (0, 1):
+        assert O.rel_fro(y[forced].double().numpy()[rows], ref) <= 1e-6
+    assert torch.equal(y[-1], y[1 if one_wave else 0])
+    if K > 128:
+        assert not torch.equal(y[0], y[1])      # they add K in different orders
