@@ -12,6 +12,13 @@ __device__ __forceinline__ double rcp_refined(double x) {
   return fma(y, fma(e, e, e), y);
 }
 
+// a / d for a normal d, corrected to the rounded quotient (Markstein): in an elimination a / a has to be 1, or what is left of a
+// singular matrix is rounding noise instead of zero.
+__device__ __forceinline__ double div_refined(double a, double d) {
+  const double y = rcp_refined(d), q = a * y;
+  return fma(fma(-d, q, a), y, q);
+}
+
 // The value of x in another lane of the same row of 16, chosen by a DPP control word (no LDS round trip).
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double x) {
@@ -151,7 +158,7 @@ __device__ __forceinline__ bool reverse_factor_group(EntryFn entry, StoreUFn sto
     double d = row[j];
     if (!(d > 0.0)) { good = false; d = 1.0; }
     if (r == j) diag = d;
-    const double f = r < j ? row[r] * rcp_refined(d) : 0.0;
+    const double f = r < j ? div_refined(row[r], d) : 0.0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) a[i] = fma(-f, row[c0 + i], a[i]);
   }
@@ -255,7 +262,7 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
         __syncthreads();
         double d = col[j];
         if (!(d > 0.0)) { bad = true; d = 1.0; }
-        const double f = col[r] * rcp_refined(d);
+        const double f = div_refined(col[r], d);
         if ((q & 3) == jb) {
           raw[ji] = a[ji];
           diag[ji] = d;

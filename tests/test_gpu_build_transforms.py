@@ -198,3 +198,25 @@ def test_repeated_singular_values(P, G, block, clusters, noise_exp):
         ut /= np.linalg.norm(ut, axis=1, keepdims=True)
         err = np.max(np.abs(ut @ ut.T - np.eye(block)))
         assert err <= 2 * block * block * 2.0 ** -53, err
+
+
+@pytest.mark.parametrize("block", [32, 16])
+def test_equal_channels_are_flagged(P, G, block):
+    """lambda = 0 and channels that are all the same: the moment is c^2 everywhere, exactly, and every step of the factorization
+    behind the first meets a pivot of exactly zero, whatever c."""
+    import torch
+    build = P.wush_build_transforms if block == 32 else P.wush_build_transforms_nvfp4
+    W = G.bf16_dev(O.bf16_values_to_bits(O.round_to_bf16(np.random.default_rng(2).standard_normal((64, 32)))))
+    T = torch.empty((32 // block, block, block), dtype=torch.bfloat16, device="cuda")
+    ws = G.empty_u8(P.wush_build_transforms_workspace(32))
+    missed = []
+    for c in range(1, 128):
+        X = torch.full((64, 32), float(c), dtype=torch.bfloat16, device="cuda")
+        for args in ((W, X), (X, W)):
+            build(*args, 0.0, T, ws)
+            try:
+                P.wush_build_transforms_status(ws, 32)
+                missed.append(c)
+            except P.WushError as e:
+                assert e.code == 7
+    assert missed == []

@@ -222,3 +222,24 @@ def test_gptq_past_float_range(P, G, scale_exp):
     assert np.array_equal(s[:, 0], sr[:, 0]) and np.array_equal(c[:, 0], cr[:, 0])
     rest = np.setdiff1d(np.arange(N), big)
     assert np.mean((s != sr)[rest]) <= 1e-4 and np.mean((c != cr)[rest]) <= 1e-4, (np.mean(s != sr), np.mean((c != cr)[rest]))
+
+
+@pytest.mark.parametrize("K", [32, 96])
+def test_gptq_equal_channels_are_flagged(P, G, K):
+    """lambda = 0 and calibration channels that are all the same: the Hessian is c^2 everywhere, exactly, and not positive
+    definite, whatever c."""
+    import torch
+    W = G.bf16_dev(O.bf16_values_to_bits(O.round_to_bf16(np.random.default_rng(2).standard_normal((32, K)))))
+    T = G.bf16_dev(O.bf16_values_to_bits(O.round_to_bf16(np.broadcast_to(O.hadamard(), (K // 32, 32, 32)).copy())))
+    q, s = G.empty_u8(32, K // 2), G.empty_u8(32, K // 32)
+    ws = torch.empty(P.wush_prepare_weight_gptq_workspace(32, K), dtype=torch.uint8, device="cuda")
+    missed = []
+    for c in range(1, 64):
+        X = torch.full((64, K), float(c), dtype=torch.bfloat16, device="cuda")
+        P.wush_prepare_weight_gptq(W, X, 0.0, T, q, s, ws, transform_given=True)
+        try:
+            P.wush_prepare_weight_gptq_status(ws, 32, K)
+            missed.append(c)
+        except P.WushError as e:
+            assert e.code == 7
+    assert missed == []
