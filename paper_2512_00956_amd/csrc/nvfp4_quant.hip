@@ -417,12 +417,12 @@ __global__ __launch_bounds__(256) void nvfp4_weight_kernel(const uint16_t* __res
     const double d = round_e4m3_f64(fmax(m.first, m.second) * c, byte) * ts;
     const double rcp = byte == 0 ? 0.0 : 1.0 / d;
     // v rcp is at most about 12 (a group maximum whose scale byte rounded down from just below twice the smallest
-    // step), so the hardware convert at scale 1 decides it as FP64 comparisons would; they give a NaN code 0
+    // step), so the hardware convert at scale 1 decides it as FP64 comparisons would; they give a NaN code 0 and the sign of y
     float v[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const double scaled = y[i] * rcp;
-      v[i] = scaled == scaled ? f64_to_f32_sticky(scaled) : 0.0f;
+      v[i] = scaled == scaled ? f64_to_f32_sticky(scaled) : (float)copysign(0.0, y[i]);
     }
     const uint32_t word = pack8_e2m1(v, 1.0f);
     const int n = 16 * t + walk.l16, row = lane >> 4;
