@@ -20,7 +20,7 @@
 //     inv(T_i);  Hbar = (T_i U_ii)(T_i U_ii)^T, R = inverse of its reverse Cholesky factor (R^T R = inv(Hbar))
 //     per output channel: transformed weights, GPTQ subroutine (32 steps of quantize at a static group scale,
 //     err = (w - q)/R[r][r], w[r'] -= err R[r][r']), G_i, and block i + 1: S += G_i U, current weights, M_W.
-// c2 (4096 calibration tokens, 4096 -> 6144): 70.4 -> 18.4 ms, of which the loop 128 x 104 us, the factor 3.1 ms and H 1.8.
+// c2 (4096 calibration tokens, 4096 -> 6144): 70.4 -> 18.6 ms, of which the loop 128 x 105 us, the factor 3.1 ms and H 1.8.
 // Summation orders are fixed (no atomics), so the result is reproducible.
 #include "weight_mfma.hpp"
 #include "wush_block.hpp"

@@ -317,7 +317,8 @@ hipError_t launch_any(int shape, const void* Xq, const void* Xs, const void* Wq,
 // constants are fits to graph replays of each shape forced, on 13 layers from 1 x 4096 -> 6144 to 8192 x 4096 -> 14336 (us,
 // 256 x 256 | 128 x 128 | the same with four slots | 64 x 128 | 64 x 64): 4096 x 14336 -> 4096 116 | 146 | 180 | 188 | 252;
 // 512 x 4096 -> 6144 31 | 16.4 | 14.8 | 15.3 | 19.5; 128 tokens 28 | 14.6 | 13.2 | 11.0 | 9.2; 1 token 26 | 10.7 | 10.9 | 9.1 |
-// 7.4.  (The one-wavefront-per-tile kernel they replace: 189 with the 256 x 256 kernel it was paired with | 89 | 31 | 18.)
+// 7.4.  (Before: 189 with a 256 x 256 kernel of two
+// stages, 89 | 31 | 18 with one wavefront per tile, mxfp4_gemm.hip, which keeps the layers of short K.)
 double shape_cost_us(int64_t M, int64_t N, int64_t K, int tm, int tn, double base, double per_tile, double lat, double thr,
                      int vec_store, int cus) {
   const int64_t tiles = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);

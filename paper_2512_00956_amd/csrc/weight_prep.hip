@@ -30,7 +30,7 @@ __global__ __launch_bounds__(256) void invert_blocks_kernel(const uint16_t* __re
 // block): a wavefront keeps its block's inverse in registers and walks tiles of 16 rows (weight_mfma.hpp), the
 // four of a workgroup on adjacent blocks, so that a tile is 16 runs of 256 bytes.  Everything behind the product
 // is decided on the FP64 values, in 32-bit arithmetic: f64_to_f32_sticky keeps every comparison with a midpoint of
-// the grid and with 1.5 x a power of two what it was.  4096 -> 6144: 42 us (one thread per row and block, inverse in
+// the grid and with 1.5 x a power of two what it was.  4096 -> 6144: 44 us (one thread per row and block, inverse in
 // LDS, FP64 comparisons: 72).
 template <int FMT>   // 0: MXFP4, 1: INT4
 __global__ __launch_bounds__(256) void weight_apply_quant_kernel(

@@ -84,7 +84,7 @@ constexpr uint32_t kPivotKey = 0x03B8F2B1u;
 // elements (two LDS buffers in turn), and behind the barrier reads the pivot column, the pivot row and its own
 // factor.  Rows are not swapped: pos = the position the row would have after the swaps.  Pivot candidates are
 // compared by their upper words less 5 bits (15 fraction bits: enough for a pivot), which those 5 bits, the first position,
-// make unique; a singular block is found at the end.  32 x 32: 12 us against 91 us for one wavefront that swapped
+// make unique; a singular block is found at the end.  128 blocks of 32 x 32: 14 us against 91 us for one wavefront that swapped
 // rows in LDS and synchronized per row.
 template <int D, class EntryFn, class StoreFn>
 __device__ __forceinline__ bool invert_block_group(EntryFn entry, StoreFn store) {
@@ -188,7 +188,7 @@ __device__ __forceinline__ bool reverse_factor_group(EntryFn entry, StoreUFn sto
 // rounds), so what counts is the latency of a step, and the threads are there to shorten it: a column pair is
 // shared by the 16 lanes of a DPP row (two LDS loads and stores per lane, the three dot products summed by
 // four DPP steps), the factors are taken column by column out of registers with one barrier per column, and the
-// products are spread over the whole workgroup.  c2 layer (128 blocks): 201 -> 107 us; a Jacobi round is 850 cycles, of
+// products are spread over the whole workgroup.  c2 layer (128 blocks): 201 -> 104 us; a Jacobi round is some 850 cycles, of
 // which some 30 dependent FP64 operations and the LDS round trip are nearly all.
 template <int D, int MODE, class LoadFn, class FinishFn>
 __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, int S_W, int S_X, double lambda,
