@@ -322,6 +322,7 @@ hipError_t launch_any(int shape, const void* Xq, const void* Xs, const void* Wq,
 double shape_cost_us(int64_t M, int64_t N, int64_t K, int tm, int tn, double base, double per_tile, double lat, double thr,
                      int vec_store, int cus) {
   const int64_t tiles = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
+  if (tiles >= (int64_t)1 << 24) return 1e30;   // 256 work items each: a grid has fewer than 2^32
   const double n = (double)((tiles + cus - 1) / cus);
   return base + (vec_store ? 1.0 : 2.5) * per_tile * n + (double)((K + 255) / 256) * fmax(lat, thr * n);
 }
