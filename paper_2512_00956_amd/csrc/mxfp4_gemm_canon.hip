@@ -26,6 +26,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "row_store.hpp"
 #include "wush_device.hpp"
 #include "wush_kernels.hpp"
 
@@ -57,8 +58,7 @@ struct Shape {
 template <bool OUT_F32, bool RAGGED, int WM, int WN, int RB, int CB, int ST>
 __global__ __launch_bounds__(256) void gemm_canon_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const uint8_t* __restrict__ Wq,
-    const uint8_t* __restrict__ Ws, int M, int N, int K, void* __restrict__ Y, int64_t ldy, int tiles_m, int tiles_n,
-    int vec_store) {
+    const uint8_t* __restrict__ Ws, int M, int N, int K, void* __restrict__ Y, int64_t ldy, int tiles_m, int tiles_n) {
   using S = Shape<WM, WN, RB, CB, ST>;
   static_assert(WM * WN == 4 && S::kTM % 32 == 0 && ST >= 2, "four wavefronts, whole 8-row loads");
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
@@ -232,55 +232,18 @@ __global__ __launch_bounds__(256) void gemm_canon_kernel(
 #undef WUSH_FENCE
   __syncthreads();   // the ring becomes the transpose buffers
 
-  // ---- epilogue: the W fragment is the first operand, so lane (r, kh) of MFMA tile (i, j) holds token row 32 i + r,
-  // accumulator e is column 32 j + 8 (e / 4) + 4 kh + e % 4 of the wavefront's tile.  Each MFMA tile is turned in a
-  // wavefront-private buffer of 32 rows so that a store instruction covers whole runs of a row.
-  constexpr int kPitch = 36;                  // floats: the 16-byte writes and the row reads are conflict free
-  float* buf = reinterpret_cast<float*>(smem) + wave * 32 * kPitch;
-  static_assert(4 * 32 * kPitch * 4 <= S::kLds, "transpose buffers");
+  // ---- epilogue (row_store.hpp): each wavefront turns its row blocks in a private buffer
+  using Out = RowStore<OUT_F32, CB>;
+  static_assert(4 * Out::kBuf <= S::kLds, "transpose buffers");
+  uint8_t* buf = smem + wave * Out::kBuf;
 #pragma unroll
   for (int i = 0; i < RB; ++i) {
+    __builtin_amdgcn_sched_barrier(0);
+    wave_lds_sync();
 #pragma unroll
-    for (int j = 0; j < CB; ++j) {
-      __builtin_amdgcn_sched_barrier(0);
-      const int row0 = m0 + (wm * RB + i) * 32, col0 = n0 + (wn * CB + j) * 32;
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        *reinterpret_cast<v4f*>(buf + r * kPitch + 8 * q + 4 * kh) =
-            (v4f){acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-      wave_lds_sync();
-      if (vec_store && col0 + 32 <= N) {
-        // rows of 16-byte aligned chunks: 8 lanes (FP32) or 4 (BF16) per row
-        constexpr int kLanes = OUT_F32 ? 8 : 4, kPer = 32 / kLanes;
-#pragma unroll
-        for (int p = 0; p < 32 * kLanes / 64; ++p) {
-          const int row = p * (64 / kLanes) + lane / kLanes, col = kPer * (lane % kLanes);
-          if (row0 + row >= M) continue;
-          const v4f a = *reinterpret_cast<const v4f*>(buf + row * kPitch + col);
-          const int64_t at = (int64_t)(row0 + row) * ldy + col0 + col;
-          if constexpr (OUT_F32) {
-            __builtin_nontemporal_store(a, reinterpret_cast<v4f*>(reinterpret_cast<float*>(Y) + at));
-          } else {
-            const v4f b = *reinterpret_cast<const v4f*>(buf + row * kPitch + col + 4);
-            typedef __bf16 v8b __attribute__((ext_vector_type(8)));
-            const v8b o = {(__bf16)a[0], (__bf16)a[1], (__bf16)a[2], (__bf16)a[3], (__bf16)b[0], (__bf16)b[1], (__bf16)b[2], (__bf16)b[3]};
-            __builtin_nontemporal_store(__builtin_bit_cast(v4u, o), reinterpret_cast<v4u*>(reinterpret_cast<uint16_t*>(Y) + at));
-          }
-        }
-      } else {
-#pragma unroll
-        for (int p = 0; p < 16; ++p) {
-          const int row = 2 * p + kh;
-          const float v = buf[row * kPitch + r];
-          if (row0 + row < M && col0 + r < N) {
-            const int64_t at = (int64_t)(row0 + row) * ldy + col0 + r;
-            if constexpr (OUT_F32) reinterpret_cast<float*>(Y)[at] = v;
-            else reinterpret_cast<uint16_t*>(Y)[at] = f32_to_bf16_bits(v);
-          }
-        }
-      }
-      wave_lds_sync();
-    }
+    for (int j = 0; j < CB; ++j) Out::put(buf, acc[i][j], j, lane);
+    wave_lds_sync();
+    Out::store(buf, Y, ldy, m0 + (wm * RB + i) * 32, n0 + wn * CB * 32, M, N, lane);
   }
 }
 
@@ -293,10 +256,9 @@ hipError_t launch_shape(const void* Xq, const void* Xs, const void* Wq, const vo
   const hipError_t attr = lds_limit.ensure(reinterpret_cast<const void*>(kernel), S::kLds);
   if (attr != hipSuccess) return attr;
   const int tiles_m = (int)((M + S::kTM - 1) / S::kTM), tiles_n = (int)((N + S::kTN - 1) / S::kTN);
-  const int vec_store = canon_vec_store(Y, ldy, OUT_F32);
   kernel<<<dim3((unsigned)((int64_t)tiles_m * tiles_n)), dim3(256), S::kLds, stream>>>(
       (const uint8_t*)Xq, (const uint8_t*)Xs, (const uint8_t*)Wq, (const uint8_t*)Ws, (int)M, (int)N, (int)K, Y, ldy, tiles_m,
-      tiles_n, vec_store);
+      tiles_n);
   return hipGetLastError();
 }
 

@@ -33,8 +33,8 @@
 // vmcnt completes in order, so the wait in front of the per-iteration barrier
 // is a fixed count: everything issued after the ring stage about to be read.
 // The W fragment is the MFMA's first operand: a lane then holds four consecutive
-// output columns of one token per accumulator quad, which the BF16 epilogue packs
-// with two converts and writes to its LDS transpose buffer as one 8-byte store.
+// output columns of one token per accumulator quad, one write to the LDS buffer
+// the outputs are turned in (row_store.hpp).
 //
 // The main-loop loads are issued from inline asm (see below), so their
 // destination registers are invisible to the compiler's dependency tracking.
@@ -44,6 +44,7 @@
 // checks both on the generated code.
 #include <type_traits>
 
+#include "row_store.hpp"
 #include "wush_device.hpp"
 #include "wush_kernels.hpp"
 
@@ -69,7 +70,7 @@ template <bool OUT_F32, int RB, int CB>
 __global__ __launch_bounds__(256) void gemm_frag_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs,
     const uint8_t* __restrict__ Wq, const uint8_t* __restrict__ Ws,
-    int M, int N, int K, void* __restrict__ Y, int64_t ldy, int tiles_m, int tiles_n, int vec_store, int w_blocks) {
+    int M, int N, int K, void* __restrict__ Y, int64_t ldy, int tiles_m, int tiles_n, int w_blocks) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
   constexpr int kTM = 32 * RB, kTN = 4 * 32 * CB;
   constexpr int kUB = RB / 4;                          // row blocks of the ring each wave fills
@@ -79,7 +80,6 @@ __global__ __launch_bounds__(256) void gemm_frag_kernel(
   constexpr int kDmaPerIter = 5 * kUB, kWPerIter = 5 * CB, kVmemPerIter = kDmaPerIter + kWPerIter;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: keeps bases in SGPRs
-  const int r = lane & 31, kh = lane >> 5;
 
   // Workgroup -> tile: every XCD (workgroup id mod 8) gets a contiguous range of
   // tile ids; ids walk the grid in bands of 8 tile rows so that the tiles an XCD
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(256) void gemm_frag_kernel(
   // pending at the loop entry shares its counter with the LDS reads and can
   // return out of order, for which the compiler answers with lgkmcnt(0) at the
   // loop top, i.e. a full LDS drain on every trip.
-  asm volatile("" ::"s"(Y), "s"(ldy), "s"(M), "s"(N), "s"(vec_store));
+  asm volatile("" ::"s"(Y), "s"(ldy), "s"(M), "s"(N));
   int kt = 0;
   const int n_main = KT - 3;                   // iterations with every stream active
   if (n_main > 0 && (n_main & 1)) {            // odd count: one iteration on set 1 first
@@ -393,73 +393,21 @@ __global__ __launch_bounds__(256) void gemm_frag_kernel(
 #undef WUSH_FENCE
   __builtin_amdgcn_sched_barrier(0);
 
-  // ---- epilogue.  The W fragment is the MFMA's first operand, so a tile of D is
-  // (32 output columns) x (32 tokens): lane (r, kh) of MFMA tile (i, j) holds token
-  // row 32*i + r, and its accumulator e is output column
-  // 32*CB*wave + 32*j + 8*(e/4) + 4*kh + e%4 -- four consecutive columns per e/4.
-  if (!OUT_F32 && vec_store) {
-    // BF16, 16-byte-aligned rows.  Four consecutive columns = two packed converts =
-    // one 8-byte LDS write; a wave-private LDS image of 32 rows x 32*CB columns is
-    // read back as 16 bytes per lane so that the stores cover whole row segments
-    // (128 or 192 bytes).  Row pitch = segment + 16 B (144 / 208): the 8-byte writes
-    // of a wave (pitch 36 / 52 dwords, +2 dwords for the upper lane half) hit every
-    // bank 4 times, the minimum.  The ring is free after the last barrier; each wave
-    // uses a private double buffer, so no barrier.
-    typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-    typedef float v2f __attribute__((ext_vector_type(2)));
-    constexpr int kChunks = 4 * CB;                       // 16-byte chunks per row segment
-    constexpr int kPitch = 16 * kChunks + 16, kBuf = 32 * kPitch;
-    static_assert(4 * 2 * kBuf <= lds_bytes(RB), "transpose buffers must fit in the ring");
-    uint8_t* area = smem + wave * (2 * kBuf);
-    uint16_t* Yb = reinterpret_cast<uint16_t*>(Y);
-#pragma unroll
-    for (int i = 0; i < RB; ++i) {
-      __builtin_amdgcn_sched_barrier(0);
-      uint8_t* buf = area + (i & 1) * kBuf;
-#pragma unroll
-      for (int j = 0; j < CB; ++j) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const v2bf lo = __builtin_convertvector((v2f){acc[i][j][4 * q], acc[i][j][4 * q + 1]}, v2bf);
-          const v2bf hi = __builtin_convertvector((v2f){acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]}, v2bf);
-          v2u two;
-          two[0] = __builtin_bit_cast(uint32_t, lo);
-          two[1] = __builtin_bit_cast(uint32_t, hi);
-          *reinterpret_cast<v2u*>(buf + r * kPitch + 2 * (32 * j + 8 * q + 4 * kh)) = two;
-        }
-      }
-#pragma unroll
-      for (int p = 0; p < 2 * CB; ++p) {                  // 32 rows x kChunks chunks, 64 per round
-        const int idx = 64 * p + lane;
-        const int row_l = idx / kChunks;
-        const int chunk = idx % kChunks;
-        const v4i v = *reinterpret_cast<const v4i*>(buf + row_l * kPitch + 16 * chunk);
-        const int row = m0 + 32 * i + row_l;
-        const int col = n0 + 32 * CB * wave + 8 * chunk;
-        // streaming store: the output is not read again by this kernel, and lines that
-        // leave the L2 as they are written shorten the write-back at the kernel's end
-        if (row < M && col < N) __builtin_nontemporal_store(v, reinterpret_cast<v4i*>(Yb + (int64_t)row * ldy + col));
-      }
-    }
-    return;
-  }
+  // ---- epilogue (row_store.hpp).  The ring is free after the last barrier; each wave turns its row blocks in a private
+  // buffer, two in turn where the ring has room for them, so no barrier.
+  using Out = RowStore<OUT_F32, CB>;
+  constexpr int kBufs = 4 * 2 * Out::kBuf <= lds_bytes(RB) ? 2 : 1;
+  static_assert(4 * kBufs * Out::kBuf <= lds_bytes(RB), "transpose buffers must fit in the ring");
+  uint8_t* area = smem + wave * (kBufs * Out::kBuf);
 #pragma unroll
   for (int i = 0; i < RB; ++i) {
+    __builtin_amdgcn_sched_barrier(0);       // one row block at a time: keeps the epilogue out of scratch
+    uint8_t* buf = area + (i % kBufs) * Out::kBuf;
+    wave_lds_sync();
 #pragma unroll
-    for (int j = 0; j < CB; ++j) {
-      __builtin_amdgcn_sched_barrier(0);   // one MFMA tile at a time: keeps the epilogue out of scratch
-      const int row = m0 + 32 * i + r;
-      if (row < M) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int col = n0 + 32 * CB * wave + 32 * j + 8 * (e >> 2) + 4 * kh + (e & 3);
-          if (col < N) {
-            if (OUT_F32) reinterpret_cast<float*>(Y)[(int64_t)row * ldy + col] = acc[i][j][e];
-            else reinterpret_cast<uint16_t*>(Y)[(int64_t)row * ldy + col] = f32_to_bf16_bits(acc[i][j][e]);
-          }
-        }
-      }
-    }
+    for (int j = 0; j < CB; ++j) Out::put(buf, acc[i][j], j, lane);
+    wave_lds_sync();
+    Out::store(buf, Y, ldy, m0 + 32 * i, n0 + 32 * CB * wave, M, N, lane);
   }
 }
 
@@ -473,12 +421,10 @@ hipError_t launch_shape(const void* Xq, const void* Xs, const void* Wq, const vo
   constexpr int kTM = 32 * RB, kTN = 4 * 32 * CB;
   const int tiles_m = (int)((M + kTM - 1) / kTM), tiles_n = (int)((N + kTN - 1) / kTN);
   dim3 grid((unsigned)(tiles_m * tiles_n)), block(256);
-  // 128-bit stores need whole 8-column chunks at 16-byte aligned addresses
-  const int vec_store = (N % 8 == 0) && (ldy % 8 == 0) && ((reinterpret_cast<uintptr_t>(Y) & 15) == 0);
   const int w_blocks = (int)((N + 255) / 256 * 8);   // 32-row blocks the packed W buffers hold
   gemm_frag_kernel<OUT_F32, RB, CB><<<grid, block, kLds, stream>>>(
       (const uint8_t*)Xq, (const uint8_t*)Xs, (const uint8_t*)Wq, (const uint8_t*)Ws, (int)M, (int)N, (int)K, Y, ldy,
-      tiles_m, tiles_n, vec_store, w_blocks);
+      tiles_m, tiles_n, w_blocks);
   return hipGetLastError();
 }
 
