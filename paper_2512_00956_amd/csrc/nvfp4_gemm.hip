@@ -32,6 +32,7 @@
 #include <utility>
 
 #include "nvfp4_layout.hpp"
+#include "row_store.hpp"
 #include "w4_dequant.hpp"
 #include "wush_device.hpp"
 #include "wush_kernels.hpp"
@@ -203,6 +204,35 @@ __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
+// A wavefront's 4 x CB accumulators (the W fragment is the MFMA's first operand) times `scale` to its 128 x 32 CB outputs, turned in
+// LDS so that they leave in 16-byte stores (row_store.hpp).  Element by element, 64 CB store instructions of 128 bytes (BF16) per
+// wavefront, it cost up to 5 us per tile (us, quantizer + GEMM, before | now: NVFP4 4096 x 8192 -> 28672 1342 | 1305, 1024 x 1024 ->
+// 16384 40.9 | 36.4; INT4 2048 x 4096 -> 6144 101.8 | 98.0).
+template <bool OUT_F32, int CB>
+__device__ __forceinline__ void store_tile(v16f (&acc)[4][CB], float scale, uint8_t* lds, void* __restrict__ Y, int64_t ldy, int row0,
+                                           int col0, int M, int N, int lane, int wave) {
+  using Out = RowStore<OUT_F32, CB>;
+  uint8_t* buf = lds + wave * Out::kBuf;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    __builtin_amdgcn_sched_barrier(0);   // one row block at a time: the accumulators leave their registers block by block
+    wave_lds_sync();
+#pragma unroll
+    for (int j = 0; j < CB; ++j) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] *= scale;
+      Out::put(buf, acc[i][j], j, lane);
+    }
+    wave_lds_sync();
+    Out::store(buf, Y, ldy, row0 + 32 * i, col0, M, N, lane);
+  }
+}
+// LDS of a kernel whose stages take `stages` bytes: they are reused for the outputs
+template <bool OUT_F32, int CB>
+constexpr int lds_with_outputs(int stages) {
+  return stages > 4 * RowStore<OUT_F32, CB>::kBuf ? stages : 4 * RowStore<OUT_F32, CB>::kBuf;
+}
+
 template <bool OUT_F32, int CB, int FMT>
 __global__ __launch_bounds__(256) void w4_f16_gemm_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const float* __restrict__ tsx,
@@ -287,7 +317,7 @@ __global__ __launch_bounds__(256) void w4_f16_gemm_kernel(
       constexpr int S = decltype(slot)::value;
       constexpr int g = S / kGroup, idx = S % kGroup, i = idx / CB, j = idx % CB;
       if (NEXT && S == kConvSlots) __syncthreads();   // every conversion write of this step is behind us
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[g & 1][i], fb[g & 1][j], acc[i][j], 0, 0, 0);
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[g & 1][j], fa[g & 1][i], acc[i][j], 0, 0, 0);
       // fragments of the next group: one LDS read per slot from the second slot of the group on
       if constexpr (g < 3) {
         if constexpr (idx >= 1 && idx - 1 < 4 + CB) read_frag(cur, g + 1, idx - 1, (g + 1) & 1);
@@ -331,22 +361,8 @@ __global__ __launch_bounds__(256) void w4_f16_gemm_kernel(
   step(KT - 1, std::false_type{});
 
   const float scale = FMT == kNvfp4 ? *tsx * *tsw : 1.0f;   // INT4 has no tensor scales (null pointers)
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-#pragma unroll
-    for (int j = 0; j < CB; ++j) {
-      const int n = n0 + wn * (32 * CB) + 32 * j + l32;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + wm * 128 + 32 * i + 8 * (r >> 2) + 4 * h + (r & 3);
-        if (m < M && n < N) {
-          const float v = acc[i][j][r] * scale;
-          if (OUT_F32) reinterpret_cast<float*>(Yv)[(int64_t)m * ldy + n] = v;
-          else reinterpret_cast<uint16_t*>(Yv)[(int64_t)m * ldy + n] = f32_to_bf16_bits(v);
-        }
-      }
-    }
-  }
+  __syncthreads();   // the stages become the transpose buffers
+  store_tile<OUT_F32, CB>(acc, scale, reinterpret_cast<uint8_t*>(lds), Yv, ldy, m0 + wm * 128, n0 + wn * (32 * CB), M, N, lane, wave);
 }
 
 // ---------------------------------------------------------------------------
@@ -526,7 +542,7 @@ __global__ __launch_bounds__(256) void w4_wreg_gemm_kernel(
       constexpr int S = decltype(slot)::value;
       constexpr int g = S / kGroup, idx = S % kGroup, i = idx / CB, j = idx % CB;
       if (S == kConvSlots) __syncthreads();
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[g & 1][i], fb[g & 1][j].v, acc[i][j], 0, 0, 0);
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[g & 1][j].v, fa[g & 1][i], acc[i][j], 0, 0, 0);
       if constexpr (g < 3) {
         if constexpr (idx >= 1 && idx <= 4) read_frag(cur, g + 1, idx - 1, (g + 1) & 1);
       }
@@ -571,24 +587,10 @@ __global__ __launch_bounds__(256) void w4_wreg_gemm_kernel(
   // arithmetic has to stay in registers across the loop.
   int te = threadIdx.x;
   asm volatile("" : "+v"(te));
-  const int e_row = m0 + (te >> 7) * 128 + 4 * ((te >> 5) & 1), e_col = n0 + ((te >> 6) & 1) * (32 * CB) + (te & 31);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-#pragma unroll
-    for (int j = 0; j < CB; ++j) {
-      const int n = e_col + 32 * j;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = e_row + 32 * i + 8 * (r >> 2) + (r & 3);
-        if (m < M && n < N) {
-          const float v = acc[i][j][r] * scale;
-          if (OUT_F32) reinterpret_cast<float*>(Yv)[(int64_t)m * ldy + n] = v;
-          else reinterpret_cast<uint16_t*>(Yv)[(int64_t)m * ldy + n] = f32_to_bf16_bits(v);
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);   // one 32 x 32 block at a time: the accumulators leave their registers block by block
-    }
-  }
+  const int ewave = __builtin_amdgcn_readfirstlane(te >> 6);
+  __syncthreads();   // the stages become the transpose buffers
+  store_tile<OUT_F32, CB>(acc, scale, reinterpret_cast<uint8_t*>(lds), Yv, ldy, m0 + (ewave >> 1) * 128, n0 + (ewave & 1) * (32 * CB), M, N,
+                          te & 63, ewave);
 }
 
 template <bool OUT_F32, int CB, int FMT>
@@ -596,10 +598,11 @@ hipError_t launch_wreg(const void* Xq, const void* Xs, const float* tsx, const v
                        const float* tsw, int64_t M, int64_t N, int64_t K, int tiled, void* Y, int64_t ldy,
                        hipStream_t stream) {
   static DynamicLdsLimit lds_limit;   // per instantiation
-  const hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(w4_wreg_gemm_kernel<OUT_F32, CB, FMT>), 2 * kXBytes);
+  constexpr int kLds = lds_with_outputs<OUT_F32, CB>(2 * kXBytes);
+  const hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(w4_wreg_gemm_kernel<OUT_F32, CB, FMT>), kLds);
   if (e != hipSuccess) return e;
   const int tiles_m = (int)((M + kBM - 1) / kBM), tiles_n = (int)((N + 64 * CB - 1) / (64 * CB));
-  w4_wreg_gemm_kernel<OUT_F32, CB, FMT><<<dim3((unsigned)(tiles_m * tiles_n)), dim3(256), 2 * kXBytes, stream>>>(
+  w4_wreg_gemm_kernel<OUT_F32, CB, FMT><<<dim3((unsigned)(tiles_m * tiles_n)), dim3(256), kLds, stream>>>(
       (const uint8_t*)Xq, (const uint8_t*)Xs, tsx, (const uint8_t*)Wq, (const uint8_t*)Ws, tsw, Y, ldy, (int)M, (int)N,
       (int)K, tiles_m, tiles_n, tiled);
   return hipGetLastError();
@@ -610,10 +613,11 @@ hipError_t launch_shape(const void* Xq, const void* Xs, const float* tsx, const 
                         const float* tsw, int64_t M, int64_t N, int64_t K, int tiled, void* Y, int64_t ldy,
                         hipStream_t stream) {
   static DynamicLdsLimit lds_limit;   // per instantiation
-  const hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(w4_f16_gemm_kernel<OUT_F32, CB, FMT>), kLdsBytes);
+  constexpr int kLds = lds_with_outputs<OUT_F32, CB>(kLdsBytes);
+  const hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(w4_f16_gemm_kernel<OUT_F32, CB, FMT>), kLds);
   if (e != hipSuccess) return e;
   const int tiles_m = (int)((M + kBM - 1) / kBM), tiles_n = (int)((N + 64 * CB - 1) / (64 * CB));
-  w4_f16_gemm_kernel<OUT_F32, CB, FMT><<<dim3((unsigned)(tiles_m * tiles_n)), dim3(256), kLdsBytes, stream>>>(
+  w4_f16_gemm_kernel<OUT_F32, CB, FMT><<<dim3((unsigned)(tiles_m * tiles_n)), dim3(256), kLds, stream>>>(
       (const uint8_t*)Xq, (const uint8_t*)Xs, tsx, (const uint8_t*)Wq, (const uint8_t*)Ws, tsw, Y, ldy, (int)M, (int)N,
       (int)K, tiles_m, tiles_n, tiled);
   return hipGetLastError();

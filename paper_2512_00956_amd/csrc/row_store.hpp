@@ -1,4 +1,4 @@
-// How the MXFP4 tile kernels write their outputs: every wavefront turns its accumulators in LDS of its own, 32 rows at a
+// How the GEMM tile kernels write their outputs: every wavefront turns its accumulators in LDS of its own, 32 rows at a
 // time, so that a store instruction covers whole runs of a row.
 //
 // The W fragment is the MFMA's first operand: lane (r, kh) = (lane % 32, lane / 32) of a 32 x 32 tile holds token row r, and
