@@ -630,18 +630,29 @@ int64_t width_cost(int64_t M, int64_t N, int CB, int cus) {
   return ((tiles + cus - 1) / cus) * (512 * CB + 600);
 }
 
-}  // namespace
+int best_width(int64_t M, int64_t N, int cus) {
+  int best = 4;
+  for (int cb = 3; cb >= 2; --cb)
+    if (width_cost(M, N, cb, cus) < width_cost(M, N, best, cus)) best = cb;   // ties keep the wider tile
+  return best;
+}
 
-namespace {
+// Estimated duration, us: rounds of the CUs times a step's time and a fixed part (prologue, epilogue).  Fits to graph replays of
+// 1 to 2048 tokens on eleven layers from 704 -> 512 to 8192 -> 28672; only compared with the estimates of the streaming
+// kernel (w4_gemm_skinny.hip), measured the same way.
+double tile_us(int fmt, int64_t M, int64_t N, int64_t K, int tiled) {
+  constexpr double kStep[2][2][3] = {{{0.86, 1.20, 1.60}, {0.95, 1.30, 1.70}},     // canonical NVFP4, INT4: CB = 2, 3, 4
+                                     {{0.80, 1.02, 1.28}, {0.90, 1.17, 1.46}}};    // tiled
+  const int cus = device_cu_count(), cb = best_width(M, N, cus);
+  const int64_t tiles = ((M + kBM - 1) / kBM) * ((N + 64 * cb - 1) / (64 * cb));
+  return (double)((tiles + cus - 1) / cus) * (kStep[tiled ? 1 : 0][fmt == kInt4 ? 1 : 0][cb - 2] * (double)(K / kBK) + 2.9 * cb);
+}
 
 template <int FMT>
 hipError_t launch_w4_f16_gemm(const void* Xq, const void* Xs, const float* tsx, const void* Wq, const void* Ws,
                               const float* tsw, int64_t M, int64_t N, int64_t K, int out_f32, int tiled, void* Y,
                               int64_t ldy, hipStream_t stream) {
-  const int cus = device_cu_count();
-  int best = 4;
-  for (int cb = 3; cb >= 2; --cb)
-    if (width_cost(M, N, cb, cus) < width_cost(M, N, best, cus)) best = cb;   // ties keep the wider tile
+  int best = best_width(M, N, device_cu_count());
   if (const int forced = debug_option(kDbgW4Width); forced >= 2 && forced <= 4) best = forced;   // tests: force a tile width
   if (K % 128 == 0) {   // an even number of K steps: W in registers
 #define WUSH_WR_LAUNCH(F32, CB) launch_wreg<F32, CB, FMT>(Xq, Xs, tsx, Wq, Ws, tsw, M, N, K, tiled, Y, ldy, stream)
@@ -657,24 +668,19 @@ hipError_t launch_w4_f16_gemm(const void* Xq, const void* Xs, const float* tsx, 
 
 }  // namespace
 
-// Up to 128 tokens the layer is bound by reading the weights once: the weight-streaming kernel of
-// w4_gemm_skinny.hip takes over (tiled layout only; the switch kDbgW4Skinny forces either kernel).
-static bool w4_streaming(int64_t M, int tiled) {
-  if (!tiled || M > 128) return false;
-  const int forced = debug_option(kDbgW4Skinny);
-  return forced >= 0 ? forced >= 1 : true;   // 1, 2: either schedule of the streaming kernel
-}
-
 hipError_t launch_nvfp4_gemm(const void* Xq, const void* Xs, const float* tsx, const void* Wq, const void* Ws,
                              const float* tsw, int64_t M, int64_t N, int64_t K, int out_f32, int tiled, void* Y,
                              int64_t ldy, hipStream_t stream) {
-  if (w4_streaming(M, tiled)) return launch_nvfp4_gemm_skinny(Xq, Xs, tsx, Wq, Ws, tsw, M, N, K, out_f32, Y, ldy, stream);
+  const W4StreamPlan plan = w4_stream_plan(kNvfp4, M, N, K, tiled, tile_us(kNvfp4, M, N, K, tiled));
+  if (plan.streams)
+    return launch_nvfp4_gemm_skinny(plan, Xq, Xs, tsx, Wq, Ws, tsw, M, N, K, out_f32, tiled, Y, ldy, stream);
   return launch_w4_f16_gemm<kNvfp4>(Xq, Xs, tsx, Wq, Ws, tsw, M, N, K, out_f32, tiled, Y, ldy, stream);
 }
 
 hipError_t launch_int4_gemm(const void* Xq, const void* Xs, const void* Wq, const void* Ws, int64_t M, int64_t N,
                             int64_t K, int out_f32, int tiled, void* Y, int64_t ldy, hipStream_t stream) {
-  if (w4_streaming(M, tiled)) return launch_int4_gemm_skinny(Xq, Xs, Wq, Ws, M, N, K, out_f32, Y, ldy, stream);
+  const W4StreamPlan plan = w4_stream_plan(kInt4, M, N, K, tiled, tile_us(kInt4, M, N, K, tiled));
+  if (plan.streams) return launch_int4_gemm_skinny(plan, Xq, Xs, Wq, Ws, M, N, K, out_f32, tiled, Y, ldy, stream);
   return launch_w4_f16_gemm<kInt4>(Xq, Xs, nullptr, Wq, Ws, nullptr, M, N, K, out_f32, tiled, Y, ldy, stream);
 }
 

@@ -1,4 +1,5 @@
-// Weight-streaming GEMM of the NVFP4 and INT4 variants for at most 128 tokens (gfx950):
+// Weight-streaming GEMM of the NVFP4 and INT4 variants (gfx950), for few tokens and for layers whose 256-row tiles leave
+// most compute units idle:
 //   Y = tsx tsw * deq(Xq, Xs) . deq(Wq, Ws)^T
 // (the sum over blocks of the layer forward-pass equation in the formats of the paper's
 // experiments that have no block-scaled MFMA path: E2M1 x E4M3 per 16 x FP32 per tensor, and
@@ -49,6 +50,21 @@ __device__ __forceinline__ void load_step(RawStep& t, const uint8_t* __restrict_
   t.s = *reinterpret_cast<const uint32_t*>(s + (blk_kt * 32 + r) * 4);
 }
 
+// The same of either layout.  Canonical rows: K / 2 bytes of codes, 32 per K step, and K / 16 of scales, 4 per step (K is a
+// multiple of 64, so the 16-byte and 4-byte loads are aligned); a row past the operand's last repeats it (never stored).  A load
+// instruction then touches 32 lines instead of 8; the K steps of a chunk share them.
+template <bool TILED>
+__device__ __forceinline__ void load_step(RawStep& t, const uint8_t* __restrict__ q, const uint8_t* __restrict__ s, int blk,
+                                          int rows, int KT, int kt, int r, int h) {
+  if constexpr (TILED) {
+    load_step(t, q, s, (int64_t)blk * KT + kt, r, h);
+  } else {
+    const int64_t at = (int64_t)min(32 * blk + r, rows - 1) * KT + kt;
+    t.q = *reinterpret_cast<const v4u*>(q + at * 32 + 16 * h);
+    t.s = *reinterpret_cast<const uint32_t*>(s + at * 4);
+  }
+}
+
 // The lane's 32 codes of a step as four MFMA operands (8 FP16 each).
 template <int FMT>
 __device__ __forceinline__ void dequant_step(const RawStep& t, int h, uint32_t sel, v8h (&f)[4]) {
@@ -64,7 +80,7 @@ __device__ __forceinline__ void dequant_step(const RawStep& t, int h, uint32_t s
 // CBW = blocks of 32 output channels a workgroup takes at a time: the X fragments of a K step are
 // converted once and multiplied with CBW weight blocks (the conversion of X is the same work in every
 // workgroup; with one block per pass it costs as much as that of the weights).
-template <int RB, int CBW, int FMT, bool OUT_F32>
+template <int RB, int CBW, int FMT, bool OUT_F32, bool TILED>
 __global__ __launch_bounds__(kWaves * 64) void w4_skinny_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const float* __restrict__ tsx,
     const uint8_t* __restrict__ Wq, const uint8_t* __restrict__ Ws, const float* __restrict__ tsw,
@@ -77,11 +93,11 @@ __global__ __launch_bounds__(kWaves * 64) void w4_skinny_kernel(
   const int KT = K >> 6, NB = (N + 31) >> 5;
   // row blocks RB blockIdx.y ... of the tokens
   const int64_t row_block = (int64_t)RB * blockIdx.y;
-  Xq += row_block * KT * 1024;
+  Xq += row_block * KT * 1024;             // 32 rows, in either layout
   Xs += row_block * KT * 128;
   Y = static_cast<uint8_t*>(Y) + 32 * row_block * ldy * (OUT_F32 ? 4 : 2);
   M -= 32 * (int)row_block;
-  const int nrb = (M + 31) >> 5;   // row blocks the X buffers hold (a multiple of 32 rows): a block past them re-reads the last, never stored
+  const int nrb = (M + 31) >> 5;   // row blocks the X buffers hold: a block past them re-reads the last, never stored
   const int groups = (NB + CBW - 1) / CBW;
   const uint32_t sel = 0x05040C0Cu + 0x02020000u * h;
   const float scale = FMT == kNvfp4 ? *tsx * *tsw : 1.0f;   // INT4 has no tensor scales (null pointers)
@@ -92,7 +108,7 @@ __global__ __launch_bounds__(kWaves * 64) void w4_skinny_kernel(
     RawStep w[CBW][U], x[RB][U];
   };
   for (int g = blockIdx.x; g < groups; g += gridDim.x) {
-    int64_t jb[CBW];   // weight blocks of this pass; one past the end repeats the last (never stored)
+    int jb[CBW];   // weight blocks of this pass; one past the end repeats the last (never stored)
 #pragma unroll
     for (int c = 0; c < CBW; ++c) jb[c] = min(g * CBW + c, NB - 1);
     v16f acc[CBW][RB];
@@ -108,13 +124,13 @@ __global__ __launch_bounds__(kWaves * 64) void w4_skinny_kernel(
       for (int u = 0; u < U; ++u) {
         const int k = min(kt + u, kt1 - 1);
 #pragma unroll
-        for (int c = 0; c < CBW; ++c) load_step(ch.w[c][u], Wq, Ws, jb[c] * KT + k, r, h);
+        for (int c = 0; c < CBW; ++c) load_step<TILED>(ch.w[c][u], Wq, Ws, jb[c], N, KT, k, r, h);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int k = min(kt + u, kt1 - 1);
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) load_step(ch.x[rb][u], Xq, Xs, (int64_t)min(rb, nrb - 1) * KT + k, r, h);
+        for (int rb = 0; rb < RB; ++rb) load_step<TILED>(ch.x[rb][u], Xq, Xs, min(rb, nrb - 1), M, KT, k, r, h);
       }
     };
     auto multiply_chunk = [&](const Chunk& ch, int kt) {
@@ -219,7 +235,7 @@ template <int RB, int CBW>
 struct Ahead { static constexpr int kChunks = RB == 1 ? 2 : (CBW == 2 ? 1 : (RB == 4 ? 3 : 2)); };
 static_assert(Chunk<4>::kPairs % kWaves == 0, "every wave converts the same number of pairs");
 
-template <int RB, int CBW, int FMT, bool OUT_F32>
+template <int RB, int CBW, int FMT, bool OUT_F32, bool TILED>
 __global__ __launch_bounds__(kWaves * 64, 2) void w4_shared_x_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const float* __restrict__ tsx,
     const uint8_t* __restrict__ Wq, const uint8_t* __restrict__ Ws, const float* __restrict__ tsw,
@@ -232,6 +248,12 @@ __global__ __launch_bounds__(kWaves * 64, 2) void w4_shared_x_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 31, h = lane >> 5;
   const int KT = K >> 6, NB = (N + 31) >> 5;
+  // row blocks RB blockIdx.y ... of the tokens
+  const int64_t row_block = (int64_t)RB * blockIdx.y;
+  Xq += row_block * KT * 1024;             // 32 rows, in either layout
+  Xs += row_block * KT * 128;
+  Y = static_cast<uint8_t*>(Y) + 32 * row_block * ldy * (OUT_F32 ? 4 : 2);
+  M -= 32 * (int)row_block;
   const int nrb = (M + 31) >> 5;   // row blocks the X buffers hold: a block past them re-reads the last, never stored
   const int groups = (NB + kWaves * CBW - 1) / (kWaves * CBW);
   const int nch = (KT + U - 1) / U;
@@ -239,7 +261,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void w4_shared_x_kernel(
   const float scale = FMT == kNvfp4 ? *tsx * *tsw : 1.0f;
 
   for (int g = blockIdx.x; g < groups; g += gridDim.x) {
-    int64_t jb[CBW];   // this wave's weight blocks; one past the end repeats the last (never stored)
+    int jb[CBW];   // this wave's weight blocks; one past the end repeats the last (never stored)
 #pragma unroll
     for (int c = 0; c < CBW; ++c) jb[c] = min((g * kWaves + wave) * CBW + c, NB - 1);
     v16f acc[CBW][RB];
@@ -254,7 +276,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void w4_shared_x_kernel(
 #pragma unroll
       for (int m = 0; m < kMine; ++m) {
         const int p = wave + kWaves * m, u = p / RB, rb = p % RB;
-        load_step(xr[m], Xq, Xs, (int64_t)min(rb, nrb - 1) * KT + min(ch * U + u, KT - 1), r, h);
+        load_step<TILED>(xr[m], Xq, Xs, min(rb, nrb - 1), M, KT, min(ch * U + u, KT - 1), r, h);
       }
     };
     auto convert_x = [&](int buf) {
@@ -270,7 +292,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void w4_shared_x_kernel(
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int c = 0; c < CBW; ++c) load_step(w[c][u], Wq, Ws, jb[c] * KT + min(ch * U + u, KT - 1), r, h);
+        for (int c = 0; c < CBW; ++c) load_step<TILED>(w[c][u], Wq, Ws, jb[c], N, KT, min(ch * U + u, KT - 1), r, h);
     };
     auto multiply = [&](const RawStep (&w)[CBW][U], int ch, int buf) {
 #pragma unroll
@@ -327,23 +349,20 @@ __global__ __launch_bounds__(kWaves * 64, 2) void w4_shared_x_kernel(
   }
 }
 
-template <int FMT>
-hipError_t launch_split_k(const void* Xq, const void* Xs, const float* tsx, const void* Wq, const void* Ws,
-                          const float* tsw, int64_t M, int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy,
-                          hipStream_t stream) {
-  const int NB = (int)((N + 31) / 32);
-  // Row blocks of 32 tokens (rb) and weight blocks (cbw) a workgroup takes at a time.  Every workgroup converts all of its
-  // tokens' activations, so with few output channels the tokens are dealt out to idle compute units, and with many two
-  // weight blocks share the conversion (us, NVFP4 | INT4, a workgroup with all tokens and one weight block before:
-  // 100 x 14336 -> 4096 33.8 -> 23.4 | 46.0 -> 30.3; 64 x 14336 -> 4096 21.1 -> 17.0 | 28.1 -> 21.4; 100 x 2048 -> 2048
-  // 8.5 -> 4.9 | 10.2 -> 5.5; 128 x 8192 -> 28672 81 -> 77 | 119 -> 93; 128 x 4096 -> 24576 34.6 -> 33.0 | 50.4 -> 39.0).
-  // Up to 64 tokens two weight blocks pay from where the coarser grid takes no round more: 64 x 8192 -> 28672, 3.5 blocks per
-  // compute unit, 49.3 -> 43.1 | 61.9 -> 51.2, 16 tokens INT4 44.1 -> 40.1, but 16 x 8192 -> 20480 (2.5 blocks) NVFP4 25.1 against
-  // 27.2.  NVFP4 between three and four blocks (replayed graphs, from HBM | weights in the last-level cache, one -> two weight
-  // blocks): 16 x 8192 -> 28672 35.2 -> 33.7 | 28.8 -> 28.3, 16 x 8192 -> 25088 33.1 -> 31.4 | 27.9 -> 27.0, 32 x 4096 -> 28672 21.4 ->
-  // 21.2 | 17.9 -> 17.4, 1 x 16384 -> 28672 64.6 -> 60.3 | 53.9 -> 51.5.
+// Tiled operands, at most 128 tokens: row blocks of 32 tokens (rb) and weight blocks (cbw) a workgroup takes at a time.
+// Every workgroup converts all of its tokens' activations, so with few output channels the tokens are dealt out to idle compute
+// units, and with many two weight blocks share the conversion (us, NVFP4 | INT4, a workgroup with all tokens and one weight
+// block before: 100 x 14336 -> 4096 33.8 -> 23.4 | 46.0 -> 30.3; 64 x 14336 -> 4096 21.1 -> 17.0 | 28.1 -> 21.4; 100 x 2048 ->
+// 2048 8.5 -> 4.9 | 10.2 -> 5.5; 128 x 8192 -> 28672 81 -> 77 | 119 -> 93; 128 x 4096 -> 24576 34.6 -> 33.0 | 50.4 -> 39.0). Up
+// to 64 tokens two weight blocks pay from where the coarser grid takes no round more: 64 x 8192 -> 28672, 3.5 blocks per
+// compute unit, 49.3 -> 43.1 | 61.9 -> 51.2, 16 tokens INT4 44.1 -> 40.1, but 16 x 8192 -> 20480 (2.5 blocks) NVFP4 25.1
+// against 27.2.  NVFP4 between three and four blocks (replayed graphs, from HBM | weights in the last-level cache, one -> two
+// weight blocks): 16 x 8192 -> 28672 35.2 -> 33.7 | 28.8 -> 28.3, 16 x 8192 -> 25088 33.1 -> 31.4 | 27.9 -> 27.0, 32 x 4096 ->
+// 28672 21.4 -> 21.2 | 17.9 -> 17.4, 1 x 16384 -> 28672 64.6 -> 60.3 | 53.9 -> 51.5.
+void few_token_blocks(int64_t M, int64_t N, int& rb, int& cbw) {
+  const int64_t NB = (N + 31) / 32;
   const int64_t cus = device_cu_count(), tokens = (M + 31) / 32;
-  int rb = 2, cbw = 2;
+  rb = cbw = 2;
   if (M <= 32 || NB * tokens <= cus) {
     rb = 1;
     cbw = M <= 32 && NB > 3 * cus ? 2 : 1;
@@ -352,15 +371,25 @@ hipError_t launch_split_k(const void* Xq, const void* Xs, const float* tsx, cons
   } else if (2 * NB <= cus) {
     cbw = 1;
   }
+}
+
+template <int FMT>
+hipError_t launch_split_k(const void* Xq, const void* Xs, const float* tsx, const void* Wq, const void* Ws,
+                          const float* tsw, int64_t M, int64_t N, int64_t K, int out_f32, int tiled, int rb, int cbw, void* Y,
+                          int64_t ldy, hipStream_t stream) {
+  const int NB = (int)((N + 31) / 32);
   const int groups = (NB + cbw - 1) / cbw;
   dim3 grid((unsigned)(groups < 4096 ? groups : 4096), (unsigned)((M + 32 * rb - 1) / (32 * rb))), block(kWaves * 64);
   const int vec = skinny::decode_vec_store(Y, N, ldy, out_f32);
-#define WUSH_W4S_LAUNCH(RB, CBW, F32)                                                                          \
-  w4_skinny_kernel<RB, CBW, FMT, F32><<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs, tsx, \
-                                                                  (const uint8_t*)Wq, (const uint8_t*)Ws, tsw, \
-                                                                  (int)M, (int)N, (int)K, Y, ldy, vec)
-#define WUSH_W4S_BY_OUT(RB, CBW) \
-  { if (out_f32) WUSH_W4S_LAUNCH(RB, CBW, true); else WUSH_W4S_LAUNCH(RB, CBW, false); }
+#define WUSH_W4S_LAUNCH(RB, CBW, F32, TILED)                                                                          \
+  w4_skinny_kernel<RB, CBW, FMT, F32, TILED><<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs, tsx, \
+                                                                         (const uint8_t*)Wq, (const uint8_t*)Ws, tsw, \
+                                                                         (int)M, (int)N, (int)K, Y, ldy, vec)
+#define WUSH_W4S_BY_OUT(RB, CBW)                                                                                      \
+  {                                                                                                                   \
+    if (tiled) { if (out_f32) WUSH_W4S_LAUNCH(RB, CBW, true, true); else WUSH_W4S_LAUNCH(RB, CBW, false, true); }     \
+    else { if (out_f32) WUSH_W4S_LAUNCH(RB, CBW, true, false); else WUSH_W4S_LAUNCH(RB, CBW, false, false); }         \
+  }
   if (rb == 1) {
     if (cbw == 2) WUSH_W4S_BY_OUT(1, 2) else WUSH_W4S_BY_OUT(1, 1)
   } else {
@@ -371,30 +400,26 @@ hipError_t launch_split_k(const void* Xq, const void* Xs, const float* tsx, cons
   return hipGetLastError();
 }
 
-// The shared-X schedule is built for 65..128 tokens with one weight block per wave: the only shape in which it
-// beats the K split, and only on the layers shared_x_pays() names.  With fewer tokens the K split's conversions are
+// The shared-X schedule takes 128 tokens and one weight block per wave: the only shape in which it
+// beats the K split, and only on the layers that shared_x_pays() and w4_stream_plan() name.  With fewer tokens the K split's conversions are
 // already cheap, with two weight blocks per wave too few workgroups are left, and with fewer output channels the whole-K
 // walk of a wave leaves CUs idle.
 template <int FMT>
 hipError_t launch_shared_x(const void* Xq, const void* Xs, const float* tsx, const void* Wq, const void* Ws,
-                           const float* tsw, int64_t M, int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy,
+                           const float* tsw, int64_t M, int64_t N, int64_t K, int out_f32, int tiled, void* Y, int64_t ldy,
                            hipStream_t stream) {
   const int NB = (int)((N + 31) / 32);
   const int groups = (NB + kWaves - 1) / kWaves;
-  dim3 grid((unsigned)(groups < 4096 ? groups : 4096)), block(kWaves * 64);
+  dim3 grid((unsigned)(groups < 4096 ? groups : 4096), (unsigned)((M + 127) / 128)), block(kWaves * 64);
   const int vec = skinny::decode_vec_store(Y, N, ldy, out_f32);
-  if (out_f32)
-    w4_shared_x_kernel<4, 1, FMT, true><<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs, tsx,
-                                                                    (const uint8_t*)Wq, (const uint8_t*)Ws, tsw,
-                                                                    (int)M, (int)N, (int)K, Y, ldy, vec);
-  else
-    w4_shared_x_kernel<4, 1, FMT, false><<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs, tsx,
-                                                                     (const uint8_t*)Wq, (const uint8_t*)Ws, tsw,
-                                                                     (int)M, (int)N, (int)K, Y, ldy, vec);
+  auto kernel = out_f32 ? (tiled ? w4_shared_x_kernel<4, 1, FMT, true, true> : w4_shared_x_kernel<4, 1, FMT, true, false>)
+                        : (tiled ? w4_shared_x_kernel<4, 1, FMT, false, true> : w4_shared_x_kernel<4, 1, FMT, false, false>);
+  kernel<<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs, tsx, (const uint8_t*)Wq, (const uint8_t*)Ws, tsw,
+                                     (int)M, (int)N, (int)K, Y, ldy, vec);
   return hipGetLastError();
 }
 
-// Whether the shared-X schedule is the faster one for 65..128 tokens.  Its time goes in rounds of two workgroups, eight blocks of 32
+// Whether the shared-X schedule is the faster one for 65..128 tokens, tiled operands.  Its time goes in rounds of two workgroups, eight blocks of 32
 // channels, per CU, while the K split's finer grid grows with the channels; so it pays where a round is nearly full, for INT4, whose
 // conversions cost more, from six blocks per CU, for NVFP4 from seven, but not where a second round has only begun.  Measured at
 // 100 tokens from HBM, us, K split | shared X, by blocks per CU:
@@ -408,27 +433,84 @@ bool shared_x_pays(int fmt, int64_t N) {
                       : NB >= 7 * cus && !(NB > 8 * cus && NB <= 10 * cus);
 }
 
-// The switch kDbgW4Skinny forces a schedule (1 = K split across the waves, 2 = shared X where it exists).
-template <int FMT>
-hipError_t launch(const void* Xq, const void* Xs, const float* tsx, const void* Wq, const void* Ws, const float* tsw,
-                  int64_t M, int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy, hipStream_t stream) {
+// Estimated duration, us, of `wgs` workgroups of KT K steps: `one` per step while every compute unit has one at most, otherwise
+// `full` per step and round, and a fixed part per round (its first loads, sums and stores; more where the K range of a wave is too
+// short to hide a load).
+struct StreamCost {
+  double one, full, fixed;
+};
+double stream_us(const StreamCost& c, int64_t wgs, int64_t KT, int cus) {
+  const double x = (double)wgs / cus, step = (double)KT;
+  if (x <= 1.0) return 4.0 + c.one * step + c.fixed;
+  return 4.0 + (x <= 2.0 ? 2.0 : x + 0.25) * (c.full * step + c.fixed + (KT < 16 ? 0.7 : 0.0));
+}
+
+// Row and weight blocks per workgroup -- 1 x 1, 1 x 2, 2 x 1, 2 x 2 --, then the shared-X schedule; by layout and format.
+// Fits to graph replays with every schedule forced, 1 to 2048 tokens on eleven layers from 704 -> 512 to 8192 -> 28672; a canonical
+// operand costs more per step, its loads being 16-byte pieces of 32 rows.
+constexpr StreamCost kStreamCost[2][2][5] = {
+    {{{0.125, 0.140, 0.5}, {0.185, 0.237, 1.0}, {0.175, 0.204, 0.6}, {0.245, 0.314, 0.8}, {0.70, 0.63, 3.5}},     // canonical NVFP4
+     {{0.125, 0.140, 0.5}, {0.185, 0.237, 1.0}, {0.175, 0.204, 0.6}, {0.245, 0.314, 0.8}, {0.70, 0.63, 3.5}}},    // and INT4
+    {{{0.053, 0.052, 0.4}, {0.0755, 0.088, 0.9}, {0.0725, 0.079, 0.5}, {0.120, 0.139, 0.6}, {0.62, 0.51, 2.3}},   // tiled NVFP4
+     {{0.075, 0.069, 0.4}, {0.109, 0.113, 0.9}, {0.107, 0.106, 0.5}, {0.154, 0.163, 0.6}, {0.66, 0.57, 2.3}}}};   // and INT4
+
+}  // namespace
+
+// A tiled layer of at most 128 tokens always streams, by the rules above.  Any other one takes the schedule with the smallest
+// estimate, if that is below the estimate for the 256-row tiles (tile_us, which the caller has): those leave compute units idle until
+// tokens / 256 x channels / 128 reaches their number (us, tiles | streaming: NVFP4 224 x 16384 -> 1024 182 | 20, 320 x 14336 ->
+// 4096 160 | 54, 1024 x 4096 -> 4096 52 | 40, 2048 x 4096 -> 4096 61 | 71; canonical INT4 16 x 8192 -> 28672 134 | 60).
+W4StreamPlan w4_stream_plan(int fmt, int64_t M, int64_t N, int64_t K, int tiled, double tile_us) {
   const int forced = debug_option(kDbgW4Skinny);
-  const bool shared_x = M > 64 && (forced == 2 || (forced != 1 && shared_x_pays(FMT, N)));
-  if (shared_x) return launch_shared_x<FMT>(Xq, Xs, tsx, Wq, Ws, tsw, M, N, K, out_f32, Y, ldy, stream);
-  return launch_split_k<FMT>(Xq, Xs, tsx, Wq, Ws, tsw, M, N, K, out_f32, Y, ldy, stream);
+  W4StreamPlan plan;
+  if (forced == 0 || M > 4096) return plan;          // beyond it the tiles have enough rows; keeps blockIdx.y small
+  if (tiled && M <= 128) {
+    plan.streams = true;
+    plan.shared_x = M > 64 && (forced == 2 || (forced != 1 && shared_x_pays(fmt, N)));
+    few_token_blocks(M, N, plan.rb, plan.cbw);
+    return plan;
+  }
+  if (forced < 0 && debug_option(kDbgW4Width) >= 0) return plan;   // tests: a width of the tiles
+  const int cus = device_cu_count();
+  const int64_t NB = (N + 31) / 32, T = (M + 31) / 32, KT = K / 64;
+  const StreamCost* cost = kStreamCost[tiled ? 1 : 0][fmt == kInt4 ? 1 : 0];
+  double best = forced >= 1 ? 1e30 : tile_us;
+  for (int c = 0; c < 5; ++c) {
+    const bool shared = c == 4;
+    const int rb = shared ? 4 : 1 + c / 2, cbw = shared ? 4 : 1 + c % 2;   // shared X: one weight block for each of four waves
+    if ((forced == 1 && shared) || (forced == 2 && !shared)) continue;
+    // a second row block needs more than 32 tokens; canonical rows: so few tokens that the lanes of an activation load share
+    // lines make the conversion cheap, and one weight block is the faster
+    if (!shared && ((rb == 2 && M <= 32) || (cbw == 2 && !tiled && M <= 8))) continue;
+    const double us = stream_us(cost[c], ((NB + cbw - 1) / cbw) * ((T + rb - 1) / rb), KT, cus);
+    if (us >= best) continue;
+    best = us;
+    plan = {true, shared, rb, cbw};
+  }
+  return plan;
+}
+
+namespace {
+
+template <int FMT>
+hipError_t launch(const W4StreamPlan& plan, const void* Xq, const void* Xs, const float* tsx, const void* Wq, const void* Ws,
+                  const float* tsw, int64_t M, int64_t N, int64_t K, int out_f32, int tiled, void* Y, int64_t ldy, hipStream_t stream) {
+  if (plan.shared_x) return launch_shared_x<FMT>(Xq, Xs, tsx, Wq, Ws, tsw, M, N, K, out_f32, tiled, Y, ldy, stream);
+  return launch_split_k<FMT>(Xq, Xs, tsx, Wq, Ws, tsw, M, N, K, out_f32, tiled, plan.rb, plan.cbw, Y, ldy, stream);
 }
 
 }  // namespace
 
-hipError_t launch_nvfp4_gemm_skinny(const void* Xq, const void* Xs, const float* tsx, const void* Wq, const void* Ws,
-                                    const float* tsw, int64_t M, int64_t N, int64_t K, int out_f32, void* Y,
-                                    int64_t ldy, hipStream_t stream) {
-  return launch<kNvfp4>(Xq, Xs, tsx, Wq, Ws, tsw, M, N, K, out_f32, Y, ldy, stream);
+hipError_t launch_nvfp4_gemm_skinny(const W4StreamPlan& plan, const void* Xq, const void* Xs, const float* tsx, const void* Wq,
+                                    const void* Ws, const float* tsw, int64_t M, int64_t N, int64_t K, int out_f32, int tiled,
+                                    void* Y, int64_t ldy, hipStream_t stream) {
+  return launch<kNvfp4>(plan, Xq, Xs, tsx, Wq, Ws, tsw, M, N, K, out_f32, tiled, Y, ldy, stream);
 }
 
-hipError_t launch_int4_gemm_skinny(const void* Xq, const void* Xs, const void* Wq, const void* Ws, int64_t M, int64_t N,
-                                   int64_t K, int out_f32, void* Y, int64_t ldy, hipStream_t stream) {
-  return launch<kInt4>(Xq, Xs, nullptr, Wq, Ws, nullptr, M, N, K, out_f32, Y, ldy, stream);
+hipError_t launch_int4_gemm_skinny(const W4StreamPlan& plan, const void* Xq, const void* Xs, const void* Wq, const void* Ws,
+                                   int64_t M, int64_t N, int64_t K, int out_f32, int tiled, void* Y, int64_t ldy,
+                                   hipStream_t stream) {
+  return launch<kInt4>(plan, Xq, Xs, nullptr, Wq, Ws, nullptr, M, N, K, out_f32, tiled, Y, ldy, stream);
 }
 
 }  // namespace wush

@@ -20,7 +20,7 @@ enum DebugOption {
   kDbgGemmSkinny = 1,        // MXFP4 GEMM, up to 128 tokens: 1 = weight-streaming kernel, 0 = tiled kernel
   kDbgGemmSimple = 2,        // canonical layout: 1 = the one-wave-per-tile kernel
   kDbgW4Width = 3,           // NVFP4 / INT4 tiled GEMM: tile width 2..4 (x 64 output channels)
-  kDbgW4Skinny = 4,          // NVFP4 / INT4 GEMM, up to 128 tokens: 0 = tiled kernel, 1, 2 = weight-streaming kernel (K split,
+  kDbgW4Skinny = 4,          // NVFP4 / INT4 GEMM, up to 4096 tokens: 0 = 256-row tiles, 1, 2 = weight-streaming kernel (K split,
                              // shared X)
   kDbgDecodeFused = 5,       // wush_layer_decode: 1 = single launch with a grid-wide barrier
   kDbgDecodeTestTimeout = 6, // wush_layer_decode: 1 = the barrier wait gives up at once (error-path test)
@@ -141,12 +141,19 @@ hipError_t launch_nvfp4_gemm(const void* Xq, const void* Xs, const float* tsx, c
                              const float* tsw, int64_t M, int64_t N, int64_t K, int out_f32, int tiled, void* Y,
                              int64_t ldy, hipStream_t stream);
 
-// Weight-streaming GEMMs of the two formats for M <= 128, tiled layout only (w4_gemm_skinny.hip).
-hipError_t launch_nvfp4_gemm_skinny(const void* Xq, const void* Xs, const float* tsx, const void* Wq, const void* Ws,
-                                    const float* tsw, int64_t M, int64_t N, int64_t K, int out_f32, void* Y,
-                                    int64_t ldy, hipStream_t stream);
-hipError_t launch_int4_gemm_skinny(const void* Xq, const void* Xs, const void* Wq, const void* Ws, int64_t M, int64_t N,
-                                   int64_t K, int out_f32, void* Y, int64_t ldy, hipStream_t stream);
+// Weight-streaming GEMMs of the two formats (w4_gemm_skinny.hip): whether and how they take a layer that the 256-row tiles
+// would take tile_us for.  fmt = 0 for NVFP4, 1 for INT4; rb, cbw = blocks of 32 tokens and of 32 output channels per workgroup.
+struct W4StreamPlan {
+  bool streams = false, shared_x = false;
+  int rb = 1, cbw = 1;
+};
+W4StreamPlan w4_stream_plan(int fmt, int64_t M, int64_t N, int64_t K, int tiled, double tile_us);
+hipError_t launch_nvfp4_gemm_skinny(const W4StreamPlan& plan, const void* Xq, const void* Xs, const float* tsx, const void* Wq,
+                                    const void* Ws, const float* tsw, int64_t M, int64_t N, int64_t K, int out_f32, int tiled,
+                                    void* Y, int64_t ldy, hipStream_t stream);
+hipError_t launch_int4_gemm_skinny(const W4StreamPlan& plan, const void* Xq, const void* Xs, const void* Wq, const void* Ws,
+                                   int64_t M, int64_t N, int64_t K, int out_f32, int tiled, void* Y, int64_t ldy,
+                                   hipStream_t stream);
 
 // INT4 variant (two's-complement codes, BF16 scale per 32, 32 x 32 transforms); layouts as for NVFP4
 // (the 4 scale bytes of a K step of 64 are two BF16 numbers).  Weight workspace: as launch_weight_prep.
