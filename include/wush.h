@@ -467,8 +467,9 @@ wush_status wush_unpack_tiled(const void* q_tiled, const void* s_tiled, int64_t 
  * the accumulation order of a GEMM; nothing reads the environment.
  *   WUSH_DEBUG_GEMM_TILE            wush_linear, tiled layout: 0..3 = 256x256, 128x384, 128x256, 128x128 tiles; canonical
  *                                   layout: 0..4 = 256x256, 128x128, 128x128 with more steps in flight, 64x128, 64x64
- *   WUSH_DEBUG_GEMM_SKINNY          wush_linear up to 128 tokens: 1 = weight-streaming kernel, 0 = tiled kernel
- *   WUSH_DEBUG_GEMM_SIMPLE          wush_linear, canonical layout: 1 = the one-wave-per-tile kernel, 0 = the pipelined one
+ *   WUSH_DEBUG_GEMM_SKINNY          wush_linear, tiled layout, up to 1024 tokens: 1 = weight-streaming kernel, 0 = tiled kernel;
+ *                                   canonical layout: 0 = not the streaming kernel
+ *   WUSH_DEBUG_GEMM_SIMPLE          wush_linear, canonical layout: 1 = the one-wave-per-tile kernel, 0 = not that one
  *   WUSH_DEBUG_W4_WIDTH             wush_linear_nvfp4 / _int4: tile width 2..4 (x 64 output channels)
  *   WUSH_DEBUG_W4_SKINNY            wush_linear_nvfp4 / _int4 up to 4096 tokens: 0 = 256-row tiles; weight-streaming kernel with
  *                                   1 = K split over a workgroup's waves, 2 = activations shared through LDS (tiled layout: from

@@ -1,7 +1,7 @@
 // Decode-sized layer forward (at most 64 tokens) for gfx950:
 //   Y = sum_i Wq(i)^T q(T(i) X(i))      (layer forward-pass equation)
 // with the weights already transformed and quantized, in two forms:
-//   * gemm_skinny_kernel: the MXFP4 GEMM alone for M <= 128 (wush_linear);
+//   * gemm_skinny_kernel: the MXFP4 GEMM alone for few tokens, or few output channels (wush_linear);
 //   * layer_decode_kernel: activation transform + quantization + GEMM in ONE
 //     launch (wush_layer_decode).
 // At these sizes the layer is bound by streaming the weights once (K/2 + K/32

@@ -114,13 +114,23 @@ hipError_t launch_mxfp4_gemm(const void* Xq, const void* Xs, const void* Wq, con
       const double tiled_us = fmax(4.3 + 0.3 * (double)(K / 256) * tile_rounds, weight_mib / 6.4 + 4.0);
       skinny = skinny_us < tiled_us;
     }
-    if (M <= 128 && debug_option(kDbgGemmSkinny) >= 0) skinny = debug_option(kDbgGemmSkinny) == 1;   // tests: force either kernel
+    // Up to 1024 tokens the streaming kernel also takes the layers of so few output channels that it needs no more than one workgroup
+    // per compute unit, where 128-row tiles leave most of them idle (us, tiles | streaming: 256 x 4096 -> 1024 8.7 | 5.0, 1024 x 4096 ->
+    // 1024 10.2 | 9.3, 256 x 16384 -> 1024 24.3 | 10.2, 448 x 28672 -> 512 40 | 16, 256 x 14336 -> 4096 22.6 | 18.8, 256 x 4096 -> 4096
+    // 8.9 | 7.8; with more workgroups 448 x 4096 -> 4096 10.1 | 12.2, 448 x 14336 -> 4096 23.4 | 29).
+    if (M > 128 && M <= 1024 && debug_option(kDbgGemmTile) < 0) {
+      const int rb = skinny_row_blocks(M, N);
+      skinny = ((M + 32 * rb - 1) / (32 * rb)) * ((N + 31) / 32) <= device_cu_count();
+    }
+    if (M <= 1024 && debug_option(kDbgGemmSkinny) >= 0) skinny = debug_option(kDbgGemmSkinny) == 1;   // tests: force either kernel
     if (skinny) return launch_mxfp4_gemm_skinny(Xq, Xs, Wq, Ws, M, N, K, out_f32, Y, ldy, stream);
     return launch_mxfp4_gemm_frag(Xq, Xs, Wq, Ws, M, N, K, out_f32, Y, ldy, stream);
   }
   bool simple = short_k(M, N, K, canon_vec_store(Y, ldy, out_f32));
   if (debug_option(kDbgGemmTile) >= 0) simple = false;                                       // tests: a tile shape of the other kernel
   if (const int forced = debug_option(kDbgGemmSimple); forced >= 0) simple = forced == 1;    // tests: either kernel
+  if (!simple && canon_streams(M, N) && debug_option(kDbgGemmTile) < 0 && debug_option(kDbgGemmSkinny) != 0)
+    return launch_mxfp4_gemm_canon_stream(Xq, Xs, Wq, Ws, M, N, K, out_f32, Y, ldy, stream);
   if (!simple) return launch_mxfp4_gemm_canon(Xq, Xs, Wq, Ws, M, N, K, out_f32, Y, ldy, stream);
   const int64_t tiles = ((M + 31) / 32) * ((N + 31) / 32);
   gemm_simple_kernel<<<dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, stream>>>(

@@ -17,7 +17,7 @@ int device_cu_count();
 // -1 = unset = the library's own choice.  The numbering is that of the WUSH_DEBUG_* constants of wush.h.
 enum DebugOption {
   kDbgGemmTile = 0,          // tiled MXFP4 GEMM: 0..3 = 256x256, 128x384, 128x256, 128x128
-  kDbgGemmSkinny = 1,        // MXFP4 GEMM, up to 128 tokens: 1 = weight-streaming kernel, 0 = tiled kernel
+  kDbgGemmSkinny = 1,        // MXFP4 GEMM, tiled layout, up to 1024 tokens: 1 = weight-streaming kernel, 0 = tiled kernel; canonical: 0 = no streaming
   kDbgGemmSimple = 2,        // canonical layout: 1 = the one-wave-per-tile kernel
   kDbgW4Width = 3,           // NVFP4 / INT4 tiled GEMM: tile width 2..4 (x 64 output channels)
   kDbgW4Skinny = 4,          // NVFP4 / INT4 GEMM, up to 4096 tokens: 0 = 256-row tiles, 1, 2 = weight-streaming kernel (K split,
@@ -91,6 +91,10 @@ inline int canon_vec_store(const void* Y, int64_t ldy, int out_f32) {
 hipError_t launch_mxfp4_gemm_canon(const void* Xq, const void* Xs, const void* Wq, const void* Ws,
                                    int64_t M, int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy,
                                    hipStream_t stream);
+// The same where a 32 x 32 block of outputs gets a compute unit of its own (mxfp4_gemm_canon_stream.hip).
+bool canon_streams(int64_t M, int64_t N);
+hipError_t launch_mxfp4_gemm_canon_stream(const void* Xq, const void* Xs, const void* Wq, const void* Ws, int64_t M, int64_t N,
+                                          int64_t K, int out_f32, void* Y, int64_t ldy, hipStream_t stream);
 // Operands in the fragment-order layout (K % 256 == 0).
 hipError_t launch_mxfp4_gemm_frag(const void* Xq, const void* Xs, const void* Wq, const void* Ws,
                                   int64_t M, int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy,
@@ -104,7 +108,7 @@ hipError_t launch_gptq_prep(const void* W, int64_t N, int64_t K, int64_t ldw, co
                             double lambda, int transform_given, int rule, int tiled, void* T_blocks, void* Wq, void* Ws,
                             void* workspace, hipStream_t stream);
 
-// Decode-sized paths (GEMM: M <= 128; fused layer: M <= 64; fragment-order operands).
+// Decode-sized paths (GEMM: M <= 1024; fused layer: M <= 64; fragment-order operands).
 int skinny_row_blocks(int64_t M, int64_t N);
 hipError_t launch_mxfp4_gemm_skinny(const void* Xq, const void* Xs, const void* Wq, const void* Ws, int64_t M,
                                     int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy, hipStream_t stream);
