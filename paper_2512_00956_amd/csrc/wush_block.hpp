@@ -171,6 +171,163 @@ __device__ __forceinline__ bool reverse_factor_group(EntryFn entry, StoreUFn sto
   return good;
 }
 
+// Columns of A (A[column][row], D = 32 or 16) turned by right rotations until they are orthogonal, A V = U S: one-sided Jacobi by the
+// first 4 D of a workgroup's 8 D threads (all of them call it: the workgroup barrier is everybody's).
+//
+// A sweep is D - 1 rounds of D / 2 rotations, each round waiting for the one before.  With 16 lanes per column pair and a round trip
+// through LDS and a barrier per round it took 850 cycles a round: some 60 instructions of 4 cycles, 16 the square roots and
+// reciprocals, on the chain or not, the round trip, the barrier.  So:
+//   * A slot of 16 lanes takes four columns, two blocks of two, and turns all four pairs between the blocks before the columns go
+//     back to LDS: two rounds per round trip, one more trip per sweep for the pairs inside the blocks.
+//   * The two pairs of a round are computed side by side: a lane holds D / 16 rows of all four columns and adds up both scalar
+//     products; each half of the slot gathers and evaluates one pair ("own") and hands cosine and sine to the other half, so
+//     that a wavefront's 60 instructions serve eight pairs instead of four.  One wavefront for all (four rows per lane) is slower: it
+//     is the issue of instructions that bounds that.
+// (x1, y1) is the own pair of a lane's half, (x2, y2) the other half's; the second round of a trip pairs x1 with y2.
+// 32 x 32 Gaussian blocks: 170k cycles for the whole iteration (one wavefront 194k); c2 layer's blocks (128, with moments and factors) 104 -> 83
+// us, the GPTQ chain's step 72 -> 61.
+template <int D>
+__device__ __forceinline__ void jacobi_group(double (*A)[D + 2], double* norm2, int* again) {
+  constexpr int NT = 8 * D, R = D / 16, B = D / 2;
+  const int t = threadIdx.x, slot = t / 16, l = t % 16;
+  const bool hi = l >= 8, active = t < 4 * D;
+  if (D == 16 && !active) return;                      // one wavefront: nobody to wait for
+  auto sync = [&]() {
+    if constexpr (D == 32) __syncthreads();
+    else wave_lds_sync();
+  };
+  typedef double rows_t[R];
+  auto load = [&](rows_t& v, int c) {
+    const double* p = &A[0][0] + __umul24(c, D + 2) + R * l;
+    if constexpr (R == 2) {
+      const v2d w = *reinterpret_cast<const v2d*>(p);
+      v[0] = w[0];
+      v[1] = w[1];
+    } else {
+      v[0] = p[0];
+    }
+  };
+  auto store = [&](const rows_t& v, int c) {
+    double* p = &A[0][0] + __umul24(c, D + 2) + R * l;
+    if constexpr (R == 2) *reinterpret_cast<v2d*>(p) = (v2d){v[0], v[1]};
+    else p[0] = v[0];
+  };
+  auto dot = [&](const rows_t& a, const rows_t& b) {
+    double s = a[0] * b[0];
+    if constexpr (R == 2) s = fma(a[1], b[1], s);
+    return s;
+  };
+  bool large;
+  double nx, ny;                                       // squared norms of the own pair
+  // The rotation by the angle of smaller magnitude that makes two columns orthogonal:
+  // tan(2 theta) = 2 ga / (be - al), |theta| <= pi / 4.  With h = hypot(be - al, 2 ga):
+  // cos^2 = (1 + |be - al| / h) / 2 and tan = (|ga| / h) / cos^2.  The tangent only has to be about
+  // right (the hardware's estimates, some 2^-24: the next sweep sees what is left); that cos and sin form a
+  // rotation to FP64 accuracy is the last reciprocal square root's business, refined by a cubic step.
+  auto rotate = [&](rows_t& x1, rows_t& y1, rows_t& x2, rows_t& y2) {
+    double ga = dot(x1, y1);
+    {
+#pragma clang fp contract(off)
+      ga += dpp_f64<0x140>(dot(x2, y2));               // row_mirror: the other half's partial sums of this half's pair
+      ga += dpp_f64<0xB1>(ga);
+      ga += dpp_f64<0x4E>(ga);
+      ga += dpp_f64<0x141>(ga);
+    }
+    const double dd = ny - nx, ab = nx * ny, gg = ga * ga, ga2 = ga + ga;
+    const double ih = __builtin_amdgcn_rsq(fma(ga2, ga2, dd * dd));
+    const double c2 = fma(0.5 * fabs(dd), ih, 0.5);
+    double tn = ga * ih * __builtin_amdgcn_rcp(c2);
+    tn = __longlong_as_double(__double_as_longlong(tn) ^ (__double_as_longlong(dd) & (1ll << 63)));
+    tn = gg > 1e-30 * ab ? tn : 0.0;                   // |ga| <= 1e-15 sqrt(al be): left alone
+    large |= gg > 1e-20 * ab || fabs(tn) > 1e-7;
+    const double x = fma(tn, tn, 1.0);
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    const double cs = fma(y * e, fma(e, 0.375, 0.5), y), sn = tn * cs;
+    const double cp = dpp_f64<0x140>(cs), sp = dpp_f64<0x140>(sn);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const double a = fma(-sn, y1[i], cs * x1[i]);
+      y1[i] = fma(sn, x1[i], cs * y1[i]);
+      x1[i] = a;
+      const double b = fma(-sp, y2[i], cp * x2[i]);
+      y2[i] = fma(sp, x2[i], cp * y2[i]);
+      x2[i] = b;
+    }
+    nx = fma(-tn, ga, nx);
+    ny = fma(tn, ga, ny);
+  };
+  for (int sweep = 0; sweep < 40; ++sweep) {
+    // squared norms of the columns: computed once a sweep, updated by the rotations in between (they only
+    // decide angles, so the updates' cancellation costs no accuracy of U)
+    constexpr int kGroups = D == 32 ? NT / 16 : 4;
+    for (int c = slot; c < D; c += kGroups) {
+      rows_t v;
+      load(v, c);
+      const double n2 = row_sum(dot(v, v));
+      if (l == 0) norm2[c] = n2;
+    }
+    sync();
+    large = false;
+    rows_t x1, y1, x2, y2;
+    int cx, cy;                                        // columns of the own pair
+    auto fetch = [&](int ax, int ay, int bx, int by) { // low half: pair (ax, ay), high half: pair (bx, by)
+      cx = hi ? bx : ax;
+      cy = hi ? by : ay;
+      load(x1, cx);
+      load(y1, cy);
+      load(x2, hi ? ax : bx);
+      load(y2, hi ? ay : by);
+      nx = norm2[cx];
+      ny = norm2[cy];
+    };
+    auto leave = [&](int ox, int oy, const rows_t& yo, const rows_t& yp) {   // the other pair's columns; the own pair's second, the other's
+      store(x1, cx);
+      store(yo, cy);
+      store(x2, ox);
+      store(yp, oy);
+      norm2[cx] = nx;                                  // the same from every lane of the half
+      norm2[cy] = ny;
+    };
+    // the pair inside every block
+    if (active) {
+      fetch(4 * slot, 4 * slot + 1, 4 * slot + 2, 4 * slot + 3);
+      rotate(x1, y1, x2, y2);
+      leave(hi ? 4 * slot : 4 * slot + 2, hi ? 4 * slot + 1 : 4 * slot + 3, y1, y2);
+    }
+    sync();
+    // the blocks against each other, circle method: position 0 fixed, the other B - 1 rotate
+    int p = slot, q = B - 1 - slot;
+    for (int rnd = 0; rnd < B - 1; ++rnd) {
+      if (active) {
+        fetch(2 * p, 2 * q, 2 * p + 1, 2 * q + 1);
+        rotate(x1, y1, x2, y2);
+        ny = dpp_f64<0x140>(ny);                       // the halves swap their second columns
+        cy ^= 1;
+        rotate(x1, y2, x2, y1);
+        leave(cx ^ 1, cy ^ 1, y2, y1);
+        p = slot == 0 ? 0 : (p == B - 1 ? 1 : p + 1);
+        q = q == B - 1 ? 1 : q + 1;
+      }
+      sync();
+    }
+    // A rotation by tan(theta) = tn undoes what earlier ones of its sweep zeroed by tn times the cosines it mixes in (the
+    // ratio of the two columns' norms is in tn), 2 D of them per pair at most.  So a sweep that met cosines up to 1e-10 and
+    // tangents up to 1e-7 only leaves cosines of some 1e-16, and the last ones' own, 2^-24 of what they were: no
+    // further sweep is needed.  Equal or nearly equal singular values turn by large angles at any cosine; there the sweeps go on until
+    // no cosine is above 1e-15.  (Stopping at cosines of 1e-10 alone left the columns of such a block orthogonal to 3e-11.)
+    if constexpr (D == 32) {
+      if (active && large) again[sweep & 1] = 1;
+      __syncthreads();
+      const int more = again[sweep & 1];
+      if (t == 0) again[(sweep + 1) & 1] = 0;          // read last a sweep ago, set next a sweep from now
+      if (!more) break;
+    } else {
+      if (!__any(large)) break;
+    }
+  }
+}
+
 // Alg. 1 for one D x D block (D = 32, or 16 for the NVFP4 variant), by a workgroup of 8 D threads:
 //   W' W'^T = M_W + lambda d^-1 tr(M_W) I,  X' X'^T likewise  (Cholesky, side by side)
 //   U S V^T = W'^T X'  (one-sided Jacobi on the columns; V never needed)
@@ -185,11 +342,9 @@ __device__ __forceinline__ bool reverse_factor_group(EntryFn entry, StoreUFn sto
 // V_out; the identity where the moments give none) and leaves the status alone.
 //
 // A block is one chain of dependent steps (2 x D columns of the factors, 6 to 8 sweeps of D - 1 Jacobi
-// rounds), so what counts is the latency of a step, and the threads are there to shorten it: a column pair is
-// shared by the 16 lanes of a DPP row (two LDS loads and stores per lane, the three dot products summed by
-// four DPP steps), the factors are taken column by column out of registers with one barrier per column, and the
-// products are spread over the whole workgroup.  c2 layer (128 blocks): 201 -> 104 us; a Jacobi round is some 850 cycles, of
-// which some 30 dependent FP64 operations and the LDS round trip are nearly all.
+// rounds), so what counts is the latency of a step, and the threads are there to shorten it: the factors are taken column by
+// column out of registers with one barrier per column, the products are spread over the whole workgroup, and the Jacobi
+// rounds are jacobi_group's.
 template <int D, int MODE, class LoadFn, class FinishFn>
 __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, int S_W, int S_X, double lambda,
                                                  const double* __restrict__ V0, uint16_t* __restrict__ T_bits,
@@ -314,84 +469,9 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
   }
   __syncthreads();
   // ---- one-sided Jacobi on the columns of A (right rotations): A V = U S
-  const int pr = t / 16, sub = t % 16;                 // pair slot; rows kRpl sub ... of its two columns
-  for (int sweep = 0; sweep < 40; ++sweep) {
-    // squared norms of the columns: computed once a sweep, updated by the rotations in between (they only
-    // decide angles, so the updates' cancellation costs no accuracy of U)
-    for (int c = pr; c < D; c += NT / 16) {
-      double n2 = 0.0;
-#pragma unroll
-      for (int i = 0; i < kRpl; ++i) n2 = fma(A[c][kRpl * sub + i], A[c][kRpl * sub + i], n2);
-      n2 = row_sum(n2);
-      if (sub == 0) norm2[c] = n2;
-    }
-    __syncthreads();
-    bool large = false;
-    // circle method: position 0 fixed, the other D - 1 rotate
-    int p = pr, q = D - 1 - pr;
-    for (int rnd = 0; rnd < D - 1; ++rnd) {
-      double *cp = &A[p][kRpl * sub], *cq = &A[q][kRpl * sub];
-      double ap[kRpl], aq[kRpl];
-      if constexpr (kRpl == 2) {
-        const v2d vp = *reinterpret_cast<const v2d*>(cp), vq = *reinterpret_cast<const v2d*>(cq);
-        ap[0] = vp[0]; ap[1] = vp[1]; aq[0] = vq[0]; aq[1] = vq[1];
-      } else {
-        ap[0] = *cp; aq[0] = *cq;
-      }
-      const double al = norm2[p], be = norm2[q];
-      double ga = ap[0] * aq[0];
-#pragma unroll
-      for (int i = 1; i < kRpl; ++i) ga = fma(ap[i], aq[i], ga);
-      ga = row_sum(ga);
-      const double ab = al * be, gg = ga * ga;
-      // The rotation by the angle of smaller magnitude that makes the two columns orthogonal:
-      // tan(2 theta) = 2 ga / (be - al), |theta| <= pi / 4.  With h = hypot(be - al, 2 ga):
-      // cos^2 = (1 + |be - al| / h) / 2 and tan = (|ga| / h) / cos^2.  The tangent only has to be about
-      // right (the hardware's estimates, some 2^-24: the next sweep sees what is left); that cos and sin form a
-      // rotation to FP64 accuracy is the last reciprocal square root's business, refined by a cubic step.
-      const double dd = be - al;
-      const double ih = __builtin_amdgcn_rsq(fma(dd, dd, 4.0 * gg));
-      const double c2 = fma(0.5 * fabs(dd), ih, 0.5);
-      double tn = fabs(ga) * ih * __builtin_amdgcn_rcp(c2);
-      tn = dd == 0.0 || (dd > 0.0) == (ga > 0.0) ? tn : -tn;
-      tn = gg > 1e-30 * ab ? tn : 0.0;                 // |ga| <= 1e-15 sqrt(al be): left alone
-      large |= gg > 1e-20 * ab || fabs(tn) > 1e-7;
-      const double x = fma(tn, tn, 1.0);
-      const double y = __builtin_amdgcn_rsq(x);
-      const double e = fma(-x * y, y, 1.0);
-      const double cs = fma(y * e, fma(e, 0.375, 0.5), y);
-      const double sn = tn * cs;
-#pragma unroll
-      for (int i = 0; i < kRpl; ++i) {
-        const double np = fma(-sn, aq[i], cs * ap[i]);
-        aq[i] = fma(sn, ap[i], cs * aq[i]);
-        ap[i] = np;
-      }
-      if constexpr (kRpl == 2) {
-        *reinterpret_cast<v2d*>(cp) = (v2d){ap[0], ap[1]};
-        *reinterpret_cast<v2d*>(cq) = (v2d){aq[0], aq[1]};
-      } else {
-        *cp = ap[0]; *cq = aq[0];
-      }
-      if (sub == 0) {
-        norm2[p] = fma(-tn, ga, al);
-        norm2[q] = fma(tn, ga, be);
-      }
-      p = pr == 0 ? 0 : (p == D - 1 ? 1 : p + 1);
-      q = q == D - 1 ? 1 : q + 1;
-      __syncthreads();
-    }
-    // A rotation by tan(theta) = tn undoes what earlier ones of its sweep zeroed by tn times the cosines it mixes in (the
-    // ratio of the two columns' norms is in tn), 2 D of them per pair at most.  So a sweep that met cosines up to 1e-10 and
-    // tangents up to 1e-7 only leaves cosines of some 1e-16, and the last ones' own, 2^-24 of what they were: no
-    // further sweep is needed.  Equal or nearly equal singular values turn by large angles at any cosine; there the sweeps go on until
-    // no cosine is above 1e-15.  (Stopping at cosines of 1e-10 alone left the columns of such a block orthogonal to 3e-11.)
-    if (large) again[sweep & 1] = 1;
-    __syncthreads();
-    const int more = again[sweep & 1];
-    if (t == 0) again[(sweep + 1) & 1] = 0;            // read last a sweep ago, set next a sweep from now
-    if (!more) break;
-  }
+  jacobi_group<D>(A, norm2, again);
+  __syncthreads();
+  const int pr = t / 16, sub = t % 16;                 // column; rows kRpl sub ... of it
   // ---- singular values, descending order, U with the sign convention (16 lanes per column)
   for (int c = pr; c < D; c += NT / 16) {
     double n2 = 0.0;
