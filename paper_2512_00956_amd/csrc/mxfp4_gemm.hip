@@ -77,6 +77,9 @@ __global__ __launch_bounds__(256) void gemm_simple_kernel(
 //   K < 512, a partial second step: up to 16 tokens 1.0 to 1.25 times slower pipelined (288 -> 32768), at 200 and more tokens faster (352 ->
 //             8192 0.80); rows without 16-byte alignment 1.02 to 1.4 times slower up to some 4 M outputs, at 2048 x 416 -> 8192 0.90
 //   whole steps (256, 512): pipelined, 0.3 to 0.95 of the time
+// (Measured before the pipelined kernel's stores and scale loads took rows of any alignment; since then, one wave | pipelined: 2048 x 416 ->
+// 8191 31.6 | 18.7, 300 x 480 -> 1001 5.7 | 5.6, 1000 x 416 -> 3001 FP32 10.7 | 8.1, 2048 x 192 -> 32768 FP32 67.6 | 59.3, 500 x 160 -> 3001
+// FP32 5.6 | 5.9, 2048 x 96 -> 32768 FP32 55.0 | 55.6.)
 bool short_k(int64_t M, int64_t N, int64_t K, int vec_store) {
   if (M * N >= (int64_t)1 << 35) return false;   // its grid of 32 x 32 tiles
   if (K <= 128) return true;

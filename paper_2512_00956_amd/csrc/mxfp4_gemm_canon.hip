@@ -14,7 +14,8 @@
 //     free as long as both operands agree.  Its fragments are read during the issue before.
 //   * Scale rows are K / 32 bytes at any alignment.  Read where an MFMA needs them, they were as many cache-line lookups
 //     as the operands; instead each thread fetches the 16 bytes of one row's next two steps at a time and leaves them
-//     in LDS, where a lane picks its dword per step (its bytes are the four issues').
+//     in LDS, where a lane picks its dword per step (its bytes are the four issues').  What is left of a row at its end comes
+//     as its last 16 bytes, shifted into place on the way to LDS (byte by byte it cost 777 x 1376 -> 3001 1.8 us of 11.6).
 // The direct loads are issued from inline asm (and the barrier's fences name LDS only) for the reason given in
 // mxfp4_gemm_frag.hip: the compiler would drain them at every LDS read.  They have no register destination; their
 // arrival is the explicit vmcnt's business.  The scale loads are ordinary ones; the compiler's wait for them, one in two
@@ -108,31 +109,56 @@ __global__ __launch_bounds__(256) void gemm_canon_kernel(
   };
 
   // ---- scales: rows threadIdx.x + 256 i of [X tile; W tile], 16 bytes (two steps) at a time
+  // The pointers advance in place: an address put together for a load could land in the registers of the load before, which the
+  // compiler then waits for, draining the ring.
   v4u scale_next[S::kScaleRows];
-  auto fetch_scales = [&](int pair) {
+  typedef const __attribute__((address_space(1))) uint8_t* global_bytes;   // the asm below would make a plain pointer a flat one
+  typedef const __attribute__((address_space(1))) v4u_unaligned* global_scales;
+  global_bytes scale_at[S::kScaleRows];
+#pragma unroll
+  for (int i = 0; i < S::kScaleRows; ++i) {
+    const int row = min((int)threadIdx.x + 256 * i, S::kRows - 1);
+    const bool x = row < S::kTM;
+    scale_at[i] = (global_bytes)(x ? Xs : Ws) + (int64_t)(x ? min(m0 + row, M - 1) : min(n0 + row - S::kTM, N - 1)) * C;
+  }
+  auto fetch_first_scales = [&]() {
 #pragma unroll
     for (int i = 0; i < S::kScaleRows; ++i) {
-      const int row = threadIdx.x + 256 * i;
-      if (row >= S::kRows) continue;
-      const bool x = row < S::kTM;
-      const int64_t g = (int64_t)(x ? min(m0 + row, M - 1) : min(n0 + row - S::kTM, N - 1));
-      const uint8_t* p = (x ? Xs : Ws) + g * C + 16 * pair;
-      if (16 * pair + 16 <= C) {              // the same in every thread
-        scale_next[i] = *reinterpret_cast<const v4u_unaligned*>(p);
+      if (C >= 16) {                          // the same in every thread
+        scale_next[i] = *(global_scales)scale_at[i];
       } else {
         v4u v = {0x7F7F7F7Fu, 0x7F7F7F7Fu, 0x7F7F7F7Fu, 0x7F7F7F7Fu};
+        const int bytes = RAGGED ? 16 : 8;
 #pragma unroll
-        for (int b = 0; b < 16; ++b)
-          if (16 * pair + b < C) v[b >> 2] = (v[b >> 2] & ~(0xFFu << (8 * (b & 3)))) | (uint32_t)p[b] << (8 * (b & 3));
+        for (int b = 0; b < bytes; ++b)
+          if (b < C) v[b >> 2] = (v[b >> 2] & ~(0xFFu << (8 * (b & 3)))) | (uint32_t)scale_at[i][b] << (8 * (b & 3));
         scale_next[i] = v;
       }
     }
   };
+  auto fetch_scales = [&](int pair) {         // pair >= 1: the row has more than 16 groups
+    const int step = min(16, C - 16 * pair);  // past the row's end: its last 16 bytes instead, shifted into place by leave_scales
+#pragma unroll
+    for (int i = 0; i < S::kScaleRows; ++i) {
+      scale_at[i] += step;
+      asm volatile("" : "+v"(scale_at[i]));
+      if (threadIdx.x + 256 * i < S::kRows) scale_next[i] = *(global_scales)scale_at[i];
+    }
+  };
   auto leave_scales = [&](int pair) {
+    int past = C >= 16 ? max(16 * pair + 16 - C, 0) : 0;   // bytes past the row's end: 0 .. 15 (8 groups: whole steps), the same in every thread
 #pragma unroll
     for (int i = 0; i < S::kScaleRows; ++i) {
       const int row = threadIdx.x + 256 * i;
-      if (row < S::kRows) *reinterpret_cast<v4u*>(smem + S::kScaleBase + (pair & 1) * S::kScaleB + 16 * row) = scale_next[i];
+      v4u v = scale_next[i];
+      if (past > 0) {
+        asm volatile("" : "+s"(past));        // a branch, not selects in every step
+        if (past & 8) v = (v4u){v[2], v[3], 0, 0};
+        if (past & 4) v = (v4u){v[1], v[2], v[3], 0};
+        v = (v4u){__builtin_amdgcn_alignbyte(v[1], v[0], past & 3), __builtin_amdgcn_alignbyte(v[2], v[1], past & 3),
+                  __builtin_amdgcn_alignbyte(v[3], v[2], past & 3), __builtin_amdgcn_alignbyte(0, v[3], past & 3)};
+      }
+      if (row < S::kRows) *reinterpret_cast<v4u*>(smem + S::kScaleBase + (pair & 1) * S::kScaleB + 16 * row) = v;
     }
   };
 
@@ -161,7 +187,7 @@ __global__ __launch_bounds__(256) void gemm_canon_kernel(
 
 #define WUSH_FENCE __builtin_amdgcn_sched_barrier(0);
   // ---- prologue: ST - 1 steps on their way
-  fetch_scales(0);
+  fetch_first_scales();
   leave_scales(0);
   WUSH_FENCE
 #pragma unroll
@@ -281,12 +307,16 @@ hipError_t launch_any(int shape, const void* Xq, const void* Xs, const void* Wq,
 // 512 x 4096 -> 6144 31 | 16.4 | 14.8 | 15.3 | 19.5; 128 tokens 28 | 14.6 | 13.2 | 11.0 | 9.2; 1 token 26 | 10.7 | 10.9 | 9.1 |
 // 7.4.  (Before: 189 with a 256 x 256 kernel of two
 // stages, 89 | 31 | 18 with one wavefront per tile, mxfp4_gemm.hip, which keeps the layers of short K.)
-double shape_cost_us(int64_t M, int64_t N, int64_t K, int tm, int tn, double base, double per_tile, double lat, double thr,
+// Rows of Y without 16-byte alignment make the fixed part per tile longer (per_tile.other; 777 x 256 -> 3001 FP32 15.0 | 7.0 | 7.1 | 6.4 | 6.9).
+struct PerTile {
+  double aligned, other;
+};
+double shape_cost_us(int64_t M, int64_t N, int64_t K, int tm, int tn, double base, PerTile per_tile, double lat, double thr,
                      int vec_store, int cus) {
   const int64_t tiles = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
   if (tiles >= (int64_t)1 << 24) return 1e30;   // 256 work items each: a grid has fewer than 2^32
   const double n = (double)((tiles + cus - 1) / cus);
-  return base + (vec_store ? 1.0 : 2.5) * per_tile * n + (double)((K + 255) / 256) * fmax(lat, thr * n);
+  return base + (vec_store ? per_tile.aligned : per_tile.other) * n + (double)((K + 255) / 256) * fmax(lat, thr * n);
 }
 
 }  // namespace
@@ -296,11 +326,11 @@ hipError_t launch_mxfp4_gemm_canon(const void* Xq, const void* Xs, const void* W
   const int cus = device_cu_count();
   const bool one_each = ((M + 127) / 128) * ((N + 127) / 128) <= cus;   // 128 x 128: a compute unit's one workgroup gets four slots
   const int vec = canon_vec_store(Y, ldy, out_f32);
-  const double cost[5] = {shape_cost_us(M, N, K, 256, 256, 1.0, 6.6, 1.95, 1.95, vec, cus),
-                          shape_cost_us(M, N, K, 128, 128, 2.5, 1.8, 0.77, 0.64, vec, cus),
-                          one_each ? shape_cost_us(M, N, K, 128, 128, 2.5, 1.8, 0.67, 0.67, vec, cus) : 1e30,
-                          shape_cost_us(M, N, K, 64, 128, 2.7, 0.6, 0.47, 0.42, vec, cus),
-                          shape_cost_us(M, N, K, 64, 64, 2.2, 0.8, 0.38, 0.28, vec, cus)};
+  const double cost[5] = {shape_cost_us(M, N, K, 256, 256, 1.0, {6.6, 13.0}, 1.95, 1.95, vec, cus),
+                          shape_cost_us(M, N, K, 128, 128, 2.5, {1.8, 2.0}, 0.77, 0.64, vec, cus),
+                          one_each ? shape_cost_us(M, N, K, 128, 128, 2.5, {1.8, 2.0}, 0.67, 0.67, vec, cus) : 1e30,
+                          shape_cost_us(M, N, K, 64, 128, 2.7, {0.6, 1.2}, 0.47, 0.47, vec, cus),
+                          shape_cost_us(M, N, K, 64, 64, 2.2, {0.8, 0.9}, 0.38, 0.28, vec, cus)};
   int shape = 0;
   for (int c = 1; c < 5; ++c)
     if (cost[c] < cost[shape]) shape = c;

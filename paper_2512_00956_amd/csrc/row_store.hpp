@@ -44,10 +44,13 @@ struct RowStore {
   // streaming stores: the output is not read again by the kernel, and lines that leave the L2 as they are written shorten the write-back
   // at its end.  Others by plain ones: chunks that straddle lines are put together in the L2 (us, whole call, element by
   // element | streaming | plain: 2439 x 3328 -> 12521 BF16 131 | 68 | 64, FP32 142 | 80 | 74; 402 x 768 -> 31143 53.8 | 20.3 |
-  // 17.7; 3000 x 1280 -> 10081 - | 50.2 | 35.2, 10080 - | 32.8 | 33.6, 2439 x 3328 -> 12520 73 | 71 | 68; 2048 x 4096 -> 6144 FP32 57.7 | 33.9 | -).
+  // 17.7; 3000 x 1280 -> 10081 - | 50.2 | 35.2, 10080 - | 32.8 | 33.6, 2439 x 3328 -> 12520 73 | 71 | 68; 2048 x 4096 -> 6144 FP32 57.7 | 33.9 | -).  FP32 outputs of 4 to 16 MiB stream at any
+  // alignment: plain, they are mostly still in the L2s when the kernel ends (777 x 1376 -> 3001 14.1 | 14.6, 1214 x 14368 -> 1620 58.6 | 60.4; smaller
+  // and larger ones 3 to 16 % slower streaming).
   static __device__ __forceinline__ void store(const uint8_t* buf, void* __restrict__ Y, int64_t ldy, int row0, int col0, int M,
                                                int N, int lane) {
-    const bool aligned = ((ldy * kElem | (int64_t)(uintptr_t)Y) & 63) == 0;
+    const int64_t bytes = (int64_t)M * ldy * kElem;
+    const bool stream = ((ldy * kElem | (int64_t)(uintptr_t)Y) & 63) == 0 || (OUT_F32 && bytes > (4 << 20) && bytes <= (16 << 20));
     const bool whole = row0 + 32 <= M && col0 + 32 * CB <= N;      // both the same in every lane
     auto chunk_at = [&](int p, int& row, int& col) {               // 32 kChunks chunks, 64 per round
       const int idx = 64 * p + lane, row_l = idx / kChunks, chunk = idx % kChunks;
@@ -57,11 +60,11 @@ struct RowStore {
     };
     auto at = [&](int row, int col) { return static_cast<uint8_t*>(Y) + ((int64_t)row * ldy + col) * kElem; };
     int row, col;
-    if (whole && aligned) {
+    if (whole && stream) {
 #pragma unroll
       for (int p = 0; p < kChunks / 2; ++p) {
         const v4i v = chunk_at(p, row, col);
-        __builtin_nontemporal_store(v, reinterpret_cast<v4i*>(at(row, col)));
+        __builtin_nontemporal_store(v, reinterpret_cast<v4i_any*>(at(row, col)));
       }
     } else {
 #pragma unroll
