@@ -20,7 +20,7 @@
 //     inv(T_i);  Hbar = (T_i U_ii)(T_i U_ii)^T, R = inverse of its reverse Cholesky factor (R^T R = inv(Hbar))
 //     per output channel: transformed weights, GPTQ subroutine (32 steps of quantize at a static group scale,
 //     err = (w - q)/R[r][r], w[r'] -= err R[r][r']), G_i, and block i + 1: S += G_i U, current weights, M_W.
-// c2 (4096 calibration tokens, 4096 -> 6144): 70.4 -> 18.6 ms, of which the loop 128 x 105 us, the factor 3.1 ms and H 1.8.
+// c2 (4096 calibration tokens, 4096 -> 6144): 70.4 -> 17.2 ms, of which the loop 128 x 94 us, the factor 3.1 ms and H 1.8.
 // Summation orders are fixed (no atomics), so the result is reproducible.
 #include "weight_mfma.hpp"
 #include "wush_block.hpp"
@@ -299,7 +299,7 @@ __host__ __device__ inline Pending pending_of(int i, int C, int index) {
 }
 constexpr int kMostPending = 2 * kGroup - 2;
 
-// Workgroup 0: Alg. 1 on (M_W of block i's current weights, M_X = diagonal block of H) -> T_i, a chain of some 70 us on
+// Workgroup 0: Alg. 1 on (M_W of block i's current weights, M_X = diagonal block of H) -> T_i, a chain of some 60 us on
 // one compute unit (110 before).  The others meanwhile: S_l += sum_b G_b U_bl for the pending blocks l.  A workgroup holds its U_bl
 // in LDS in operand order, its wavefronts walk tiles of 16 rows (64 bytes per lane and operand, the next tile's
 // requested before this one's products); the panels G_b (the errors; block b's, whose S is used up) and S_l are [N][32].

@@ -1,7 +1,7 @@
 """NVFP4 / INT4 layers the weight-streaming kernel takes beyond 128 tokens and in the canonical layout: token counts around its row
 blocks, a last block of channels and of tokens that is not whole, K ranges shorter than a workgroup's waves, both schedules and the
-default, every output against the FP64 product of the dequantized codes (FP32 accumulation of exact FP16 products, K <= 1088: 1e-5 of the
-norm) and nothing past row M written.  The default's bits say which kernel ran."""
+default, eight wavefronts from K = 8192 on, every output against the FP64 product of the dequantized codes (FP32 accumulation of exact FP16
+products, chains of at most 2048 of them: 1e-5 of the norm) and nothing past row M written.  The default's bits say which kernel ran."""
 import numpy as np
 import pytest
 
@@ -25,7 +25,7 @@ def P():
 # (tokens, K, output channels, layout, the default streams)
 SIZES = [(129, 1088, 70, 1, True), (160, 64, 512, 1, True), (300, 512, 130, 1, True), (321, 256, 4100, 1, True),
          (1, 64, 1, 0, True), (1, 1088, 70, 0, True), (31, 512, 2048, 0, True), (33, 192, 8200, 0, True), (100, 256, 130, 0, True),
-         (130, 1024, 300, 0, True), (2048, 64, 8192, 1, False), (2048, 64, 8192, 0, False)]
+         (130, 1024, 300, 0, True), (1, 8128, 70, 1, True), (33, 8192, 70, 1, True), (70, 8256, 33, 1, True), (2048, 64, 8192, 1, False), (2048, 64, 8192, 0, False)]
 
 
 @pytest.mark.parametrize("fmt", ["nvfp4", "int4"])
