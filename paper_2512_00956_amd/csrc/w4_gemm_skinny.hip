@@ -80,12 +80,12 @@ __device__ __forceinline__ void dequant_step(const RawStep& t, int h, uint32_t s
 // CBW = blocks of 32 output channels a workgroup takes at a time: the X fragments of a K step are
 // converted once and multiplied with CBW weight blocks (the conversion of X is the same work in every
 // workgroup; with one block per pass it costs as much as that of the weights).
-template <int WAVES, int RB, int CBW, int FMT, bool OUT_F32, bool TILED>
-__global__ __launch_bounds__(WAVES * 64) void w4_skinny_kernel(
+template <int RB, int CBW, int FMT, bool OUT_F32, bool TILED>
+__global__ __launch_bounds__(kWaves * 64) void w4_skinny_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const float* __restrict__ tsx,
     const uint8_t* __restrict__ Wq, const uint8_t* __restrict__ Ws, const float* __restrict__ tsw,
     int M, int N, int K, void* __restrict__ Y, int64_t ldy, int vec_store) {
-  __shared__ float red[WAVES][RB][16][64];
+  __shared__ float red[kWaves][RB][16][64];
   constexpr int U = Depth<RB>::U;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(WAVES * 64) void w4_skinny_kernel(
   const uint32_t sel = 0x05040C0Cu + 0x02020000u * h;
   const float scale = FMT == kNvfp4 ? *tsx * *tsw : 1.0f;   // INT4 has no tensor scales (null pointers)
   int kt0, kt1;
-  skinny::wave_k_range<WAVES>(KT, wave, kt0, kt1);
+  skinny::wave_k_range(KT, wave, kt0, kt1);
 
   struct Chunk {
     RawStep w[CBW][U], x[RB][U];
@@ -168,8 +168,8 @@ __global__ __launch_bounds__(WAVES * 64) void w4_skinny_kernel(
 #pragma unroll
     for (int c = 0; c < CBW; ++c)
       if (g * CBW + c < NB)
-        skinny::reduce_store_block<RB, OUT_F32, FMT == kNvfp4, WAVES>(acc[c], red, g * CBW + c, M, N, Y, ldy, vec_store, lane,
-                                                                      wave, scale);
+        skinny::reduce_store_block<RB, OUT_F32, FMT == kNvfp4>(acc[c], red, g * CBW + c, M, N, Y, ldy, vec_store, lane,
+                                                               wave, scale);
   }
 }
 
@@ -376,39 +376,27 @@ void few_token_blocks(int64_t M, int64_t N, int& rb, int& cbw) {
   }
 }
 
-// Wavefronts that split K.  Eight where the workgroups are no more than the compute units, so that each has two wavefronts per SIMD
-// rather than one, and every wavefront keeps 16 steps at least (us, four | eight, tiled: NVFP4 100 x 27840 -> 384 26.7 | 22.9, 16 x 16384 -> 1024
-// 17.1 | 15.2, 1 x 8192 -> 4096 11.1 | 10.7, INT4 100 x 27840 -> 384 36.2 | 31.8, 16 x 14336 -> 4096 21.6 | 19.8; with shorter K 16 x 2048 ->
-// 1024 5.1 | 5.6, 16 x 4096 -> 2048 6.7 | 6.7; canonical rows, bound by their scattered loads, 16 x 14336 -> 4096 27.1 | 30.6).
-int w4_waves(int64_t M, int64_t N, int64_t K, int tiled, int rb, int cbw) {
-  const bool resident = ((M + 31) / 32) * ((N + 31) / 32) <= device_cu_count();
-  return tiled && rb == 1 && cbw == 1 && resident && K >= 8192 ? 8 : 4;
-}
-
 template <int FMT>
 hipError_t launch_split_k(const void* Xq, const void* Xs, const float* tsx, const void* Wq, const void* Ws,
                           const float* tsw, int64_t M, int64_t N, int64_t K, int out_f32, int tiled, int rb, int cbw, void* Y,
                           int64_t ldy, hipStream_t stream) {
   const int NB = (int)((N + 31) / 32);
   const int groups = (NB + cbw - 1) / cbw;
-  const int waves = w4_waves(M, N, K, tiled, rb, cbw);
-  dim3 grid((unsigned)(groups < 4096 ? groups : 4096), (unsigned)((M + 32 * rb - 1) / (32 * rb))), block(waves * 64);
+  dim3 grid((unsigned)(groups < 4096 ? groups : 4096), (unsigned)((M + 32 * rb - 1) / (32 * rb))), block(kWaves * 64);
   const int vec = skinny::decode_vec_store(Y, N, ldy, out_f32);
-#define WUSH_W4S_LAUNCH(W, RB, CBW, F32, TILED)                                                                          \
-  w4_skinny_kernel<W, RB, CBW, FMT, F32, TILED><<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs, tsx, \
-                                                                            (const uint8_t*)Wq, (const uint8_t*)Ws, tsw, \
-                                                                            (int)M, (int)N, (int)K, Y, ldy, vec)
-#define WUSH_W4S_BY_OUT(W, RB, CBW)                                                                                         \
-  {                                                                                                                         \
-    if (tiled) { if (out_f32) WUSH_W4S_LAUNCH(W, RB, CBW, true, true); else WUSH_W4S_LAUNCH(W, RB, CBW, false, true); }     \
-    else { if (out_f32) WUSH_W4S_LAUNCH(W, RB, CBW, true, false); else WUSH_W4S_LAUNCH(W, RB, CBW, false, false); }         \
+#define WUSH_W4S_LAUNCH(RB, CBW, F32, TILED)                                                                          \
+  w4_skinny_kernel<RB, CBW, FMT, F32, TILED><<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs, tsx, \
+                                                                         (const uint8_t*)Wq, (const uint8_t*)Ws, tsw, \
+                                                                         (int)M, (int)N, (int)K, Y, ldy, vec)
+#define WUSH_W4S_BY_OUT(RB, CBW)                                                                                      \
+  {                                                                                                                   \
+    if (tiled) { if (out_f32) WUSH_W4S_LAUNCH(RB, CBW, true, true); else WUSH_W4S_LAUNCH(RB, CBW, false, true); }     \
+    else { if (out_f32) WUSH_W4S_LAUNCH(RB, CBW, true, false); else WUSH_W4S_LAUNCH(RB, CBW, false, false); }         \
   }
-  if (waves == 8) {
-    if (out_f32) WUSH_W4S_LAUNCH(8, 1, 1, true, true); else WUSH_W4S_LAUNCH(8, 1, 1, false, true);
-  } else if (rb == 1) {
-    if (cbw == 2) WUSH_W4S_BY_OUT(4, 1, 2) else WUSH_W4S_BY_OUT(4, 1, 1)
+  if (rb == 1) {
+    if (cbw == 2) WUSH_W4S_BY_OUT(1, 2) else WUSH_W4S_BY_OUT(1, 1)
   } else {
-    if (cbw == 2) WUSH_W4S_BY_OUT(4, 2, 2) else WUSH_W4S_BY_OUT(4, 2, 1)
+    if (cbw == 2) WUSH_W4S_BY_OUT(2, 2) else WUSH_W4S_BY_OUT(2, 1)
   }
 #undef WUSH_W4S_BY_OUT
 #undef WUSH_W4S_LAUNCH

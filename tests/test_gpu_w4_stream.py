@@ -1,6 +1,6 @@
 """NVFP4 / INT4 layers the weight-streaming kernel takes beyond 128 tokens and in the canonical layout: token counts around its row
 blocks, a last block of channels and of tokens that is not whole, K ranges shorter than a workgroup's waves, both schedules and the
-default, eight wavefronts from K = 8192 on, every output against the FP64 product of the dequantized codes (FP32 accumulation of exact FP16
+default, long K, every output against the FP64 product of the dequantized codes (FP32 accumulation of exact FP16
 products, chains of at most 2048 of them: 1e-5 of the norm) and nothing past row M written.  The default's bits say which kernel ran."""
 import numpy as np
 import pytest
