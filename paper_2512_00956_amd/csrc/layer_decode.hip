@@ -49,7 +49,6 @@ namespace {
 using skinny::kWaves;
 using skinny::reduce_store_block;
 using skinny::wave_k_range;
-using skinny::decode_vec_store;
 constexpr uint32_t kSpinLimit = 1u << 21;   // polls of about 0.5 us each
 constexpr int kMaxGrid = 1024;              // barrier slots in the workspace
 
@@ -127,7 +126,7 @@ __device__ __forceinline__ void accumulate_block(v16f (&acc)[RB], FragTile (&w)[
 template <int RB, bool OUT_F32>
 __global__ __launch_bounds__(kWaves * 64) void gemm_skinny_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const uint8_t* __restrict__ Wq,
-    const uint8_t* __restrict__ Ws, int M, int N, int K, void* __restrict__ Y, int64_t ldy, int vec_store) {
+    const uint8_t* __restrict__ Ws, int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
   __shared__ float red[kWaves][RB][16][64];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -148,7 +147,7 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_skinny_kernel(
       load_w_chunk<Depth<RB>::U>(w, Wq, Ws, (int64_t)j * KT + kt0, min(Depth<RB>::U, kt1 - kt0), lane);
       accumulate_block<RB>(acc, w, Xq, Xs, Wq, Ws, KT, j, kt0, kt1, lane);
     }
-    reduce_store_block<RB, OUT_F32>(acc, red, j, M, N, Y, ldy, vec_store, lane, wave);
+    reduce_store_block<RB, OUT_F32>(acc, red, j, M, N, Y, ldy, lane, wave);
   }
 }
 
@@ -156,7 +155,7 @@ template <int RB, bool OUT_F32>
 __global__ __launch_bounds__(kWaves * 64) void layer_decode_kernel(
     const uint16_t* __restrict__ X, int64_t ldx, const uint16_t* __restrict__ T, const uint8_t* __restrict__ Wq,
     const uint8_t* __restrict__ Ws, uint8_t* __restrict__ Xq, uint8_t* __restrict__ Xs, uint32_t* __restrict__ state,
-    int M, int N, int K, void* __restrict__ Y, int64_t ldy, int vec_store, int rule, uint32_t expected_blocks,
+    int M, int N, int K, void* __restrict__ Y, int64_t ldy, int rule, uint32_t expected_blocks,
     uint32_t spin_limit) {
   __shared__ float red[kWaves][RB][16][64];
   __shared__ int barrier_ok;
@@ -249,7 +248,7 @@ __global__ __launch_bounds__(kWaves * 64) void layer_decode_kernel(
       if (j != (int)blockIdx.x) load_w_chunk<U>(w_first, Wq, Ws, (int64_t)j * KT + kt0, n_first, lane);
       accumulate_block<RB>(acc, w_first, Xq, Xs, Wq, Ws, KT, j, kt0, kt1, lane);
     }
-    reduce_store_block<RB, OUT_F32>(acc, red, j, M, N, Y, ldy, vec_store, lane, wave);
+    reduce_store_block<RB, OUT_F32>(acc, red, j, M, N, Y, ldy, lane, wave);
   }
 }
 
@@ -295,13 +294,12 @@ int skinny_row_blocks(int64_t M, int64_t N) {
 hipError_t launch_mxfp4_gemm_skinny(const void* Xq, const void* Xs, const void* Wq, const void* Ws, int64_t M,
                                     int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy, hipStream_t stream) {
   const int NB = (int)((N + 31) / 32);
-  const int vec = decode_vec_store(Y, N, ldy, out_f32);
   const int rb = skinny_row_blocks(M, N), groups = (int)((M + 32 * rb - 1) / (32 * rb));
   dim3 grid((unsigned)(NB < 4096 ? NB : 4096), (unsigned)groups), block(kWaves * 64);
 #define WUSH_SKINNY_LAUNCH(RB, F32)                                                                         \
   gemm_skinny_kernel<RB, F32><<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs,           \
                                                           (const uint8_t*)Wq, (const uint8_t*)Ws, (int)M,   \
-                                                          (int)N, (int)K, Y, ldy, vec)
+                                                          (int)N, (int)K, Y, ldy)
   if (rb == 1) {
     if (out_f32) WUSH_SKINNY_LAUNCH(1, true); else WUSH_SKINNY_LAUNCH(1, false);
   } else if (rb == 2) {
@@ -335,7 +333,6 @@ hipError_t launch_layer_decode(const void* X, int64_t M, int64_t K, int64_t ldx,
   uint8_t* Xs = ws + layer_decode_codes_bytes(K);
   uint32_t* state = reinterpret_cast<uint32_t*>(ws + layer_decode_state_offset(K));
   const int NB = (int)((N + 31) / 32);
-  const int vec = decode_vec_store(Y, N, ldy, out_f32);
   dim3 block(kWaves * 64);
 #define WUSH_DECODE_LAUNCH(RB, F32)                                                                          \
   {                                                                                                          \
@@ -352,7 +349,7 @@ hipError_t launch_layer_decode(const void* X, int64_t M, int64_t K, int64_t ldx,
     const uint32_t spin = test_timeout ? 16u : kSpinLimit;                                                   \
     layer_decode_kernel<RB, F32><<<dim3(g), block, 0, stream>>>(                                             \
         (const uint16_t*)X, ldx, (const uint16_t*)T, (const uint8_t*)Wq, (const uint8_t*)Ws, Xq, Xs, state,  \
-        (int)M, (int)N, (int)K, Y, ldy, vec, rule, expected, spin);                                          \
+        (int)M, (int)N, (int)K, Y, ldy, rule, expected, spin);                                          \
   }
   if (M <= 32) {
     if (out_f32) WUSH_DECODE_LAUNCH(1, true) else WUSH_DECODE_LAUNCH(1, false)

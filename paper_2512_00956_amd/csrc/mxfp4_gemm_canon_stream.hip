@@ -65,7 +65,7 @@ __device__ __forceinline__ v16f multiply_tile(v16f acc, const Tile& w, const Til
 template <bool OUT_F32>
 __global__ __launch_bounds__(kWaves * 64) void gemm_canon_stream_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const uint8_t* __restrict__ Wq,
-    const uint8_t* __restrict__ Ws, int M, int N, int K, void* __restrict__ Y, int64_t ldy, int vec_store) {
+    const uint8_t* __restrict__ Ws, int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
   constexpr int U = 4;                        // tiles in flight
   __shared__ float red[kWaves][1][16][64];
   const int lane = threadIdx.x & 63;
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_canon_stream_kernel(
     acc[0] = multiply_tile(acc[0], w, x);
   }
   skinny::reduce_store_block<1, OUT_F32>(acc, red, j, M - 32 * rb, N, static_cast<uint8_t*>(Y) + 32 * (int64_t)rb * ldy * (OUT_F32 ? 4 : 2),
-                                         ldy, vec_store, lane, wave);
+                                         ldy, lane, wave);
 }
 
 }  // namespace
@@ -110,8 +110,7 @@ hipError_t launch_mxfp4_gemm_canon_stream(const void* Xq, const void* Xs, const 
                                           int64_t K, int out_f32, void* Y, int64_t ldy, hipStream_t stream) {
   auto kernel = out_f32 ? gemm_canon_stream_kernel<true> : gemm_canon_stream_kernel<false>;
   kernel<<<dim3((unsigned)((N + 31) / 32), (unsigned)((M + 31) / 32)), dim3(kWaves * 64), 0, stream>>>(
-      (const uint8_t*)Xq, (const uint8_t*)Xs, (const uint8_t*)Wq, (const uint8_t*)Ws, (int)M, (int)N, (int)K, Y, ldy,
-      skinny::decode_vec_store(Y, N, ldy, out_f32));
+      (const uint8_t*)Xq, (const uint8_t*)Xs, (const uint8_t*)Wq, (const uint8_t*)Ws, (int)M, (int)N, (int)K, Y, ldy);
   return hipGetLastError();
 }
 

@@ -84,7 +84,7 @@ template <int RB, int CBW, int FMT, bool OUT_F32, bool TILED>
 __global__ __launch_bounds__(kWaves * 64) void w4_skinny_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const float* __restrict__ tsx,
     const uint8_t* __restrict__ Wq, const uint8_t* __restrict__ Ws, const float* __restrict__ tsw,
-    int M, int N, int K, void* __restrict__ Y, int64_t ldy, int vec_store) {
+    int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
   __shared__ float red[kWaves][RB][16][64];
   constexpr int U = Depth<RB>::U;
   const int lane = threadIdx.x & 63;
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(kWaves * 64) void w4_skinny_kernel(
 #pragma unroll
     for (int c = 0; c < CBW; ++c)
       if (g * CBW + c < NB)
-        skinny::reduce_store_block<RB, OUT_F32, FMT == kNvfp4>(acc[c], red, g * CBW + c, M, N, Y, ldy, vec_store, lane,
+        skinny::reduce_store_block<RB, OUT_F32, FMT == kNvfp4>(acc[c], red, g * CBW + c, M, N, Y, ldy, lane,
                                                                wave, scale);
   }
 }
@@ -190,7 +190,8 @@ __global__ __launch_bounds__(kWaves * 64) void w4_skinny_kernel(
 // Accumulator e of lane (r, h), row block rb: token 32 rb + r, output channel 32 j + 8 (e / 4) + 4 h + e % 4.
 template <int RB, bool OUT_F32>
 __device__ __forceinline__ void store_block(const v16f (&acc)[RB], int j, int M, int N, void* __restrict__ Y,
-                                            int64_t ldy, int vec_store, int r, int h, float scale) {
+                                            int64_t ldy, int r, int h, float scale) {
+  const bool whole = 32 * j + 32 <= N;          // the same in every lane of a wavefront
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const int row = 32 * rb + r;
@@ -198,32 +199,11 @@ __device__ __forceinline__ void store_block(const v16f (&acc)[RB], int j, int M,
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int col = 32 * j + 8 * q + 4 * h;
-      if (col >= N) continue;
+      if (!whole && col >= N) continue;
       float v[4];
 #pragma unroll
       for (int t = 0; t < 4; ++t) v[t] = acc[rb][4 * q + t] * scale;
-      if (OUT_F32) {
-        float* y = reinterpret_cast<float*>(Y) + (int64_t)row * ldy + col;
-        if (vec_store) {
-          *reinterpret_cast<v4f*>(y) = (v4f){v[0], v[1], v[2], v[3]};
-        } else {
-#pragma unroll
-          for (int t = 0; t < 4; ++t)
-            if (col + t < N) y[t] = v[t];
-        }
-      } else {
-        uint16_t* y = reinterpret_cast<uint16_t*>(Y) + (int64_t)row * ldy + col;
-        if (vec_store) {
-          v2u two;
-          two[0] = (uint32_t)f32_to_bf16_bits(v[0]) | ((uint32_t)f32_to_bf16_bits(v[1]) << 16);
-          two[1] = (uint32_t)f32_to_bf16_bits(v[2]) | ((uint32_t)f32_to_bf16_bits(v[3]) << 16);
-          *reinterpret_cast<v2u*>(y) = two;
-        } else {
-#pragma unroll
-          for (int t = 0; t < 4; ++t)
-            if (col + t < N) y[t] = f32_to_bf16_bits(v[t]);
-        }
-      }
+      skinny::store_quad<OUT_F32>(Y, ldy, row, col, N, whole, v);
     }
   }
 }
@@ -242,7 +222,7 @@ template <int RB, int CBW, int FMT, bool OUT_F32, bool TILED>
 __global__ __launch_bounds__(kWaves * 64, 2) void w4_shared_x_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const float* __restrict__ tsx,
     const uint8_t* __restrict__ Wq, const uint8_t* __restrict__ Ws, const float* __restrict__ tsw,
-    int M, int N, int K, void* __restrict__ Y, int64_t ldy, int vec_store) {
+    int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
   constexpr int kPairs = Chunk<RB>::kPairs;
   constexpr int U = kPairs / RB;            // K steps per chunk
   constexpr int kMine = kPairs / kWaves;    // pairs a wave converts per chunk
@@ -347,7 +327,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void w4_shared_x_kernel(
 #pragma unroll
     for (int c = 0; c < CBW; ++c) {
       const int j = (g * kWaves + wave) * CBW + c;
-      if (j < NB) store_block<RB, OUT_F32>(acc[c], j, M, N, Y, ldy, vec_store, r, h, scale);
+      if (j < NB) store_block<RB, OUT_F32>(acc[c], j, M, N, Y, ldy, r, h, scale);
     }
   }
 }
@@ -383,11 +363,10 @@ hipError_t launch_split_k(const void* Xq, const void* Xs, const float* tsx, cons
   const int NB = (int)((N + 31) / 32);
   const int groups = (NB + cbw - 1) / cbw;
   dim3 grid((unsigned)(groups < 4096 ? groups : 4096), (unsigned)((M + 32 * rb - 1) / (32 * rb))), block(kWaves * 64);
-  const int vec = skinny::decode_vec_store(Y, N, ldy, out_f32);
 #define WUSH_W4S_LAUNCH(RB, CBW, F32, TILED)                                                                          \
   w4_skinny_kernel<RB, CBW, FMT, F32, TILED><<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs, tsx, \
                                                                          (const uint8_t*)Wq, (const uint8_t*)Ws, tsw, \
-                                                                         (int)M, (int)N, (int)K, Y, ldy, vec)
+                                                                         (int)M, (int)N, (int)K, Y, ldy)
 #define WUSH_W4S_BY_OUT(RB, CBW)                                                                                      \
   {                                                                                                                   \
     if (tiled) { if (out_f32) WUSH_W4S_LAUNCH(RB, CBW, true, true); else WUSH_W4S_LAUNCH(RB, CBW, false, true); }     \
@@ -414,11 +393,10 @@ hipError_t launch_shared_x(const void* Xq, const void* Xs, const float* tsx, con
   const int NB = (int)((N + 31) / 32);
   const int groups = (NB + kWaves - 1) / kWaves;
   dim3 grid((unsigned)(groups < 4096 ? groups : 4096), (unsigned)((M + 127) / 128)), block(kWaves * 64);
-  const int vec = skinny::decode_vec_store(Y, N, ldy, out_f32);
   auto kernel = out_f32 ? (tiled ? w4_shared_x_kernel<4, 1, FMT, true, true> : w4_shared_x_kernel<4, 1, FMT, true, false>)
                         : (tiled ? w4_shared_x_kernel<4, 1, FMT, false, true> : w4_shared_x_kernel<4, 1, FMT, false, false>);
   kernel<<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs, tsx, (const uint8_t*)Wq, (const uint8_t*)Ws, tsw,
-                                     (int)M, (int)N, (int)K, Y, ldy, vec);
+                                     (int)M, (int)N, (int)K, Y, ldy);
   return hipGetLastError();
 }
 

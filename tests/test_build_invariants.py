@@ -202,3 +202,19 @@ def test_quantizers_do_not_spill_and_keep_three_waves_per_simd(src, pattern, cou
         if pattern in m.group(1) and "kernelILb1E" not in m.group(1):
             budget = 256 if "ELi2ELi2EE" in m.group(1) else 176
             assert int(m.group(2)) <= budget, (m.group(1), m.group(2))
+
+
+@pytest.mark.parametrize("src,pattern,count", [("layer_decode.hip", "gemm_skinny_kernel", 6),
+                                                ("mxfp4_gemm_canon_stream.hip", "gemm_canon_stream_kernel", 2),
+                                                ("w4_gemm_skinny.hip", "w4_(?:skinny|shared_x)_kernel", 40)])
+def test_streaming_kernels_store_four_outputs_at_a_time(src, pattern, count):
+    """The streaming GEMMs write a lane's four outputs in one store at any alignment of the rows: every site of it comes with
+    the three element stores of a row's last channels and no others (rows off the alignment stored element by
+    element would add a fourth)."""
+    parts = re.split(rf"^(_ZN4wush\S*{pattern}\S*):.*$", _compile(src), flags=re.M)
+    kernels = {parts[i]: parts[i + 1].split(".Lfunc_end")[0] for i in range(1, len(parts) - 1, 2)}
+    assert len(kernels) == count, list(kernels)
+    for name, body in kernels.items():
+        wide = len(re.findall(r"^\s*global_store_dwordx[24]\b", body, flags=re.M))
+        single = len(re.findall(r"^\s*global_store_(?:dword|short\w*)\s", body, flags=re.M))
+        assert wide > 0 and single <= 3 * wide, (name, wide, single)
