@@ -120,10 +120,13 @@ hipError_t launch_mxfp4_gemm(const void* Xq, const void* Xs, const void* Wq, con
     // Up to 1024 tokens the streaming kernel also takes the layers of so few output channels that it needs no more than one workgroup
     // per compute unit, where 128-row tiles leave most of them idle (us, tiles | streaming: 256 x 4096 -> 1024 8.7 | 5.0, 1024 x 4096 ->
     // 1024 10.2 | 9.3, 256 x 16384 -> 1024 24.3 | 10.2, 448 x 28672 -> 512 40 | 16, 256 x 14336 -> 4096 22.6 | 18.8, 256 x 4096 -> 4096
-    // 8.9 | 7.8; with more workgroups 448 x 4096 -> 4096 10.1 | 12.2, 448 x 14336 -> 4096 23.4 | 29).
+    // 8.9 | 7.8; with more workgroups 448 x 4096 -> 4096 10.1 | 12.2, 448 x 14336 -> 4096 23.4 | 29).  One or two row blocks per
+    // workgroup take 0.3 to 0.9 of the tiles' time at any K from 256 to 28672; four 0.75 to 1.02 from K = 512, but 0.9 to 1.09 with the
+    // one K tile of 256 (512 x 256 -> 1984 3.85 | 4.12), and 1.3 to 1.6 where the grid's spare workgroups start a second round.
     if (M > 128 && M <= 1024 && debug_option(kDbgGemmTile) < 0) {
       const int rb = skinny_row_blocks(M, N);
-      skinny = ((M + 32 * rb - 1) / (32 * rb)) * ((N + 31) / 32) <= device_cu_count();
+      const int64_t groups = (M + 32 * rb - 1) / (32 * rb), blocks = rb < 4 ? (N + 31) / 32 : skinny_grid_width(N);
+      skinny = groups * blocks <= device_cu_count() && (rb < 4 || K > 256);
     }
     if (M <= 1024 && debug_option(kDbgGemmSkinny) >= 0) skinny = debug_option(kDbgGemmSkinny) == 1;   // tests: force either kernel
     if (skinny) return launch_mxfp4_gemm_skinny(Xq, Xs, Wq, Ws, M, N, K, out_f32, Y, ldy, stream);

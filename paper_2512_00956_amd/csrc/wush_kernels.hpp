@@ -110,6 +110,7 @@ hipError_t launch_gptq_prep(const void* W, int64_t N, int64_t K, int64_t ldw, co
 
 // Decode-sized paths (GEMM: M <= 1024; fused layer: M <= 64; fragment-order operands).
 int skinny_row_blocks(int64_t M, int64_t N);
+int64_t skinny_grid_width(int64_t N);
 hipError_t launch_mxfp4_gemm_skinny(const void* Xq, const void* Xs, const void* Wq, const void* Ws, int64_t M,
                                     int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy, hipStream_t stream);
 // workspace layout: Xq for 64 tokens | Xs | barrier words (generation, error flag, arrival and release slots).

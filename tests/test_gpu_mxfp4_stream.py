@@ -21,8 +21,9 @@ def P():
 
 
 # (tokens, K, output channels, layout, the default streams), 256 compute units
-SIZES = [(129, 1280, 70, 1, True), (256, 1024, 1024, 1, True), (257, 1024, 1024, 1, True), (513, 512, 1632, 1, True), (513, 512, 1664, 1, False),
+SIZES = [(129, 1280, 70, 1, True), (256, 1024, 1024, 1, True), (257, 1024, 1024, 1, True), (513, 512, 1536, 1, True), (513, 512, 1632, 1, False),
          (1000, 1024, 260, 1, True), (1024, 1024, 1024, 1, True), (1025, 1024, 70, 1, False),
+         (449, 512, 1984, 1, True), (768, 1024, 1344, 1, False),
          (1, 1056, 1, 0, True), (33, 544, 130, 0, True), (63, 800, 4096, 0, True), (65, 1024, 4096, 0, False),
          (256, 1024, 1024, 0, True), (257, 1024, 1024, 0, False), (300, 1504, 70, 0, True)]
 
