@@ -262,6 +262,7 @@ __global__ __launch_bounds__(256) void gemm_canon_kernel(
   using Out = RowStore<OUT_F32, CB>;
   static_assert(4 * Out::kBuf <= S::kLds, "transpose buffers");
   uint8_t* buf = smem + wave * Out::kBuf;
+  const bool stream = Out::streams(Y, ldy, M, N, K);
 #pragma unroll
   for (int i = 0; i < RB; ++i) {
     __builtin_amdgcn_sched_barrier(0);
@@ -269,7 +270,7 @@ __global__ __launch_bounds__(256) void gemm_canon_kernel(
 #pragma unroll
     for (int j = 0; j < CB; ++j) Out::put(buf, acc[i][j], j, lane);
     wave_lds_sync();
-    Out::store(buf, Y, ldy, m0 + (wm * RB + i) * 32, n0 + wn * CB * 32, M, N, lane);
+    Out::store(buf, Y, ldy, m0 + (wm * RB + i) * 32, n0 + wn * CB * 32, M, N, lane, stream);
   }
 }
 

@@ -399,6 +399,7 @@ __global__ __launch_bounds__(256) void gemm_frag_kernel(
   constexpr int kBufs = 4 * 2 * Out::kBuf <= lds_bytes(RB) ? 2 : 1;
   static_assert(4 * kBufs * Out::kBuf <= lds_bytes(RB), "transpose buffers must fit in the ring");
   uint8_t* area = smem + wave * (kBufs * Out::kBuf);
+  const bool stream = Out::streams(Y, ldy, M, N, K);
 #pragma unroll
   for (int i = 0; i < RB; ++i) {
     __builtin_amdgcn_sched_barrier(0);       // one row block at a time: keeps the epilogue out of scratch
@@ -407,7 +408,7 @@ __global__ __launch_bounds__(256) void gemm_frag_kernel(
 #pragma unroll
     for (int j = 0; j < CB; ++j) Out::put(buf, acc[i][j], j, lane);
     wave_lds_sync();
-    Out::store(buf, Y, ldy, m0 + 32 * i, n0 + 32 * CB * wave, M, N, lane);
+    Out::store(buf, Y, ldy, m0 + 32 * i, n0 + 32 * CB * wave, M, N, lane, stream);
   }
 }
 

@@ -210,9 +210,10 @@ __device__ __forceinline__ void static_for(F&& f) {
 // 16384 40.9 | 36.4; INT4 2048 x 4096 -> 6144 101.8 | 98.0).
 template <bool OUT_F32, int CB>
 __device__ __forceinline__ void store_tile(v16f (&acc)[4][CB], float scale, uint8_t* lds, void* __restrict__ Y, int64_t ldy, int row0,
-                                           int col0, int M, int N, int lane, int wave) {
+                                           int col0, int M, int N, int K, int lane, int wave) {
   using Out = RowStore<OUT_F32, CB>;
   uint8_t* buf = lds + wave * Out::kBuf;
+  const bool stream = Out::streams(Y, ldy, M, N, K);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     __builtin_amdgcn_sched_barrier(0);   // one row block at a time: the accumulators leave their registers block by block
@@ -224,7 +225,7 @@ __device__ __forceinline__ void store_tile(v16f (&acc)[4][CB], float scale, uint
       Out::put(buf, acc[i][j], j, lane);
     }
     wave_lds_sync();
-    Out::store(buf, Y, ldy, row0 + 32 * i, col0, M, N, lane);
+    Out::store(buf, Y, ldy, row0 + 32 * i, col0, M, N, lane, stream);
   }
 }
 // LDS of a kernel whose stages take `stages` bytes: they are reused for the outputs
@@ -362,7 +363,7 @@ __global__ __launch_bounds__(256) void w4_f16_gemm_kernel(
 
   const float scale = FMT == kNvfp4 ? *tsx * *tsw : 1.0f;   // INT4 has no tensor scales (null pointers)
   __syncthreads();   // the stages become the transpose buffers
-  store_tile<OUT_F32, CB>(acc, scale, reinterpret_cast<uint8_t*>(lds), Yv, ldy, m0 + wm * 128, n0 + wn * (32 * CB), M, N, lane, wave);
+  store_tile<OUT_F32, CB>(acc, scale, reinterpret_cast<uint8_t*>(lds), Yv, ldy, m0 + wm * 128, n0 + wn * (32 * CB), M, N, K, lane, wave);
 }
 
 // ---------------------------------------------------------------------------
@@ -590,7 +591,7 @@ __global__ __launch_bounds__(256) void w4_wreg_gemm_kernel(
   const int ewave = __builtin_amdgcn_readfirstlane(te >> 6);
   __syncthreads();   // the stages become the transpose buffers
   store_tile<OUT_F32, CB>(acc, scale, reinterpret_cast<uint8_t*>(lds), Yv, ldy, m0 + (ewave >> 1) * 128, n0 + (ewave & 1) * (32 * CB), M, N,
-                          te & 63, ewave);
+                          K, te & 63, ewave);
 }
 
 template <bool OUT_F32, int CB, int FMT>

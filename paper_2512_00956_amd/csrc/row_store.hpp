@@ -40,18 +40,27 @@ struct RowStore {
     }
   }
 
-  // The buffer's 32 rows, 32 CB columns to rows row0 ... and columns col0 ... of Y.  Whole blocks of rows at multiples of 64 bytes by
-  // streaming stores: the output is not read again by the kernel, and lines that leave the L2 as they are written shorten the write-back
-  // at its end.  Others by plain ones: chunks that straddle lines are put together in the L2 (us, whole call, element by
-  // element | streaming | plain: 2439 x 3328 -> 12521 BF16 131 | 68 | 64, FP32 142 | 80 | 74; 402 x 768 -> 31143 53.8 | 20.3 |
-  // 17.7; 3000 x 1280 -> 10081 - | 50.2 | 35.2, 10080 - | 32.8 | 33.6, 2439 x 3328 -> 12520 73 | 71 | 68; 2048 x 4096 -> 6144 FP32 57.7 | 33.9 | -).  FP32 outputs of 4 to 16 MiB stream at any
-  // alignment: plain, they are mostly still in the L2s when the kernel ends (777 x 1376 -> 3001 14.1 | 14.6, 1214 x 14368 -> 1620 58.6 | 60.4; smaller
-  // and larger ones 3 to 16 % slower streaming).
+  // Whether the outputs go out as streaming stores (the same in every lane).  They are not read again by the kernel, and lines that leave the
+  // L2 as they are written shorten the write-back at its end; but chunks that straddle cache lines are better put together in the L2.
+  // Streaming against plain stores, whole call, both MXFP4 layouts, K = 256 .. 16384, rows of 1000 to 20008 outputs, 2 to 100 MiB of them:
+  //   * rows at multiples of 64 bytes: no line is written in parts, streaming (plain, 4096 x 14336 -> 4096 118.7 -> 126.7 us).
+  //   * long K: the products hide the stores, and the L2 is better left to the operands.  Rows at multiples of 16 bytes, K = 4096: -24 .. +10 %
+  //     (2079 -> 10088 56.7 | 51.3 us, 4048 x 10496 -> 2416 63.1 | 58.7), K = 3072: -24 .. +11 %, K <= 1024: up to +119 %.  Other rows,
+  //     K = 8192: -18 .. +10 %, K = 4096: -19 .. +12 %.
+  //   * shorter K, FP32 outputs of 4 to 16 MiB: 2 MiB -3 .. +16 %, 4 MiB -8 .. +5, 8 MiB -10 .. 0, 12 MiB -11 .. +3, 16 MiB
+  //     -14 .. +8, 20 MiB -11 .. +19, 28 MiB -21 .. +57 (777 x 1376 -> 3001 10.4 | 10.8 plain).  No such range for BF16: 6 MiB -8 .. +7, 8 MiB
+  //     -9 .. +5, 12 MiB -11 .. +24, 28 MiB -12 .. +76.
+  // NVFP4 and INT4 alike, with smaller differences: K = 4096 -7 .. +2 %, FP32 below it 12 MiB -13 .. -2, 24 MiB -13 .. +14.
+  static __device__ __forceinline__ bool streams(const void* Y, int64_t ldy, int M, int N, int K) {
+    const int64_t start = ldy * kElem | (int64_t)(uintptr_t)Y;   // alignment of every row
+    const int64_t bytes = (int64_t)M * N * kElem;
+    return (start & 63) == 0 || K >= ((start & 15) == 0 ? 4096 : 8192) || (OUT_F32 && bytes > (4 << 20) && bytes <= (16 << 20));
+  }
+
+  // The buffer's 32 rows, 32 CB columns to rows row0 ... and columns col0 ... of Y.
   static __device__ __forceinline__ void store(const uint8_t* buf, void* __restrict__ Y, int64_t ldy, int row0, int col0, int M,
-                                               int N, int lane) {
-    const int64_t bytes = (int64_t)M * ldy * kElem;
-    const bool stream = ((ldy * kElem | (int64_t)(uintptr_t)Y) & 63) == 0 || (OUT_F32 && bytes > (4 << 20) && bytes <= (16 << 20));
-    const bool whole = row0 + 32 <= M && col0 + 32 * CB <= N;      // both the same in every lane
+                                               int N, int lane, bool stream) {
+    const bool whole = row0 + 32 <= M && col0 + 32 * CB <= N;      // the same in every lane
     auto chunk_at = [&](int p, int& row, int& col) {               // 32 kChunks chunks, 64 per round
       const int idx = 64 * p + lane, row_l = idx / kChunks, chunk = idx % kChunks;
       row = row0 + row_l;

@@ -1,7 +1,8 @@
 """Outputs of the NVFP4 / INT4 tile kernels at every alignment of a row (row strides and first columns off 16 bytes, a last
 chunk of 1..7 columns, rows past the end), for every tile width, both layouts, with W in registers (K a multiple of 128) and staged:
 FP32 output against the FP64 product of the dequantized codes (FP32 accumulation of exact products, K <= 256: 1e-6 of the
-norm), BF16 output the FP32 output rounded to nearest even, bit for bit, and nothing outside the M x N outputs written."""
+norm; K = 8192, whose rows leave in streaming stores: 2 sqrt(K) 2^-24), BF16 output the FP32 output rounded to nearest even, bit
+for bit, and nothing outside the M x N outputs written."""
 import numpy as np
 import pytest
 
@@ -25,7 +26,7 @@ def P():
 @pytest.mark.parametrize("layout", [0, 1])
 @pytest.mark.parametrize("fmt", ["nvfp4", "int4"])
 @pytest.mark.parametrize("width", [2, 3, 4])
-@pytest.mark.parametrize("M,K,N", [(129, 128, 1), (140, 192, 259), (257, 256, 390), (290, 64, 520)])
+@pytest.mark.parametrize("M,K,N", [(129, 128, 1), (140, 192, 259), (257, 256, 390), (290, 64, 520), (161, 8192, 259)])
 def test_row_alignments(P, M, K, N, width, fmt, layout):
     import torch
     rng = np.random.default_rng(M + K + N)
@@ -59,7 +60,7 @@ def test_row_alignments(P, M, K, N, width, fmt, layout):
                 y[out] = Y.cpu()
                 Y[:] = 7.0
                 assert (whole == 7.0).all(), (out, pad, first)
-            assert O.rel_fro(y[1].double().numpy(), ref) <= 1e-6, (pad, first)
+            assert O.rel_fro(y[1].double().numpy(), ref) <= (1e-6 if K <= 256 else 2 * K ** 0.5 * 2.0 ** -24), (pad, first)
             assert torch.equal(y[0], y[1].bfloat16()), (pad, first)
     finally:
         P.wush_debug_set(P.WUSH_DEBUG_W4_SKINNY, -1)
