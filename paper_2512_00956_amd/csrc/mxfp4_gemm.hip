@@ -68,24 +68,38 @@ __global__ __launch_bounds__(256) void gemm_simple_kernel(
   }
 }
 
-// Canonical layout: whether K is so short that the one-wave-per-tile kernel is the faster one.  The pipelined kernel
-// (mxfp4_gemm_canon.hip) spends a fixed part per tile on its prologue and on turning the outputs in LDS; with one or two steps of K
-// nothing hides that.  us, pipelined | one wave per tile:
-//   K <= 128: 2048 x 96 -> 32768 FP32 88 | 47, BF16 56 | 33, 2048 x 128 -> 4096 7.0 | 7.1
-//   K < 256:  2048 x 192 -> 32768 FP32 89 | 60; small BF16 outputs are up to 1.15 times faster pipelined; rows without 16-byte alignment
-//             1.1 to 1.5 times slower at any size
-//   K < 512, a partial second step: up to 16 tokens 1.0 to 1.25 times slower pipelined (288 -> 32768), at 200 and more tokens faster (352 ->
-//             8192 0.80); rows without 16-byte alignment 1.02 to 1.4 times slower up to some 4 M outputs, at 2048 x 416 -> 8192 0.90
-//   whole steps (256, 512): pipelined, 0.3 to 0.95 of the time
-// (Measured before the pipelined kernel's stores and scale loads took rows of any alignment; since then, one wave | pipelined: 2048 x 416 ->
-// 8191 31.6 | 18.7, 300 x 480 -> 1001 5.7 | 5.6, 1000 x 416 -> 3001 FP32 10.7 | 8.1, 2048 x 192 -> 32768 FP32 67.6 | 59.3, 500 x 160 -> 3001
-// FP32 5.6 | 5.9, 2048 x 96 -> 32768 FP32 55.0 | 55.6.)
-bool short_k(int64_t M, int64_t N, int64_t K, int vec_store) {
-  if (M * N >= (int64_t)1 << 35) return false;   // its grid of 32 x 32 tiles
-  if (K <= 128) return true;
-  if (K < 256) return !vec_store || M * N >= (int64_t)1 << 24;
-  if (K % 256 != 0 && K < 512) return vec_store ? M <= 16 : M * N <= (int64_t)1 << 22;
-  return false;
+// Canonical layout: whether K is so short that the one-wave-per-tile kernel is the faster one.  The others spend a fixed part on their
+// prologue and on turning the outputs in LDS, which one or two steps of K do not hide; what that costs depends on the outputs'
+// width, on their rows' alignment and, once they no longer fit the L2s, on their number.  Ratio of times, one wave per tile : the other kernel
+// (graph replays, 1 to 8192 tokens, 512 to 65536 channels), on either side of the lines:
+//   Against the streaming kernel: one token, K <= 128 0.91 to 1.03, two 0.95 to 1.01, K = 288 to 480 1.16 to 1.4; from four tokens 0.92 to 1.8
+//   (16 x 480 -> 8192 4.5 us : 3.2).
+//   Against the pipelined kernel ("aligned": rows at multiples of 16 bytes):
+//   * BF16, aligned: up to 16 tokens, K <= 128 0.78 to 0.99.  More: K = 32 and 64 0.82 to 1.19; 96 and 128 0.89 to 1.15, from 2^24 outputs on
+//     1.06 to 1.36 (2048 x 96 -> 8192 12.9 us : 10.1).  K = 160 to 224 0.85 to 1.62 (2048 x 192 -> 32768 54.7 : 43.7).
+//   * FP32, aligned: K <= 128 0.58 to 1.08.  K = 160 to 224, from 2^24 outputs on 0.73 to 1.29 (2048 x 192 -> 32768 67 : 86), fewer 0.80 to 1.25.
+//   * Other rows: K <= 64 0.58 to 1.23; 96 and 128 0.62 to 1.16, from 3 x 2^23 outputs on 1.01 to 1.30.  K = 160 to 224, FP32 0.64 to 1.17, from
+//     2^24 on 0.92 to 1.36; BF16 0.65 to 1.26, from 2^23 on 0.97 to 1.74, K = 224 beyond 128 tokens 0.96 to 1.74.
+//   * A partial second step of K: aligned, up to 16 tokens 0.79 to 1.20, more 0.93 to 2.4.  Other rows, up to 64 tokens and 2^22 outputs
+//     0.62 to 1.18; more tokens, up to 2^21 outputs, BF16 K = 288 0.94 to 1.13, FP32 K = 288 and 352 0.84 to 1.07; beyond these 0.96 to 2.3
+//     (1000 x 416 -> 3001 BF16 9.7 us : 6.6, FP32 10.1 : 7.9).
+//   * Whole steps: 1.05 to 4.2 beyond 16 tokens, 0.73 to 1.55 up to there.
+bool short_k(int64_t M, int64_t N, int64_t K, int out_f32, int vec_store) {
+  if (canon_streams(M, N)) return M <= 2 && K <= 128;
+  const int64_t outputs = M * N;
+  if (outputs >= (int64_t)1 << 35) return false;   // its grid of 32 x 32 tiles
+  const bool many = outputs >= (int64_t)1 << 24;
+  if (K <= 128) {
+    if (vec_store && !out_f32) return M <= 16 || K <= 64 || !many;
+    return vec_store || K <= 64 || outputs < (int64_t)3 << 23;
+  }
+  if (K < 256) {
+    if (vec_store) return out_f32 && many;
+    return out_f32 ? !many : outputs < (int64_t)1 << 23 && (K < 224 || M <= 128);
+  }
+  if (K % 256 == 0 || K >= 512) return false;
+  if (vec_store) return M <= 16;
+  return M <= 64 ? outputs <= (int64_t)1 << 22 : outputs <= (int64_t)1 << 21 && K < (out_f32 ? 416 : 352);
 }
 
 }  // namespace
@@ -132,7 +146,7 @@ hipError_t launch_mxfp4_gemm(const void* Xq, const void* Xs, const void* Wq, con
     if (skinny) return launch_mxfp4_gemm_skinny(Xq, Xs, Wq, Ws, M, N, K, out_f32, Y, ldy, stream);
     return launch_mxfp4_gemm_frag(Xq, Xs, Wq, Ws, M, N, K, out_f32, Y, ldy, stream);
   }
-  bool simple = short_k(M, N, K, canon_vec_store(Y, ldy, out_f32));
+  bool simple = short_k(M, N, K, out_f32, canon_vec_store(Y, ldy, out_f32));
   if (debug_option(kDbgGemmTile) >= 0) simple = false;                                       // tests: a tile shape of the other kernel
   if (const int forced = debug_option(kDbgGemmSimple); forced >= 0) simple = forced == 1;    // tests: either kernel
   if (!simple && canon_streams(M, N) && debug_option(kDbgGemmTile) < 0 && debug_option(kDbgGemmSkinny) != 0)
