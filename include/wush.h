@@ -473,7 +473,8 @@ wush_status wush_unpack_tiled(const void* q_tiled, const void* s_tiled, int64_t 
  *   WUSH_DEBUG_W4_WIDTH             wush_linear_nvfp4 / _int4: tile width 2..4 (x 64 output channels)
  *   WUSH_DEBUG_W4_SKINNY            wush_linear_nvfp4 / _int4 up to 4096 tokens: 0 = 256-row tiles; weight-streaming kernel with
  *                                   1 = K split over a workgroup's waves, 2 = activations shared through LDS (tiled layout: from
- *                                   65 tokens, with fewer it is 1)
+ *                                   65 tokens, with fewer it is 1), 3..6 = K split with 1 x 1, 1 x 2, 2 x 1, 2 x 2 blocks of 32
+ *                                   tokens and 32 channels per workgroup
  *   WUSH_DEBUG_DECODE_FUSED         wush_layer_decode: 1 = one launch with a grid-wide barrier
  *   WUSH_DEBUG_DECODE_TEST_TIMEOUT  wush_layer_decode: 1 = the barrier wait gives up at once (error-path test)
  * Returns WUSH_ERR_FMT for an unknown option, WUSH_ERR_SHAPE for a value outside -1 .. 1023.

@@ -441,10 +441,14 @@ constexpr StreamCost kStreamCost[2][2][5] = {
 // estimate, if that is below the estimate for the 256-row tiles (tile_us, which the caller has): those leave compute units idle until
 // tokens / 256 x channels / 128 reaches their number (us, tiles | streaming: NVFP4 224 x 16384 -> 1024 182 | 20, 320 x 14336 ->
 // 4096 160 | 54, 1024 x 4096 -> 4096 52 | 40, 2048 x 4096 -> 4096 61 | 71; canonical INT4 16 x 8192 -> 28672 134 | 60).
+// With every schedule forced on eleven layers from 704 -> 512 to 8192 -> 28672, 8 to 4096 tokens, the choice is within 7 % of the fastest; the
+// canonical INT4 costs, taken from NVFP4's, hold as well as those.  On 640 drawn layers of K from 64 on, 25 lose 8 % or more, 13 of them
+// with K <= 192, where a wave's K range is a step or none.
 W4StreamPlan w4_stream_plan(int fmt, int64_t M, int64_t N, int64_t K, int tiled, double tile_us) {
   const int forced = debug_option(kDbgW4Skinny);
   W4StreamPlan plan;
   if (forced == 0 || M > 4096) return plan;          // beyond it the tiles have enough rows; keeps blockIdx.y small
+  if (forced >= 3 && forced <= 6) return {true, false, 1 + (forced - 3) / 2, 1 + (forced - 3) % 2};   // tests: the blocks of the K split
   if (tiled && M <= 128) {
     plan.streams = true;
     plan.shared_x = M > 64 && (forced == 2 || (forced != 1 && shared_x_pays(fmt, N)));

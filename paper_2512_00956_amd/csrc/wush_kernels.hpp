@@ -21,7 +21,7 @@ enum DebugOption {
   kDbgGemmSimple = 2,        // canonical layout: 1 = the one-wave-per-tile kernel
   kDbgW4Width = 3,           // NVFP4 / INT4 tiled GEMM: tile width 2..4 (x 64 output channels)
   kDbgW4Skinny = 4,          // NVFP4 / INT4 GEMM, up to 4096 tokens: 0 = 256-row tiles, 1, 2 = weight-streaming kernel (K split,
-                             // shared X)
+                             // shared X), 3..6 = K split with 1 x 1, 1 x 2, 2 x 1, 2 x 2 blocks of tokens and channels
   kDbgDecodeFused = 5,       // wush_layer_decode: 1 = single launch with a grid-wide barrier
   kDbgDecodeTestTimeout = 6, // wush_layer_decode: 1 = the barrier wait gives up at once (error-path test)
   kDbgCount
@@ -84,7 +84,8 @@ hipError_t launch_build_transforms(const void* W, int64_t N, int64_t ldw, const 
                                    int64_t K, double lambda, int block, void* T_out, double* T_f64, void* workspace,
                                    hipStream_t stream);   // block = 32, or 16 for the NVFP4 variant
 
-// Row-major operands, any K % 32 == 0.  canon_vec_store: whether every row of Y takes 16-byte stores.
+// Row-major operands, any K % 32 == 0.  canon_vec_store: whether every row of Y starts at a multiple
+// of 16 bytes (stores take any start; lines and estimates of time depend on it).
 inline int canon_vec_store(const void* Y, int64_t ldy, int out_f32) {
   return ldy % (out_f32 ? 4 : 8) == 0 && (reinterpret_cast<uintptr_t>(Y) & 15) == 0;
 }

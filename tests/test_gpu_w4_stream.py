@@ -1,6 +1,6 @@
 """NVFP4 / INT4 layers the weight-streaming kernel takes beyond 128 tokens and in the canonical layout: token counts around its row
-blocks, a last block of channels and of tokens that is not whole, K ranges shorter than a workgroup's waves, both schedules and the
-default, long K, every output against the FP64 product of the dequantized codes (FP32 accumulation of exact FP16
+blocks, a last block of channels and of tokens that is not whole, K ranges shorter than a workgroup's waves, both schedules, every number of
+blocks per workgroup and the default, long K, every output against the FP64 product of the dequantized codes (FP32 accumulation of exact FP16
 products, chains of at most 2048 of them: 1e-5 of the norm) and nothing past row M written.  The default's bits say which kernel ran."""
 import numpy as np
 import pytest
@@ -22,10 +22,11 @@ def P():
     return P
 
 
-# (tokens, K, output channels, layout, the default streams)
-SIZES = [(129, 1088, 70, 1, True), (160, 64, 512, 1, True), (300, 512, 130, 1, True), (321, 256, 4100, 1, True),
-         (1, 64, 1, 0, True), (1, 1088, 70, 0, True), (31, 512, 2048, 0, True), (33, 192, 8200, 0, True), (100, 256, 130, 0, True),
-         (130, 1024, 300, 0, True), (1, 8128, 70, 1, True), (33, 8192, 70, 1, True), (70, 8256, 33, 1, True), (2048, 64, 8192, 1, False), (2048, 64, 8192, 0, False)]
+# (tokens, K, output channels, layout, the default streams; None: K too short to tell by the bits)
+SIZES = [(129, 1088, 70, 1, True), (160, 64, 512, 1, None), (300, 512, 130, 1, True), (321, 256, 4100, 1, True),
+         (1, 64, 1, 0, None), (1, 1088, 70, 0, True), (31, 512, 2048, 0, True), (33, 192, 8200, 0, None), (100, 256, 130, 0, True),
+         (16, 512, 8224, 0, True), (48, 512, 4128, 0, True), (33, 512, 8200, 0, True), (300, 512, 1030, 0, True),
+         (130, 1024, 300, 0, True), (1, 8128, 70, 1, True), (33, 8192, 70, 1, True), (70, 8256, 33, 1, True), (2048, 256, 8192, 1, False), (2048, 256, 8192, 0, False)]
 
 
 @pytest.mark.parametrize("fmt", ["nvfp4", "int4"])
@@ -49,7 +50,7 @@ def test_streaming(P, M, K, N, layout, streams, fmt):
     else:
         xt, wt = ([torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in p] for p in ((X, xs), (W, ws)))
     y = {}
-    for forced in (-1, 0, 1, 2):
+    for forced in range(-1, 7):
         Y = torch.full((M + 1, N), 7.0, dtype=torch.float32, device="cuda")
         P.wush_debug_set(P.WUSH_DEBUG_W4_SKINNY, forced)
         try:
@@ -62,8 +63,8 @@ def test_streaming(P, M, K, N, layout, streams, fmt):
         y[forced] = Y[:M].cpu()
         assert (Y[M:] == 7.0).all()
         assert O.rel_fro(y[forced].double().numpy()[rows], ref) <= 1e-5, forced
+    for blocks in (3, 4, 5, 6):                 # tokens and channels per workgroup: the same sums
+        assert torch.equal(y[blocks], y[1]), blocks
     if K >= 256:                                # the kernels add K in different orders
         assert not torch.equal(y[0], y[1])
         assert torch.equal(y[-1], y[0]) != streams
-    elif not streams:
-        assert torch.equal(y[-1], y[0])
