@@ -209,14 +209,14 @@ wush_status wush_prepare_weight_gptq_status(const void* workspace, int64_t N, in
  *   Wq, Ws   in   u8 [N][K/2], u8 [N][K/32]
  *   Y        out  [M][ldy], bf16 (fmt.out_dtype == WUSH_OUT_BF16, rounded to
  *                 nearest even from the FP32 accumulator) or f32
- * ldy >= N (elements); Y aligned to its element size; any such Y is accepted.  Stores are wide where
- * the rows allow it: canonical layout, 16 bytes where Y is 16-byte aligned and ldy keeps it (with K
- * below 512 some sizes are stored element by element); tiled layout, BF16, 16 bytes where also
- * N % 8 == 0, FP32 element by element; weight-streaming kernel, four channels (8 bytes BF16, 16
- * bytes FP32) where N % 4 == 0, ldy % 4 == 0 and Y is aligned to that.
- * In the tiled layout M <= 32, and M <= 128 where a timing model puts it first, takes the
- * weight-streaming kernel (a workgroup per 32 output channels, beyond 32 tokens also per 32 or 64 tokens
- * while compute units would idle) instead of output tiles.
+ * ldy >= N (elements); Y aligned to its element size; any such Y is accepted, and stores are wide
+ * whatever its rows' alignment: 16 bytes from output tiles, four channels (8 bytes BF16, 16 bytes
+ * FP32) from the weight-streaming kernels, the last channels of a row one by one.  (Canonical layout,
+ * K below 512: the kernel with one wavefront per 32 x 32 outputs, which some sizes take, stores element by element.)
+ * Weight-streaming kernels instead of output tiles (a workgroup per 32 output channels and, beyond 32
+ * tokens, per 32, 64 or 128 tokens while compute units would idle): tiled layout, M <= 32, M <= 128 where
+ * a timing model puts it first, and M <= 1024 where the layer has no more such blocks than compute
+ * units; canonical layout, where its blocks of 32 x 32 outputs are no more than those.
  */
 wush_status wush_linear(const void* Xq, const void* Xs, const void* Wq, const void* Ws,
                         int64_t M, int64_t N, int64_t K, wush_fmt fmt,

@@ -184,7 +184,7 @@ __device__ __forceinline__ bool reverse_factor_group(EntryFn entry, StoreUFn sto
 //     that a wavefront's 60 instructions serve eight pairs instead of four.  One wavefront for all (four rows per lane) is slower: it
 //     is the issue of instructions that bounds that.
 // (x1, y1) is the own pair of a lane's half, (x2, y2) the other half's; the second round of a trip pairs x1 with y2.
-// 32 x 32 Gaussian blocks: 170k cycles for the whole iteration (one wavefront 194k); c2 layer's blocks (128, with moments and factors) 104 -> 83
+// 32 x 32 Gaussian blocks: 170k cycles for the whole iteration of 8 or 9 sweeps, some 650 a round with the sweep's norms (one wavefront 194k); c2 layer's blocks (128, with moments and factors) 104 -> 83
 // us, the GPTQ chain's step 72 -> 61.
 template <int D>
 __device__ __forceinline__ void jacobi_group(double (*A)[D + 2], double* norm2, int* again) {
@@ -341,7 +341,7 @@ __device__ __forceinline__ void jacobi_group(double (*A)[D + 2], double* norm2, 
 // to the right singular vectors leaves little for the sweeps to do.  MODE 1 computes such a V0 in place of T (into
 // V_out; the identity where the moments give none) and leaves the status alone.
 //
-// A block is one chain of dependent steps (2 x D columns of the factors, 6 to 8 sweeps of D - 1 Jacobi
+// A block is one chain of dependent steps (2 x D columns of the factors, 6 to 9 sweeps of D - 1 Jacobi
 // rounds), so what counts is the latency of a step, and the threads are there to shorten it: the factors are taken column by
 // column out of registers with one barrier per column, the products are spread over the whole workgroup, and the Jacobi
 // rounds are jacobi_group's.
