@@ -51,7 +51,7 @@ struct RowStore {
   //     -14 .. +8, 20 MiB -11 .. +19, 28 MiB -21 .. +57 (777 x 1376 -> 3001 10.4 | 10.8 plain).  No such range for BF16: 6 MiB -8 .. +7, 8 MiB
   //     -9 .. +5, 12 MiB -11 .. +24, 28 MiB -12 .. +76.
   // NVFP4 and INT4 alike, with smaller differences: K = 4096 -7 .. +2 %, FP32 below it 12 MiB -13 .. -2, 24 MiB -13 .. +14.
-  static __device__ __forceinline__ bool streams(const void* Y, int64_t ldy, int M, int N, int K) {
+  static __host__ __device__ __forceinline__ bool streams(const void* Y, int64_t ldy, int M, int N, int K) {
     const int64_t start = ldy * kElem | (int64_t)(uintptr_t)Y;   // alignment of every row
     const int64_t bytes = (int64_t)M * N * kElem;
     return (start & 63) == 0 || K >= ((start & 15) == 0 ? 4096 : 8192) || (OUT_F32 && bytes > (4 << 20) && bytes <= (16 << 20));
