@@ -27,8 +27,6 @@ namespace {
 
 constexpr int kRowsPerStep = 128;
 
-typedef double v4d __attribute__((ext_vector_type(4)));
-
 // Row of the 16 x 16 result block that accumulator element v of a lane holds (v_mfma_f64_16x16x4_f64;
 // its column is lane % 16).  Checked by the parity tests of the transforms: the other candidate,
 // 4 (lane / 16) + v, gives moments that are not positive definite.

@@ -58,6 +58,7 @@ __device__ __forceinline__ double readlane_f64(double x, int lane) {
 }
 
 typedef double v2d __attribute__((ext_vector_type(2)));
+typedef double v4d __attribute__((ext_vector_type(4)));
 
 // Largest of the keys of the D lanes that hold the rows of a block (the upper lanes repeat them), in every lane.
 template <int D>
@@ -171,8 +172,8 @@ __device__ __forceinline__ bool reverse_factor_group(EntryFn entry, StoreUFn sto
   return good;
 }
 
-// Columns of A (A[column][row], D = 32 or 16) turned by right rotations until they are orthogonal, A V = U S: one-sided Jacobi by the
-// first 4 D of a workgroup's 8 D threads (all of them call it: the workgroup barrier is everybody's).
+// One sweep of one-sided Jacobi over the columns of A (A[column][row], D = 32 or 16) by the first 4 D of a workgroup's 8 D threads (for
+// D = 32 all of them call it, the barriers are everybody's; for D = 16 the first wavefront alone).
 //
 // A sweep is D - 1 rounds of D / 2 rotations, each round waiting for the one before.  With 16 lanes per column pair and a round trip
 // through LDS and a barrier per round it took 850 cycles a round: some 60 instructions of 4 cycles, 16 the square roots and
@@ -184,14 +185,12 @@ __device__ __forceinline__ bool reverse_factor_group(EntryFn entry, StoreUFn sto
 //     that a wavefront's 60 instructions serve eight pairs instead of four.  One wavefront for all (four rows per lane) is slower: it
 //     is the issue of instructions that bounds that.
 // (x1, y1) is the own pair of a lane's half, (x2, y2) the other half's; the second round of a trip pairs x1 with y2.
-// 32 x 32 Gaussian blocks: 170k cycles for the whole iteration of 8 or 9 sweeps, some 650 a round with the sweep's norms (one wavefront 194k); c2 layer's blocks (128, with moments and factors) 104 -> 83
-// us, the GPTQ chain's step 72 -> 61.
+// 32 x 32 blocks: some 650 cycles a round with the sweep's norms.
 template <int D>
-__device__ __forceinline__ void jacobi_group(double (*A)[D + 2], double* norm2, int* again) {
+__device__ __forceinline__ void jacobi_sweep(double (*A)[D + 2], double* norm2) {
   constexpr int NT = 8 * D, R = D / 16, B = D / 2;
   const int t = threadIdx.x, slot = t / 16, l = t % 16;
   const bool hi = l >= 8, active = t < 4 * D;
-  if (D == 16 && !active) return;                      // one wavefront: nobody to wait for
   auto sync = [&]() {
     if constexpr (D == 32) __syncthreads();
     else wave_lds_sync();
@@ -217,7 +216,6 @@ __device__ __forceinline__ void jacobi_group(double (*A)[D + 2], double* norm2, 
     if constexpr (R == 2) s = fma(a[1], b[1], s);
     return s;
   };
-  bool large;
   double nx, ny;                                       // squared norms of the own pair
   // The rotation by the angle of smaller magnitude that makes two columns orthogonal:
   // tan(2 theta) = 2 ga / (be - al), |theta| <= pi / 4.  With h = hypot(be - al, 2 ga):
@@ -239,7 +237,6 @@ __device__ __forceinline__ void jacobi_group(double (*A)[D + 2], double* norm2, 
     double tn = ga * ih * __builtin_amdgcn_rcp(c2);
     tn = __longlong_as_double(__double_as_longlong(tn) ^ (__double_as_longlong(dd) & (1ll << 63)));
     tn = gg > 1e-30 * ab ? tn : 0.0;                   // |ga| <= 1e-15 sqrt(al be): left alone
-    large |= gg > 1e-20 * ab || fabs(tn) > 1e-7;
     const double x = fma(tn, tn, 1.0);
     const double y = __builtin_amdgcn_rsq(x);
     const double e = fma(-x * y, y, 1.0);
@@ -257,74 +254,233 @@ __device__ __forceinline__ void jacobi_group(double (*A)[D + 2], double* norm2, 
     nx = fma(-tn, ga, nx);
     ny = fma(tn, ga, ny);
   };
-  for (int sweep = 0; sweep < 40; ++sweep) {
-    // squared norms of the columns: computed once a sweep, updated by the rotations in between (they only
-    // decide angles, so the updates' cancellation costs no accuracy of U)
-    constexpr int kGroups = D == 32 ? NT / 16 : 4;
-    for (int c = slot; c < D; c += kGroups) {
-      rows_t v;
-      load(v, c);
-      const double n2 = row_sum(dot(v, v));
-      if (l == 0) norm2[c] = n2;
-    }
-    sync();
-    large = false;
-    rows_t x1, y1, x2, y2;
-    int cx, cy;                                        // columns of the own pair
-    auto fetch = [&](int ax, int ay, int bx, int by) { // low half: pair (ax, ay), high half: pair (bx, by)
-      cx = hi ? bx : ax;
-      cy = hi ? by : ay;
-      load(x1, cx);
-      load(y1, cy);
-      load(x2, hi ? ax : bx);
-      load(y2, hi ? ay : by);
-      nx = norm2[cx];
-      ny = norm2[cy];
-    };
-    auto leave = [&](int ox, int oy, const rows_t& yo, const rows_t& yp) {   // the other pair's columns; the own pair's second, the other's
-      store(x1, cx);
-      store(yo, cy);
-      store(x2, ox);
-      store(yp, oy);
-      norm2[cx] = nx;                                  // the same from every lane of the half
-      norm2[cy] = ny;
-    };
-    // the pair inside every block
+  // squared norms of the columns: computed once a sweep, updated by the rotations in between (they only
+  // decide angles, so the updates' cancellation costs no accuracy of U)
+  constexpr int kGroups = D == 32 ? NT / 16 : 4;
+  for (int c = slot; c < D; c += kGroups) {
+    rows_t v;
+    load(v, c);
+    const double n2 = row_sum(dot(v, v));
+    if (l == 0) norm2[c] = n2;
+  }
+  sync();
+  rows_t x1, y1, x2, y2;
+  int cx, cy;                                        // columns of the own pair
+  auto fetch = [&](int ax, int ay, int bx, int by) { // low half: pair (ax, ay), high half: pair (bx, by)
+    cx = hi ? bx : ax;
+    cy = hi ? by : ay;
+    load(x1, cx);
+    load(y1, cy);
+    load(x2, hi ? ax : bx);
+    load(y2, hi ? ay : by);
+    nx = norm2[cx];
+    ny = norm2[cy];
+  };
+  auto leave = [&](int ox, int oy, const rows_t& yo, const rows_t& yp) {   // the other pair's columns; the own pair's second, the other's
+    store(x1, cx);
+    store(yo, cy);
+    store(x2, ox);
+    store(yp, oy);
+    norm2[cx] = nx;                                  // the same from every lane of the half
+    norm2[cy] = ny;
+  };
+  // the pair inside every block
+  if (active) {
+    fetch(4 * slot, 4 * slot + 1, 4 * slot + 2, 4 * slot + 3);
+    rotate(x1, y1, x2, y2);
+    leave(hi ? 4 * slot : 4 * slot + 2, hi ? 4 * slot + 1 : 4 * slot + 3, y1, y2);
+  }
+  sync();
+  // the blocks against each other, circle method: position 0 fixed, the other B - 1 rotate
+  int p = slot, q = B - 1 - slot;
+  for (int rnd = 0; rnd < B - 1; ++rnd) {
     if (active) {
-      fetch(4 * slot, 4 * slot + 1, 4 * slot + 2, 4 * slot + 3);
+      fetch(2 * p, 2 * q, 2 * p + 1, 2 * q + 1);
       rotate(x1, y1, x2, y2);
-      leave(hi ? 4 * slot : 4 * slot + 2, hi ? 4 * slot + 1 : 4 * slot + 3, y1, y2);
+      ny = dpp_f64<0x140>(ny);                       // the halves swap their second columns
+      cy ^= 1;
+      rotate(x1, y2, x2, y1);
+      leave(cx ^ 1, cy ^ 1, y2, y1);
+      p = slot == 0 ? 0 : (p == B - 1 ? 1 : p + 1);
+      q = q == B - 1 ? 1 : q + 1;
     }
     sync();
-    // the blocks against each other, circle method: position 0 fixed, the other B - 1 rotate
-    int p = slot, q = B - 1 - slot;
-    for (int rnd = 0; rnd < B - 1; ++rnd) {
-      if (active) {
-        fetch(2 * p, 2 * q, 2 * p + 1, 2 * q + 1);
-        rotate(x1, y1, x2, y2);
-        ny = dpp_f64<0x140>(ny);                       // the halves swap their second columns
-        cy ^= 1;
-        rotate(x1, y2, x2, y1);
-        leave(cx ^ 1, cy ^ 1, y2, y1);
-        p = slot == 0 ? 0 : (p == B - 1 ? 1 : p + 1);
-        q = q == B - 1 ? 1 : q + 1;
-      }
-      sync();
-    }
-    // A rotation by tan(theta) = tn undoes what earlier ones of its sweep zeroed by tn times the cosines it mixes in (the
-    // ratio of the two columns' norms is in tn), 2 D of them per pair at most.  So a sweep that met cosines up to 1e-10 and
-    // tangents up to 1e-7 only leaves cosines of some 1e-16, and the last ones' own, 2^-24 of what they were: no
-    // further sweep is needed.  Equal or nearly equal singular values turn by large angles at any cosine; there the sweeps go on until
-    // no cosine is above 1e-15.  (Stopping at cosines of 1e-10 alone left the columns of such a block orthogonal to 3e-11.)
-    if constexpr (D == 32) {
-      if (active && large) again[sweep & 1] = 1;
-      __syncthreads();
-      const int more = again[sweep & 1];
-      if (t == 0) again[(sweep + 1) & 1] = 0;          // read last a sweep ago, set next a sweep from now
-      if (!more) break;
+  }
+}
+
+// Tile (rows x0 ..., columns y0 ...) of X Y^T, added to acc, on the FP64 MFMA (16 x 16 x 4): a lane's operands are D / 4 consecutive
+// elements of row l16 of either matrix; accumulator v is element (x0 + l4 + 4 v, y0 + l16).  Stored across == true: Y instead of Y^T.
+template <int D, bool ACROSS = false>
+__device__ __forceinline__ v4d product_tile(const double (*X)[D + 2], int x0, const double (*Y)[D + 2], int y0, v4d acc) {
+  constexpr int kPer = D / 4;
+  const int l16 = threadIdx.x & 15, k0 = kPer * ((threadIdx.x & 63) >> 4);
+  double x[kPer], y[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; k += 2) {
+    const v2d u = *reinterpret_cast<const v2d*>(&X[x0 + l16][k0 + k]);
+    x[k] = u[0];
+    x[k + 1] = u[1];
+    if constexpr (ACROSS) {
+      y[k] = Y[k0 + k][y0 + l16];
+      y[k + 1] = Y[k0 + k + 1][y0 + l16];
     } else {
-      if (!__any(large)) break;
+      const v2d w = *reinterpret_cast<const v2d*>(&Y[y0 + l16][k0 + k]);
+      y[k] = w[0];
+      y[k + 1] = w[1];
     }
+  }
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[k], y[k], acc, 0, 0, 0);
+  return acc;
+}
+
+// The columns of A made orthogonal by right rotations, A V = U S (V is never needed): sweeps of Jacobi until all that is left are small
+// angles, then all pairs at once.
+//
+// The simultaneous step: with K[i][j] = the tangent that makes columns i and j orthogonal by themselves (antisymmetric), A <- A P with
+// an orthogonal P = exp(K) up to FP64's resolution; what it leaves is of second order in K, as behind a sweep.  It is five to
+// seven 32 x 32 products on the FP64 MFMA, a tile per wavefront, 1.5 to 2.5 us, where a sweep is a chain of 31 dependent rounds of 650 cycles, 8.7 us.
+//   G = A^T A gives the angles;  K^2;  P = I + K + K^2 / 2 (tangents up to 1e-5), + K^3 / 6 + K^4 / 24;  beyond 1e-3 Newton-Schulz steps
+//   P <- P (3 I - P^T P) / 2 until P^T P differs from I by 2e-9 at most before the last one;  A P.
+// Everything is graded as A's columns are (K[i][j] is about cosine x ratio of the norms), so small columns keep their relative accuracy.
+// P is kept transposed, so that both operands of all products but two are read along their rows.
+// It is taken up to tangents of 0.1 (blocks of the 4096 -> 6144 layer, sweeps + steps from the Cholesky factors: none 5.9 + 0, 0.003: 3.3 +
+// 2.1, 0.03: 2.9 + 2.6, 0.1: 2.4 + 3.3, 0.2: 2.2 + 3.7), at most eight times: on blocks of nearly equal singular values, where second
+// order is not small against their distance, the sweeps end it.
+//
+// End: a step or sweep that met cosines up to 1e-10 and tangents up to 1e-7 only is the last one: it turns what earlier rotations
+// zeroed by a tangent times the cosines it mixes in (the ratio of the two columns' norms is in the tangent), 2 D of them per pair at
+// most, and so leaves cosines of some 1e-16, and its own ones, 2^-24 of what they were.  Equal or nearly equal singular values turn by
+// large angles at any cosine; there the sweeps go on until no cosine is above 1e-15.
+//
+// All threads of the workgroup call it (D = 16: the first wavefront does the work).  K, Q, R: scratch; votes: 8 words; cold: nothing is
+// known of A's columns, so a sweep comes first.
+template <int D>
+__device__ __forceinline__ void orthogonalize_group(double (*A)[D + 2], double (*K)[D + 2], double (*Q)[D + 2], double (*R)[D + 2],
+                                                    double* norm2, int* votes, bool cold) {
+  constexpr int kTurn = 1, kSweep = 2, kMore = 4, kFourth = 8, kFix = 16;
+  if (D == 16 && threadIdx.x >= 64) return;            // one wavefront: nobody to wait for
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, l4 = lane >> 4;
+  const int i0 = D == 32 ? 16 * (wave >> 1) : 0, j0 = D == 32 ? 16 * (wave & 1) : 0;   // this wavefront's tile of every product
+  auto sync = [&]() {
+    if constexpr (D == 32) __syncthreads();
+    else wave_lds_sync();
+  };
+  int round = 0;
+  // the bits set by any lane, in every lane; a barrier for LDS as well
+  auto vote = [&](int bits) {
+    int mine = 0;
+#pragma unroll
+    for (int b = 1; b <= kFix; b *= 2)
+      if (__any(bits & b)) mine |= b;
+    if constexpr (D == 32) {
+      int* v = votes + 4 * (round++ & 1);              // read by everybody before the barrier of the next vote
+      if (lane == 0) v[wave] = mine;
+      __syncthreads();
+      mine = __builtin_amdgcn_readfirstlane(v[0] | v[1] | v[2] | v[3]);
+    } else {
+      wave_lds_sync();
+    }
+    return mine;
+  };
+  auto put = [&](double (*m)[D + 2], const v4d& x) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) m[i0 + l4 + 4 * v][j0 + l16] = x[v];
+  };
+  const v4d zero = {0, 0, 0, 0};
+  v4d one;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) one[v] = i0 + l4 + 4 * v == j0 + l16 ? 1.0 : 0.0;
+  if (cold) {
+    jacobi_sweep<D>(A, norm2);
+  }
+  int steps_left = 8;
+  for (int pass = 0; pass < 40; ++pass) {
+    const v4d G = product_tile<D>(A, i0, A, j0, zero);
+    if (i0 == j0) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (l16 == l4 + 4 * v) norm2[j0 + l16] = G[v];
+    }
+    sync();
+    const double nj = norm2[j0 + l16];
+    v4d k;
+    int bits = 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      // tan(theta) as in jacobi_sweep's rotation of columns x = i, y = j
+      const double ni = norm2[i0 + l4 + 4 * v], ga = G[v], dd = nj - ni, ab = ni * nj, gg = ga * ga, ga2 = ga + ga;
+      const double ih = __builtin_amdgcn_rsq(fma(ga2, ga2, dd * dd));
+      const double c2 = fma(0.5 * fabs(dd), ih, 0.5);
+      double tn = ga * ih * __builtin_amdgcn_rcp(c2);
+      tn = __longlong_as_double(__double_as_longlong(tn) ^ (__double_as_longlong(dd) & (1ll << 63)));
+      const bool turn = one[v] == 0.0 && gg > 1e-30 * ab;
+      k[v] = turn ? tn : 0.0;
+      const double mag = fabs(k[v]);
+      bits |= (turn ? kTurn : 0) | (mag > 0.1 ? kSweep : 0) | (turn && (gg > 1e-20 * ab || mag > 1e-7) ? kMore : 0) |
+              (mag > 1e-5 ? kFourth : 0) | (mag > 1e-3 ? kFix : 0);
+    }
+    put(K, k);
+    const int seen = vote(bits);
+    if (!(seen & kTurn)) break;
+    bool step = !(seen & kSweep) && steps_left-- > 0;
+    if (step) {
+      // Q = K^2 = -K K^T
+      v4d k2 = product_tile<D>(K, i0, K, j0, zero);
+      double (*P)[D + 2] = Q;                          // P^T, all along
+      v4d p;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        k2[v] = -k2[v];
+        p[v] = fma(0.5, k2[v], one[v] - k[v]);
+      }
+      if (seen & kFourth) {
+        // P^T += K^2 (K^2 / 24 - K / 6); the second factor's transpose is K^2 / 24 + K / 6
+        v4d m;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) m[v] = fma(k2[v], 1.0 / 24.0, k[v] * (1.0 / 6.0));
+        put(Q, k2);
+        put(R, m);
+        sync();
+        p = product_tile<D>(Q, i0, R, j0, p);
+        P = K;
+      }
+      put(P, p);
+      sync();
+      if (seen & kFix) {
+        double (*other)[D + 2] = R;
+        for (int fix = 0; fix < 4; ++fix) {
+          v4d s = product_tile<D>(P, i0, P, j0, zero);
+          bool off = false, lost = false;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const double e = fabs(s[v] - one[v]);
+            off |= e > 2e-9;
+            lost |= !(e < 0.1);
+            s[v] = fma(-0.5, s[v], 1.5 * one[v]);
+          }
+          put(Q, s);
+          const int left = vote((off ? kMore : 0) | (lost ? kSweep : 0));
+          step = !(left & kSweep);
+          if (!step) break;                            // far from orthogonal: a sweep instead, A is as it was
+          p = product_tile<D, true>(Q, i0, P, j0, zero);
+          put(other, p);
+          sync();
+          double (*swap)[D + 2] = P;
+          P = other;
+          other = swap;
+          if (!(left & kMore)) break;
+        }
+      }
+      if (step) {
+        const v4d a = product_tile<D, true>(P, i0, A, j0, zero);
+        sync();
+        put(A, a);
+        sync();
+      }
+    }
+    if (!step) jacobi_sweep<D>(A, norm2);
+    if (!(seen & kMore)) break;
   }
 }
 
@@ -357,11 +513,12 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
   __shared__ double LW[D][D + 1];        // M_W, then W' (lower triangle)
   __shared__ double LX[D][D + 1];        // M_X, then X'
   __shared__ __attribute__((aligned(16))) double A[D][D + 2];   // columns of W'^T X', then of U S: A[column][row]
-  __shared__ double U[D][D + 1];         // sorted, sign-normalized: U[row][column]; then B
+  __shared__ __attribute__((aligned(16))) double scratch[3][D][D + 2];
+  double (*U)[D + 2] = scratch[0];       // sorted, sign-normalized: U[row][column]
   __shared__ double colb[2][2][D];       // the factors' current column, two buffers in turn
   __shared__ double norm2[D], sv[D], ssort[D];
   __shared__ int order[D];
-  __shared__ int again[2];
+  __shared__ int votes[8];
   const int t = threadIdx.x;
   {
     // consecutive threads fetch consecutive entries of a row; a thread's entries of one moment and eight of
@@ -387,7 +544,6 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
       for (int u = 0; u < kOut; ++u) (h ? LX : LW)[(t + NT * u) / D][(t + NT * u) % D] = finish(h, acc[u]);
     }
   }
-  if (t < 2) again[t] = 0;
   __syncthreads();
   // ---- damping and Cholesky (lower): the first half of the threads works on M_W, the second on M_X.
   // Thread q of a half owns row q / 4, columns kCpt (q % 4) ... of its matrix in registers.  Step j publishes
@@ -468,8 +624,8 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
     for (int u = 0; u < kOut; ++u) A[(t + NT * u) / D][(t + NT * u) % D] = acc[u];
   }
   __syncthreads();
-  // ---- one-sided Jacobi on the columns of A (right rotations): A V = U S
-  jacobi_group<D>(A, norm2, again);
+  // ---- columns of A made orthogonal by right rotations: A V = U S
+  orthogonalize_group<D>(A, scratch[0], scratch[1], scratch[2], norm2, votes, V0 == nullptr);
   __syncthreads();
   const int pr = t / 16, sub = t % 16;                 // column; rows kRpl sub ... of it
   // ---- singular values, descending order, U with the sign convention (16 lanes per column)
@@ -530,13 +686,13 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < kOut; ++u) U[(t + NT * u) / D][(t + NT * u) % D] = v[u];
-    if (t == 0) again[0] = 0;
+    if (t == 0) votes[0] = 0;
     __syncthreads();
     product([&](int r, int k) { return U[k][r]; }, [&](int k, int c) { return U[k][c]; }, acc);
 #pragma unroll
     for (int u = 0; u < kOut; ++u) {
       const int r = (t + NT * u) / D, c = (t + NT * u) % D;
-      if (!(fabs(acc[u] - (r == c ? 1.0 : 0.0)) < 1e-3)) again[0] = 1;
+      if (!(fabs(acc[u] - (r == c ? 1.0 : 0.0)) < 1e-3)) votes[0] = 1;
       LW[r][c] = acc[u];
     }
     __syncthreads();
@@ -544,7 +700,7 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
 #pragma unroll
     for (int u = 0; u < kOut; ++u) {
       const int r = (t + NT * u) / D, c = (t + NT * u) % D;
-      V_out[t + NT * u] = again[0] ? (r == c ? 1.0 : 0.0) : 1.5 * v[u] - 0.5 * acc[u];
+      V_out[t + NT * u] = votes[0] ? (r == c ? 1.0 : 0.0) : 1.5 * v[u] - 0.5 * acc[u];
     }
     return;
   }
