@@ -105,17 +105,18 @@ __global__ __launch_bounds__(256) void second_moment_kernel(
   }
   __syncthreads();
   if (wave == 0) {
-    double* out = partial + (((int64_t)z * S + s) * C + b) * 1024;
+    double* out = partial + (((int64_t)z * S + s) * C + b) * kMomentSize;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int e = 4 * lane + v, i = mfma_f64_row(lane, v);
       const double m00 = ((acc00[v] + red[0][e]) + red[1][e]) + red[2][e];
       const double m01 = ((acc01[v] + red[0][256 + e]) + red[1][256 + e]) + red[2][256 + e];
       const double m11 = ((acc11[v] + red[0][512 + e]) + red[1][512 + e]) + red[2][512 + e];
-      out[i * 32 + c] = m00;
-      out[i * 32 + 16 + c] = m01;
-      out[(16 + c) * 32 + i] = m01;
-      out[(16 + i) * 32 + 16 + c] = m11;
+      out[moment_beside(i, c)] = m01;
+      if (c <= i) {
+        out[lower16(i, c)] = m00;
+        out[moment_second(i, c)] = m11;
+      }
     }
   }
 }
@@ -126,11 +127,9 @@ __global__ __launch_bounds__(256) void wush_block_kernel(const double* __restric
                                                          double* __restrict__ T_f64, int* __restrict__ status) {
   const int b = blockIdx.x;
   // the partial moments are added in a fixed order and normalized
-  auto load = [&](int half, int r, int c, int s) {
-    return partial[(((int64_t)half * S + s) * C + b) * 1024 + r * 32 + c];
-  };
+  auto load = [&](int half, int e, int, int, int s) { return partial[(((int64_t)half * S + s) * C + b) * kMomentSize + e]; };
   auto finish = [&](int half, double sum) { return sum * (1.0 / (double)(half ? Mc : N)); };
-  wush_block_group<32, 0>(load, finish, S_W, S_X, lambda, nullptr, T_out + (int64_t)b * 1024,
+  wush_block_group<32, 0, 16, 16>(load, finish, S_W, S_X, lambda, nullptr, T_out + (int64_t)b * 1024,
                           T_f64 ? T_f64 + (int64_t)b * 1024 : nullptr, nullptr, status);
 }
 
@@ -139,12 +138,12 @@ __global__ __launch_bounds__(256) void wush_block_kernel(const double* __restric
 __global__ __launch_bounds__(128) void wush_block16_kernel(const double* __restrict__ partial, int S, int S_W, int S_X,
                                                            int C, int N, int Mc, double lambda, uint16_t* __restrict__ T_out,
                                                            double* __restrict__ T_f64, int* __restrict__ status) {
-  const int b = blockIdx.x, b32 = b >> 1, off = 16 * (b & 1);
-  auto load = [&](int half, int r, int c, int s) {
-    return partial[(((int64_t)half * S + s) * C + b32) * 1024 + (off + r) * 32 + off + c];
+  const int b = blockIdx.x, b32 = b >> 1, off = b & 1 ? moment_second(0, 0) : 0;
+  auto load = [&](int half, int e, int, int, int s) {
+    return partial[(((int64_t)half * S + s) * C + b32) * kMomentSize + off + e];
   };
   auto finish = [&](int half, double sum) { return sum * (1.0 / (double)(half ? Mc : N)); };
-  wush_block_group<16, 0>(load, finish, S_W, S_X, lambda, nullptr, T_out + (int64_t)b * 256,
+  wush_block_group<16, 0, 16, 16>(load, finish, S_W, S_X, lambda, nullptr, T_out + (int64_t)b * 256,
                           T_f64 ? T_f64 + (int64_t)b * 256 : nullptr, nullptr, status);
 }
 

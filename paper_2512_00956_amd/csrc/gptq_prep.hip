@@ -218,7 +218,7 @@ struct Moment {
     }
     wave_lds_sync();
   }
-  // sums of the workgroup's WAVES wavefronts in wave order -> out [32][32]
+  // sums of the workgroup's WAVES wavefronts in wave order -> out [kMomentSize]
   template <int WAVES>
   __device__ __forceinline__ void reduce(double* areas, int wave, int lane, double* __restrict__ out) {
     __syncthreads();
@@ -235,14 +235,14 @@ struct Moment {
 #pragma unroll
       for (int w = 1; w < WAVES; ++w) s += areas[w * kAreaDoubles + e];
       const int el = (e & 255) >> 2, i = (el >> 4) + 4 * (e & 3), c = el & 15;   // row, column of the 16 x 16 block
-      if (e < 256) out[i * 32 + c] = s;
-      else if (e < 512) {
-        out[i * 32 + 16 + c] = s;
-        out[(16 + c) * 32 + i] = s;
-      } else out[(16 + i) * 32 + 16 + c] = s;
+      if (e >= 256 && e < 512) out[moment_beside(i, c)] = s;
+      else if (c <= i) out[e < 256 ? lower16(i, c) : moment_second(i, c)] = s;
     }
   }
 };
+
+constexpr int kWarmSplits = 8;    // row splits of the moments of the original weights
+constexpr int kChainFlight = 24;  // partial moments of the chain's block in flight
 
 // Second moments of all blocks of the original weights (grid: splits of the rows x blocks), for the warm start.
 __global__ __launch_bounds__(256) void gptq_moment0_kernel(const uint16_t* __restrict__ W, int64_t ldw, int N,
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256) void gptq_moment0_kernel(const uint16_t* __res
       for (int q = 0; q < 8; ++q) x[q] = 0.0;
     m.add(x, areas + wave * kAreaDoubles, l16, l4);
   }
-  m.reduce<4>(areas, wave, lane, partial + ((int64_t)b * gridDim.x + blockIdx.x) * 1024);
+  m.reduce<4>(areas, wave, lane, partial + ((int64_t)b * gridDim.x + blockIdx.x) * kMomentSize);
 }
 
 // Right singular vectors of W'^T X' of every block of the ORIGINAL weights: what the SVD inside the loop starts from.
@@ -269,11 +269,11 @@ __global__ __launch_bounds__(256) void gptq_moment0_kernel(const uint16_t* __res
 __global__ __launch_bounds__(256) void gptq_warm_kernel(const double* __restrict__ partial, int splits, int N,
                                                         const double* __restrict__ MX, double lambda, double* __restrict__ V0) {
   const int b = blockIdx.x;
-  auto load = [&](int half, int r, int c, int s) {
-    return half ? MX[(int64_t)b * 1024 + r * 32 + c] : partial[((int64_t)b * splits + s) * 1024 + r * 32 + c];
+  auto load = [&](int half, int e, int r, int c, int s) {
+    return half ? MX[(int64_t)b * 1024 + r * 32 + c] : partial[((int64_t)b * splits + s) * kMomentSize + e];
   };
   auto finish = [&](int half, double sum) { return half ? sum : sum / (double)N; };
-  wush_block_group<32, 1>(load, finish, splits, 1, lambda, nullptr, nullptr, nullptr, V0 + (int64_t)b * 1024, nullptr);
+  wush_block_group<32, 1, kWarmSplits, 1>(load, finish, splits, 1, lambda, nullptr, nullptr, nullptr, V0 + (int64_t)b * 1024, nullptr);
 }
 
 // What the sums S_l still lack travels in groups of kGroup blocks: S is N x K doubles, and adding every block's error to
@@ -311,9 +311,9 @@ __global__ __launch_bounds__(256) void gptq_chain_kernel(const double* __restric
   if (blockIdx.x == 0) {
     if (given) return;
     __builtin_amdgcn_s_setprio(3);   // ahead of wavefronts that may share its compute unit
-    auto load = [&](int half, int r, int c, int s) { return half ? MX_i[r * 32 + c] : partial[(int64_t)s * 1024 + r * 32 + c]; };
+    auto load = [&](int half, int e, int r, int c, int s) { return half ? MX_i[r * 32 + c] : partial[(int64_t)s * kMomentSize + e]; };
     auto finish = [&](int half, double sum) { return half ? sum : sum / (double)N; };
-    wush_block_group<32, 0>(load, finish, splits, 1, lambda, V0_i, T_bits_i, nullptr, nullptr, status);
+    wush_block_group<32, 0, kChainFlight, 1>(load, finish, splits, 1, lambda, V0_i, T_bits_i, nullptr, nullptr, status);
     return;
   }
   extern __shared__ __attribute__((aligned(16))) double smem[];   // [block][pair of operand registers][lane][2]
@@ -589,12 +589,11 @@ __global__ __launch_bounds__(64 * kRowWaves) void gptq_rows_kernel(
       m.add(wn, area, l16, l4);
     }
   }
-  if (next < C) m.reduce<kRowWaves>(sh.areas, wave, lane, partial + (int64_t)blockIdx.x * 1024);
+  if (next < C) m.reduce<kRowWaves>(sh.areas, wave, lane, partial + (int64_t)blockIdx.x * kMomentSize);
 }
 
 // Partial moments of a block: at most this many workgroups of gptq_rows_kernel.
 constexpr int kMomentSplits = 64, kMomentSplitsLarge = 128;
-constexpr int kWarmSplits = 8;
 // From this K on the Hessian's buffer, free behind the factorization, has room for the warm start (V0, its partial
 // moments) and for more partial moments: (32 + 8 * 32) K + 128 * 1024 <= K^2.
 constexpr int64_t kLargeK = 1024;

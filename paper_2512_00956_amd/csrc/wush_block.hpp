@@ -51,6 +51,12 @@ __device__ __forceinline__ int row_min(int x) {
   x = min(x, __builtin_amdgcn_update_dpp(0, x, 0x141, 0xF, 0xF, true));
   return min(x, __builtin_amdgcn_update_dpp(0, x, 0x140, 0xF, 0xF, true));
 }
+__device__ __forceinline__ int row_sum_int(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x141, 0xF, 0xF, true);
+  return x + __builtin_amdgcn_update_dpp(0, x, 0x140, 0xF, 0xF, true);
+}
 __device__ __forceinline__ double readlane_f64(double x, int lane) {
   const long long b = __double_as_longlong(x);
   const int lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
@@ -344,9 +350,9 @@ __device__ __forceinline__ v4d product_tile(const double (*X)[D + 2], int x0, co
 //   P <- P (3 I - P^T P) / 2 until P^T P differs from I by 2e-9 at most before the last one;  A P.
 // Everything is graded as A's columns are (K[i][j] is about cosine x ratio of the norms), so small columns keep their relative accuracy.
 // P is kept transposed, so that both operands of all products but two are read along their rows.
-// It is taken up to tangents of 0.1 (blocks of the 4096 -> 6144 layer, sweeps + steps from the Cholesky factors: none 5.9 + 0, 0.003: 3.3 +
-// 2.1, 0.03: 2.9 + 2.6, 0.1: 2.4 + 3.3, 0.2: 2.2 + 3.7), at most eight times: on blocks of nearly equal singular values, where second
-// order is not small against their distance, the sweeps end it.
+// It is taken up to tangents of 0.4 (blocks of the 4096 -> 6144 layer, sweeps + steps from the Cholesky factors: never 5.9 + 0, 0.003: 3.3 +
+// 2.1, 0.05: 2.7 + 3.1, 0.1: 2.5 + 3.4, 0.4: 1.9 + 4.2, 0.6: 1.7 + 4.5; from a warm start 3.9 + 0, 1.3 + 2.5, 0.7 + 3.1, 0.4 + 3.4, 0.05 + 3.8, 0 + 3.8),
+// at most eight times: on blocks of nearly equal singular values, where second order is not small against their distance, the sweeps end it.
 //
 // End: a step or sweep that met cosines up to 1e-10 and tangents up to 1e-7 only is the last one: it turns what earlier rotations
 // zeroed by a tangent times the cosines it mixes in (the ratio of the two columns' norms is in the tangent), 2 D of them per pair at
@@ -417,7 +423,7 @@ __device__ __forceinline__ void orthogonalize_group(double (*A)[D + 2], double (
       const bool turn = one[v] == 0.0 && gg > 1e-30 * ab;
       k[v] = turn ? tn : 0.0;
       const double mag = fabs(k[v]);
-      bits |= (turn ? kTurn : 0) | (mag > 0.1 ? kSweep : 0) | (turn && (gg > 1e-20 * ab || mag > 1e-7) ? kMore : 0) |
+      bits |= (turn ? kTurn : 0) | (mag > 0.4 ? kSweep : 0) | (turn && (gg > 1e-20 * ab || mag > 1e-7) ? kMore : 0) |
               (mag > 1e-5 ? kFourth : 0) | (mag > 1e-3 ? kFix : 0);
     }
     put(K, k);
@@ -484,268 +490,309 @@ __device__ __forceinline__ void orthogonalize_group(double (*A)[D + 2], double (
   }
 }
 
+// Second moments go from kernel to kernel as the 528 entries on or below the diagonal of a symmetric 32 x 32: the lower triangle of the first
+// 16 x 16 block by rows, then the block beside it (channel i of the first half, c of the second: row i, column c), then the lower
+// triangle of the second diagonal block.  A partial moment is then half the bytes: what one compute unit has to fetch of 48 of them is 8 us of
+// the GPTQ chain's step otherwise.
+constexpr int kMomentSize = 528;
+__host__ __device__ __forceinline__ int lower16(int i, int c) { return i * (i + 1) / 2 + c; }           // c <= i < 16
+__host__ __device__ __forceinline__ int moment_beside(int i, int c) { return 136 + 16 * i + c; }        // entry (16 + c, i)
+__host__ __device__ __forceinline__ int moment_second(int i, int c) { return 392 + lower16(i, c); }     // entry (16 + i, 16 + c)
+// row and column (row >= column) of entry e of the lower triangle of a 16 x 16
+__device__ __forceinline__ void lower16_at(int e, int& r, int& c) {
+  r = (int)((sqrtf(8.0f * (float)e + 1.5f) - 1.0f) * 0.5f);   // 8 e + 1 is a square at c = 0
+  c = e - r * (r + 1) / 2;
+}
+
 // Alg. 1 for one D x D block (D = 32, or 16 for the NVFP4 variant), by a workgroup of 8 D threads:
 //   W' W'^T = M_W + lambda d^-1 tr(M_W) I,  X' X'^T likewise  (Cholesky, side by side)
-//   U S V^T = W'^T X'  (one-sided Jacobi on the columns; V never needed)
+//   U S V^T = W'^T X'  (orthogonalize_group on the columns; V never needed)
 //   T = H S^(-1/2) U^T W'^T, singular values descending, the entry of largest
 //   magnitude of every column of U positive.
-// load(h, r, c, s): partial sum s (of S_W for h = 0, S_X for h = 1) of entry (r, c) of the second moment,
-// finish(h, sum): the normalized, undamped entry, h = 0 for M_W, 1 for M_X.  T goes out as BF16 bits
-// (T_bits) and, where the pointer is non-null, as FP64 before rounding (T_f64), each [D][D] row-major.  A moment
+// load(h, e, r, c, s): partial sum s (of S_W for h = 0, S_X for h = 1) of entry (r, c), r >= c, of the second moment, e its index in the lower
+// triangle (kMomentSize's order, or lower16 for D = 16); finish(h, sum): the normalized, undamped entry, h = 0 for M_W, 1 for M_X.  T goes out as
+// BF16 bits (T_bits) and, where the pointer is non-null, as FP64 before rounding (T_f64), each [D][D] row-major.  A moment
 // that is not positive definite sets *status.
 // V0 (may be null): an orthogonal [D][D] the SVD starts from, A V0 in place of A; U and S are the same, and a V0 close
-// to the right singular vectors leaves little for the sweeps to do.  MODE 1 computes such a V0 in place of T (into
+// to the right singular vectors leaves little to do.  MODE 1 computes such a V0 in place of T (into
 // V_out; the identity where the moments give none) and leaves the status alone.
 //
-// A block is one chain of dependent steps (2 x D columns of the factors, 6 to 9 sweeps of D - 1 Jacobi
-// rounds), so what counts is the latency of a step, and the threads are there to shorten it: the factors are taken column by
-// column out of registers with one barrier per column, the products are spread over the whole workgroup, and the Jacobi
-// rounds are jacobi_group's.
-template <int D, int MODE, class LoadFn, class FinishFn>
+// A block is one chain of dependent steps (2 x D columns of the factors, the SVD's sweeps and steps), so what counts is the
+// latency of each.  The factors are taken by a wavefront each, without a barrier: a lane has D^2 / 64 entries of a row in registers, a
+// step's pivot goes to everybody through the scalar registers, its column through LDS.  Products are on the FP64 MFMA, a tile per wavefront.
+// c2 layer, 128 blocks: 83 us with Jacobi to the end, products and factors by all threads with a barrier per column; now 61, half of it the SVD.
+template <int D, int MODE, int FW, int FX, class LoadFn, class FinishFn>
 __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, int S_W, int S_X, double lambda,
                                                  const double* __restrict__ V0, uint16_t* __restrict__ T_bits,
                                                  double* __restrict__ T_f64, double* __restrict__ V_out,
                                                  int* __restrict__ status) {
   static_assert(D == 32 || D == 16, "block size");
   constexpr int NT = 8 * D;
-  constexpr int kRpl = D / 16;           // rows of a column pair per lane
-  constexpr int kOut = D * D / NT;       // entries of a D x D product per thread
-  __shared__ double LW[D][D + 1];        // M_W, then W' (lower triangle)
-  __shared__ double LX[D][D + 1];        // M_X, then X'
-  __shared__ __attribute__((aligned(16))) double A[D][D + 2];   // columns of W'^T X', then of U S: A[column][row]
-  __shared__ __attribute__((aligned(16))) double scratch[3][D][D + 2];
-  double (*U)[D + 2] = scratch[0];       // sorted, sign-normalized: U[row][column]
-  __shared__ double colb[2][2][D];       // the factors' current column, two buffers in turn
+  constexpr int kRpl = D / 16;           // rows of a column per lane, 16 lanes per column
+  typedef double matrix_t[D][D + 2];
+  __shared__ __attribute__((aligned(16))) matrix_t LW;          // M_W, then W'^T: LW[column][row]
+  __shared__ __attribute__((aligned(16))) matrix_t LX;          // M_X, then X'^T
+  __shared__ __attribute__((aligned(16))) matrix_t A;           // columns of W'^T X', then of U S: A[column][row]; then B
+  __shared__ __attribute__((aligned(16))) matrix_t scratch[3];  // [0]: V0^T, at the end U sorted and sign-normalized, U[column][row]
+  __shared__ double diag[2][D], inv_root[2][D];
   __shared__ double norm2[D], sv[D], ssort[D];
-  __shared__ int order[D];
   __shared__ int votes[8];
-  const int t = threadIdx.x;
+  matrix_t& U = scratch[0];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, l16 = lane & 15, l4 = lane >> 4;
+  // this wavefront's tile of the products (one tile for D = 16: the first wavefront's)
+  const bool tiles = D == 32 || wave == 0;
+  const int i0 = D == 32 ? 16 * (wave >> 1) : 0, j0 = D == 32 ? 16 * (wave & 1) : 0;
+  const v4d zero = {0, 0, 0, 0};
+  auto put = [&](matrix_t& m, const v4d& x) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) m[i0 + l4 + 4 * v][j0 + l16] = x[v];
+  };
+  double v0[D * D / NT];                 // fetched ahead: the same for the whole workgroup whether there is one
+#pragma unroll
+  for (int u = 0; u < D * D / NT; ++u) v0[u] = V0 ? V0[t + NT * u] : 0.0;
   {
-    // consecutive threads fetch consecutive entries of a row; a thread's entries of one moment and eight of
-    // their partial sums are in flight at a time, added in ascending order
+    // a thread's entries of both moments and FW, FX of their partial sums are in flight at a time, added in ascending order
+    constexpr int kEntries = D == 32 ? kMomentSize : 136, kPer = (kEntries + NT - 1) / NT;
+    double acc[2][kPer];
+    int row[kPer], col[kPer];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int splits = h ? S_X : S_W;
-      double acc[kOut];
-#pragma unroll
-      for (int u = 0; u < kOut; ++u) acc[u] = 0.0;
-      for (int s0 = 0; s0 < splits; s0 += 8) {
-        double v[kOut][8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-          for (int u = 0; u < kOut; ++u) v[u][i] = s0 + i < splits ? load(h, (t + NT * u) / D, (t + NT * u) % D, s0 + i) : 0.0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-          for (int u = 0; u < kOut; ++u) acc[u] += v[u][i];
+    for (int u = 0; u < kPer; ++u) {
+      acc[0][u] = acc[1][u] = 0.0;
+      const int e = min(t + NT * u, kEntries - 1);
+      if (D == 32 && e >= 136 && e < 392) {
+        row[u] = 16 + ((e - 136) & 15);
+        col[u] = (e - 136) >> 4;
+      } else {
+        const bool second = D == 32 && e >= 392;
+        lower16_at(second ? e - 392 : e, row[u], col[u]);
+        if (second) {
+          row[u] += 16;
+          col[u] += 16;
+        }
       }
-#pragma unroll
-      for (int u = 0; u < kOut; ++u) (h ? LX : LW)[(t + NT * u) / D][(t + NT * u) % D] = finish(h, acc[u]);
     }
-  }
-  __syncthreads();
-  // ---- damping and Cholesky (lower): the first half of the threads works on M_W, the second on M_X.
-  // Thread q of a half owns row q / 4, columns kCpt (q % 4) ... of its matrix in registers.  Step j publishes
-  // column j of what is left; with d its diagonal entry, entry (r, c) loses col[r] col[c] / d, and column j of
-  // the factor is col / sqrt(d), formed at the end by the threads that published it.
-  {
-    constexpr int kCpt = D / 4;
-    const int h = t / (NT / 2), q = t % (NT / 2), r = q / 4, c0 = kCpt * (q % 4);
-    double (*L)[D + 1] = h ? LX : LW;
-    double tr = 0.0;
-    for (int c = 0; c < D; ++c) tr += L[c][c];
-    const double add = lambda * tr / (double)D;
-    double a[kCpt], raw[kCpt], diag[kCpt];             // column c0 + i as published, and its d
+    for (int w0 = 0, x0 = 0; w0 < S_W || x0 < S_X; w0 += FW, x0 += FX) {
+      double vw[kPer][FW], vx[kPer][FX];
 #pragma unroll
-    for (int i = 0; i < kCpt; ++i) {
-      a[i] = L[r][c0 + i] + (c0 + i == r ? add : 0.0);
-      raw[i] = 0.0;
-      diag[i] = 1.0;
-    }
-    bool bad = false;
-    for (int jb = 0; jb < 4; ++jb) {
+      for (int u = 0; u < kPer; ++u)
+        if (u + 1 < kPer || NT * u + 64 * wave < kEntries) {   // wave-uniform; the last lanes' repeats are dropped below
+          const int e = min(t + NT * u, kEntries - 1);
 #pragma unroll
-      for (int ji = 0; ji < kCpt; ++ji) {
-        const int j = kCpt * jb + ji;
-        double* col = colb[ji & 1][h];
-        if ((q & 3) == jb) col[r] = a[ji];
-        __syncthreads();
-        double d = col[j];
-        if (!(d > 0.0)) { bad = true; d = 1.0; }
-        const double f = div_refined(col[r], d);
-        if ((q & 3) == jb) {
-          raw[ji] = a[ji];
-          diag[ji] = d;
+          for (int i = 0; i < FX; ++i) vx[u][i] = x0 + i < S_X ? load(1, e, row[u], col[u], x0 + i) : 0.0;
+#pragma unroll
+          for (int i = 0; i < FW; ++i) vw[u][i] = w0 + i < S_W ? load(0, e, row[u], col[u], w0 + i) : 0.0;
         }
 #pragma unroll
-        for (int i = 0; i < kCpt; ++i) a[i] = fma(-f, col[c0 + i], a[i]);
+      for (int u = 0; u < kPer; ++u) {
+#pragma unroll
+        for (int i = 0; i < FX; ++i) acc[1][u] += vx[u][i];
+#pragma unroll
+        for (int i = 0; i < FW; ++i) acc[0][u] += vw[u][i];
       }
     }
-    __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kCpt; ++i) {
-      const double root = sqrt(diag[i]);
-      L[r][c0 + i] = r > c0 + i ? raw[i] / root : (r == c0 + i ? root : 0.0);
+    for (int h = 0; h < 2; ++h) {
+      matrix_t& L = h ? LX : LW;
+#pragma unroll
+      for (int u = 0; u < kPer; ++u)
+        if (t + NT * u < kEntries) {
+          const double m = finish(h, acc[h][u]);
+          L[row[u]][col[u]] = m;
+          L[col[u]][row[u]] = m;
+        }
     }
-    if (MODE == 0 && __any(bad) && (t & 63) == 0) atomicExch(status, 1);
   }
   __syncthreads();
-  // ---- A = W'^T X':  A[i][j] = sum_k W'[k][i] X'[k][j], stored by columns
-  {
-    double acc[kOut];
+  // ---- damping and Cholesky (lower), the first wavefront M_W, the second M_X.  Lane q owns row q / kLpr, columns kCpl (q % kLpr) ... of its
+  // matrix.  Step j publishes column j of what is left (in place of row j of the matrix, which is read no more); with d its diagonal entry,
+  // entry (r, c) loses col[r] col[c] / d, and column j of the factor is col / sqrt(d), formed at the end.
+  if (wave < 2) {
+    constexpr int kLpr = 64 / D, kCpl = D / kLpr;
+    matrix_t& L = wave ? LX : LW;
+    const int r = lane / kLpr, g = lane % kLpr, c0 = kCpl * g;
+    double a[kCpl];
+    double tr = row_sum(L[l16][l16]);
+    if constexpr (D == 32) tr += row_sum(L[16 + l16][16 + l16]);
+    const double add = lambda * tr / (double)D;
 #pragma unroll
-    for (int u = 0; u < kOut; ++u) acc[u] = 0.0;
-#pragma unroll 4
-    for (int k = 0; k < D; ++k) {
+    for (int i = 0; i < kCpl; i += 2) {
+      const v2d m = *reinterpret_cast<const v2d*>(&L[r][c0 + i]);
+      a[i] = m[0] + (c0 + i == r ? add : 0.0);
+      a[i + 1] = m[1] + (c0 + i + 1 == r ? add : 0.0);
+    }
+    wave_lds_sync();
+    // column j as its owners have it up to date; the rest of what column j - 1 changes comes through LDS one step behind
+    double now = a[0];
 #pragma unroll
-      for (int u = 0; u < kOut; ++u) {
-        const int o = t + NT * u;
-        acc[u] = fma(LW[k][o % D], LX[k][o / D], acc[u]);   // zeros above the diagonals
+    for (int jb = 0; jb < kLpr; ++jb) {
+#pragma unroll
+      for (int ji = 0; ji < kCpl; ++ji) {
+        const int j = kCpl * jb + ji;
+        if (g == jb) L[j][r] = now;
+        wave_lds_sync();
+        double d = readlane_f64(now, kLpr * j + jb);
+        d = d > 0.0 ? d : 1.0;
+        // the row's entry of column j, from the lane of the row that has it
+        const double mine = kLpr == 2 ? (jb ? dpp_f64<0xF5>(now) : dpp_f64<0xA0>(now))
+                                      : (jb == 0 ? dpp_f64<0x00>(now) : jb == 1 ? dpp_f64<0x55>(now) : jb == 2 ? dpp_f64<0xAA>(now) : dpp_f64<0xFF>(now));
+        const double f = div_refined(mine, d);
+        if (j + 1 < D) {
+          const double pivot_row = readlane_f64(now, kLpr * (j + 1) + jb);
+          if (ji + 1 < kCpl) now = fma(-f, pivot_row, a[ji + 1]);
+#pragma unroll
+          for (int i = 0; i < kCpl; i += 2) {
+            if (jb == kLpr - 1 && i + 1 <= ji + 1) continue;   // columns that are done
+            const v2d m = *reinterpret_cast<const v2d*>(&L[j][c0 + i]);
+            a[i] = fma(-f, m[0], a[i]);
+            a[i + 1] = fma(-f, m[1], a[i + 1]);
+          }
+          if (ji + 1 == kCpl) now = a[0];
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-#pragma unroll
-    for (int u = 0; u < kOut; ++u) A[(t + NT * u) / D][(t + NT * u) % D] = acc[u];
   }
-  if (V0) {   // the same for the whole workgroup
+  __syncthreads();
+  if (t < 2 * D) {
+    double d = (t / D ? LX : LW)[t % D][t % D];
+    const bool bad = !(d > 0.0);
+    if (bad) d = 1.0;
+    const double root = sqrt(d);
+    diag[t / D][t % D] = root;
+    inv_root[t / D][t % D] = 1.0 / root;
+    if (MODE == 0 && __any(bad) && lane == 0) atomicExch(status, 1);
+  }
+  __syncthreads();
 #pragma unroll
-    for (int u = 0; u < kOut; ++u) U[(t + NT * u) / D][(t + NT * u) % D] = V0[t + NT * u];
+  for (int u = 0; u < 2 * D * D / NT; ++u) {
+    const int e = t + NT * u, h = e / (D * D), j = e / D % D, r = e % D;
+    matrix_t& L = h ? LX : LW;
+    const double raw = L[j][r], root = diag[h][j], inv = inv_root[h][j], q = raw * inv;
+    L[j][r] = r > j ? fma(fma(-root, q, raw), inv, q) : (r == j ? root : 0.0);
+  }
+  if (V0) {
+#pragma unroll
+    for (int u = 0; u < D * D / NT; ++u) U[(t + NT * u) % D][(t + NT * u) / D] = v0[u];
+  }
+  __syncthreads();
+  // ---- A = W'^T X':  A[j][i] = sum_k X'[k][j] W'[k][i]
+  if (tiles) {
+    const v4d a = product_tile<D>(LX, i0, LW, j0, zero);
+    put(V0 ? scratch[1] : A, a);
+  }
+  if (V0) {
     __syncthreads();
-    double acc[kOut];
-#pragma unroll
-    for (int u = 0; u < kOut; ++u) acc[u] = 0.0;
-#pragma unroll 4
-    for (int k = 0; k < D; ++k) {
-#pragma unroll
-      for (int u = 0; u < kOut; ++u) acc[u] = fma(A[k][(t + NT * u) % D], U[k][(t + NT * u) / D], acc[u]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < kOut; ++u) A[(t + NT * u) / D][(t + NT * u) % D] = acc[u];
+    if (tiles) put(A, product_tile<D, true>(U, i0, scratch[1], j0, zero));
   }
   __syncthreads();
   // ---- columns of A made orthogonal by right rotations: A V = U S
   orthogonalize_group<D>(A, scratch[0], scratch[1], scratch[2], norm2, votes, V0 == nullptr);
   __syncthreads();
-  const int pr = t / 16, sub = t % 16;                 // column; rows kRpl sub ... of it
-  // ---- singular values, descending order, U with the sign convention (16 lanes per column)
-  for (int c = pr; c < D; c += NT / 16) {
-    double n2 = 0.0;
+  // ---- singular values, descending order, U with the sign convention (16 lanes per column, two columns one after the other)
+  {
+    constexpr int kGroups = NT / 16;
+    static_assert(D == 2 * kGroups, "two columns per 16 lanes");
+    const int pr = t / 16, sub = t % 16;               // column; rows kRpl sub ... of it
+    double x[2][kRpl], s[2];
 #pragma unroll
-    for (int i = 0; i < kRpl; ++i) n2 = fma(A[c][kRpl * sub + i], A[c][kRpl * sub + i], n2);
-    n2 = row_sum(n2);
-    if (sub == 0) sv[c] = sqrt(n2);
-  }
-  __syncthreads();
-  if (t < D) {
-    const double mine = sv[t];
-    int rank = 0;
-    for (int k = 0; k < D; ++k) rank += (sv[k] > mine) || (sv[k] == mine && k < t);
-    order[rank] = t;
-    ssort[rank] = mine;
-  }
-  __syncthreads();
-  for (int c = pr; c < D; c += NT / 16) {
-    const int src = order[c];
-    const double s = ssort[c];
-    double v[kRpl], best = 0.0;
+    for (int u = 0; u < 2; ++u) {
+      const int c = pr + kGroups * u;
+      double n2 = 0.0, best = 0.0;
 #pragma unroll
-    for (int i = 0; i < kRpl; ++i) {
-      v[i] = A[src][kRpl * sub + i] / s;
-      best = fmax(best, fabs(v[i]));
+      for (int i = 0; i < kRpl; ++i) {
+        x[u][i] = A[c][kRpl * sub + i];
+        n2 = fma(x[u][i], x[u][i], n2);
+      }
+      s[u] = sqrt(row_sum(n2));
+      if (sub == 0) sv[c] = s[u];
+#pragma unroll
+      for (int i = 0; i < kRpl; ++i) {
+        x[u][i] /= s[u];
+        best = fmax(best, fabs(x[u][i]));
+      }
+      best = row_max(best);
+      int first = 1 << 20;                             // 2 row + sign bit of the first row of largest magnitude
+#pragma unroll
+      for (int i = kRpl - 1; i >= 0; --i)
+        if (fabs(x[u][i]) == best) first = 2 * (kRpl * sub + i) + (x[u][i] < 0.0);
+      first = row_min(first);
+#pragma unroll
+      for (int i = 0; i < kRpl; ++i) x[u][i] = (first & 1) ? -x[u][i] : x[u][i];
     }
-    best = row_max(best);
-    int first = 1 << 20;                               // 2 row + sign bit of the first row of largest magnitude
+    __syncthreads();
 #pragma unroll
-    for (int i = kRpl - 1; i >= 0; --i)
-      if (fabs(v[i]) == best) first = 2 * (kRpl * sub + i) + (v[i] < 0.0);
-    first = row_min(first);
+    for (int u = 0; u < 2; ++u) {
+      const int c = pr + kGroups * u;
+      int rank = 0;
 #pragma unroll
-    for (int i = 0; i < kRpl; ++i) U[kRpl * sub + i][c] = (first & 1) ? -v[i] : v[i];
+      for (int i = 0; i < kRpl; ++i) {
+        const int k = kRpl * sub + i;
+        rank += (sv[k] > s[u]) || (sv[k] == s[u] && k < c);
+      }
+      rank = row_sum_int(rank);
+      if (sub == 0) ssort[rank] = MODE == 1 ? 1.0 / s[u] : 1.0 / sqrt(s[u]);
+#pragma unroll
+      for (int i = 0; i < kRpl; ++i) U[rank][kRpl * sub + i] = x[u][i];
+    }
+  }
+  __syncthreads();
+  // ---- U^T W'^T, row i times s_i^-1/2 (B), or s_i^-1
+  if (tiles) {
+    v4d b = product_tile<D, true>(U, i0, LW, j0, zero);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) b[v] *= ssort[i0 + l4 + 4 * v];
+    put(A, b);
   }
   __syncthreads();
   if constexpr (MODE == 1) {
-    // V = A^T U S^-1 = X'^T (W' U) S^-1, made orthogonal to FP64 accuracy by one Newton-Schulz step
-    // V (3 I - V^T V) / 2; the identity if it is not close to orthogonal (a singular moment)
-    auto product = [&](auto left, auto right, double (&acc)[kOut]) {
-#pragma unroll
-      for (int u = 0; u < kOut; ++u) acc[u] = 0.0;
-#pragma unroll 4
-      for (int k = 0; k < D; ++k) {
-#pragma unroll
-        for (int u = 0; u < kOut; ++u) acc[u] = fma(left((t + NT * u) / D, k), right(k, (t + NT * u) % D), acc[u]);
-      }
-    };
-    double acc[kOut], v[kOut];
-    product([&](int r, int k) { return LW[r][k]; }, [&](int k, int c) { return U[k][c]; }, acc);
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < kOut; ++u) A[(t + NT * u) / D][(t + NT * u) % D] = acc[u] / ssort[(t + NT * u) % D];
-    __syncthreads();
-    product([&](int r, int k) { return LX[k][r]; }, [&](int k, int c) { return A[k][c]; }, v);
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < kOut; ++u) U[(t + NT * u) / D][(t + NT * u) % D] = v[u];
+    // V = A^T U S^-1 = X'^T (S^-1 U^T W'^T)^T, made orthogonal to FP64 accuracy by one Newton-Schulz step
+    // V (3 I - V^T V) / 2; the identity if it is not close to orthogonal (a singular moment).  V^T all along.
+    v4d x, e;
     if (t == 0) votes[0] = 0;
-    __syncthreads();
-    product([&](int r, int k) { return U[k][r]; }, [&](int k, int c) { return U[k][c]; }, acc);
-#pragma unroll
-    for (int u = 0; u < kOut; ++u) {
-      const int r = (t + NT * u) / D, c = (t + NT * u) % D;
-      if (!(fabs(acc[u] - (r == c ? 1.0 : 0.0)) < 1e-3)) votes[0] = 1;
-      LW[r][c] = acc[u];
+    if (tiles) {
+      x = product_tile<D>(A, i0, LX, j0, zero);        // V^T[c][r] = sum_k (W' U S^-1)[k][c] X'[k][r]
+      put(U, x);
     }
     __syncthreads();
-    product([&](int r, int k) { return U[r][k]; }, [&](int k, int c) { return LW[k][c]; }, acc);
+    if (tiles) {
+      e = product_tile<D>(U, i0, U, j0, zero);
 #pragma unroll
-    for (int u = 0; u < kOut; ++u) {
-      const int r = (t + NT * u) / D, c = (t + NT * u) % D;
-      V_out[t + NT * u] = votes[0] ? (r == c ? 1.0 : 0.0) : 1.5 * v[u] - 0.5 * acc[u];
+      for (int v = 0; v < 4; ++v) {
+        const double one = i0 + l4 + 4 * v == j0 + l16 ? 1.0 : 0.0;
+        if (!(fabs(e[v] - one) < 1e-3)) votes[0] = 1;
+        e[v] = fma(-0.5, e[v], 1.5 * one);
+      }
+      put(scratch[1], e);
+    }
+    __syncthreads();
+    if (tiles) {
+      x = product_tile<D, true>(scratch[1], i0, U, j0, zero);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int c = i0 + l4 + 4 * v, r = j0 + l16;
+        V_out[r * D + c] = votes[0] ? (r == c ? 1.0 : 0.0) : x[v];
+      }
     }
     return;
   }
-  // ---- B = diag(s^-1/2) U^T W'^T :  B[i][k] = s_i^-1/2 sum_m U[m][i] W'[k][m]
-  {
-    double acc[kOut];
-#pragma unroll
-    for (int u = 0; u < kOut; ++u) acc[u] = 0.0;
-#pragma unroll 4
-    for (int m = 0; m < D; ++m) {                      // W' is zero past its diagonal
-#pragma unroll
-      for (int u = 0; u < kOut; ++u) {
-        const int o = t + NT * u;
-        acc[u] = fma(U[m][o / D], LW[o % D][m], acc[u]);
-      }
-    }
-    // A's columns are read no more: B[i][k] goes to A[i][k]
-#pragma unroll
-    for (int u = 0; u < kOut; ++u) {
-      const int o = t + NT * u;
-      A[o / D][o % D] = acc[u] / sqrt(ssort[o / D]);
-    }
-  }
-  __syncthreads();
   // ---- T = H B with the normalized Sylvester matrix H[j][i] = (-1)^popcount(j & i) / sqrt(D)
-  const double hn = 1.0 / sqrt((double)D);
-  double acc[kOut];
+  if (tiles) {
+    constexpr int kPer = D / 4;
+    const double hn = 1.0 / sqrt((double)D);
+    v4d acc = zero;
 #pragma unroll
-  for (int u = 0; u < kOut; ++u) acc[u] = 0.0;
-#pragma unroll 4
-  for (int i = 0; i < D; ++i) {
-#pragma unroll
-    for (int u = 0; u < kOut; ++u) {
-      const int o = t + NT * u;
-      const double b = A[i][o % D];
-      acc[u] += (__popc((o / D) & i) & 1) ? -b : b;
+    for (int k = 0; k < kPer; ++k) {
+      const int i = kPer * l4 + k;
+      const double sign = (__popc((i0 + l16) & i) & 1) ? -1.0 : 1.0;
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(sign, A[i][j0 + l16], acc, 0, 0, 0);
     }
-  }
 #pragma unroll
-  for (int u = 0; u < kOut; ++u) {
-    const int o = t + NT * u;
-    const double v = acc[u] * hn;
-    const uint16_t bits = f64_to_bf16_bits(v);
-    T_bits[o] = bits;
-    if (T_f64) T_f64[o] = v;
+    for (int v = 0; v < 4; ++v) {
+      const int o = (i0 + l4 + 4 * v) * D + j0 + l16;
+      const double x = acc[v] * hn;
+      T_bits[o] = f64_to_bf16_bits(x);
+      if (T_f64) T_f64[o] = x;
+    }
   }
 }
 
