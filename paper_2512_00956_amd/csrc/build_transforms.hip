@@ -129,7 +129,8 @@ __global__ __launch_bounds__(256) void wush_block_kernel(const double* __restric
   // the partial moments are added in a fixed order and normalized
   auto load = [&](int half, int e, int, int, int s) { return partial[(((int64_t)half * S + s) * C + b) * kMomentSize + e]; };
   auto finish = [&](int half, double sum) { return sum * (1.0 / (double)(half ? Mc : N)); };
-  wush_block_group<32, 0, 16, 16>(load, finish, S_W, S_X, lambda, nullptr, T_out + (int64_t)b * 1024,
+  __shared__ BlockShared<32> sh;
+  wush_block_group<32, 0, 16, 16>(sh, load, finish, S_W, S_X, lambda, nullptr, T_out + (int64_t)b * 1024,
                           T_f64 ? T_f64 + (int64_t)b * 1024 : nullptr, nullptr, status);
 }
 
@@ -143,7 +144,8 @@ __global__ __launch_bounds__(128) void wush_block16_kernel(const double* __restr
     return partial[(((int64_t)half * S + s) * C + b32) * kMomentSize + off + e];
   };
   auto finish = [&](int half, double sum) { return sum * (1.0 / (double)(half ? Mc : N)); };
-  wush_block_group<16, 0, 16, 16>(load, finish, S_W, S_X, lambda, nullptr, T_out + (int64_t)b * 256,
+  __shared__ BlockShared<16> sh;
+  wush_block_group<16, 0, 16, 16>(sh, load, finish, S_W, S_X, lambda, nullptr, T_out + (int64_t)b * 256,
                           T_f64 ? T_f64 + (int64_t)b * 256 : nullptr, nullptr, status);
 }
 

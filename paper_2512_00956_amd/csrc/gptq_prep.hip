@@ -273,7 +273,8 @@ __global__ __launch_bounds__(256) void gptq_warm_kernel(const double* __restrict
     return half ? MX[(int64_t)b * 1024 + r * 32 + c] : partial[((int64_t)b * splits + s) * kMomentSize + e];
   };
   auto finish = [&](int half, double sum) { return half ? sum : sum / (double)N; };
-  wush_block_group<32, 1, kWarmSplits, 1>(load, finish, splits, 1, lambda, nullptr, nullptr, nullptr, V0 + (int64_t)b * 1024, nullptr);
+  __shared__ BlockShared<32> sh;
+  wush_block_group<32, 1, kWarmSplits, 1>(sh, load, finish, splits, 1, lambda, nullptr, nullptr, nullptr, V0 + (int64_t)b * 1024, nullptr);
 }
 
 // What the sums S_l still lack travels in groups of kGroup blocks: S is N x K doubles, and adding every block's error to
@@ -307,17 +308,91 @@ __global__ __launch_bounds__(256) void gptq_chain_kernel(const double* __restric
                                                          const double* __restrict__ MX_i, double lambda,
                                                          const double* __restrict__ V0_i, uint16_t* __restrict__ T_bits_i,
                                                          int given, const double* __restrict__ U, double* __restrict__ S,
-                                                         int row_groups, int* __restrict__ status) {
+                                                         int row_groups, double* __restrict__ Tinv, double* __restrict__ R,
+                                                         int* __restrict__ status) {
+  extern __shared__ __attribute__((aligned(16))) double smem[];   // workgroup 0: BlockShared; others [block][pair of operand registers][lane][2]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, l4 = lane >> 4;
   if (blockIdx.x == 0) {
-    if (given) return;
+    BlockShared<32>& sh = *reinterpret_cast<BlockShared<32>*>(smem);
     __builtin_amdgcn_s_setprio(3);   // ahead of wavefronts that may share its compute unit
+    const int t = threadIdx.x, i0 = 16 * (wave >> 1), j0 = 16 * (wave & 1);
+    double u[4];                     // U_ii, fetched ahead
+#pragma unroll
+    for (int q = 0; q < 4; ++q) u[q] = U[(int64_t)(32 * i + (t >> 5) + 8 * q) * K + 32 * i + (t & 31)];
     auto load = [&](int half, int e, int r, int c, int s) { return half ? MX_i[r * 32 + c] : partial[(int64_t)s * kMomentSize + e]; };
     auto finish = [&](int half, double sum) { return half ? sum : sum / (double)N; };
-    wush_block_group<32, 0, kChainFlight, 1>(load, finish, splits, 1, lambda, V0_i, T_bits_i, nullptr, nullptr, status);
+    double (*T)[34] = sh.scratch[1], (*Um)[34] = sh.scratch[2], (*B)[34] = sh.scratch[0], (*Hb)[34] = sh.LX;
+    if (!given) {
+      wush_block_group<32, 0, kChainFlight, 1>(sh, load, finish, splits, 1, lambda, V0_i, T_bits_i, nullptr, nullptr, status);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) T[(t >> 5) + 8 * q][t & 31] = (double)bf16_bits_to_f32(T_bits_i[t + 256 * q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) Um[(t >> 5) + 8 * q][t & 31] = u[q];
+    __syncthreads();
+    // R = the inverse of the reverse factor of Hbar = B B^T, B = T_i U_ii, and inv(T_i) = U_ii B^T inv(Hbar) = (U_ii B^T R^T) R, which
+    // squares the condition of B, and a Newton step X (2 I - T_i X) or two, which bring it back; should they not start close
+    // enough, by elimination.  (Elimination always, beside R's: 1200 cycles a step of 32, 16 us a block.)
+    const v4d zero = {0, 0, 0, 0};
+    auto put = [&](double (*m)[34], const v4d& x) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) m[i0 + l4 + 4 * v][j0 + l16] = x[v];
+    };
+    double (*Q)[34] = sh.A, (*Rm)[34] = Um, (*Z)[34] = B;
+    put(B, product_tile<32, true>(T, i0, Um, j0, zero));
+    __syncthreads();
+    put(Hb, product_tile<32>(B, i0, B, j0, zero));
+    put(Q, product_tile<32>(Um, i0, B, j0, zero));
+    __syncthreads();
+    if (t < 8) sh.votes[t] = 0;
+    const bool definite = reverse_factor_group([&](int r, int c) { return Hb[r][c]; }, [](int, int, double) {},
+                                               [&](int r, int c, double x) {
+                                                 Rm[r][c] = x;
+                                                 R[32 * r + c] = x;
+                                               });
+    if (!definite && t == 0) atomicExch(status, 1);
+    __syncthreads();
+    put(Z, product_tile<32>(Q, i0, Rm, j0, zero));
+    __syncthreads();
+    double (*X)[34] = sh.LW, (*E)[34] = sh.LX, (*other)[34] = sh.A;
+    put(X, product_tile<32, true>(Z, i0, Rm, j0, zero));
+    __syncthreads();
+    bool close = false;
+    for (int newton = 0; newton < 4 && !close; ++newton) {
+      v4d e = product_tile<32, true>(T, i0, X, j0, zero);
+      bool far = false, lost = false;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const double one = i0 + l4 + 4 * v == j0 + l16 ? 1.0 : 0.0, off = fabs(e[v] - one);
+        far |= off > 1e-9;           // squared by the step, 32 terms at most: far below rounding
+        lost |= !(off < 1e-2);
+        e[v] = 2.0 * one - e[v];
+      }
+      put(E, e);
+      if (far) sh.votes[newton] = 1;
+      if (lost) sh.votes[4 + newton] = 1;
+      __syncthreads();
+      if (sh.votes[4 + newton]) break;
+      close = !sh.votes[newton];
+      const v4d x = product_tile<32, true>(X, i0, E, j0, zero);
+      if (close) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) Tinv[32 * (i0 + l4 + 4 * v) + j0 + l16] = x[v];
+      } else {
+        put(other, x);
+        double (*swap)[34] = X;
+        X = other;
+        other = swap;
+        __syncthreads();
+      }
+    }
+    if (!close) {
+      const bool good = invert_block_group<32>([&](int r, int c) { return T[r][c]; }, [&](int r, int c, double v) { Tinv[32 * r + c] = v; });
+      if (!good && t == 0) atomicExch(status, 1);
+    }
     return;
   }
-  extern __shared__ __attribute__((aligned(16))) double smem[];   // [block][pair of operand registers][lane][2]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, l4 = lane >> 4;
   const int g = ((int)blockIdx.x - 1) % row_groups;
   const Pending job = pending_of(i, K >> 5, ((int)blockIdx.x - 1) / row_groups);
   const int nb = job.hi - job.lo;
@@ -363,46 +438,6 @@ __global__ __launch_bounds__(256) void gptq_chain_kernel(const double* __restric
     }
     if (16 * t + l16 < N) store8(sum + here, s);
   }
-}
-
-// From T_i (BF16) and U_ii: workgroup 0 inv(T_i), workgroup 1 R = inverse of the reverse Cholesky factor of
-// Hbar = (T_i U_ii)(T_i U_ii)^T.
-__global__ __launch_bounds__(256) void gptq_block_mats_kernel(const uint16_t* __restrict__ T, const double* __restrict__ U,
-                                                              int K, int i, double* __restrict__ Tinv,
-                                                              double* __restrict__ R, int* __restrict__ status) {
-  const int t = threadIdx.x;
-  if (blockIdx.x == 0) {
-    const bool good = invert_block_group<32>([&](int r, int c) { return (double)bf16_bits_to_f32(T[32 * r + c]); },
-                                             [&](int r, int c, double v) { Tinv[32 * r + c] = v; });
-    if (!good && t == 0) atomicExch(status, 1);
-    return;
-  }
-  __shared__ double Tm[32][33], Um[32][33], B[32][33];
-  for (int o = t; o < 1024; o += 256) {
-    Tm[o >> 5][o & 31] = (double)bf16_bits_to_f32(T[o]);
-    Um[o >> 5][o & 31] = U[(int64_t)(32 * i + (o >> 5)) * K + 32 * i + (o & 31)];
-  }
-  __syncthreads();
-  double acc[4] = {};
-#pragma unroll 4
-  for (int m = 0; m < 32; ++m)
-#pragma unroll
-    for (int u = 0; u < 4; ++u) acc[u] = fma(Tm[(t >> 5) + 8 * u][m], Um[m][t & 31], acc[u]);
-#pragma unroll
-  for (int u = 0; u < 4; ++u) B[(t >> 5) + 8 * u][t & 31] = acc[u];
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < 4; ++u) acc[u] = 0.0;
-#pragma unroll 4
-  for (int m = 0; m < 32; ++m)
-#pragma unroll
-    for (int u = 0; u < 4; ++u) acc[u] = fma(B[(t >> 5) + 8 * u][m], B[t & 31][m], acc[u]);
-#pragma unroll
-  for (int u = 0; u < 4; ++u) Tm[(t >> 5) + 8 * u][t & 31] = acc[u];
-  __syncthreads();
-  const bool good = reverse_factor_group([&](int r, int c) { return Tm[r][c]; }, [](int, int, double) {},
-                                         [&](int r, int c, double v) { R[32 * r + c] = v; });
-  if (!good && t == 0) atomicExch(status, 1);
 }
 
 // One element of the GPTQ subroutine: code of v at the group's scale (in float range: through the hardware converts, which
@@ -662,7 +697,8 @@ hipError_t launch_gptq_prep(const void* W, int64_t N, int64_t K, int64_t ldw, co
   static DynamicLdsLimit rows_lds;
   hipError_t attr = rows_lds.ensure(reinterpret_cast<const void*>(gptq_rows_kernel), (int)sizeof(RowShared));
   if (attr != hipSuccess) return attr;
-  constexpr int kChainLds = kMostPending * 1024 * (int)sizeof(double);
+  constexpr int kPendingLds = kMostPending * 1024 * (int)sizeof(double), kBlockLds = (int)sizeof(BlockShared<32>);
+  constexpr int kChainLds = kPendingLds > kBlockLds ? kPendingLds : kBlockLds;
   static DynamicLdsLimit chain_lds;
   attr = chain_lds.ensure(reinterpret_cast<const void*>(gptq_chain_kernel), kChainLds);
   if (attr != hipSuccess) return attr;
@@ -691,9 +727,7 @@ hipError_t launch_gptq_prep(const void* W, int64_t N, int64_t K, int64_t ldw, co
       if (columns > 0 && row_groups < 1) row_groups = 1;
       gptq_chain_kernel<<<(unsigned)(1 + columns * row_groups), 256, kChainLds, st>>>(
           partial, splits, Ni, Ki, i, MX + (int64_t)i * 1024, lambda, V0 ? V0 + (int64_t)i * 1024 : nullptr,
-          Tbits + (int64_t)i * 1024, transform_given, U, S, row_groups, status);
-      WUSH_GPTQ_CHECK()
-      gptq_block_mats_kernel<<<2, 256, 0, st>>>(Tbits + (int64_t)i * 1024, U, Ki, i, Tinv, R, status);
+          Tbits + (int64_t)i * 1024, transform_given, U, S, row_groups, Tinv, R, status);
       WUSH_GPTQ_CHECK()
     }
     gptq_rows_kernel<<<(unsigned)splits, 64 * kRowWaves, sizeof(RowShared), st>>>(Wb, ldw, Ni, Ki, i, S, U, Vd,

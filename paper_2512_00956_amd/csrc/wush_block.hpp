@@ -178,6 +178,12 @@ __device__ __forceinline__ bool reverse_factor_group(EntryFn entry, StoreUFn sto
   return good;
 }
 
+// x / root from the root's reciprocal, corrected.
+__device__ __forceinline__ double over_root(double x, double root, double inv) {
+  const double q = x * inv;
+  return fma(fma(-root, q, x), inv, q);
+}
+
 // One sweep of one-sided Jacobi over the columns of A (A[column][row], D = 32 or 16) by the first 4 D of a workgroup's 8 D threads (for
 // D = 32 all of them call it, the barriers are everybody's; for D = 16 the first wavefront alone).
 //
@@ -519,25 +525,37 @@ __device__ __forceinline__ void lower16_at(int e, int& r, int& c) {
 //
 // A block is one chain of dependent steps (2 x D columns of the factors, the SVD's sweeps and steps), so what counts is the
 // latency of each.  The factors are taken by a wavefront each, without a barrier: a lane has D^2 / 64 entries of a row in registers, a
-// step's pivot goes to everybody through the scalar registers, its column through LDS.  Products are on the FP64 MFMA, a tile per wavefront.
+// step's pivot goes to everybody through the scalar registers, its column through LDS; the registers are shifted so that the loop stays a loop
+// (unrolled over the columns it took 290 cycles a step, bound by instruction fetch).  Products are on the FP64 MFMA, a tile per wavefront.
 // c2 layer, 128 blocks: 83 us with Jacobi to the end, products and factors by all threads with a barrier per column; now 61, half of it the SVD.
+template <int N>
+struct Count { static constexpr int value = N; };
+
+template <int D>
+struct __attribute__((aligned(16))) BlockShared {
+  typedef double matrix_t[D][D + 2];
+  matrix_t LW;          // M_W, then W'^T: LW[column][row]
+  matrix_t LX;          // M_X, then X'^T
+  matrix_t A;           // columns of W'^T X', then of U S: A[column][row]; then B
+  matrix_t scratch[3];  // [0]: V0^T, at the end U sorted and sign-normalized, U[column][row]; [1]: T as rounded to BF16 (MODE 0)
+  double diag[2][D], inv_root[2][D];
+  double norm2[D], sv[D], ssort[D];
+  int votes[8];
+};
 template <int D, int MODE, int FW, int FX, class LoadFn, class FinishFn>
-__device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, int S_W, int S_X, double lambda,
+__device__ __forceinline__ void wush_block_group(BlockShared<D>& sh, LoadFn load, FinishFn finish, int S_W, int S_X, double lambda,
                                                  const double* __restrict__ V0, uint16_t* __restrict__ T_bits,
                                                  double* __restrict__ T_f64, double* __restrict__ V_out,
                                                  int* __restrict__ status) {
   static_assert(D == 32 || D == 16, "block size");
   constexpr int NT = 8 * D;
   constexpr int kRpl = D / 16;           // rows of a column per lane, 16 lanes per column
-  typedef double matrix_t[D][D + 2];
-  __shared__ __attribute__((aligned(16))) matrix_t LW;          // M_W, then W'^T: LW[column][row]
-  __shared__ __attribute__((aligned(16))) matrix_t LX;          // M_X, then X'^T
-  __shared__ __attribute__((aligned(16))) matrix_t A;           // columns of W'^T X', then of U S: A[column][row]; then B
-  __shared__ __attribute__((aligned(16))) matrix_t scratch[3];  // [0]: V0^T, at the end U sorted and sign-normalized, U[column][row]
-  __shared__ double diag[2][D], inv_root[2][D];
-  __shared__ double norm2[D], sv[D], ssort[D];
-  __shared__ int votes[8];
-  matrix_t& U = scratch[0];
+  typedef typename BlockShared<D>::matrix_t matrix_t;
+  matrix_t &LW = sh.LW, &LX = sh.LX, &A = sh.A, &U = sh.scratch[0];
+  matrix_t (&scratch)[3] = sh.scratch;
+  double (&diag)[2][D] = sh.diag, (&inv_root)[2][D] = sh.inv_root;
+  double (&norm2)[D] = sh.norm2, (&sv)[D] = sh.sv, (&ssort)[D] = sh.ssort;
+  int (&votes)[8] = sh.votes;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, l16 = lane & 15, l4 = lane >> 4;
   // this wavefront's tile of the products (one tile for D = 16: the first wavefront's)
   const bool tiles = D == 32 || wave == 0;
@@ -603,54 +621,64 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
     }
   }
   __syncthreads();
-  // ---- damping and Cholesky (lower), the first wavefront M_W, the second M_X.  Lane q owns row q / kLpr, columns kCpl (q % kLpr) ... of its
+  // ---- damping and Cholesky (lower), the first wavefront M_W, the second M_X.  Lane q owns row q / kLpr, columns q % kLpr, + kLpr, ... of its
   // matrix.  Step j publishes column j of what is left (in place of row j of the matrix, which is read no more); with d its diagonal entry,
   // entry (r, c) loses col[r] col[c] / d, and column j of the factor is col / sqrt(d), formed at the end.
   if (wave < 2) {
     constexpr int kLpr = 64 / D, kCpl = D / kLpr;
     matrix_t& L = wave ? LX : LW;
-    const int r = lane / kLpr, g = lane % kLpr, c0 = kCpl * g;
-    double a[kCpl];
+    double* window = &scratch[wave][0][0];             // column j by the lanes that read it: row r at (r % kLpr) 2 kCpl + r / kLpr
+    const int r = lane / kLpr, g = lane % kLpr;
+    double* const at = window + 2 * kCpl * (r % kLpr) + r / kLpr;
+    double a[kCpl + 1], m[kCpl], f = 0.0;
     double tr = row_sum(L[l16][l16]);
     if constexpr (D == 32) tr += row_sum(L[16 + l16][16 + l16]);
     const double add = lambda * tr / (double)D;
 #pragma unroll
-    for (int i = 0; i < kCpl; i += 2) {
-      const v2d m = *reinterpret_cast<const v2d*>(&L[r][c0 + i]);
-      a[i] = m[0] + (c0 + i == r ? add : 0.0);
-      a[i + 1] = m[1] + (c0 + i + 1 == r ? add : 0.0);
+    for (int i = 0; i < kCpl; ++i) {
+      a[i + 1] = L[r][kLpr * i + g] + (kLpr * i + g == r ? add : 0.0);
+      m[i] = 0.0;
     }
+    a[0] = 0.0;
     wave_lds_sync();
-    // column j as its owners have it up to date; the rest of what column j - 1 changes comes through LDS one step behind
-    double now = a[0];
+    double now = a[1];
+    // steps j = kLpr q ... + kLpr - 1, SIZE registers of columns still to do.  What step j takes off them is taken off in step j + 1, beside
+    // that one's quotient; behind the last owner's with a shift.
+    auto steps = [&](int q, auto size) {
+      constexpr int SIZE = decltype(size)::value;
+      const double* mine_at = window + 2 * kCpl * g + q;
 #pragma unroll
-    for (int jb = 0; jb < kLpr; ++jb) {
-#pragma unroll
-      for (int ji = 0; ji < kCpl; ++ji) {
-        const int j = kCpl * jb + ji;
-        if (g == jb) L[j][r] = now;
+      for (int o = 0; o < kLpr; ++o) {
+        const int j = kLpr * q + o;
+        if (g == o) {
+          L[j][r] = now;
+          *at = now;
+        }
         wave_lds_sync();
-        double d = readlane_f64(now, kLpr * j + jb);
+        double fetched[SIZE];
+#pragma unroll
+        for (int i = 0; i < SIZE; ++i) fetched[i] = mine_at[i];
+#pragma unroll
+        for (int i = 0; i < SIZE; ++i) {
+          if (o > 0) a[i] = fma(-f, m[i], a[i]);
+          else a[i] = i + 1 < kCpl ? fma(-f, m[i + 1], a[i + 1]) : a[i + 1];
+        }
+        double d = readlane_f64(now, kLpr * j + o);
         d = d > 0.0 ? d : 1.0;
         // the row's entry of column j, from the lane of the row that has it
-        const double mine = kLpr == 2 ? (jb ? dpp_f64<0xF5>(now) : dpp_f64<0xA0>(now))
-                                      : (jb == 0 ? dpp_f64<0x00>(now) : jb == 1 ? dpp_f64<0x55>(now) : jb == 2 ? dpp_f64<0xAA>(now) : dpp_f64<0xFF>(now));
-        const double f = div_refined(mine, d);
-        if (j + 1 < D) {
-          const double pivot_row = readlane_f64(now, kLpr * (j + 1) + jb);
-          if (ji + 1 < kCpl) now = fma(-f, pivot_row, a[ji + 1]);
+        const double mine = D == 32 ? (o ? dpp_f64<0xF5>(now) : dpp_f64<0xA0>(now))
+                                    : (o == 0 ? dpp_f64<0x00>(now) : o == 1 ? dpp_f64<0x55>(now) : o == 2 ? dpp_f64<0xAA>(now) : dpp_f64<0xFF>(now));
+        f = div_refined(mine, d);
+        now = fma(-f, readlane_f64(now, (kLpr * (j + 1) + o) & 63), a[o + 1 < kLpr ? 0 : 1]);
 #pragma unroll
-          for (int i = 0; i < kCpl; i += 2) {
-            if (jb == kLpr - 1 && i + 1 <= ji + 1) continue;   // columns that are done
-            const v2d m = *reinterpret_cast<const v2d*>(&L[j][c0 + i]);
-            a[i] = fma(-f, m[0], a[i]);
-            a[i + 1] = fma(-f, m[1], a[i + 1]);
-          }
-          if (ji + 1 == kCpl) now = a[0];
-        }
-        __builtin_amdgcn_sched_barrier(0);
+        for (int i = 0; i < SIZE; ++i) m[i] = fetched[i];
+        wave_lds_sync();
       }
-    }
+    };
+#pragma unroll 1
+    for (int q = 0; q < kCpl / 2; ++q) steps(q, Count<kCpl>{});
+#pragma unroll 1
+    for (int q = kCpl / 2; q < kCpl; ++q) steps(q, Count<kCpl / 2>{});
   }
   __syncthreads();
   if (t < 2 * D) {
@@ -667,8 +695,8 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
   for (int u = 0; u < 2 * D * D / NT; ++u) {
     const int e = t + NT * u, h = e / (D * D), j = e / D % D, r = e % D;
     matrix_t& L = h ? LX : LW;
-    const double raw = L[j][r], root = diag[h][j], inv = inv_root[h][j], q = raw * inv;
-    L[j][r] = r > j ? fma(fma(-root, q, raw), inv, q) : (r == j ? root : 0.0);
+    const double root = diag[h][j];
+    L[j][r] = r > j ? over_root(L[j][r], root, inv_root[h][j]) : (r == j ? root : 0.0);
   }
   if (V0) {
 #pragma unroll
@@ -790,7 +818,9 @@ __device__ __forceinline__ void wush_block_group(LoadFn load, FinishFn finish, i
     for (int v = 0; v < 4; ++v) {
       const int o = (i0 + l4 + 4 * v) * D + j0 + l16;
       const double x = acc[v] * hn;
-      T_bits[o] = f64_to_bf16_bits(x);
+      const uint16_t bits = f64_to_bf16_bits(x);
+      T_bits[o] = bits;
+      scratch[1][i0 + l4 + 4 * v][j0 + l16] = (double)bf16_bits_to_f32(bits);
       if (T_f64) T_f64[o] = x;
     }
   }
