@@ -51,13 +51,19 @@ __device__ __forceinline__ void store8(double* __restrict__ p, const double (&x)
 // H = Xc^T Xc / M, 64 x 64 tile per workgroup, tiles on or above the diagonal (the factorization reads no other).
 // Products of BF16 values are exact.  Arithmetic bound (K^2 M multiply-adds): FP64 MFMA, a wavefront per 32 x 32
 // quarter, operands widened as they come out of LDS; row pitch 80 floats: the four rows of an operand read hit
-// distinct banks.  c2: 1.8 ms = 39 TFLOP/s (2.6 on the vector unit).
+// distinct banks.  The tiles are numbered along the triangle and every XCD takes a contiguous run of them: as a square grid whose lower
+// half leaves at once, an XCD got up to a tenth more of them than the mean.  Two LDS stages, one barrier per 32 rows, with the fetches left in
+// flight.  4096 x 4096: 1.37 ms = 50 TFLOP/s (square grid 1.75, one stage 1.40; the MFMAs alone 67 TFLOP/s; operands
+// staged as the upper words of their FP64 values, without a conversion behind LDS: 1.54).
 __global__ __launch_bounds__(256) void gptq_hessian_kernel(const uint16_t* __restrict__ X, int64_t ldx, int Mc, int K,
                                                            double* __restrict__ H, int* __restrict__ status) {
-  const int ti = blockIdx.y, tj = blockIdx.x;
-  if (ti == 0 && tj == 0 && threadIdx.x < 4) status[threadIdx.x] = 0;   // later kernels set it
-  if (tj < ti) return;
-  __shared__ __attribute__((aligned(16))) float side_a[32][80], side_b[32][80];
+  if (blockIdx.x == 0 && threadIdx.x < 4) status[threadIdx.x] = 0;   // later kernels set it
+  const int id = xcd_contiguous_id((int)blockIdx.x, (int)gridDim.x);
+  int tj = (int)((sqrt(8.0 * (double)id + 1.0) - 1.0) * 0.5);
+  while ((int64_t)tj * (tj + 1) / 2 > id) --tj;
+  while ((int64_t)(tj + 1) * (tj + 2) / 2 <= id) ++tj;
+  const int ti = id - (int)((int64_t)tj * (tj + 1) / 2);
+  __shared__ __attribute__((aligned(16))) float side_a[2][32][80], side_b[2][32][80];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, l4 = lane >> 4;
   const int wr = 32 * (wave >> 1), wc = 32 * (wave & 1);
   v4d acc[2][2] = {};
@@ -78,25 +84,32 @@ __global__ __launch_bounds__(256) void gptq_hessian_kernel(const uint16_t* __res
     }
   };
   fetch(0);
+  widen(ra, &side_a[0][lr][lc]);
+  widen(rb, &side_b[0][lr][lc]);
+  fetch(32);
+  lds_barrier();
+  int stage = 0;
   for (int m0 = 0; m0 < Mc; m0 += 32) {
-    __syncthreads();
-    widen(ra, &side_a[lr][lc]);
-    widen(rb, &side_b[lr][lc]);
-    __syncthreads();
-    if (m0 + 32 < Mc) fetch(m0 + 32);
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
       double a[2], b[2];
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        a[u] = (double)side_a[4 * kk + l4][wr + 16 * u + l16];
-        b[u] = (double)side_b[4 * kk + l4][wc + 16 * u + l16];
+        a[u] = (double)side_a[stage][4 * kk + l4][wr + 16 * u + l16];
+        b[u] = (double)side_b[stage][4 * kk + l4][wc + 16 * u + l16];
       }
 #pragma unroll
       for (int u = 0; u < 2; ++u)
 #pragma unroll
         for (int v = 0; v < 2; ++v) acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[v], acc[u][v], 0, 0, 0);
+      if (kk == 4) {   // the other stage was read last before the barrier
+        widen(ra, &side_a[stage ^ 1][lr][lc]);
+        widen(rb, &side_b[stage ^ 1][lr][lc]);
+        fetch(m0 + 64);
+      }
     }
+    lds_barrier();
+    stage ^= 1;
   }
 #pragma unroll
   for (int u = 0; u < 2; ++u)
@@ -538,19 +551,45 @@ __global__ __launch_bounds__(64 * kRowWaves) void gptq_rows_kernel(
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, l4 = lane >> 4;
   const int next = i + 1, C = K >> 5, tiles = (N + 15) / 16;
   double* area = sh.areas + wave * kAreaDoubles;
-  if (i >= 0) {
-    for (int o = threadIdx.x; o < 1024; o += 64 * kRowWaves) {
-      const int k = o >> 5, j = o & 31;
-      op.r[k][j] = R[o];
-      sh.inv[k][j] = Tinv[o];
-      sh.tm[k][j] = (double)bf16_bits_to_f32(T[o]);
-      if (next < C) {
-        sh.u[k][j] = U[(int64_t)(32 * i + k) * K + 32 * next + j];
-        sh.v[k][j] = -Vd[(int64_t)next * 1024 + o];
-      }
+  // what the first rows need is on its way while the matrices are brought to LDS
+  v4u raw, raw_next;
+  double s[8], w[8];
+  auto fetch = [&](int t) {
+    const int64_t nc = min(16 * t + l16, N - 1);
+    const uint16_t* wrow = W + nc * ldw + 8 * l4;
+    raw = *reinterpret_cast<const v4u*>(wrow + 32 * max(i, 0));
+    raw_next = *reinterpret_cast<const v4u*>(wrow + 32 * min(next, C - 1));
+    if (i > 0) {
+      load8(current + nc * 32 + 8 * l4, w);
+      if (next < C) load8(S + ((int64_t)next * N + nc) * 32 + 8 * l4, s);
     }
-    if (threadIdx.x < 32) op.rinv[threadIdx.x] = 1.0 / R[33 * threadIdx.x];
-    __syncthreads();
+  };
+  fetch(kRowWaves * blockIdx.x + wave);
+  if (i >= 0) {
+    constexpr int kPer = 1024 / (64 * kRowWaves);
+    double r[kPer], inv[kPer], u[kPer], v[kPer], rinv = 0.0;
+    uint16_t tm[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int o = threadIdx.x + 64 * kRowWaves * q;
+      r[q] = R[o];
+      inv[q] = Tinv[o];
+      tm[q] = T[o];
+      u[q] = U[(int64_t)(32 * i + (o >> 5)) * K + 32 * min(next, C - 1) + (o & 31)];
+      v[q] = Vd[(int64_t)min(next, C - 1) * 1024 + o];
+    }
+    if (threadIdx.x < 32) rinv = R[33 * threadIdx.x];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int o = threadIdx.x + 64 * kRowWaves * q, k = o >> 5, j = o & 31;
+      op.r[k][j] = r[q];
+      sh.inv[k][j] = inv[q];
+      sh.tm[k][j] = (double)bf16_bits_to_f32(tm[q]);
+      sh.u[k][j] = u[q];
+      sh.v[k][j] = -v[q];
+    }
+    if (threadIdx.x < 32) op.rinv[threadIdx.x] = 1.0 / rinv;
+    lds_barrier();
   }
   // y += w M, M one of the four matrices in LDS (in registers they would take 128 of a lane's 256)
   auto multiply = [&](const double (*m)[33], const double (&w)[8], double (&y)[8]) {
@@ -560,24 +599,19 @@ __global__ __launch_bounds__(64 * kRowWaves) void gptq_rows_kernel(
   };
   Moment m;
   for (int t = kRowWaves * blockIdx.x + wave; t < tiles; t += kRowWaves * gridDim.x) {
-    const int n = 16 * t + l16, nc = min(n, N - 1);
-    const uint16_t* wrow = W + (int64_t)nc * ldw + 8 * l4;
-    const int64_t at = (int64_t)nc * 32 + 8 * l4;
+    const int n = 16 * t + l16;
+    const int64_t at = (int64_t)min(n, N - 1) * 32 + 8 * l4;
+    if (t != kRowWaves * (int)blockIdx.x + wave) fetch(t);
     double wn[8];   // current weights of block i + 1
     if (i >= 0) {
-      v4u raw = *reinterpret_cast<const v4u*>(wrow + 32 * i), raw_next = {0, 0, 0, 0};
-      double s[8] = {};
-      if (next < C) {
-        raw_next = *reinterpret_cast<const v4u*>(wrow + 32 * next);
-        if (i > 0) load8(S + (int64_t)next * N * 32 + at, s);
-      }
-      double w[8], y[8] = {}, dq[8], g[8];
+      double y[8] = {}, dq[8], g[8];
       wm::widen8(raw, g);
-      if (i > 0) {
-        load8(current + at, w);
-      } else {
+      if (i == 0) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q) w[q] = g[q];
+        for (int q = 0; q < 8; ++q) {
+          w[q] = g[q];
+          s[q] = 0.0;
+        }
       }
       multiply(sh.inv, w, y);
       // static group scale: taken before any update
@@ -615,7 +649,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void gptq_rows_kernel(
         if (n < N) store8(current + at, wn);
       }
     } else {
-      wm::widen8(*reinterpret_cast<const v4u*>(wrow), wn);
+      wm::widen8(raw, wn);
     }
     if (next < C) {
       if (n >= N)
@@ -682,8 +716,8 @@ hipError_t launch_gptq_prep(const void* W, int64_t N, int64_t K, int64_t ldw, co
   const uint16_t* Wb = static_cast<const uint16_t*>(W);
   uint16_t* Tbits = static_cast<uint16_t*>(T_blocks);
 
-  const unsigned t64 = (unsigned)((K + 63) / 64);
-  gptq_hessian_kernel<<<dim3(t64, t64), 256, 0, st>>>((const uint16_t*)Xc, ldx, (int)Mc, Ki, H, status);
+  const int64_t t64 = (K + 63) / 64;
+  gptq_hessian_kernel<<<(unsigned)(t64 * (t64 + 1) / 2), 256, 0, st>>>((const uint16_t*)Xc, ldx, (int)Mc, Ki, H, status);
   WUSH_GPTQ_CHECK()
   gptq_trace_kernel<<<1, 256, 0, st>>>(H, Ki, tr);
   WUSH_GPTQ_CHECK()
