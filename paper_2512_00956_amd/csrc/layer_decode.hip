@@ -151,6 +151,76 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_skinny_kernel(
   }
 }
 
+// The same where every workgroup has a compute unit of its own, one wavefront per SIMD: no other workgroup fills the gap between a chunk's
+// last product and the next one's data.  RING K tiles are in flight at any time, each slot refilled as soon as it has been multiplied
+// (replayed graphs, four sets of operands, us, in chunks | ring: 16 x 14336 -> 4096 9.6 | 9.0, 1 x 4096 -> 6144 5.4 | 5.0, 32 x 8192 -> 8192 9.2 | 8.1,
+// 64 x 14336 -> 4096 10.0 | 9.1, 100 x 14336 -> 4096 12.3 | 11.5, 256 x 4096 -> 4096 8.9 | 7.9, 1024 x 4096 -> 1024 9.7 | 8.5, 448 x 28672 -> 512
+// 14.3 | 14.4).  Deeper rings, up to what the counter of outstanding loads allows, are no faster (one row block 6 tiles 9.0 | 4 9.0 | 3 9.1,
+// 448 x 28672 -> 512 14.7 | 14.3 | 14.4; two row blocks 4 tiles 11.7 | 3 11.6 | 2 11.5; four 2 tiles 8.9 | 1 8.5): what bounds these layers is
+// what a compute unit gets out of the L2 and beyond, some 80 GB/s.
+template <int RB>
+struct Ring { static constexpr int R = RB == 1 ? 4 : RB == 2 ? 2 : 1; };
+template <int RB, bool OUT_F32>
+__global__ __launch_bounds__(kWaves * 64, 1) void gemm_skinny_ring_kernel(
+    const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const uint8_t* __restrict__ Wq,
+    const uint8_t* __restrict__ Ws, int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
+  constexpr int R = Ring<RB>::R;
+  __shared__ float red[kWaves][RB][16][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int KT = K >> 8, NB = (N + 31) >> 5, j = blockIdx.x;
+  if (j >= NB) return;                        // the grid's padding
+  const int64_t row_block = (int64_t)RB * blockIdx.y;
+  Xq += row_block * KT * 4096;
+  Xs += row_block * KT * 256;
+  Wq += (int64_t)j * KT * 4096;
+  Ws += (int64_t)j * KT * 256;
+  Y = static_cast<uint8_t*>(Y) + 32 * row_block * ldy * (OUT_F32 ? 4 : 2);
+  M -= 32 * (int)row_block;
+  int kt, kt1;
+  wave_k_range(KT, wave, kt, kt1);
+  v16f acc[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) acc[rb] = (v16f){0};
+  FragTile w[R], x[R][RB];
+  auto load = [&](int u, int t) {
+    load_frag_tile(w[u], Wq, Ws, t, lane);
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) load_frag_tile(x[u][rb], Xq, Xs, (int64_t)rb * KT + t, lane);
+  };
+  auto multiply = [&](int u) {
+#define WUSH_RING_ISSUE(KK)                                                                                            {                                                                                                                      const v8i A_ = {w[u].f[KK][0], w[u].f[KK][1], w[u].f[KK][2], w[u].f[KK][3], 0, 0, 0, 0};                             _Pragma("unroll") for (int rb = 0; rb < RB; ++rb) {                                                                    const v8i B_ = {x[u][rb].f[KK][0], x[u][rb].f[KK][1], x[u][rb].f[KK][2], x[u][rb].f[KK][3], 0, 0, 0, 0};             acc[rb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A_, B_, acc[rb], 4, 4, KK, w[u].s, KK, x[u][rb].s);      }                                                                                                                  }
+    WUSH_RING_ISSUE(0)
+    WUSH_RING_ISSUE(1)
+    WUSH_RING_ISSUE(2)
+    WUSH_RING_ISSUE(3)
+#undef WUSH_RING_ISSUE
+  };
+#pragma unroll
+  for (int u = 0; u < R; ++u)
+    if (kt + u < kt1) load(u, kt + u);
+  __builtin_amdgcn_sched_barrier(0);
+  // no branch around a refill in this loop: the compiler's wait counts stay exact
+  for (; kt + 2 * R <= kt1; kt += R) {
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+      multiply(u);
+      load(u, kt + R + u);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < R; ++u)
+    if (kt + u < kt1) {
+      multiply(u);
+      if (kt + R + u < kt1) load(u, kt + R + u);
+    }
+#pragma unroll
+  for (int u = 0; u < R; ++u)
+    if (kt + R + u < kt1) multiply(u);
+  reduce_store_block<RB, OUT_F32>(acc, red, j, M, N, Y, ldy, lane, wave);
+}
+
 template <int RB, bool OUT_F32>
 __global__ __launch_bounds__(kWaves * 64) void layer_decode_kernel(
     const uint16_t* __restrict__ X, int64_t ldx, const uint16_t* __restrict__ T, const uint8_t* __restrict__ Wq,
@@ -302,10 +372,10 @@ hipError_t launch_mxfp4_gemm_skinny(const void* Xq, const void* Xs, const void* 
   const int rb = skinny_row_blocks(M, N), groups = (int)((M + 32 * rb - 1) / (32 * rb));
   const int64_t wide = rb == 4 && groups > 1 ? skinny_grid_width(N) : NB;
   dim3 grid((unsigned)(wide < 4096 ? wide : 4096), (unsigned)groups), block(kWaves * 64);
+  const bool alone = wide * groups <= device_cu_count();
 #define WUSH_SKINNY_LAUNCH(RB, F32)                                                                         \
-  gemm_skinny_kernel<RB, F32><<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs,           \
-                                                          (const uint8_t*)Wq, (const uint8_t*)Ws, (int)M,   \
-                                                          (int)N, (int)K, Y, ldy)
+  (alone ? gemm_skinny_ring_kernel<RB, F32> : gemm_skinny_kernel<RB, F32>)<<<grid, block, 0, stream>>>(     \
+      (const uint8_t*)Xq, (const uint8_t*)Xs, (const uint8_t*)Wq, (const uint8_t*)Ws, (int)M, (int)N, (int)K, Y, ldy)
   if (rb == 1) {
     if (out_f32) WUSH_SKINNY_LAUNCH(1, true); else WUSH_SKINNY_LAUNCH(1, false);
   } else if (rb == 2) {
