@@ -173,6 +173,111 @@ __global__ __launch_bounds__(kWaves * 64) void w4_skinny_kernel(
   }
 }
 
+// The K split for at most 16 tokens, on v_mfma_f32_16x16x32_f16: a row block's upper half would be padding, half of the activations' loads
+// and conversions and half of every MFMA.  A lane is (row l16 of 16, quarter l4): quarters 0, 1 hold the two halves of the row's first K step
+// of a pair, 2 and 3 those of the second, 16 bytes each as above; MFMA d of the pair takes dword d of all four.  A weight block is two operands
+// of 16 output channels.  Behind the last K step of an odd number the activations' scale is zero.  Replayed graphs, four sets of operands, us,
+// 32 x 32 | this: NVFP4 16 x 8192 -> 28672 36.6 | 31.3 (132 MB of weights: 4.2 TB/s), 8192 -> 57344 65.9 | 59.3, 14336 -> 4096 15.6 | 12.0, 1 x 4096 ->
+// 6144 7.0 | 6.0, canonical 16 x 8192 -> 28672 58.5 | 49.0; INT4 40.6 | 32.8, 73.2 | 60.4, 20.0 | 15.2, 8.4 | 6.7, canonical 1 x 8192 -> 28672
+// 52.6 | 44.5.
+// Accumulator v of lane (l16, l4), half a of block c: token l16, output channel 32 c + 16 a + 4 l4 + v.
+template <int CBW, int FMT, bool OUT_F32, bool TILED>
+__global__ __launch_bounds__(kWaves * 64) void w4_skinny16_kernel(
+    const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const float* __restrict__ tsx,
+    const uint8_t* __restrict__ Wq, const uint8_t* __restrict__ Ws, const float* __restrict__ tsw,
+    int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
+  __shared__ v4f red[kWaves][CBW][2][64];
+  constexpr int U = 2;                       // pairs of K steps per chunk
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, l4 = lane >> 4, h = l4 & 1;
+  const int KT = K >> 6, NB = (N + 31) >> 5;
+  const int groups = (NB + CBW - 1) / CBW;
+  const uint32_t sel = 0x05040C0Cu + 0x02020000u * h;
+  const float scale = FMT == kNvfp4 ? *tsx * *tsw : 1.0f;
+  int kp0, kp1;
+  skinny::wave_k_range((KT + 1) >> 1, wave, kp0, kp1);
+
+  struct Chunk {
+    RawStep w[CBW][2][U], x[U];
+  };
+  for (int g = blockIdx.x; g < groups; g += gridDim.x) {
+    int jb[CBW];   // weight blocks of this pass; one past the end repeats the last (never stored)
+#pragma unroll
+    for (int c = 0; c < CBW; ++c) jb[c] = min(g * CBW + c, NB - 1);
+    v4f acc[CBW][2];
+#pragma unroll
+    for (int c = 0; c < CBW; ++c)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) acc[c][a] = (v4f){0, 0, 0, 0};
+    // as above: every load is unconditional, but for a whole chunk past the range of canonical rows
+    auto load_chunk = [&](Chunk& ch, int kp) {
+      if (!TILED && kp >= kp1) return;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = min(2 * min(kp + u, kp1 - 1) + (l4 >> 1), KT - 1);
+#pragma unroll
+        for (int c = 0; c < CBW; ++c)
+#pragma unroll
+          for (int a = 0; a < 2; ++a) load_step<TILED>(ch.w[c][a][u], Wq, Ws, jb[c], N, KT, k, 16 * a + l16, h);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = min(2 * min(kp + u, kp1 - 1) + (l4 >> 1), KT - 1);
+        load_step<TILED>(ch.x[u], Xq, Xs, 0, M, KT, k, l16, h);
+      }
+    };
+    auto multiply_chunk = [&](Chunk& ch, int kp) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (kp + u < kp1) {
+          if (2 * (kp + u) + (l4 >> 1) >= KT) ch.x[u].s = 0;
+          v8h fx[4];
+          dequant_step<FMT>(ch.x[u], h, sel, fx);
+#pragma unroll
+          for (int c = 0; c < CBW; ++c)
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+              v8h fw[4];
+              dequant_step<FMT>(ch.w[c][a][u], h, sel, fw);
+#pragma unroll
+              for (int d = 0; d < 4; ++d) acc[c][a] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fw[d], fx[d], acc[c][a], 0, 0, 0);
+            }
+        }
+    };
+    if (kp0 < kp1) {
+      Chunk a, b;
+      load_chunk(a, kp0);
+      for (int kp = kp0; kp < kp1; kp += 2 * U) {
+        load_chunk(b, kp + U);
+        multiply_chunk(a, kp);
+        load_chunk(a, kp + 2 * U);
+        multiply_chunk(b, kp + U);
+      }
+    }
+    // the waves' sums in their order; wave w finishes the half blocks w, w + 4, ...
+#pragma unroll
+    for (int c = 0; c < CBW; ++c)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) red[wave][c][a][lane] = acc[c][a];
+    __syncthreads();
+    for (int ca = wave; ca < 2 * CBW; ca += kWaves) {
+      const int j = g * CBW + (ca >> 1), col = 32 * j + 16 * (ca & 1) + 4 * l4;
+      const v4f* part = &red[0][ca >> 1][ca & 1][lane];
+      constexpr int kNext = CBW * 2 * 64;    // the next wave's
+      const v4f sum = ((part[0] + part[kNext]) + part[2 * kNext]) + part[3 * kNext];
+      const bool whole = 32 * j + 32 <= N;
+      if (l16 < M && j < NB && (whole || col < N)) {
+        float v[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] = FMT == kNvfp4 ? sum[t] * scale : sum[t];
+        skinny::store_quad<OUT_F32>(Y, ldy, l16, col, N, whole, v);
+      }
+    }
+    __syncthreads();   // red is rewritten by the next blocks
+  }
+}
+
 // Second schedule, for 65..128 tokens on layers with many output channels.  Above, every wave converts the
 // X fragments it multiplies, RB row blocks per K step and workgroup of 32 output channels: with four row blocks the
 // activations, read from the L2 and converted once per workgroup, outweigh the weight stream (four times its bytes
@@ -372,7 +477,14 @@ hipError_t launch_split_k(const void* Xq, const void* Xs, const float* tsx, cons
     if (tiled) { if (out_f32) WUSH_W4S_LAUNCH(RB, CBW, true, true); else WUSH_W4S_LAUNCH(RB, CBW, false, true); }     \
     else { if (out_f32) WUSH_W4S_LAUNCH(RB, CBW, true, false); else WUSH_W4S_LAUNCH(RB, CBW, false, false); }         \
   }
-  if (rb == 1) {
+  if (M <= 16) {
+    auto kernel = cbw == 2 ? (out_f32 ? (tiled ? w4_skinny16_kernel<2, FMT, true, true> : w4_skinny16_kernel<2, FMT, true, false>)
+                                      : (tiled ? w4_skinny16_kernel<2, FMT, false, true> : w4_skinny16_kernel<2, FMT, false, false>))
+                           : (out_f32 ? (tiled ? w4_skinny16_kernel<1, FMT, true, true> : w4_skinny16_kernel<1, FMT, true, false>)
+                                      : (tiled ? w4_skinny16_kernel<1, FMT, false, true> : w4_skinny16_kernel<1, FMT, false, false>));
+    kernel<<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs, tsx, (const uint8_t*)Wq, (const uint8_t*)Ws, tsw,
+                                       (int)M, (int)N, (int)K, Y, ldy);
+  } else if (rb == 1) {
     if (cbw == 2) WUSH_W4S_BY_OUT(1, 2) else WUSH_W4S_BY_OUT(1, 1)
   } else {
     if (cbw == 2) WUSH_W4S_BY_OUT(2, 2) else WUSH_W4S_BY_OUT(2, 1)
