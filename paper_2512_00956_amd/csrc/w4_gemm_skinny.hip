@@ -38,9 +38,11 @@ struct RawStep {   // what a lane holds of one (32-row block, K step): its row's
   uint32_t s;
 };
 
-// K steps per chunk of loads; a wave keeps two chunks in flight (one being multiplied, one on its way).
-template <int RB>
-struct Depth { static constexpr int U = RB == 1 ? 4 : 2; };
+// K steps per chunk of loads; a wave keeps two chunks in flight (one being multiplied, one on its way).  Two, which leaves registers for
+// more workgroups (four | two steps, one row block: 32 x 8192 -> 28672 NVFP4 38.2 | 33.8, INT4 42.0 | 38.0; 32 x 14336 -> 4096 15.6 | 14.8;
+// two row blocks, two | one: 128 x 14336 -> 4096 25.5 | 29.7), but four of canonical rows, whose steps share lines (64.4 | 70.2).
+template <int RB, bool TILED>
+struct Depth { static constexpr int U = RB == 1 && !TILED ? 4 : 2; };
 
 // Block `blk` (32 rows) of a tiled operand with KT K steps: codes at
 // (((blk KT + kt) 2 + h) 32 + r) 16, scale dword at ((blk KT + kt) 32 + r) 4.
@@ -86,7 +88,7 @@ __global__ __launch_bounds__(kWaves * 64) void w4_skinny_kernel(
     const uint8_t* __restrict__ Wq, const uint8_t* __restrict__ Ws, const float* __restrict__ tsw,
     int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
   __shared__ float red[kWaves][RB][16][64];
-  constexpr int U = Depth<RB>::U;
+  constexpr int U = Depth<RB, TILED>::U;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 31, h = lane >> 5;
@@ -180,14 +182,17 @@ __global__ __launch_bounds__(kWaves * 64) void w4_skinny_kernel(
 // 32 x 32 | this: NVFP4 16 x 8192 -> 28672 36.6 | 31.3 (132 MB of weights: 4.2 TB/s), 8192 -> 57344 65.9 | 59.3, 14336 -> 4096 15.6 | 12.0, 1 x 4096 ->
 // 6144 7.0 | 6.0, canonical 16 x 8192 -> 28672 58.5 | 49.0; INT4 40.6 | 32.8, 73.2 | 60.4, 20.0 | 15.2, 8.4 | 6.7, canonical 1 x 8192 -> 28672
 // 52.6 | 44.5.
+// U = pairs of K steps per chunk, of which two are in flight: one where two weight blocks share the activations or a wave's range is four pairs or
+// less (canonical rows two), two otherwise (U = 2 | 1: NVFP4 16 x 8192 -> 57344 59.3 | 57.6, 16 x 704 -> 28672 6.5 | 5.5, 8 x 2048 -> 20480
+// 7.8 | 7.3, 1 x 4096 -> 6144 6.0 | 6.9, 16 x 14336 -> 4096 11.9 | 15.8; canonical 3 x 512 -> 1000 INT4 3.4 | 2.8, 16 x 8192 -> 28672 49.0 | 51.6;
+// three 12.5, 62.0 on 16 x 14336 -> 4096 and 8192 -> 57344).
 // Accumulator v of lane (l16, l4), half a of block c: token l16, output channel 32 c + 16 a + 4 l4 + v.
-template <int CBW, int FMT, bool OUT_F32, bool TILED>
+template <int CBW, int U, int FMT, bool OUT_F32, bool TILED>
 __global__ __launch_bounds__(kWaves * 64) void w4_skinny16_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const float* __restrict__ tsx,
     const uint8_t* __restrict__ Wq, const uint8_t* __restrict__ Ws, const float* __restrict__ tsw,
     int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
   __shared__ v4f red[kWaves][CBW][2][64];
-  constexpr int U = 2;                       // pairs of K steps per chunk
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, l4 = lane >> 4, h = l4 & 1;
@@ -478,10 +483,13 @@ hipError_t launch_split_k(const void* Xq, const void* Xs, const float* tsx, cons
     else { if (out_f32) WUSH_W4S_LAUNCH(RB, CBW, true, false); else WUSH_W4S_LAUNCH(RB, CBW, false, false); }         \
   }
   if (M <= 16) {
-    auto kernel = cbw == 2 ? (out_f32 ? (tiled ? w4_skinny16_kernel<2, FMT, true, true> : w4_skinny16_kernel<2, FMT, true, false>)
-                                      : (tiled ? w4_skinny16_kernel<2, FMT, false, true> : w4_skinny16_kernel<2, FMT, false, false>))
-                           : (out_f32 ? (tiled ? w4_skinny16_kernel<1, FMT, true, true> : w4_skinny16_kernel<1, FMT, true, false>)
-                                      : (tiled ? w4_skinny16_kernel<1, FMT, false, true> : w4_skinny16_kernel<1, FMT, false, false>));
+    const int64_t per_wave = (K + 511) / 512;   // pairs of K steps
+    const bool single = tiled ? cbw == 2 || per_wave <= 4 : per_wave <= 2;
+#define WUSH_W4S16(CBW, U)                                                                                                  \
+  (out_f32 ? (tiled ? w4_skinny16_kernel<CBW, U, FMT, true, true> : w4_skinny16_kernel<CBW, U, FMT, true, false>)           \
+           : (tiled ? w4_skinny16_kernel<CBW, U, FMT, false, true> : w4_skinny16_kernel<CBW, U, FMT, false, false>))
+    auto kernel = cbw == 2 ? (single ? WUSH_W4S16(2, 1) : WUSH_W4S16(2, 2)) : (single ? WUSH_W4S16(1, 1) : WUSH_W4S16(1, 2));
+#undef WUSH_W4S16
     kernel<<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs, tsx, (const uint8_t*)Wq, (const uint8_t*)Ws, tsw,
                                        (int)M, (int)N, (int)K, Y, ldy);
   } else if (rb == 1) {
