@@ -1,7 +1,7 @@
 // Decode-sized layer forward (at most 64 tokens) for gfx950:
 //   Y = sum_i Wq(i)^T q(T(i) X(i))      (layer forward-pass equation)
 // with the weights already transformed and quantized, in two forms:
-//   * gemm_skinny_kernel: the MXFP4 GEMM alone for few tokens, or few output channels (wush_linear);
+//   * gemm_skinny_kernel and its variants: the MXFP4 GEMM alone for few tokens, or few output channels (wush_linear);
 //   * layer_decode_kernel: activation transform + quantization + GEMM in ONE
 //     launch (wush_layer_decode).
 // At these sizes the layer is bound by streaming the weights once (K/2 + K/32
@@ -221,6 +221,100 @@ __global__ __launch_bounds__(kWaves * 64, 1) void gemm_skinny_ring_kernel(
   reduce_store_block<RB, OUT_F32>(acc, red, j, M, N, Y, ldy, lane, wave);
 }
 
+// At most 16 tokens, on v_mfma_scale_f32_16x16x128_f8f6f4: half of the activations' fragments and of every product would be a row block's padding.
+// Lane quarter q of instruction p takes group kk = 2 p + q / 2 of K half kh = q % 2, for both operands: the fragments as they lie, and with
+// the scale dword shifted by q / 2 bytes its scale is byte 2 p in every lane.  HALVES = 16-channel halves of a block of 32 output channels
+// a workgroup takes: both, or one where the blocks are so few that halves still find idle compute units.  A ring of R K tiles per wavefront as above:
+// two, one up to K = 2048 (us, R = 1 | 2 | 4: 16 x 256 -> 57344 3.9 | 4.5 | 6.6, 8 x 2048 -> 20480 5.6 | 5.9 | 6.4, 16 x 8192 -> 57344
+// 47.7 | 45.7 | 45.5, 9 x 28672 -> 4096 13.0 | 11.8 | 12.1, 9 x 28672 -> 1024 11.9 | 8.9 | 8.4).  Replayed graphs, four sets of operands, us,
+// 32 x 32 fragments in chunks | this: 16 x 8192 -> 57344 49.6 | 45.3 (250 MB of weights: 5.5 TB/s), 16 x 4096 -> 28672 13.5 | 11.1, 16 x 28672 ->
+// 8192 26.6 | 23.0, 1 x 14336 -> 4096 9.6 | 7.5, 1 x 4096 -> 6144 5.3 | 4.4, 9 x 28672 -> 1024 12.6 | 8.9.
+struct HalfTile {   // 16 rows of one (row block, K tile)
+  v4i f[2];
+  int s;
+};
+template <int HALVES, int R, bool OUT_F32>
+__global__ __launch_bounds__(kWaves * 64) void gemm_skinny16_kernel(
+    const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const uint8_t* __restrict__ Wq,
+    const uint8_t* __restrict__ Ws, int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
+  __shared__ v4f red[kWaves][HALVES][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, q = lane >> 4;
+  const int KT = K >> 8, NB = HALVES == 2 ? (N + 31) >> 5 : (N + 15) >> 4;
+  const int chunk = ((q >> 1) * 64 + (q & 1) * 32 + l16) * 16, scale = ((q & 1) * 32 + l16) * 4;
+  int kt0, kt1;
+  wave_k_range(KT, wave, kt0, kt1);
+  auto load_half = [&](HalfTile& t, const uint8_t* qp, const uint8_t* sp, int64_t rb_kt, int a) {
+    const uint8_t* p = qp + rb_kt * 4096 + chunk + 256 * a;
+    t.f[0] = *reinterpret_cast<const v4i*>(p);
+    t.f[1] = *reinterpret_cast<const v4i*>(p + 2048);
+    t.s = *reinterpret_cast<const int*>(sp + rb_kt * 256 + scale + 64 * a);
+  };
+  for (int j = blockIdx.x; j < NB; j += gridDim.x) {
+    const int64_t block = HALVES == 2 ? j : j >> 1;
+    const int first = HALVES == 2 ? 0 : j & 1;
+    v4f acc[HALVES];
+#pragma unroll
+    for (int a = 0; a < HALVES; ++a) acc[a] = (v4f){0, 0, 0, 0};
+    HalfTile w[R][HALVES], x[R];
+    auto load = [&](int u, int kt) {
+#pragma unroll
+      for (int a = 0; a < HALVES; ++a) load_half(w[u][a], Wq, Ws, block * KT + kt, first + a);
+      load_half(x[u], Xq, Xs, kt, 0);
+    };
+    auto multiply = [&](int u) {
+      const int sx = x[u].s >> (8 * (q >> 1));
+#pragma unroll
+      for (int a = 0; a < HALVES; ++a) {
+        const int sw = w[u][a].s >> (8 * (q >> 1));
+#define WUSH_HALF_ISSUE(P)                                                                                                    \
+  {                                                                                                                           \
+    const v8i A_ = {w[u][a].f[P][0], w[u][a].f[P][1], w[u][a].f[P][2], w[u][a].f[P][3], 0, 0, 0, 0};                          \
+    const v8i B_ = {x[u].f[P][0], x[u].f[P][1], x[u].f[P][2], x[u].f[P][3], 0, 0, 0, 0};                                      \
+    acc[a] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A_, B_, acc[a], 4, 4, 2 * P, sw, 2 * P, sx);                    \
+  }
+        WUSH_HALF_ISSUE(0)
+        WUSH_HALF_ISSUE(1)
+#undef WUSH_HALF_ISSUE
+      }
+    };
+    int kt = kt0;
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+      if (kt + u < kt1) load(u, kt + u);
+    __builtin_amdgcn_sched_barrier(0);
+    for (; kt + 2 * R <= kt1; kt += R) {
+#pragma unroll
+      for (int u = 0; u < R; ++u) {
+        multiply(u);
+        load(u, kt + R + u);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+      if (kt + u < kt1) {
+        multiply(u);
+        if (kt + R + u < kt1) load(u, kt + R + u);
+      }
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+      if (kt + R + u < kt1) multiply(u);
+    // the waves' sums in their order; accumulator v of lane (l16, q) is token l16, output channel 4 q + v of the half
+#pragma unroll
+    for (int a = 0; a < HALVES; ++a) red[wave][a][lane] = acc[a];
+    __syncthreads();
+    if (wave < HALVES) {
+      const v4f sum = ((red[0][wave][lane] + red[1][wave][lane]) + red[2][wave][lane]) + red[3][wave][lane];
+      const int col = HALVES == 2 ? 32 * j + 16 * wave + 4 * q : 16 * j + 4 * q;
+      const float v[4] = {sum[0], sum[1], sum[2], sum[3]};
+      if (l16 < M && col < N) skinny::store_quad<OUT_F32>(Y, ldy, l16, col, N, col + 4 <= N, v);
+    }
+    __syncthreads();   // red is rewritten by the next block
+  }
+}
+
 template <int RB, bool OUT_F32>
 __global__ __launch_bounds__(kWaves * 64) void layer_decode_kernel(
     const uint16_t* __restrict__ X, int64_t ldx, const uint16_t* __restrict__ T, const uint8_t* __restrict__ Wq,
@@ -369,6 +463,19 @@ int64_t skinny_grid_width(int64_t N) { return ((N + 31) / 32 + 7) & ~(int64_t)7;
 hipError_t launch_mxfp4_gemm_skinny(const void* Xq, const void* Xs, const void* Wq, const void* Ws, int64_t M,
                                     int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy, hipStream_t stream) {
   const int NB = (int)((N + 31) / 32);
+  if (M <= 16) {
+    const int cus = device_cu_count();
+    const bool halves = 2 * NB <= cus;
+    const int blocks = halves ? (int)((N + 15) / 16) : NB;
+    const bool shallow = K <= 2048;   // a wavefront's range is one or two tiles
+    auto kernel = halves ? (out_f32 ? (shallow ? gemm_skinny16_kernel<1, 1, true> : gemm_skinny16_kernel<1, 2, true>)
+                                    : (shallow ? gemm_skinny16_kernel<1, 1, false> : gemm_skinny16_kernel<1, 2, false>))
+                         : (out_f32 ? (shallow ? gemm_skinny16_kernel<2, 1, true> : gemm_skinny16_kernel<2, 2, true>)
+                                    : (shallow ? gemm_skinny16_kernel<2, 1, false> : gemm_skinny16_kernel<2, 2, false>));
+    kernel<<<dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(kWaves * 64), 0, stream>>>(
+        (const uint8_t*)Xq, (const uint8_t*)Xs, (const uint8_t*)Wq, (const uint8_t*)Ws, (int)M, (int)N, (int)K, Y, ldy);
+    return hipGetLastError();
+  }
   const int rb = skinny_row_blocks(M, N), groups = (int)((M + 32 * rb - 1) / (32 * rb));
   const int64_t wide = rb == 4 && groups > 1 ? skinny_grid_width(N) : NB;
   dim3 grid((unsigned)(wide < 4096 ? wide : 4096), (unsigned)groups), block(kWaves * 64);
