@@ -149,7 +149,7 @@ hipError_t launch_mxfp4_gemm(const void* Xq, const void* Xs, const void* Wq, con
   bool simple = short_k(M, N, K, out_f32, canon_vec_store(Y, ldy, out_f32));
   if (debug_option(kDbgGemmTile) >= 0) simple = false;                                       // tests: a tile shape of the other kernel
   if (const int forced = debug_option(kDbgGemmSimple); forced >= 0) simple = forced == 1;    // tests: either kernel
-  if (!simple && canon_streams(M, N) && debug_option(kDbgGemmTile) < 0 && debug_option(kDbgGemmSkinny) != 0)
+  if (!simple && (canon_streams(M, N) || canon_streams16(M, N, K)) && debug_option(kDbgGemmTile) < 0 && debug_option(kDbgGemmSkinny) != 0)
     return launch_mxfp4_gemm_canon_stream(Xq, Xs, Wq, Ws, M, N, K, out_f32, Y, ldy, stream);
   if (!simple) return launch_mxfp4_gemm_canon(Xq, Xs, Wq, Ws, M, N, K, out_f32, Y, ldy, stream);
   const int64_t tiles = ((M + 31) / 32) * ((N + 31) / 32);

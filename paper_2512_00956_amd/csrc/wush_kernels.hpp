@@ -94,6 +94,7 @@ hipError_t launch_mxfp4_gemm_canon(const void* Xq, const void* Xs, const void* W
                                    hipStream_t stream);
 // The same where a 32 x 32 block of outputs gets a compute unit of its own (mxfp4_gemm_canon_stream.hip).
 bool canon_streams(int64_t M, int64_t N);
+bool canon_streams16(int64_t M, int64_t N, int64_t K);
 hipError_t launch_mxfp4_gemm_canon_stream(const void* Xq, const void* Xs, const void* Wq, const void* Ws, int64_t M, int64_t N,
                                           int64_t K, int out_f32, void* Y, int64_t ldy, hipStream_t stream);
 // Operands in the fragment-order layout (K % 256 == 0).
