@@ -141,47 +141,63 @@ __device__ __forceinline__ bool invert_block_group(EntryFn entry, StoreFn store)
   return good;
 }
 
+// x / root from the root's reciprocal, corrected.
+__device__ __forceinline__ double over_root(double x, double root, double inv) {
+  const double q = x * inv;
+  return fma(fma(-root, q, x), inv, q);
+}
+
 // Reverse Cholesky factor of a symmetric positive definite 32 x 32 S and its inverse, by 256 threads: S = U U^T with
 // U upper triangular, V = U^-1, from the elimination of [S | I] row by row from the last: with d the diagonal entry
 // of row j of what is left, row j over sqrt(d) is column j of U (left half) and row j of V (right half), and a row
 // r < j loses row j times its own entry over d -- which is row j's entry r, S being symmetric.  Thread t owns row
-// t / 8, columns 8 (t % 8) ... + 7 of the 64; one barrier per row.  Returns false if S is not positive definite (the
-// same in every thread).
+// t / 8, columns 8 (t % 8) ... + 7 of the 64.  Two rows per barrier: j and j - 1 go out together, and every thread takes row j off its part of
+// row j - 1 by itself (one row per barrier: 520 cycles a row, most of them the way through LDS).  Returns false if S is not positive
+// definite (the same in every thread).
 template <class EntryFn, class StoreUFn, class StoreVFn>
 __device__ __forceinline__ bool reverse_factor_group(EntryFn entry, StoreUFn store_u, StoreVFn store_v) {
-  __shared__ __attribute__((aligned(16))) double rowb[2][64];
+  __shared__ __attribute__((aligned(16))) double rowb[2][2][64];
   const int t = threadIdx.x, r = t >> 3, c0 = 8 * (t & 7);
   double a[8], diag = 1.0;
 #pragma unroll
   for (int i = 0; i < 8; ++i) a[i] = c0 < 32 ? entry(r, c0 + i) : (c0 - 32 + i == r ? 1.0 : 0.0);
   bool good = true;
-  for (int j = 31; j >= 0; --j) {
-    double* row = rowb[j & 1];
-    if (r == j) {
+  for (int j = 31; j > 0; j -= 2) {
+    double (*rows)[64] = rowb[(j >> 1) & 1];
+    if ((r | 1) == j) {
 #pragma unroll
-      for (int i = 0; i < 8; i += 2) *reinterpret_cast<v2d*>(&row[c0 + i]) = (v2d){a[i], a[i + 1]};
+      for (int i = 0; i < 8; i += 2) *reinterpret_cast<v2d*>(&rows[r & 1][c0 + i]) = (v2d){a[i], a[i + 1]};
     }
     __syncthreads();
-    double d = row[j];
-    if (!(d > 0.0)) { good = false; d = 1.0; }
-    if (r == j) diag = d;
-    const double f = r < j ? div_refined(row[r], d) : 0.0;
+    const double *hi = rows[1], *lo = rows[0];         // rows j and j - 1
+    double x[8], y[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) a[i] = fma(-f, row[c0 + i], a[i]);
+    for (int i = 0; i < 8; i += 2) {
+      const v2d u = *reinterpret_cast<const v2d*>(&hi[c0 + i]), v = *reinterpret_cast<const v2d*>(&lo[c0 + i]);
+      x[i] = u[0];
+      x[i + 1] = u[1];
+      y[i] = v[0];
+      y[i + 1] = v[1];
+    }
+    const double beside = hi[j - 1], hi_r = hi[r], lo_r = lo[r];
+    double d1 = hi[j];
+    if (!(d1 > 0.0)) { good = false; d1 = 1.0; }
+    const double g = div_refined(beside, d1), f1 = r < j ? div_refined(hi_r, d1) : 0.0;
+    double d0 = fma(-g, beside, lo[j - 1]);
+    if (!(d0 > 0.0)) { good = false; d0 = 1.0; }
+    const double f0 = r < j - 1 ? div_refined(fma(-g, hi_r, lo_r), d0) : 0.0;
+    if (r == j) diag = d1;
+    if (r == j - 1) diag = d0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) a[i] = fma(-f0, fma(-g, x[i], y[i]), fma(-f1, x[i], a[i]));
   }
-  const double root = sqrt(diag);
+  const double root = sqrt(diag), inv = 1.0 / root;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    if (c0 < 32) store_u(c0 + i, r, c0 + i <= r ? a[i] / root : 0.0);
-    else store_v(r, c0 - 32 + i, c0 - 32 + i >= r ? a[i] / root : 0.0);
+    if (c0 < 32) store_u(c0 + i, r, c0 + i <= r ? over_root(a[i], root, inv) : 0.0);
+    else store_v(r, c0 - 32 + i, c0 - 32 + i >= r ? over_root(a[i], root, inv) : 0.0);
   }
   return good;
-}
-
-// x / root from the root's reciprocal, corrected.
-__device__ __forceinline__ double over_root(double x, double root, double inv) {
-  const double q = x * inv;
-  return fma(fma(-root, q, x), inv, q);
 }
 
 // One sweep of one-sided Jacobi over the columns of A (A[column][row], D = 32 or 16) by the first 4 D of a workgroup's 8 D threads (for
