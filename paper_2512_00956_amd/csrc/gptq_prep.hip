@@ -22,6 +22,8 @@
 //     err = (w - q)/R[r][r], w[r'] -= err R[r][r']), G_i, and block i + 1: S += G_i U, current weights, M_W.
 // c2 (4096 calibration tokens, 4096 -> 6144): 70.4 -> 17.2 ms, of which the loop 128 x 94 us, the factor 3.1 ms and H 1.8.
 // Summation orders are fixed (no atomics), so the result is reproducible.
+#include <algorithm>
+
 #include "weight_mfma.hpp"
 #include "wush_block.hpp"
 #include "wush_kernels.hpp"
@@ -321,7 +323,7 @@ __global__ __launch_bounds__(256) void gptq_chain_kernel(const double* __restric
                                                          const double* __restrict__ MX_i, double lambda,
                                                          const double* __restrict__ V0_i, uint16_t* __restrict__ T_bits_i,
                                                          int given, const double* __restrict__ U, double* __restrict__ S,
-                                                         int row_groups, double* __restrict__ Tinv, double* __restrict__ R,
+                                                         int near_groups, int far_groups, double* __restrict__ Tinv, double* __restrict__ R,
                                                          int* __restrict__ status) {
   extern __shared__ __attribute__((aligned(16))) double smem[];   // workgroup 0: BlockShared; others [block][pair of operand registers][lane][2]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, l4 = lane >> 4;
@@ -406,8 +408,11 @@ __global__ __launch_bounds__(256) void gptq_chain_kernel(const double* __restric
     }
     return;
   }
-  const int g = ((int)blockIdx.x - 1) % row_groups;
-  const Pending job = pending_of(i, K >> 5, ((int)blockIdx.x - 1) / row_groups);
+  // the first near_groups workgroups share the rows of block i + 1, every far_groups behind them those of a later one
+  const int id = (int)blockIdx.x - 1;
+  const bool near = id < near_groups;
+  const int row_groups = near ? near_groups : far_groups, g = near ? id : (id - near_groups) % far_groups;
+  const Pending job = pending_of(i, K >> 5, near ? 0 : (near_groups > 0 ? 1 : 0) + (id - near_groups) / far_groups);
   const int nb = job.hi - job.lo;
   for (int b = wave; b < nb; b += 4) {
     Block32 u;
@@ -754,14 +759,21 @@ hipError_t launch_gptq_prep(const void* W, int64_t N, int64_t K, int64_t ldw, co
   const int splits = (int)(groups < most ? groups : most);
   for (int i = -1; i < C; ++i) {
     if (i >= 0) {
-      // workgroup 0: T_i; the others: pending errors, one round of workgroups (one per compute unit, by their LDS)
-      const int columns = pending_columns(i, C);
-      int row_groups = columns > 0 ? (device_cu_count() - 1) / columns : 0;
-      if (row_groups > (tiles + 3) / 4) row_groups = (int)((tiles + 3) / 4);
-      if (columns > 0 && row_groups < 1) row_groups = 1;
-      gptq_chain_kernel<<<(unsigned)(1 + columns * row_groups), 256, kChainLds, st>>>(
+      // workgroup 0: T_i; the others: pending errors, one round of workgroups (one per compute unit, by their LDS), dealt out by the products
+      // they have to form: block i + 1 lacks up to six blocks' errors where the others take four (as many workgroups for each: the steps of the
+      // first third of the c2 layer took 44 to 61 us, by that number, where the chain itself takes 40)
+      const bool near = i > 0 && i + 1 < C;
+      const int far = pending_columns(i, C) - near, others = device_cu_count() - 1, most = (int)((tiles + 3) / 4);
+      int near_groups = 0, far_groups = 0;
+      if (near) {
+        const Pending job = pending_of(i, C, 0);
+        const int nb = job.hi - job.lo;
+        near_groups = std::min(most, std::max(1, others * nb / (nb + kGroup * far)));
+      }
+      if (far > 0) far_groups = std::min(most, std::max(1, (others - near_groups) / far));
+      gptq_chain_kernel<<<(unsigned)(1 + near_groups + far * far_groups), 256, kChainLds, st>>>(
           partial, splits, Ni, Ki, i, MX + (int64_t)i * 1024, lambda, V0 ? V0 + (int64_t)i * 1024 : nullptr,
-          Tbits + (int64_t)i * 1024, transform_given, U, S, row_groups, Tinv, R, status);
+          Tbits + (int64_t)i * 1024, transform_given, U, S, near_groups, far_groups, Tinv, R, status);
       WUSH_GPTQ_CHECK()
     }
     gptq_rows_kernel<<<(unsigned)splits, 64 * kRowWaves, sizeof(RowShared), st>>>(Wb, ldw, Ni, Ki, i, S, U, Vd,
