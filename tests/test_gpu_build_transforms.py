@@ -220,3 +220,31 @@ def test_equal_channels_are_flagged(P, G, block):
             except P.WushError as e:
                 assert e.code == 7
     assert missed == []
+
+
+@pytest.mark.parametrize("block", [32, 16])
+@pytest.mark.parametrize("spread", [0.0, 1.0, 2.5])
+@pytest.mark.parametrize("rows", [40, 2000])
+def test_transforms_diagonalize_graded_moments(P, G, block, spread, rows):
+    """Channels whose scales spread over exp(spread N(0, 1)), lambda = 0: H^T T M_X T^T H = S is diagonal.  Its off-diagonal entries relative to
+    the diagonal ones: what the right rotations lack of orthogonality, some 50 rounds and steps of 32 rounded terms each, 50 x 32 x 2^-53 = 2e-13,
+    and T's own rounding.  An entry of T is a sum over the rows S^(-1/2) U^T W'^T of either sign, rounded relative to the largest; a row
+    comes back with 2^-53 of that, the square root of the singular values' ratio, and meets the largest direction of M_X, the same again:
+    2^-53 x ratio for each of the 2 x 32 terms of a pair of rows.  The check itself is in long double."""
+    import torch
+    rng = np.random.default_rng(rows + int(10 * spread))
+    K = 64
+    W, X = (O.round_to_bf16(rng.standard_normal((rows, K)) * s) for s in (1.0, np.exp(spread * rng.standard_normal(K))))
+    T = torch.empty((K // block, block, block), dtype=torch.bfloat16, device="cuda")
+    T64 = torch.full((K // block, block, block), float("nan"), dtype=torch.float64, device="cuda")
+    ws = G.empty_u8(P.wush_build_transforms_workspace(K))
+    build = P.wush_build_transforms if block == 32 else P.wush_build_transforms_nvfp4
+    build(*(G.bf16_dev(O.bf16_values_to_bits(a)) for a in (W, X)), 0.0, T, ws, T_f64=T64)
+    P.wush_build_transforms_status(ws, K)
+    H = O.hadamard(block).astype(np.longdouble)
+    for i, t in enumerate(T64.cpu().numpy().astype(np.longdouble)):
+        x = X[:, block * i:block * (i + 1)].astype(np.longdouble)
+        S = H.T @ t @ (x.T @ x / rows) @ t.T @ H
+        d = np.sqrt(np.diag(S))
+        off, ratio = np.max(np.abs(S / np.outer(d, d) - np.eye(block))), (d.max() / d.min()) ** 2
+        assert off <= 2e-13 + 64 * 2.0 ** -53 * ratio, (off, ratio)
