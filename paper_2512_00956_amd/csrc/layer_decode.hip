@@ -13,9 +13,8 @@
 // 33..64 tokens) partial tiles on the scaled 32x32x64 MFMA, and reduce the four
 // partials through LDS in a fixed order.  The W fragment is the first MFMA
 // operand, so a lane's accumulator quad is four consecutive output channels of one
-// token.  A wave issues the loads of 4 K tiles (2 for 33..64 tokens) of W and X
-// together and then consumes them; beyond that, latency is hidden by occupancy
-// (several workgroups per CU), not by a software pipeline.
+// token.  Latency is hidden by the workgroups a CU holds and by a short ring of K tiles
+// per wave (gemm_skinny_kernel); the fused form takes 4 K tiles (2 for 33..64 tokens) at a time.
 //
 // Fused form.  Phase 1: the (token tile, 4 blocks) units of the activation
 // quantizer are dealt out one per wave over the grid and write Xq/Xs (fragment
@@ -122,53 +121,24 @@ __device__ __forceinline__ void accumulate_block(v16f (&acc)[RB], FragTile (&w)[
   }
 }
 
-// Row blocks RB blockIdx.y ... of the tokens.
-template <int RB, bool OUT_F32>
-__global__ __launch_bounds__(kWaves * 64) void gemm_skinny_kernel(
+// The GEMM: workgroup (j, y) takes output channels 32 j ... + 31 of row blocks RB y ... + RB - 1 of the tokens.  A wavefront has RING K tiles in flight
+// at any time, each slot refilled as soon as it has been multiplied; in chunks, all of whose loads were awaited before the first product (four
+// tiles, two for more row blocks), nothing covered the gap between a chunk's last product and the next one's data, with a compute unit's
+// one workgroup least of all.  Replayed graphs, four sets of operands, us, chunks | ring: 64 x 14336 -> 4096 10.0 | 9.1, 100 x 14336 -> 4096 12.3 | 11.5,
+// 32 x 8192 -> 8192 9.2 | 8.1, 256 x 4096 -> 4096 8.9 | 7.9, 1024 x 4096 -> 1024 9.7 | 8.5, 448 x 28672 -> 512 14.3 | 14.4; several workgroups per
+// unit 32 x 8192 -> 57344 51.0 | 48.6, 24 x 4096 -> 28672 14.1 | 13.1, 32 x 512 -> 57344 8.8 | 6.2, 48 x 4096 -> 12288 9.7 | 8.2, 100 x 28672 -> 9000
+// 71.4 | 71.4.  Tiles in flight: one row block four, two up to K = 2048, where a wavefront's range is no longer than that (24 x 4096 -> 28672
+// 13.1 | 13.6, 20 x 2048 -> 20480 6.7 | 6.4, 448 x 28672 -> 512 with six 14.7); two row blocks two, one up to 4096 (64 x 28672 -> 10240 52.9 | 53.8, 48 x
+// 4096 -> 12288 8.9 | 8.2); four row blocks one (1024 x 4096 -> 1024 with two 8.9).  More registers for deeper rings cost resident workgroups, and
+// one alone is bound by what a compute unit gets out of the L2 and beyond, some 80 GB/s.
+template <int RB, int R, bool OUT_F32>
+__global__ __launch_bounds__(kWaves * 64, 1) void gemm_skinny_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const uint8_t* __restrict__ Wq,
     const uint8_t* __restrict__ Ws, int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
   __shared__ float red[kWaves][RB][16][64];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int KT = K >> 8, NB = (N + 31) >> 5;
-  const int64_t row_block = (int64_t)RB * blockIdx.y;
-  Xq += row_block * KT * 4096;
-  Xs += row_block * KT * 256;
-  Y = static_cast<uint8_t*>(Y) + 32 * row_block * ldy * (OUT_F32 ? 4 : 2);
-  M -= 32 * (int)row_block;
-  int kt0, kt1;
-  wave_k_range(KT, wave, kt0, kt1);
-  for (int j = blockIdx.x; j < NB; j += gridDim.x) {
-    v16f acc[RB];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) acc[rb] = (v16f){0};
-    if (kt0 < kt1) {
-      FragTile w[Depth<RB>::U];
-      load_w_chunk<Depth<RB>::U>(w, Wq, Ws, (int64_t)j * KT + kt0, min(Depth<RB>::U, kt1 - kt0), lane);
-      accumulate_block<RB>(acc, w, Xq, Xs, Wq, Ws, KT, j, kt0, kt1, lane);
-    }
-    reduce_store_block<RB, OUT_F32>(acc, red, j, M, N, Y, ldy, lane, wave);
-  }
-}
-
-// The same where every workgroup has a compute unit of its own, one wavefront per SIMD: no other workgroup fills the gap between a chunk's
-// last product and the next one's data.  RING K tiles are in flight at any time, each slot refilled as soon as it has been multiplied
-// (replayed graphs, four sets of operands, us, in chunks | ring: 16 x 14336 -> 4096 9.6 | 9.0, 1 x 4096 -> 6144 5.4 | 5.0, 32 x 8192 -> 8192 9.2 | 8.1,
-// 64 x 14336 -> 4096 10.0 | 9.1, 100 x 14336 -> 4096 12.3 | 11.5, 256 x 4096 -> 4096 8.9 | 7.9, 1024 x 4096 -> 1024 9.7 | 8.5, 448 x 28672 -> 512
-// 14.3 | 14.4).  Deeper rings, up to what the counter of outstanding loads allows, are no faster (one row block 6 tiles 9.0 | 4 9.0 | 3 9.1,
-// 448 x 28672 -> 512 14.7 | 14.3 | 14.4; two row blocks 4 tiles 11.7 | 3 11.6 | 2 11.5; four 2 tiles 8.9 | 1 8.5): what bounds these layers is
-// what a compute unit gets out of the L2 and beyond, some 80 GB/s.
-template <int RB>
-struct Ring { static constexpr int R = RB == 1 ? 4 : RB == 2 ? 2 : 1; };
-template <int RB, bool OUT_F32>
-__global__ __launch_bounds__(kWaves * 64, 1) void gemm_skinny_ring_kernel(
-    const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const uint8_t* __restrict__ Wq,
-    const uint8_t* __restrict__ Ws, int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
-  constexpr int R = Ring<RB>::R;
-  __shared__ float red[kWaves][RB][16][64];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int KT = K >> 8, NB = (N + 31) >> 5, j = blockIdx.x;
+  const int KT = K >> 8, NB = (N + 31) >> 5, j = blockIdx.x + gridDim.x * blockIdx.z;
   if (j >= NB) return;                        // the grid's padding
   const int64_t row_block = (int64_t)RB * blockIdx.y;
   Xq += row_block * KT * 4096;
@@ -460,6 +430,8 @@ int skinny_row_blocks(int64_t M, int64_t N) {
 // L2 (us, tiles | as many workgroups as blocks | this: 512 x 1024 -> 1984 4.89 | 5.86 | 4.76, 384 x 1536 -> 1984 5.59 | 6.27 | 5.48).
 int64_t skinny_grid_width(int64_t N) { return ((N + 31) / 32 + 7) & ~(int64_t)7; }
 
+constexpr int64_t kMostWide = 1 << 20;   // workgroups along x; 2^30 output channels are 2^25 blocks, 256 threads each
+
 hipError_t launch_mxfp4_gemm_skinny(const void* Xq, const void* Xs, const void* Wq, const void* Ws, int64_t M,
                                     int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy, hipStream_t stream) {
   const int NB = (int)((N + 31) / 32);
@@ -478,19 +450,13 @@ hipError_t launch_mxfp4_gemm_skinny(const void* Xq, const void* Xs, const void* 
   }
   const int rb = skinny_row_blocks(M, N), groups = (int)((M + 32 * rb - 1) / (32 * rb));
   const int64_t wide = rb == 4 && groups > 1 ? skinny_grid_width(N) : NB;
-  dim3 grid((unsigned)(wide < 4096 ? wide : 4096), (unsigned)groups), block(kWaves * 64);
-  const bool alone = wide * groups <= device_cu_count();
-#define WUSH_SKINNY_LAUNCH(RB, F32)                                                                         \
-  (alone ? gemm_skinny_ring_kernel<RB, F32> : gemm_skinny_kernel<RB, F32>)<<<grid, block, 0, stream>>>(     \
-      (const uint8_t*)Xq, (const uint8_t*)Xs, (const uint8_t*)Wq, (const uint8_t*)Ws, (int)M, (int)N, (int)K, Y, ldy)
-  if (rb == 1) {
-    if (out_f32) WUSH_SKINNY_LAUNCH(1, true); else WUSH_SKINNY_LAUNCH(1, false);
-  } else if (rb == 2) {
-    if (out_f32) WUSH_SKINNY_LAUNCH(2, true); else WUSH_SKINNY_LAUNCH(2, false);
-  } else {
-    if (out_f32) WUSH_SKINNY_LAUNCH(4, true); else WUSH_SKINNY_LAUNCH(4, false);
-  }
-#undef WUSH_SKINNY_LAUNCH
+  dim3 grid((unsigned)(wide < kMostWide ? wide : kMostWide), (unsigned)groups, (unsigned)((wide + kMostWide - 1) / kMostWide)), block(kWaves * 64);
+#define WUSH_SKINNY(RB, R) (out_f32 ? gemm_skinny_kernel<RB, R, true> : gemm_skinny_kernel<RB, R, false>)
+  auto kernel = rb == 1 ? (K <= 2048 ? WUSH_SKINNY(1, 2) : WUSH_SKINNY(1, 4))
+              : rb == 2 ? (K <= 4096 ? WUSH_SKINNY(2, 1) : WUSH_SKINNY(2, 2)) : WUSH_SKINNY(4, 1);
+#undef WUSH_SKINNY
+  kernel<<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs, (const uint8_t*)Wq, (const uint8_t*)Ws, (int)M, (int)N,
+                                     (int)K, Y, ldy);
   return hipGetLastError();
 }
 
