@@ -13,8 +13,8 @@
 //      sums go to the workspace (fixed split -> fixed summation order, no atomics).
 //   2. wush_block_kernel: one workgroup of four wavefronts per block (two for 16 x 16
 //      blocks): reduce the partials, damp, Cholesky of both moments side by side, A = W'^T X',
-//      one-sided Jacobi SVD on the columns of A (16 disjoint column pairs per
-//      round; V is never needed), sort, sign convention
+//      SVD of A by right rotations (sweeps of one-sided Jacobi, then all small
+//      angles at once; V is never needed), sort, sign convention
 //      (largest-magnitude entry of each column of U positive), then
 //      T = H diag(s^-1/2) U^T W'^T, rounded to BF16 (nearest even, straight from
 //      FP64).

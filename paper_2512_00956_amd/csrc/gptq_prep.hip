@@ -15,12 +15,12 @@
 // the propagation needs the factor U and the inverses of its diagonal blocks, no other part of U^-1 (whose
 // computation, a triangular inverse, took 5.6 ms of the c2 layer's 70).
 //
-// Steps: H; its factor (one launch per 32 columns); then the sequential loop over blocks, three launches each:
-//     M_W of block i's current weights, Alg. 1 -> T_i (rounded to BF16);   beside it errors G U onto later S
-//     inv(T_i);  Hbar = (T_i U_ii)(T_i U_ii)^T, R = inverse of its reverse Cholesky factor (R^T R = inv(Hbar))
+// Steps: H; its factor (one launch per 32 columns); then the sequential loop over blocks, two launches each:
+//     M_W of block i's current weights, Alg. 1 -> T_i (rounded to BF16);  Hbar = (T_i U_ii)(T_i U_ii)^T, R = inverse of its
+//       reverse Cholesky factor (R^T R = inv(Hbar));  inv(T_i);   beside it errors G U onto later S
 //     per output channel: transformed weights, GPTQ subroutine (32 steps of quantize at a static group scale,
 //     err = (w - q)/R[r][r], w[r'] -= err R[r][r']), G_i, and block i + 1: S += G_i U, current weights, M_W.
-// c2 (4096 calibration tokens, 4096 -> 6144): 70.4 -> 17.2 ms, of which the loop 128 x 94 us, the factor 3.1 ms and H 1.8.
+// c2 (4096 calibration tokens, 4096 -> 6144): 70.4 -> 12.2 ms, of which the loop 128 x 61 us, the factor 3.0 ms and H 1.3.
 // Summation orders are fixed (no atomics), so the result is reproducible.
 #include <algorithm>
 
@@ -279,8 +279,8 @@ __global__ __launch_bounds__(256) void gptq_moment0_kernel(const uint16_t* __res
 }
 
 // Right singular vectors of W'^T X' of every block of the ORIGINAL weights: what the SVD inside the loop starts from.
-// All blocks at once (they fill the chip), while inside the loop a block waits for its SVD alone: there the sweeps left
-// to do fall from 7..9 to about 5.
+// All blocks at once (they fill the chip), while inside the loop a block waits for its SVD alone: there two
+// sweeps and four steps (orthogonalize_group) become four steps.
 __global__ __launch_bounds__(256) void gptq_warm_kernel(const double* __restrict__ partial, int splits, int N,
                                                         const double* __restrict__ MX, double lambda, double* __restrict__ V0) {
   const int b = blockIdx.x;
@@ -315,8 +315,8 @@ __host__ __device__ inline Pending pending_of(int i, int C, int index) {
 }
 constexpr int kMostPending = 2 * kGroup - 2;
 
-// Workgroup 0: Alg. 1 on (M_W of block i's current weights, M_X = diagonal block of H) -> T_i, a chain of some 60 us on
-// one compute unit (110 before).  The others meanwhile: S_l += sum_b G_b U_bl for the pending blocks l.  A workgroup holds its U_bl
+// Workgroup 0: Alg. 1 on (M_W of block i's current weights, M_X = diagonal block of H) -> T_i, then inv(T_i) and R, a chain of some 40 us on
+// one compute unit.  The others meanwhile: S_l += sum_b G_b U_bl for the pending blocks l.  A workgroup holds its U_bl
 // in LDS in operand order, its wavefronts walk tiles of 16 rows (64 bytes per lane and operand, the next tile's
 // requested before this one's products); the panels G_b (the errors; block b's, whose S is used up) and S_l are [N][32].
 __global__ __launch_bounds__(256) void gptq_chain_kernel(const double* __restrict__ partial, int splits, int N, int K, int i,

@@ -132,7 +132,7 @@ __device__ __forceinline__ void accumulate_block(v16f (&acc)[RB], FragTile (&w)[
 // 4096 -> 12288 8.9 | 8.2); four row blocks one (1024 x 4096 -> 1024 with two 8.9).  More registers for deeper rings cost resident workgroups, and
 // one alone is bound by what a compute unit gets out of the L2 and beyond, some 80 GB/s.
 template <int RB, int R, bool OUT_F32>
-__global__ __launch_bounds__(kWaves * 64, 1) void gemm_skinny_kernel(
+__device__ __forceinline__ void gemm_skinny_ring(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const uint8_t* __restrict__ Wq,
     const uint8_t* __restrict__ Ws, int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
   __shared__ float red[kWaves][RB][16][64];
@@ -189,6 +189,19 @@ __global__ __launch_bounds__(kWaves * 64, 1) void gemm_skinny_kernel(
   for (int u = 0; u < R; ++u)
     if (kt + R + u < kt1) multiply(u);
   reduce_store_block<RB, OUT_F32>(acc, red, j, M, N, Y, ldy, lane, wave);
+}
+
+template <int RB, bool OUT_F32>
+__global__ __launch_bounds__(kWaves * 64, 1) void gemm_skinny_kernel(
+    const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const uint8_t* __restrict__ Wq,
+    const uint8_t* __restrict__ Ws, int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
+  gemm_skinny_ring<RB, RB == 1 ? 4 : RB == 2 ? 2 : 1, OUT_F32>(Xq, Xs, Wq, Ws, M, N, K, Y, ldy);
+}
+template <int RB, bool OUT_F32>   // short K
+__global__ __launch_bounds__(kWaves * 64, 1) void gemm_skinny_short_kernel(
+    const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const uint8_t* __restrict__ Wq,
+    const uint8_t* __restrict__ Ws, int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
+  gemm_skinny_ring<RB, RB == 1 ? 2 : 1, OUT_F32>(Xq, Xs, Wq, Ws, M, N, K, Y, ldy);
 }
 
 // At most 16 tokens, on v_mfma_scale_f32_16x16x128_f8f6f4: half of the activations' fragments and of every product would be a row block's padding.
@@ -451,9 +464,10 @@ hipError_t launch_mxfp4_gemm_skinny(const void* Xq, const void* Xs, const void* 
   const int rb = skinny_row_blocks(M, N), groups = (int)((M + 32 * rb - 1) / (32 * rb));
   const int64_t wide = rb == 4 && groups > 1 ? skinny_grid_width(N) : NB;
   dim3 grid((unsigned)(wide < kMostWide ? wide : kMostWide), (unsigned)groups, (unsigned)((wide + kMostWide - 1) / kMostWide)), block(kWaves * 64);
-#define WUSH_SKINNY(RB, R) (out_f32 ? gemm_skinny_kernel<RB, R, true> : gemm_skinny_kernel<RB, R, false>)
-  auto kernel = rb == 1 ? (K <= 2048 ? WUSH_SKINNY(1, 2) : WUSH_SKINNY(1, 4))
-              : rb == 2 ? (K <= 4096 ? WUSH_SKINNY(2, 1) : WUSH_SKINNY(2, 2)) : WUSH_SKINNY(4, 1);
+#define WUSH_SKINNY(KERNEL, RB) (out_f32 ? KERNEL<RB, true> : KERNEL<RB, false>)
+  auto kernel = rb == 1 ? (K <= 2048 ? WUSH_SKINNY(gemm_skinny_short_kernel, 1) : WUSH_SKINNY(gemm_skinny_kernel, 1))
+              : rb == 2 ? (K <= 4096 ? WUSH_SKINNY(gemm_skinny_short_kernel, 2) : WUSH_SKINNY(gemm_skinny_kernel, 2))
+                        : WUSH_SKINNY(gemm_skinny_kernel, 4);
 #undef WUSH_SKINNY
   kernel<<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs, (const uint8_t*)Wq, (const uint8_t*)Ws, (int)M, (int)N,
                                      (int)K, Y, ldy);
