@@ -366,10 +366,15 @@ __device__ __forceinline__ v4d product_tile(const double (*X)[D + 2], int x0, co
 // angles, then all pairs at once.
 //
 // The simultaneous step: with K[i][j] = the tangent that makes columns i and j orthogonal by themselves (antisymmetric), A <- A P with
-// an orthogonal P = exp(K) up to FP64's resolution; what it leaves is of second order in K, as behind a sweep.  It is five to
-// seven 32 x 32 products on the FP64 MFMA, a tile per wavefront, 1.5 to 2.5 us, where a sweep is a chain of 31 dependent rounds of 650 cycles, 8.7 us.
-//   G = A^T A gives the angles;  K^2;  P = I + K + K^2 / 2 (tangents up to 1e-5), + K^3 / 6 + K^4 / 24;  beyond 1e-3 Newton-Schulz steps
+// P = exp(K) nearly, orthogonal to FP64's resolution; what it leaves is of second order in K, as behind a sweep.  Its 32 x 32 products
+// are on the FP64 MFMA, a tile per wavefront: three for tangents up to 1e-5, four up to 3e-4, two more with every step of correction, 1.5 to 4 us where a
+// sweep is a chain of 31 dependent rounds of 650 cycles, 8.7 us.
+//   G = A^T A gives the angles;  K^2;  P = I + K + K^2 / 2, + K^3 / 6 + K^4 / 24 beyond 1e-5;  beyond 3e-4 Newton-Schulz steps
 //   P <- P (3 I - P^T P) / 2 until P^T P differs from I by 2e-9 at most before the last one;  A P.
+// Everything behind relies on A P having A's singular values, so a P that is not orthogonal is never applied.  What decides is the norm of K, which
+// 31 tangents of one size in every row make up to 20.4 times as large as one of them: there P^T P - I is ||K||^4 / 4 = 4e-16 at 1e-5 and
+// ||K||^6 / 72 = 7e-16 at 3e-4 (5e-13 with that line at 1e-3), and the correction takes one to four steps for angles as they come, but up to eight
+// for such rows of 0.05 to 0.15; behind the eighth, or with an entry of P^T P - I at 0.1 or more, the step is refused and a sweep takes its place.
 // Everything is graded as A's columns are (K[i][j] is about cosine x ratio of the norms), so small columns keep their relative accuracy.
 // P is kept transposed, so that both operands of all products but two are read along their rows.
 // It is taken up to tangents of 0.4 (blocks of the 4096 -> 6144 layer, sweeps + steps from the Cholesky factors: never 5.9 + 0, 0.003: 3.3 +
@@ -386,7 +391,7 @@ __device__ __forceinline__ v4d product_tile(const double (*X)[D + 2], int x0, co
 template <int D>
 __device__ __forceinline__ void orthogonalize_group(double (*A)[D + 2], double (*K)[D + 2], double (*Q)[D + 2], double (*R)[D + 2],
                                                     double* norm2, int* votes, bool cold) {
-  constexpr int kTurn = 1, kSweep = 2, kMore = 4, kFourth = 8, kFix = 16;
+  constexpr int kTurn = 1, kSweep = 2, kMore = 4, kFourth = 8, kFix = 16, kMostFixes = 8;
   if (D == 16 && threadIdx.x >= 64) return;            // one wavefront: nobody to wait for
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, l4 = lane >> 4;
   const int i0 = D == 32 ? 16 * (wave >> 1) : 0, j0 = D == 32 ? 16 * (wave & 1) : 0;   // this wavefront's tile of every product
@@ -446,7 +451,7 @@ __device__ __forceinline__ void orthogonalize_group(double (*A)[D + 2], double (
       k[v] = turn ? tn : 0.0;
       const double mag = fabs(k[v]);
       bits |= (turn ? kTurn : 0) | (mag > 0.4 ? kSweep : 0) | (turn && (gg > 1e-20 * ab || mag > 1e-7) ? kMore : 0) |
-              (mag > 1e-5 ? kFourth : 0) | (mag > 1e-3 ? kFix : 0);
+              (mag > 1e-5 ? kFourth : 0) | (mag > 3e-4 ? kFix : 0);
     }
     put(K, k);
     const int seen = vote(bits);
@@ -477,7 +482,7 @@ __device__ __forceinline__ void orthogonalize_group(double (*A)[D + 2], double (
       sync();
       if (seen & kFix) {
         double (*other)[D + 2] = R;
-        for (int fix = 0; fix < 4; ++fix) {
+        for (int fix = 0; fix < kMostFixes; ++fix) {
           v4d s = product_tile<D>(P, i0, P, j0, zero);
           bool off = false, lost = false;
 #pragma unroll
@@ -489,8 +494,8 @@ __device__ __forceinline__ void orthogonalize_group(double (*A)[D + 2], double (
           }
           put(Q, s);
           const int left = vote((off ? kMore : 0) | (lost ? kSweep : 0));
-          step = !(left & kSweep);
-          if (!step) break;                            // far from orthogonal: a sweep instead, A is as it was
+          step = !(left & kSweep) && (fix + 1 < kMostFixes || !(left & kMore));
+          if (!step) break;                            // not orthogonal: a sweep instead, A is as it was
           p = product_tile<D, true>(Q, i0, P, j0, zero);
           put(other, p);
           sync();

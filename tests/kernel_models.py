@@ -1,4 +1,4 @@
-"""Kernel arithmetic models of the NVFP4 and INT4 quantizers -- test helpers, NOT oracles.
+"""Kernel arithmetic models of the NVFP4 and INT4 quantizers and of the SVD's simultaneous rotations -- test helpers, NOT oracles.
 
 The GPU quantizers take every decision step as one IEEE operation in one working
 precision (FP32 on the accumulators of the activation kernels, FP64 in the offline
@@ -118,3 +118,25 @@ def nvfp4_explained(vals64, ts, codes_gpu, sb_gpu, codes_ref, sb_ref, tol):
     near_mid = np.min(np.abs(v[..., None] - emid), axis=-1) <= tol * a[..., None]
     unexplained = bad & ~near_mid & ~near_scale[..., None]
     return float(np.mean(bad)), int(unexplained.sum())
+
+
+def simultaneous_rotation(K):
+    """The rotation P the SVD of a block applies for the antisymmetric tangents K, all at once, step for step: the exponential's series by the largest
+    tangent, Newton-Schulz corrections.  None where the kernel refuses it and takes a sweep of Jacobi."""
+    one, mag = np.eye(len(K)), np.abs(K).max()
+    if mag > 0.4:
+        return None
+    K2 = -K @ K.T
+    Pt = one - K + 0.5 * K2
+    if mag > 1e-5:
+        Pt = Pt + K2 @ (K2 / 24.0 + K / 6.0).T
+    if mag <= 3e-4:
+        return Pt.T
+    for fix in range(8):
+        S = Pt @ Pt.T
+        err = np.abs(S - one).max()
+        if not err < 0.1 or (err > 2e-9 and fix == 7):
+            return None
+        Pt = (1.5 * one - 0.5 * S) @ Pt
+        if err <= 2e-9:
+            return Pt.T

@@ -243,3 +243,36 @@ def test_gptq_equal_channels_are_flagged(P, G, K):
         except P.WushError as e:
             assert e.code == 7
     assert missed == []
+
+
+def _dense_turn(tangent, N=1024, K=1024):
+    """A layer whose block 1, at its turn, needs a rotation by `tangent` between every two of the directions it starts from.  The calibration moments
+    are exact: I, but 1/2 I between blocks 0 and 1 and (1/4 + 49/64) I in block 1, so block 1's weights lose 32/65 of block 0's errors E.  Those
+    are made part of them, W_1 = F + E B with F orthogonal to E, such that the moment of W_1 is diag(d), the one of what W_1
+    then is diag(d) + P, with P_ij = |d_i - d_j| tan(2 theta) / 2."""
+    rng = np.random.default_rng(int(1e4 * tangent))
+    Xc = np.ones((1, 1))
+    while Xc.shape[0] < K:
+        Xc = np.block([[Xc, Xc], [Xc, -Xc]])
+    Xc[:, 32:64] = 0.5 * Xc[:, :32] + 0.875 * Xc[:, 32:64]
+    W = O.round_to_bf16(rng.standard_normal((N, K)) * np.where(np.arange(K) < 32, 8.0, 1.0))
+    T, codes, scales = Q.gptq_wush_layer(W[:, :64], Xc[:, :64], 0.0)
+    E = O.dequantize(codes[:, :32], scales[:, :1]) @ T[0] - W[:, :32]
+    d, e, S = 1.31 - 0.01 * np.arange(32), -32.0 / 65.0, E.T @ E / N
+    P = np.abs(d[:, None] - d) * tangent / (1.0 - tangent ** 2)
+    SB = (P - e * e * S) / (2.0 * e)
+    F = rng.standard_normal((N, 32))
+    F = np.linalg.qr(F - E @ np.linalg.solve(E.T @ E, E.T @ F))[0] * np.sqrt(N)
+    W[:, 32:64] = O.round_to_bf16(F @ np.linalg.cholesky(np.diag(d) - SB @ np.linalg.solve(S, SB)).T + E @ np.linalg.solve(S, SB))
+    return W, Xc
+
+
+@pytest.mark.parametrize("tangent", [0.1, 0.12, 0.1475, 0.18])
+def test_gptq_block_that_turns_by_many_angles_at_once(P, G, tangent):
+    """31 tangents a row add up: the rotation by all of them at once is far from orthogonal as it is first formed, and its correction takes six
+    to eight steps or is refused (0.18).  One that is not orthogonal leaves other singular values, off by 2e-7 (0.1), 1e-3 (0.12) and 1e-2
+    (0.1475) with four steps."""
+    W, Xc = _dense_turn(tangent)
+    T, c, s = _run_gpu(P, G, W, Xc, 0.0)
+    Tr, cr, sr = Q.gptq_wush_layer(W, Xc, 0.0)
+    _compare(T, c, s, Tr, cr, sr, W, Xc, f"tangent {tangent}")

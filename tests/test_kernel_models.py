@@ -83,3 +83,19 @@ def test_fp32_models_against_exact_rational_arithmetic():
                 n_diff += 1
                 assert abs(k - int(c[g, i] & 7)) == 1
     assert n_diff <= 4
+
+
+@pytest.mark.parametrize("tangent", [1e-6, 1e-5, 3e-5, 2.9e-4, 3.1e-4, 1e-3, 0.01, 0.05, 0.08, 0.1, 0.11, 0.12, 0.13, 0.14, 0.1475, 0.1485, 0.15, 0.2, 0.3, 0.4])
+def test_simultaneous_rotations_are_orthogonal(tangent):
+    """Tangents of one size between all 32 columns, in an order (the largest norm) and with random signs, and random ones up to that size: a
+    rotation that is not refused has singular values of 1, up to the rounding of products of 32 terms and the series' remainder."""
+    rng = np.random.default_rng(5)
+    ordered = np.triu(np.ones((32, 32)), 1)
+    draws = [ordered] + [np.triu(rng.choice([-1.0, 1.0], (32, 32)), 1) for _ in range(40)] + [np.triu(rng.uniform(-1, 1, (32, 32)), 1) for _ in range(40)]
+    for up in draws:
+        P = KM.simultaneous_rotation(tangent * (up - up.T))
+        if P is None:
+            assert tangent > 0.14
+            continue
+        off = np.abs(np.linalg.svd(P, compute_uv=False) - 1).max()
+        assert off <= 32 * 2.0 ** -52, off
