@@ -122,6 +122,9 @@ __global__ __launch_bounds__(256) void second_moment_kernel(
 }
 
 // The first S_W splits of S hold rows of W, the first S_X rows of X.
+// FLIGHT = partial moments of either operand in flight.  16 of them take a wavefront's 404 registers, a compute unit's one workgroup; 4, all there are
+// where the blocks are so many that they go round by round, 122 (16 x 16 blocks 270 and 89), and three workgroups share a compute unit.
+template <int FLIGHT>
 __global__ __launch_bounds__(256) void wush_block_kernel(const double* __restrict__ partial, int S, int S_W, int S_X,
                                                          int C, int N, int Mc, double lambda, uint16_t* __restrict__ T_out,
                                                          double* __restrict__ T_f64, int* __restrict__ status) {
@@ -130,12 +133,13 @@ __global__ __launch_bounds__(256) void wush_block_kernel(const double* __restric
   auto load = [&](int half, int e, int, int, int s) { return partial[(((int64_t)half * S + s) * C + b) * kMomentSize + e]; };
   auto finish = [&](int half, double sum) { return sum * (1.0 / (double)(half ? Mc : N)); };
   __shared__ BlockShared<32> sh;
-  wush_block_group<32, 0, 16, 16>(sh, load, finish, S_W, S_X, lambda, nullptr, T_out + (int64_t)b * 1024,
-                          T_f64 ? T_f64 + (int64_t)b * 1024 : nullptr, nullptr, status);
+  wush_block_group<32, 0, FLIGHT, FLIGHT>(sh, load, finish, S_W, S_X, lambda, nullptr, T_out + (int64_t)b * 1024,
+                                          T_f64 ? T_f64 + (int64_t)b * 1024 : nullptr, nullptr, status);
 }
 
 // The same for 16 x 16 blocks (the NVFP4 variant: transform block = quantization group of 16).  The
 // moments of block b are the diagonal 16 x 16 sub-block (b & 1) of the 32-channel moments of block b / 2.
+template <int FLIGHT>
 __global__ __launch_bounds__(128) void wush_block16_kernel(const double* __restrict__ partial, int S, int S_W, int S_X,
                                                            int C, int N, int Mc, double lambda, uint16_t* __restrict__ T_out,
                                                            double* __restrict__ T_f64, int* __restrict__ status) {
@@ -145,8 +149,8 @@ __global__ __launch_bounds__(128) void wush_block16_kernel(const double* __restr
   };
   auto finish = [&](int half, double sum) { return sum * (1.0 / (double)(half ? Mc : N)); };
   __shared__ BlockShared<16> sh;
-  wush_block_group<16, 0, 16, 16>(sh, load, finish, S_W, S_X, lambda, nullptr, T_out + (int64_t)b * 256,
-                          T_f64 ? T_f64 + (int64_t)b * 256 : nullptr, nullptr, status);
+  wush_block_group<16, 0, FLIGHT, FLIGHT>(sh, load, finish, S_W, S_X, lambda, nullptr, T_out + (int64_t)b * 256,
+                                          T_f64 ? T_f64 + (int64_t)b * 256 : nullptr, nullptr, status);
 }
 
 // Splits of the rows, for about four workgroups of each moment per compute unit.  Every split costs a partial moment of 8 KiB per
@@ -159,6 +163,11 @@ int splits_for(int64_t C) {
   if (s > 256) s = 256;
   return (int)s;
 }
+
+// Partial moments in flight, by how many there are: four at most from 205 blocks of 32 channels on, where the blocks start to outnumber the compute
+// units (both kernels, us, 16 | 4 in flight, 32 x 32 blocks; 16 x 16: 8192 channels, 8192 + 2048 rows 143 | 141; 109 | 109; 12288, 2048 + 2048 rows
+// 159 | 131; 100 | 82; 16384, 4096 + 2048 rows 205 | 169; 148 | 123; 28672, 1024 + 1024 rows 268 | 206; 148 | 101, 8192 + 2048 rows 465 | 399; 353 | 311).
+constexpr int kFewSplits = 4, kManySplits = 16;
 
 }  // namespace
 
@@ -182,12 +191,14 @@ hipError_t launch_build_transforms(const void* W, int64_t N, int64_t ldw, const 
                                                                ldx, (int)Mc, per(N), per(Mc), S, C, partial, status);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (block == 16)
-    wush_block16_kernel<<<dim3(2 * C), dim3(128), 0, stream>>>(partial, S, used(N), used(Mc), C, (int)N, (int)Mc, lambda,
-                                                              (uint16_t*)T_out, T_f64, status);
-  else
-    wush_block_kernel<<<dim3(C), dim3(256), 0, stream>>>(partial, S, used(N), used(Mc), C, (int)N, (int)Mc, lambda,
-                                                        (uint16_t*)T_out, T_f64, status);
+  const bool few = used(N) <= kFewSplits && used(Mc) <= kFewSplits;
+  if (block == 16) {
+    auto kernel = few ? wush_block16_kernel<kFewSplits> : wush_block16_kernel<kManySplits>;
+    kernel<<<dim3(2 * C), dim3(128), 0, stream>>>(partial, S, used(N), used(Mc), C, (int)N, (int)Mc, lambda, (uint16_t*)T_out, T_f64, status);
+  } else {
+    auto kernel = few ? wush_block_kernel<kFewSplits> : wush_block_kernel<kManySplits>;
+    kernel<<<dim3(C), dim3(256), 0, stream>>>(partial, S, used(N), used(Mc), C, (int)N, (int)Mc, lambda, (uint16_t*)T_out, T_f64, status);
+  }
   return hipGetLastError();
 }
 

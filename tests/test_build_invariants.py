@@ -218,3 +218,12 @@ def test_streaming_kernels_store_four_outputs_at_a_time(src, pattern, count):
         wide = len(re.findall(r"^\s*global_store_dwordx[24]\b", body, flags=re.M))
         single = len(re.findall(r"^\s*global_store_(?:dword|short\w*)\s", body, flags=re.M))
         assert wide > 0 and single <= 3 * wide, (name, wide, single)
+
+
+def test_block_kernels_of_wide_layers_share_their_compute_unit():
+    """More blocks than compute units go round by round, as many workgroups to a unit as its registers and LDS hold: with the few partial moments
+    such layers have in flight, three waves per SIMD of 512 registers for the 32 x 32 blocks (four a workgroup, 54 of 160 KB), five for the 16 x 16."""
+    text = _compile("build_transforms.hip")
+    for pattern, budget in (("17wush_block_kernelILi4E", 168), ("19wush_block16_kernelILi4E", 96)):
+        counts = [int(c) for name, c in re.findall(r"\.name:\s+(\S+)\n(?:.*\n)*?\s+\.vgpr_count:\s+(\d+)", text) if pattern in name]
+        assert len(counts) == 1 and counts[0] <= budget, (pattern, counts)

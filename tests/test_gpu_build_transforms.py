@@ -155,10 +155,10 @@ def test_build_transforms_16_matches_oracle(P, G, name):
     assert O.fp_model_objective(t64[b], Wp, Xp) == pytest.approx(s.sum() ** 2 / 16, rel=1e-8)
 
 
-@pytest.mark.parametrize("rows", [(33, 128), (129, 127), (128, 1025), (257, 33)])
+@pytest.mark.parametrize("rows", [(33, 128), (129, 127), (128, 1025), (257, 33), (512, 500), (512, 513)])
 def test_row_splits_without_rows_are_not_read(P, G, rows):
     """Row counts around the splits of 128 rows, a workspace full of NaN: partial moments of splits that hold no rows stay
-    unwritten and must not be read (the bar of the parity test above)."""
+    unwritten and must not be read (the bar of the parity test above); four splits and five, on either side of the kernel for few."""
     import torch
     cfg = I.scaled(I.CONFIGS["c1"], K=96, N=rows[0], calib_tokens=rows[1], n_outlier=2)
     L = I.make_layer(cfg)
