@@ -178,7 +178,8 @@ __global__ __launch_bounds__(kWaves * 64) void w4_skinny_kernel(
 // The K split for at most 16 tokens, on v_mfma_f32_16x16x32_f16: a row block's upper half would be padding, half of the activations' loads
 // and conversions and half of every MFMA.  A lane is (row l16 of 16, quarter l4): quarters 0, 1 hold the two halves of the row's first K step
 // of a pair, 2 and 3 those of the second, 16 bytes each as above; MFMA d of the pair takes dword d of all four.  A weight block is two operands
-// of 16 output channels.  Behind the last K step of an odd number the activations' scale is zero.  Replayed graphs, four sets of operands, us,
+// of 16 output channels.  Behind the last K step of an odd number the activations' scales are zero, and for INT4 the weights' too: theirs may be
+// infinite there.  Replayed graphs, four sets of operands, us,
 // 32 x 32 | this: NVFP4 16 x 8192 -> 28672 36.6 | 31.3 (132 MB of weights: 4.2 TB/s), 8192 -> 57344 65.9 | 59.3, 14336 -> 4096 15.6 | 12.0, 1 x 4096 ->
 // 6144 7.0 | 6.0, canonical 16 x 8192 -> 28672 58.5 | 49.0; INT4 40.6 | 32.8, 73.2 | 60.4, 20.0 | 15.2, 8.4 | 6.7, canonical 1 x 8192 -> 28672
 // 52.6 | 44.5.
@@ -236,15 +237,17 @@ __global__ __launch_bounds__(kWaves * 64) void w4_skinny16_kernel(
 #pragma unroll
       for (int u = 0; u < U; ++u)
         if (kp + u < kp1) {
-          if (2 * (kp + u) + (l4 >> 1) >= KT) ch.x[u].s = 0;
+          const bool past = 2 * (kp + u) + (l4 >> 1) >= KT;
+          if (FMT == kNvfp4 && past) ch.x[u].s = 0;
+          const uint32_t from = FMT == kInt4 && past ? 0x0C0C0C0Cu : sel;   // zero bytes
           v8h fx[4];
-          dequant_step<FMT>(ch.x[u], h, sel, fx);
+          dequant_step<FMT>(ch.x[u], h, from, fx);
 #pragma unroll
           for (int c = 0; c < CBW; ++c)
 #pragma unroll
             for (int a = 0; a < 2; ++a) {
               v8h fw[4];
-              dequant_step<FMT>(ch.w[c][a][u], h, sel, fw);
+              dequant_step<FMT>(ch.w[c][a][u], h, from, fw);
 #pragma unroll
               for (int d = 0; d < 4; ++d) acc[c][a] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fw[d], fx[d], acc[c][a], 0, 0, 0);
             }

@@ -97,3 +97,26 @@ def test_wide_canonical_layers(P, M, K, N, streams):
     for out in (y, tiles):
         assert O.rel_fro(out.double().numpy()[:, cols], ref) <= 1e-6
     assert torch.equal(y, tiles) != streams        # the kernels add K in different orders
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("M", [1, 16, 17])
+@pytest.mark.parametrize("K", [64, 128, 192, 1088])
+def test_int4_infinite_scale_in_the_last_step(P, layout, M, K):
+    """An output of positive codes, one group of whose weights has an infinite scale, is infinite: what stands in for the missing step of
+    an odd number has to be zero in both operands.  The other outputs are exact (code 1 in every place: K)."""
+    import torch
+    N = 40
+    X, W = (np.full((n, K // 2), 0x11, dtype=np.uint8) for n in (M, N))
+    xs, ws = (O.bf16_values_to_bits(np.ones((n, K // 32))) for n in (M, N))
+    ws[5, -1] = 0x7F80
+    xs, ws = (np.ascontiguousarray(s).view(np.uint8).reshape(-1, K // 16) for s in (xs, ws))
+    if layout:
+        args = (*_tiled(P, X, xs, M, K, "int4"), *_tiled(P, W, ws, N, K, "int4"))
+    else:
+        args = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (X, xs, W, ws)]
+    Y = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    P.wush_linear_int4(*args, Y, layout, 1, K=K)
+    ref = torch.full((M, N), float(K))
+    ref[:, 5] = float("inf")
+    assert torch.equal(Y.cpu(), ref)
