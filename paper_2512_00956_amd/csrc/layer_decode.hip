@@ -135,7 +135,7 @@ template <int RB, int R, bool OUT_F32>
 __device__ __forceinline__ void gemm_skinny_ring(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const uint8_t* __restrict__ Wq,
     const uint8_t* __restrict__ Ws, int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
-  __shared__ float red[kWaves][RB][16][64];
+  __shared__ v4f red[kWaves][RB][4][64];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int KT = K >> 8, NB = (N + 31) >> 5, j = blockIdx.x + gridDim.x * blockIdx.z;
@@ -304,7 +304,7 @@ __global__ __launch_bounds__(kWaves * 64) void layer_decode_kernel(
     const uint8_t* __restrict__ Ws, uint8_t* __restrict__ Xq, uint8_t* __restrict__ Xs, uint32_t* __restrict__ state,
     int M, int N, int K, void* __restrict__ Y, int64_t ldy, int rule, uint32_t expected_blocks,
     uint32_t spin_limit) {
-  __shared__ float red[kWaves][RB][16][64];
+  __shared__ v4f red[kWaves][RB][4][64];
   __shared__ int barrier_ok;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

@@ -67,7 +67,7 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_canon_stream_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const uint8_t* __restrict__ Wq,
     const uint8_t* __restrict__ Ws, int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
   constexpr int U = 4;                        // tiles in flight
-  __shared__ float red[kWaves][1][16][64];
+  __shared__ v4f red[kWaves][1][4][64];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int C = K >> 5, j = blockIdx.x, rb = blockIdx.y;

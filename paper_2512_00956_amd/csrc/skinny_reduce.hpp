@@ -48,7 +48,7 @@ __device__ __forceinline__ void store_quad(void* __restrict__ Y, int64_t ldy, in
 // SCALED (the product of the tensor scales of a format that has them), and store.  Accumulator e of lane (r, kh), row block rb is token 32*rb + r, output
 // channel 32*j + 8*(e/4) + 4*kh + e%4; wave w finishes the quads e/4 == w.
 template <int RB, bool OUT_F32, bool SCALED = false>
-__device__ __forceinline__ void reduce_store_block(const v16f (&acc)[RB], float (*red)[RB][16][64], int j, int M, int N,
+__device__ __forceinline__ void reduce_store_block(const v16f (&acc)[RB], v4f (*red)[RB][4][64], int j, int M, int N,
                                                    void* __restrict__ Y, int64_t ldy, int lane, int wave,
                                                    float scale = 1.0f) {
   const int r = lane & 31, kh = lane >> 5;
@@ -56,17 +56,14 @@ __device__ __forceinline__ void reduce_store_block(const v16f (&acc)[RB], float 
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) red[wave][rb][e][lane] = acc[rb][e];
+    for (int q = 0; q < 4; ++q) red[wave][rb][q][lane] = (v4f){acc[rb][4 * q], acc[rb][4 * q + 1], acc[rb][4 * q + 2], acc[rb][4 * q + 3]};
   __syncthreads();
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
+    const v4f sum = ((red[0][rb][wave][lane] + red[1][rb][wave][lane]) + red[2][rb][wave][lane]) + red[3][rb][wave][lane];
     float v[4];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int e = 4 * wave + t;
-      v[t] = ((red[0][rb][e][lane] + red[1][rb][e][lane]) + red[2][rb][e][lane]) + red[3][rb][e][lane];
-      if (SCALED) v[t] *= scale;
-    }
+    for (int t = 0; t < 4; ++t) v[t] = SCALED ? sum[t] * scale : sum[t];
     const int row = 32 * rb + r;
     const int col = 32 * j + 8 * wave + 4 * kh;
     if (row < M && (whole || col < N)) store_quad<OUT_F32>(Y, ldy, row, col, N, whole, v);

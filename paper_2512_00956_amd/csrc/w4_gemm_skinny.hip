@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kWaves * 64) void w4_skinny_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const float* __restrict__ tsx,
     const uint8_t* __restrict__ Wq, const uint8_t* __restrict__ Ws, const float* __restrict__ tsw,
     int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
-  __shared__ float red[kWaves][RB][16][64];
+  __shared__ v4f red[kWaves][RB][4][64];
   constexpr int U = Depth<RB, TILED>::U;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
