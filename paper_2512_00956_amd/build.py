@@ -39,21 +39,27 @@ def hipcc_path() -> str:
 
 
 def check_generated_code(hipcc: str, bdir: str) -> None:
-    """The MXFP4 GEMMs issue their main-loop loads from inline asm; what that relies on in the
-    generated code (build_checks.py) is verified on every build, with the flags of the build."""
-    from .build_checks import check_gemm_canon_asm, check_gemm_frag_asm, check_lds_load_asm
-    for name, checks in (("mxfp4_gemm_frag", (check_gemm_frag_asm, check_lds_load_asm)),
-                         ("mxfp4_gemm_canon", (check_gemm_canon_asm, check_lds_load_asm))):
-        asm = os.path.join(bdir, name + ".s")
-        cmd = [hipcc, *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-S", "--cuda-device-only",
-               os.path.join(CSRC, name + ".hip"), "-o", asm]
-        r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-        if r.returncode != 0:
-            raise RuntimeError(f"hipcc -S failed on {name}.hip:\n{r.stdout}")
+    """What the kernels rely on in the generated code (build_checks.py) is verified on every build, with the flags of the build: the
+    wait states behind matrix instructions in all of them, and what the MXFP4 GEMMs that issue their main-loop loads from inline asm need."""
+    from .build_checks import check_gemm_canon_asm, check_gemm_frag_asm, check_lds_load_asm, check_mfma_result_waits
+    more = {"mxfp4_gemm_frag.hip": (check_gemm_frag_asm, check_lds_load_asm),
+            "mxfp4_gemm_canon.hip": (check_gemm_canon_asm, check_lds_load_asm)}
+    procs = []
+    for src in SOURCES:
+        asm = os.path.join(bdir, src.replace(".hip", ".s"))
+        cmd = [hipcc, *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-S", "--cuda-device-only", os.path.join(CSRC, src), "-o", asm]
+        procs.append((src, asm, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    texts = {}
+    for src, asm, p in procs:                       # all of them end before a check may raise
+        out, _ = p.communicate()
+        if p.returncode != 0:
+            raise RuntimeError(f"hipcc -S failed on {src}:\n{out}")
         with open(asm) as f:
-            text = f.read()
-        for check in checks:
-            check(text)                    # raises InvariantError
+            texts[src] = f.read()
+        os.remove(asm)
+    for src, text in texts.items():
+        for check in (check_mfma_result_waits, *more.get(src, ())):
+            check(text)                             # raises InvariantError
 
 
 def build_call_module() -> str | None:

@@ -19,6 +19,11 @@ ring is filled behind the compiler's back.  It is only correct while every LDS r
 between the step's barrier and the next, with the explicit count of outstanding loads in front of
 the barrier; it is only fast while nothing spills and nothing but the documented wait for the
 scale loads drains the ring.
+
+All kernels with matrix instructions: nothing interlocks their results against a read by another kind of instruction, so the
+compiler counts wait states and adds s_nop.  It walks back from the read over every path, but each block only once: where a loop around the read is so
+short that the walk reaches the instruction's block that way first, the direct path is not looked at any more, and the read
+follows the product at once (seen in a kernel whose product ended a branch before a store to LDS, inside a loop over blocks of outputs: old values).
 """
 from __future__ import annotations
 
@@ -152,3 +157,71 @@ def check_gemm_canon_asm(text: str, expected_kernels: int = 20) -> None:
                 if "vmcnt(0)" in b and "s_barrier" not in b and "ds_write_b128" not in b and "global_load_ubyte" not in b \
                         and re.search(r"ds_read|global_load_lds", b):
                     raise InvariantError(f"{where}: a full drain of the ring")
+
+
+# wait states between a matrix instruction and another kind's read of its result, by its shape: passes of four cycles + 4 (FP64: + 2)
+_RESULT_WAIT = {"4x4x": 6, "16x16x128_f8f6f4": 8, "16x16x32_": 8, "32x32x64_f8f6f4": 12, "32x32x16_": 12, "f64_16x16x4": 18}
+_TAKEN = 4            # what a taken branch costs at least
+
+
+def _operand_regs(text: str) -> set:
+    m = re.match(r"-?\|?([va])(?:\[(\d+):(\d+)\]|(\d+))", text)
+    if not m:
+        return set()
+    lo, hi = (m.group(2), m.group(3)) if m.group(2) else (m.group(4), m.group(4))
+    return {(m.group(1), r) for r in range(int(lo), int(hi) + 1)}
+
+
+def _instructions(body: str):
+    """[(mnemonic, operands, text)] of a kernel and {label: index of the instruction behind it}."""
+    ins, labels = [], {}
+    for line in body.split("\n"):
+        s = line.split(";")[0].strip()
+        label = re.match(r"([\w.$]+):$", s)
+        if label:
+            labels[label.group(1)] = len(ins)
+        elif re.match(r"[a-z]", s):
+            op, _, rest = s.partition(" ")
+            ins.append((op, [x.strip() for x in re.split(r",\s*(?![^\[]*\])", rest)] if rest else [], s))
+    return ins, labels
+
+
+def check_mfma_result_waits(text: str) -> int:
+    """Every path from a matrix instruction to the first other instruction that reads its result has the wait states it needs.  Returns the number
+    of matrix instructions followed."""
+    parts, followed = re.split(r"^(_Z\S+):.*$", text, flags=re.M), 0
+    for name, body in zip(parts[1::2], parts[2::2]):
+        ins, labels = _instructions(body.split(".Lfunc_end")[0])
+        for at, (op, args, line) in enumerate(ins):
+            if not op.startswith("v_mfma"):
+                continue
+            need = next((n for shape, n in _RESULT_WAIT.items() if shape in op), None)
+            if need is None:
+                raise InvariantError(f"{name}: no wait states known for {op}")
+            result, seen, paths = _operand_regs(args[0]), {}, [(at + 1, 0)]
+            while paths:
+                k, waited = paths.pop()
+                while k < len(ins) and waited < need and seen.get(k, need) > waited:
+                    seen[k] = waited
+                    o, a, s = ins[k]
+                    if o == "s_endpgm":
+                        break
+                    if o.startswith("v_mfma"):            # interlocked; a later one's result has waits of its own
+                        if _operand_regs(a[0]) & result:
+                            break
+                    elif not o.startswith("s_"):
+                        stores = o.startswith(("ds_write", "global_store", "buffer_store", "flat_store", "scratch_store"))
+                        if any(_operand_regs(x) & result for x in (a if stores else a[1:])):
+                            raise InvariantError(f"{name}: {s!r} {waited} wait states behind {line!r}, {need} needed")
+                    if o == "s_nop":
+                        waited += int(a[0], 0) + 1
+                    elif o == "s_branch":
+                        k, waited = labels.get(a[0], len(ins)), waited + _TAKEN
+                        continue
+                    else:
+                        if o.startswith("s_cbranch") and a[0] in labels:
+                            paths.append((labels[a[0]], waited + _TAKEN))
+                        waited += 1
+                    k += 1
+            followed += 1
+    return followed

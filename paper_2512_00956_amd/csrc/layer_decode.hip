@@ -121,16 +121,18 @@ __device__ __forceinline__ void accumulate_block(v16f (&acc)[RB], FragTile (&w)[
   }
 }
 
-// The GEMM: workgroup (j, y) takes output channels 32 j ... + 31 of row blocks RB y ... + RB - 1 of the tokens.  A wavefront has RING K tiles in flight
-// at any time, each slot refilled as soon as it has been multiplied; in chunks, all of whose loads were awaited before the first product (four
-// tiles, two for more row blocks), nothing covered the gap between a chunk's last product and the next one's data, with a compute unit's
-// one workgroup least of all.  Replayed graphs, four sets of operands, us, chunks | ring: 64 x 14336 -> 4096 10.0 | 9.1, 100 x 14336 -> 4096 12.3 | 11.5,
-// 32 x 8192 -> 8192 9.2 | 8.1, 256 x 4096 -> 4096 8.9 | 7.9, 1024 x 4096 -> 1024 9.7 | 8.5, 448 x 28672 -> 512 14.3 | 14.4; several workgroups per
-// unit 32 x 8192 -> 57344 51.0 | 48.6, 24 x 4096 -> 28672 14.1 | 13.1, 32 x 512 -> 57344 8.8 | 6.2, 48 x 4096 -> 12288 9.7 | 8.2, 100 x 28672 -> 9000
-// 71.4 | 71.4.  Tiles in flight: one row block four, two up to K = 2048, where a wavefront's range is no longer than that (24 x 4096 -> 28672
-// 13.1 | 13.6, 20 x 2048 -> 20480 6.7 | 6.4, 448 x 28672 -> 512 with six 14.7); two row blocks two, one up to 4096 (64 x 28672 -> 10240 52.9 | 53.8, 48 x
-// 4096 -> 12288 8.9 | 8.2); four row blocks one (1024 x 4096 -> 1024 with two 8.9).  More registers for deeper rings cost resident workgroups, and
-// one alone is bound by what a compute unit gets out of the L2 and beyond, some 80 GB/s.
+// The GEMM: workgroup (j, y) takes output channels 32 j ... + 31 of row blocks RB y ... + RB - 1 of the tokens.  A wavefront has R K tiles in flight
+// at any time, each slot refilled as soon as it has been multiplied (skinny::ring); in chunks, all of whose loads were awaited before the first product
+// (four tiles, two for more row blocks), nothing covered the gap between a chunk's last product and the next one's data, with a compute unit's
+// one workgroup least of all.  Replayed graphs, four sets of operands, us, chunks | ring: 64 x 14336 -> 4096 10.1 | 8.3, 100 x 14336 -> 4096 12.2 | 10.7,
+// 32 x 8192 -> 8192 9.1 | 7.5, 256 x 4096 -> 4096 8.8 | 7.7, 1024 x 4096 -> 1024 9.4 | 8.2, 448 x 28672 -> 512 13.8 | 12.9; several workgroups per
+// unit 32 x 8192 -> 57344 50.0 | 48.2, 24 x 4096 -> 28672 13.5 | 12.4, 32 x 512 -> 57344 8.9 | 6.0, 48 x 4096 -> 12288 9.5 | 8.1, 100 x 28672 -> 9000
+// 70.8 | 71.0.  Tiles in flight: one row block four, two up to K = 2048, where a wavefront's range is no longer than that (geomeans of four against two
+// there: 1.01 to 1.02 with one workgroup per unit, 1.03 to 1.25 with several); two row blocks two, one up to K = 1024, or 4096 where there are several
+// workgroups per unit (two against one: K = 1024 to 4096 0.95 with one workgroup per unit, 1.02 with several); four row blocks two, held to 256
+// registers (against one: 0.95 with one workgroup per unit, 0.95 to 1.02 with several; left to itself the compiler takes 268, and with one workgroup
+// per unit instead of two it is 1.1 to 1.4).  More registers for deeper rings cost resident workgroups, and one alone is bound by
+// what a compute unit gets out of the L2 and beyond, some 80 GB/s.
 template <int RB, int R, bool OUT_F32>
 __device__ __forceinline__ void gemm_skinny_ring(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const uint8_t* __restrict__ Wq,
@@ -159,45 +161,31 @@ __device__ __forceinline__ void gemm_skinny_ring(
     for (int rb = 0; rb < RB; ++rb) load_frag_tile(x[u][rb], Xq, Xs, (int64_t)rb * KT + t, lane);
   };
   auto multiply = [&](int u) {
-#define WUSH_RING_ISSUE(KK)                                                                                            {                                                                                                                      const v8i A_ = {w[u].f[KK][0], w[u].f[KK][1], w[u].f[KK][2], w[u].f[KK][3], 0, 0, 0, 0};                             _Pragma("unroll") for (int rb = 0; rb < RB; ++rb) {                                                                    const v8i B_ = {x[u][rb].f[KK][0], x[u][rb].f[KK][1], x[u][rb].f[KK][2], x[u][rb].f[KK][3], 0, 0, 0, 0};             acc[rb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A_, B_, acc[rb], 4, 4, KK, w[u].s, KK, x[u][rb].s);      }                                                                                                                  }
+#define WUSH_RING_ISSUE(KK)                                                                                          \
+  {                                                                                                                  \
+    const v8i A_ = {w[u].f[KK][0], w[u].f[KK][1], w[u].f[KK][2], w[u].f[KK][3], 0, 0, 0, 0};                         \
+    _Pragma("unroll") for (int rb = 0; rb < RB; ++rb) {                                                              \
+      const v8i B_ = {x[u][rb].f[KK][0], x[u][rb].f[KK][1], x[u][rb].f[KK][2], x[u][rb].f[KK][3], 0, 0, 0, 0};       \
+      acc[rb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A_, B_, acc[rb], 4, 4, KK, w[u].s, KK, x[u][rb].s);  \
+    }                                                                                                                \
+  }
     WUSH_RING_ISSUE(0)
     WUSH_RING_ISSUE(1)
     WUSH_RING_ISSUE(2)
     WUSH_RING_ISSUE(3)
 #undef WUSH_RING_ISSUE
   };
-#pragma unroll
-  for (int u = 0; u < R; ++u)
-    if (kt + u < kt1) load(u, kt + u);
-  __builtin_amdgcn_sched_barrier(0);
-  // no branch around a refill in this loop: the compiler's wait counts stay exact
-  for (; kt + 2 * R <= kt1; kt += R) {
-#pragma unroll
-    for (int u = 0; u < R; ++u) {
-      multiply(u);
-      load(u, kt + R + u);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < R; ++u)
-    if (kt + u < kt1) {
-      multiply(u);
-      if (kt + R + u < kt1) load(u, kt + R + u);
-    }
-#pragma unroll
-  for (int u = 0; u < R; ++u)
-    if (kt + R + u < kt1) multiply(u);
+  skinny::ring<R>(kt, kt1, load, multiply);
   reduce_store_block<RB, OUT_F32>(acc, red, j, M, N, Y, ldy, lane, wave);
 }
 
 template <int RB, bool OUT_F32>
-__global__ __launch_bounds__(kWaves * 64, 1) void gemm_skinny_kernel(
+__global__ __launch_bounds__(kWaves * 64, RB == 4 ? 2 : 1) void gemm_skinny_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const uint8_t* __restrict__ Wq,
     const uint8_t* __restrict__ Ws, int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
-  gemm_skinny_ring<RB, RB == 1 ? 4 : RB == 2 ? 2 : 1, OUT_F32>(Xq, Xs, Wq, Ws, M, N, K, Y, ldy);
+  gemm_skinny_ring<RB, RB == 1 ? 4 : 2, OUT_F32>(Xq, Xs, Wq, Ws, M, N, K, Y, ldy);
 }
-template <int RB, bool OUT_F32>   // short K
+template <int RB, bool OUT_F32>   // short K, by the lines above
 __global__ __launch_bounds__(kWaves * 64, 1) void gemm_skinny_short_kernel(
     const uint8_t* __restrict__ Xq, const uint8_t* __restrict__ Xs, const uint8_t* __restrict__ Wq,
     const uint8_t* __restrict__ Ws, int M, int N, int K, void* __restrict__ Y, int64_t ldy) {
@@ -208,10 +196,10 @@ __global__ __launch_bounds__(kWaves * 64, 1) void gemm_skinny_short_kernel(
 // Lane quarter q of instruction p takes group kk = 2 p + q / 2 of K half kh = q % 2, for both operands: the fragments as they lie, and with
 // the scale dword shifted by q / 2 bytes its scale is byte 2 p in every lane.  HALVES = 16-channel halves of a block of 32 output channels
 // a workgroup takes: both, or one where the blocks are so few that halves still find idle compute units.  A ring of R K tiles per wavefront as above:
-// two, one up to K = 2048 (us, R = 1 | 2 | 4: 16 x 256 -> 57344 3.9 | 4.5 | 6.6, 8 x 2048 -> 20480 5.6 | 5.9 | 6.4, 16 x 8192 -> 57344
-// 47.7 | 45.7 | 45.5, 9 x 28672 -> 4096 13.0 | 11.8 | 12.1, 9 x 28672 -> 1024 11.9 | 8.9 | 8.4).  Replayed graphs, four sets of operands, us,
-// 32 x 32 fragments in chunks | this: 16 x 8192 -> 57344 49.6 | 45.3 (250 MB of weights: 5.5 TB/s), 16 x 4096 -> 28672 13.5 | 11.1, 16 x 28672 ->
-// 8192 26.6 | 23.0, 1 x 14336 -> 4096 9.6 | 7.5, 1 x 4096 -> 6144 5.3 | 4.4, 9 x 28672 -> 1024 12.6 | 8.9.
+// two, one up to K = 2048 (geomeans, two against one: up to K = 512 1.01, 1024 1.03 with several workgroups per unit, 2048 0.98 to 1.00; four
+// against two: 4096 and more 0.99, halves beyond 8192 0.95, less than that 1.02 to 1.09).  Replayed graphs, four sets of operands, us,
+// 32 x 32 fragments in chunks | this: 16 x 8192 -> 57344 48.9 | 44.4 (250 MB of weights: 5.6 TB/s), 16 x 4096 -> 28672 13.4 | 11.6, 16 x 28672 ->
+// 8192 26.5 | 22.4, 1 x 14336 -> 4096 9.6 | 7.0, 1 x 4096 -> 6144 5.3 | 4.3, 9 x 28672 -> 1024 12.6 | 7.8, 16 x 256 -> 57344 7.3 | 3.2.
 struct HalfTile {   // 16 rows of one (row block, K tile)
   v4i f[2];
   int s;
@@ -234,67 +222,45 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_skinny16_kernel(
     t.f[1] = *reinterpret_cast<const v4i*>(p + 2048);
     t.s = *reinterpret_cast<const int*>(sp + rb_kt * 256 + scale + 64 * a);
   };
-  for (int j = blockIdx.x; j < NB; j += gridDim.x) {
-    const int64_t block = HALVES == 2 ? j : j >> 1;
-    const int first = HALVES == 2 ? 0 : j & 1;
-    v4f acc[HALVES];
+  const int j = blockIdx.x + gridDim.x * blockIdx.z;
+  if (j >= NB) return;                        // the grid's padding
+  const int64_t block = HALVES == 2 ? j : j >> 1;
+  const int first = HALVES == 2 ? 0 : j & 1;
+  v4f acc[HALVES];
 #pragma unroll
-    for (int a = 0; a < HALVES; ++a) acc[a] = (v4f){0, 0, 0, 0};
-    HalfTile w[R][HALVES], x[R];
-    auto load = [&](int u, int kt) {
+  for (int a = 0; a < HALVES; ++a) acc[a] = (v4f){0, 0, 0, 0};
+  HalfTile w[R][HALVES], x[R];
+  auto load = [&](int u, int kt) {
 #pragma unroll
-      for (int a = 0; a < HALVES; ++a) load_half(w[u][a], Wq, Ws, block * KT + kt, first + a);
-      load_half(x[u], Xq, Xs, kt, 0);
-    };
-    auto multiply = [&](int u) {
-      const int sx = x[u].s >> (8 * (q >> 1));
+    for (int a = 0; a < HALVES; ++a) load_half(w[u][a], Wq, Ws, block * KT + kt, first + a);
+    load_half(x[u], Xq, Xs, kt, 0);
+  };
+  auto multiply = [&](int u) {
+    const int sx = x[u].s >> (8 * (q >> 1));
 #pragma unroll
-      for (int a = 0; a < HALVES; ++a) {
-        const int sw = w[u][a].s >> (8 * (q >> 1));
+    for (int a = 0; a < HALVES; ++a) {
+      const int sw = w[u][a].s >> (8 * (q >> 1));
 #define WUSH_HALF_ISSUE(P)                                                                                                    \
-  {                                                                                                                           \
-    const v8i A_ = {w[u][a].f[P][0], w[u][a].f[P][1], w[u][a].f[P][2], w[u][a].f[P][3], 0, 0, 0, 0};                          \
-    const v8i B_ = {x[u].f[P][0], x[u].f[P][1], x[u].f[P][2], x[u].f[P][3], 0, 0, 0, 0};                                      \
-    acc[a] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A_, B_, acc[a], 4, 4, 2 * P, sw, 2 * P, sx);                    \
+  {                                                                                                                         \
+    const v8i A_ = {w[u][a].f[P][0], w[u][a].f[P][1], w[u][a].f[P][2], w[u][a].f[P][3], 0, 0, 0, 0};                        \
+    const v8i B_ = {x[u].f[P][0], x[u].f[P][1], x[u].f[P][2], x[u].f[P][3], 0, 0, 0, 0};                                    \
+    acc[a] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A_, B_, acc[a], 4, 4, 2 * P, sw, 2 * P, sx);                  \
   }
-        WUSH_HALF_ISSUE(0)
-        WUSH_HALF_ISSUE(1)
+      WUSH_HALF_ISSUE(0)
+      WUSH_HALF_ISSUE(1)
 #undef WUSH_HALF_ISSUE
-      }
-    };
-    int kt = kt0;
-#pragma unroll
-    for (int u = 0; u < R; ++u)
-      if (kt + u < kt1) load(u, kt + u);
-    __builtin_amdgcn_sched_barrier(0);
-    for (; kt + 2 * R <= kt1; kt += R) {
-#pragma unroll
-      for (int u = 0; u < R; ++u) {
-        multiply(u);
-        load(u, kt + R + u);
-        __builtin_amdgcn_sched_barrier(0);
-      }
     }
+  };
+  skinny::ring<R>(kt0, kt1, load, multiply);
+  // the waves' sums in their order; accumulator v of lane (l16, q) is token l16, output channel 4 q + v of the half
 #pragma unroll
-    for (int u = 0; u < R; ++u)
-      if (kt + u < kt1) {
-        multiply(u);
-        if (kt + R + u < kt1) load(u, kt + R + u);
-      }
-#pragma unroll
-    for (int u = 0; u < R; ++u)
-      if (kt + R + u < kt1) multiply(u);
-    // the waves' sums in their order; accumulator v of lane (l16, q) is token l16, output channel 4 q + v of the half
-#pragma unroll
-    for (int a = 0; a < HALVES; ++a) red[wave][a][lane] = acc[a];
-    __syncthreads();
-    if (wave < HALVES) {
-      const v4f sum = ((red[0][wave][lane] + red[1][wave][lane]) + red[2][wave][lane]) + red[3][wave][lane];
-      const int col = HALVES == 2 ? 32 * j + 16 * wave + 4 * q : 16 * j + 4 * q;
-      const float v[4] = {sum[0], sum[1], sum[2], sum[3]};
-      if (l16 < M && col < N) skinny::store_quad<OUT_F32>(Y, ldy, l16, col, N, col + 4 <= N, v);
-    }
-    __syncthreads();   // red is rewritten by the next block
+  for (int a = 0; a < HALVES; ++a) red[wave][a][lane] = acc[a];
+  __syncthreads();
+  if (wave < HALVES) {
+    const v4f sum = ((red[0][wave][lane] + red[1][wave][lane]) + red[2][wave][lane]) + red[3][wave][lane];
+    const int col = HALVES == 2 ? 32 * j + 16 * wave + 4 * q : 16 * j + 4 * q;
+    const float v[4] = {sum[0], sum[1], sum[2], sum[3]};
+    if (l16 < M && col < N) skinny::store_quad<OUT_F32>(Y, ldy, l16, col, N, col + 4 <= N, v);
   }
 }
 
@@ -443,34 +409,31 @@ int skinny_row_blocks(int64_t M, int64_t N) {
 // L2 (us, tiles | as many workgroups as blocks | this: 512 x 1024 -> 1984 4.89 | 5.86 | 4.76, 384 x 1536 -> 1984 5.59 | 6.27 | 5.48).
 int64_t skinny_grid_width(int64_t N) { return ((N + 31) / 32 + 7) & ~(int64_t)7; }
 
-constexpr int64_t kMostWide = 1 << 20;   // workgroups along x; 2^30 output channels are 2^25 blocks, 256 threads each
-
 hipError_t launch_mxfp4_gemm_skinny(const void* Xq, const void* Xs, const void* Wq, const void* Ws, int64_t M,
                                     int64_t N, int64_t K, int out_f32, void* Y, int64_t ldy, hipStream_t stream) {
   const int NB = (int)((N + 31) / 32);
   if (M <= 16) {
     const int cus = device_cu_count();
     const bool halves = 2 * NB <= cus;
-    const int blocks = halves ? (int)((N + 15) / 16) : NB;
+    const int64_t blocks = halves ? (N + 15) / 16 : NB;
     const bool shallow = K <= 2048;   // a wavefront's range is one or two tiles
     auto kernel = halves ? (out_f32 ? (shallow ? gemm_skinny16_kernel<1, 1, true> : gemm_skinny16_kernel<1, 2, true>)
                                     : (shallow ? gemm_skinny16_kernel<1, 1, false> : gemm_skinny16_kernel<1, 2, false>))
                          : (out_f32 ? (shallow ? gemm_skinny16_kernel<2, 1, true> : gemm_skinny16_kernel<2, 2, true>)
                                     : (shallow ? gemm_skinny16_kernel<2, 1, false> : gemm_skinny16_kernel<2, 2, false>));
-    kernel<<<dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(kWaves * 64), 0, stream>>>(
+    kernel<<<skinny::wide_grid(blocks, 1), dim3(kWaves * 64), 0, stream>>>(
         (const uint8_t*)Xq, (const uint8_t*)Xs, (const uint8_t*)Wq, (const uint8_t*)Ws, (int)M, (int)N, (int)K, Y, ldy);
     return hipGetLastError();
   }
   const int rb = skinny_row_blocks(M, N), groups = (int)((M + 32 * rb - 1) / (32 * rb));
   const int64_t wide = rb == 4 && groups > 1 ? skinny_grid_width(N) : NB;
-  dim3 grid((unsigned)(wide < kMostWide ? wide : kMostWide), (unsigned)groups, (unsigned)((wide + kMostWide - 1) / kMostWide)), block(kWaves * 64);
 #define WUSH_SKINNY(KERNEL, RB) (out_f32 ? KERNEL<RB, true> : KERNEL<RB, false>)
   auto kernel = rb == 1 ? (K <= 2048 ? WUSH_SKINNY(gemm_skinny_short_kernel, 1) : WUSH_SKINNY(gemm_skinny_kernel, 1))
-              : rb == 2 ? (K <= 4096 ? WUSH_SKINNY(gemm_skinny_short_kernel, 2) : WUSH_SKINNY(gemm_skinny_kernel, 2))
+              : rb == 2 ? (K <= 1024 || (K <= 4096 && (int64_t)groups * NB > device_cu_count()) ? WUSH_SKINNY(gemm_skinny_short_kernel, 2) : WUSH_SKINNY(gemm_skinny_kernel, 2))
                         : WUSH_SKINNY(gemm_skinny_kernel, 4);
 #undef WUSH_SKINNY
-  kernel<<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs, (const uint8_t*)Wq, (const uint8_t*)Ws, (int)M, (int)N,
-                                     (int)K, Y, ldy);
+  kernel<<<skinny::wide_grid(wide, groups), dim3(kWaves * 64), 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs, (const uint8_t*)Wq,
+                                                                            (const uint8_t*)Ws, (int)M, (int)N, (int)K, Y, ldy);
   return hipGetLastError();
 }
 

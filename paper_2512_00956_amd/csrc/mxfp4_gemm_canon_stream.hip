@@ -100,9 +100,10 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_canon_stream_kernel(
 // At most 16 tokens, on v_mfma_scale_f32_16x16x128_f8f6f4: no padding to 32 rows.  Quarter q of the lanes has 32 of the 128 bytes of its row's
 // line, 16 for each of a tile's two instructions, so an instruction of either operand touches 16 lines and the tile uses them whole; the scales of
 // its two groups are bytes 0 and 1 of the row's dword shifted by the quarter.  HALVES and R as in the tiled layout's kernel: 16-channel halves of a
-// block of 32 output channels a workgroup takes, K tiles a wavefront keeps in flight (both halves, two | three tiles: 1 x 28672 -> 8192 40.4 | 28.1,
-// 1 x 8192 -> 8192 10.1 | 8.7, 1 x 2080 -> 20000 7.0 | 8.4; one half 1 x 14336 -> 4096 8.4 | 8.5).  Replayed graphs, four sets of operands, us, 32 rows |
-// this: 1 x 14336 -> 4096 15.0 | 8.4, 16 tokens 16.4 | 11.7; 1 x 24160 -> 1409 22.8 | 10.7; 16 x 16384 -> 1024 18.1 | 12.8; 1 x 4096 -> 4096 5.8 | 4.2.
+// block of 32 output channels a workgroup takes, K tiles a wavefront keeps in flight (three where both halves are taken from K = 4096 on; two in place
+// of them within 1 %, four 0 to 2 % slower).  Replayed graphs, four sets of operands, us, 32 rows | this:
+// 1 x 14336 -> 4096 15.1 | 7.9, 16 tokens 16.5 | 11.7; 1 x 24160 -> 1409 22.9 | 9.1; 16 x 16384 -> 1024 17.9 | 12.5; 1 x 4096 -> 4096 6.0 | 3.8;
+// tiles | this: 1 x 28672 -> 8192 36.4 | 27.3, 1 x 8192 -> 8192 10.1 | 8.7, 1 x 2080 -> 20000 8.5 | 6.8.
 struct HalfTile {   // (16 rows, 256 of K)
   v4i f[2];
   int s;
@@ -119,91 +120,72 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_canon_stream16_kernel(
   int kt0, kt1;
   skinny::wave_k_range(C >> 3, wave, kt0, kt1);
   const int64_t x_at = (int64_t)min(l16, M - 1) * C;
-  for (int j = blockIdx.x; j < NB; j += gridDim.x) {
-    int64_t w_at[HALVES];
+  const int j = blockIdx.x + gridDim.x * blockIdx.z;
+  if (j >= NB) return;                        // the grid's padding
+  int64_t w_at[HALVES];
 #pragma unroll
-    for (int a = 0; a < HALVES; ++a) w_at[a] = (int64_t)min(16 * (HALVES * j + a) + l16, N - 1) * C;
-    v4f acc[HALVES];
+  for (int a = 0; a < HALVES; ++a) w_at[a] = (int64_t)min(16 * (HALVES * j + a) + l16, N - 1) * C;
+  v4f acc[HALVES];
 #pragma unroll
-    for (int a = 0; a < HALVES; ++a) acc[a] = (v4f){0, 0, 0, 0};
-    HalfTile w[R][HALVES], x[R];
-    auto load_half = [&](HalfTile& t, const uint8_t* qp, const uint8_t* sp, int64_t at, int kt) {
-      const v4i* p = reinterpret_cast<const v4i*>(qp + 16 * (at + 8 * kt + 2 * q));
-      t.f[0] = p[0];
-      t.f[1] = p[1];
-      t.s = *reinterpret_cast<const i32_any*>(sp + at + 8 * kt + 4 * (q >> 1)) >> (16 * (q & 1));
-    };
-    // the partial last tile of a row: groups past the row's end are zeros
-    auto load_last = [&](HalfTile& t, const uint8_t* qp, const uint8_t* sp, int64_t at) {
-      t.s = 0x7F7F;
+  for (int a = 0; a < HALVES; ++a) acc[a] = (v4f){0, 0, 0, 0};
+  HalfTile w[R][HALVES], x[R];
+  auto load_half = [&](HalfTile& t, const uint8_t* qp, const uint8_t* sp, int64_t at, int kt) {
+    const v4i* p = reinterpret_cast<const v4i*>(qp + 16 * (at + 8 * kt + 2 * q));
+    t.f[0] = p[0];
+    t.f[1] = p[1];
+    t.s = *reinterpret_cast<const i32_any*>(sp + at + 8 * kt + 4 * (q >> 1));   // shifted when it is multiplied: here it would be waited for
+  };
+  // the partial last tile of a row: groups past the row's end are zeros
+  auto load_last = [&](HalfTile& t, const uint8_t* qp, const uint8_t* sp, int64_t at) {
+    int two = 0x7F7F;
 #pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        const int g = (C & ~7) + 2 * q + p;
-        t.f[p] = (v4i){0, 0, 0, 0};
-        if (g < C) {
-          t.f[p] = *reinterpret_cast<const v4i*>(qp + 16 * (at + g));
-          t.s = (t.s & ~(0xFF << (8 * p))) | (int)sp[at + g] << (8 * p);
-        }
+    for (int p = 0; p < 2; ++p) {
+      const int g = (C & ~7) + 2 * q + p;
+      t.f[p] = (v4i){0, 0, 0, 0};
+      if (g < C) {
+        t.f[p] = *reinterpret_cast<const v4i*>(qp + 16 * (at + g));
+        two = (two & ~(0xFF << (8 * p))) | (int)sp[at + g] << (8 * p);
       }
-    };
-    auto load = [&](int u, int kt) {
+    }
+    t.s = two << (16 * (q & 1));
+  };
+  auto load = [&](int u, int kt) {
 #pragma unroll
-      for (int a = 0; a < HALVES; ++a) load_half(w[u][a], Wq, Ws, w_at[a], kt);
-      load_half(x[u], Xq, Xs, x_at, kt);
-    };
-    auto multiply = [&](int u) {
+    for (int a = 0; a < HALVES; ++a) load_half(w[u][a], Wq, Ws, w_at[a], kt);
+    load_half(x[u], Xq, Xs, x_at, kt);
+  };
+  auto multiply = [&](int u) {
+    const int sx = x[u].s >> (16 * (q & 1));
 #pragma unroll
-      for (int a = 0; a < HALVES; ++a) {
+    for (int a = 0; a < HALVES; ++a) {
+      const int sw = w[u][a].s >> (16 * (q & 1));
 #define WUSH_HALF_ISSUE(P)                                                                                                    \
-  {                                                                                                                           \
-    const v8i A_ = {w[u][a].f[P][0], w[u][a].f[P][1], w[u][a].f[P][2], w[u][a].f[P][3], 0, 0, 0, 0};                          \
-    const v8i B_ = {x[u].f[P][0], x[u].f[P][1], x[u].f[P][2], x[u].f[P][3], 0, 0, 0, 0};                                      \
-    acc[a] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A_, B_, acc[a], 4, 4, P, w[u][a].s, P, x[u].s);                 \
+  {                                                                                                                         \
+    const v8i A_ = {w[u][a].f[P][0], w[u][a].f[P][1], w[u][a].f[P][2], w[u][a].f[P][3], 0, 0, 0, 0};                        \
+    const v8i B_ = {x[u].f[P][0], x[u].f[P][1], x[u].f[P][2], x[u].f[P][3], 0, 0, 0, 0};                                    \
+    acc[a] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A_, B_, acc[a], 4, 4, P, sw, P, sx);                          \
   }
-        WUSH_HALF_ISSUE(0)
-        WUSH_HALF_ISSUE(1)
+      WUSH_HALF_ISSUE(0)
+      WUSH_HALF_ISSUE(1)
 #undef WUSH_HALF_ISSUE
-      }
-    };
-    int kt = kt0;
-#pragma unroll
-    for (int u = 0; u < R; ++u)
-      if (kt + u < kt1) load(u, kt + u);
-    __builtin_amdgcn_sched_barrier(0);
-    for (; kt + 2 * R <= kt1; kt += R) {
-#pragma unroll
-      for (int u = 0; u < R; ++u) {
-        multiply(u);
-        load(u, kt + R + u);
-        __builtin_amdgcn_sched_barrier(0);
-      }
     }
+  };
+  skinny::ring<R>(kt0, kt1, load, multiply);
+  if ((C & 7) && wave == kWaves - 1) {      // the wavefront with the fewest whole tiles
 #pragma unroll
-    for (int u = 0; u < R; ++u)
-      if (kt + u < kt1) {
-        multiply(u);
-        if (kt + R + u < kt1) load(u, kt + R + u);
-      }
+    for (int a = 0; a < HALVES; ++a) load_last(w[0][a], Wq, Ws, w_at[a]);
+    load_last(x[0], Xq, Xs, x_at);
+    multiply(0);
+  }
+  // the waves' sums in their order; accumulator v of lane (l16, q) is token l16, output channel 4 q + v of the half
 #pragma unroll
-    for (int u = 0; u < R; ++u)
-      if (kt + R + u < kt1) multiply(u);
-    if ((C & 7) && wave == kWaves - 1) {      // the wavefront with the fewest whole tiles
-#pragma unroll
-      for (int a = 0; a < HALVES; ++a) load_last(w[0][a], Wq, Ws, w_at[a]);
-      load_last(x[0], Xq, Xs, x_at);
-      multiply(0);
-    }
-    // the waves' sums in their order; accumulator v of lane (l16, q) is token l16, output channel 4 q + v of the half
-#pragma unroll
-    for (int a = 0; a < HALVES; ++a) red[wave][a][lane] = acc[a];
-    __syncthreads();
-    if (wave < HALVES) {
-      const v4f sum = ((red[0][wave][lane] + red[1][wave][lane]) + red[2][wave][lane]) + red[3][wave][lane];
-      const int col = 16 * (HALVES * j + wave) + 4 * q;
-      const float v[4] = {sum[0], sum[1], sum[2], sum[3]};
-      if (l16 < M && col < N) skinny::store_quad<OUT_F32>(Y, ldy, l16, col, N, col + 4 <= N, v);
-    }
-    __syncthreads();   // red is rewritten by the next block
+  for (int a = 0; a < HALVES; ++a) red[wave][a][lane] = acc[a];
+  __syncthreads();
+  if (wave < HALVES) {
+    const v4f sum = ((red[0][wave][lane] + red[1][wave][lane]) + red[2][wave][lane]) + red[3][wave][lane];
+    const int col = 16 * (HALVES * j + wave) + 4 * q;
+    const float v[4] = {sum[0], sum[1], sum[2], sum[3]};
+    if (l16 < M && col < N) skinny::store_quad<OUT_F32>(Y, ldy, l16, col, N, col + 4 <= N, v);
   }
 }
 
@@ -235,7 +217,7 @@ hipError_t launch_mxfp4_gemm_canon_stream(const void* Xq, const void* Xs, const 
     auto kernel = halves ? (ring == 1 ? WUSH_CANON16(1, 1) : WUSH_CANON16(1, 2))
                          : (ring == 1 ? WUSH_CANON16(2, 1) : ring == 2 ? WUSH_CANON16(2, 2) : WUSH_CANON16(2, 3));
 #undef WUSH_CANON16
-    kernel<<<dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(kWaves * 64), 0, stream>>>(
+    kernel<<<skinny::wide_grid(blocks, 1), dim3(kWaves * 64), 0, stream>>>(
         (const uint8_t*)Xq, (const uint8_t*)Xs, (const uint8_t*)Wq, (const uint8_t*)Ws, (int)M, (int)N, (int)K, Y, ldy);
     return hipGetLastError();
   }

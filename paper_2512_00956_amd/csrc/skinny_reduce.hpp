@@ -78,5 +78,39 @@ __device__ __forceinline__ void wave_k_range(int KT, int wave, int& kt0, int& kt
   kt1 = min(kt0 + q, KT);
 }
 
+// A grid with `blocks` workgroups of 256 threads side by side and `groups` rows of them: 2^30 output channels are 2^25 blocks, which go on along z.
+inline dim3 wide_grid(int64_t blocks, int groups) {
+  constexpr int64_t kMost = 1 << 20;   // along x
+  return dim3((unsigned)(blocks < kMost ? blocks : kMost), (unsigned)groups, (unsigned)((blocks + kMost - 1) / kMost));
+}
+
+// K tiles [kt, kt1) of a wavefront through a ring of R: load(u, t) requests tile t into slot u, multiply(u) multiplies slot u, which is then
+// refilled at once.  The compiler's count of the loads in flight has to stay exact, or it waits for loads it has no need of.  Where the tiles are
+// no multiple of R the first slots start out empty: a branch around a product does not touch the count, one around a refill at the
+// end does, and so does a first load that may be missing (MXFP4, us, first loads and refills under branches | this:
+// 48 x 27136 -> 379 13.0 | 11.1, 62 x 7168 -> 704 5.6 | 4.6, 18 x 26880 -> 128 11.4 | 9.9, 9 x 28672 -> 1024 9.0 | 7.8; 300 layers of K from 4096 on
+// and up to 1024 channels, 17 to 256 tokens: geomean 0.89).
+// With one slot there is nothing to count, and a way around all of it would have the accumulators cleared ahead of the first load.
+template <int R, class Load, class Multiply>
+__device__ __forceinline__ void ring(int kt, int kt1, const Load& load, const Multiply& multiply) {
+  if (R > 1 && kt >= kt1) return;
+  int t = kt1 - max((kt1 - kt + R - 1) / R, 1) * R;   // tile of slot 0
+#pragma unroll
+  for (int u = 0; u < R; ++u)
+    if ((R > 1 && u == R - 1) || t + u >= kt) load(u, t + u);
+  __builtin_amdgcn_sched_barrier(0);
+  for (; t + R < kt1; t += R) {
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+      if (u == R - 1 || t + u >= kt) multiply(u);
+      load(u, t + R + u);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < R; ++u)
+    if ((R > 1 && u == R - 1) || t + u >= kt) multiply(u);
+}
+
 }  // namespace skinny
 }  // namespace wush

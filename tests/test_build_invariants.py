@@ -204,9 +204,20 @@ def test_quantizers_do_not_spill_and_keep_three_waves_per_simd(src, pattern, cou
             assert int(m.group(2)) <= budget, (m.group(1), m.group(2))
 
 
-@pytest.mark.parametrize("src,pattern,count", [("layer_decode.hip", "gemm_skinny_kernel", 6),
-                                                ("mxfp4_gemm_canon_stream.hip", "gemm_canon_stream_kernel", 2),
-                                                ("w4_gemm_skinny.hip", "w4_(?:skinny|shared_x)_kernel", 40)])
+@pytest.mark.parametrize("src", ["layer_decode.hip", "mxfp4_gemm_canon_stream.hip"])
+def test_results_of_matrix_instructions_are_waited_for(src):
+    """The build's check of every kernel, here on streaming ones, whose products end a branch before a store to LDS; a planted fault (no
+    s_nop) is caught."""
+    from paper_2512_00956_amd.build_checks import InvariantError, check_mfma_result_waits
+    text = _compile(src)
+    assert check_mfma_result_waits(text) >= text.count("v_mfma_") > 0
+    with pytest.raises(InvariantError):
+        check_mfma_result_waits(re.sub(r"s_nop \d+\n", "", text))
+
+
+@pytest.mark.parametrize("src,pattern,count", [("layer_decode.hip", "gemm_skinny(?:16|_short)?_kernel", 18),
+                                                ("mxfp4_gemm_canon_stream.hip", "gemm_canon_stream(?:16)?_kernel", 12),
+                                                ("w4_gemm_skinny.hip", "w4_(?:skinny|skinny16|shared_x)_kernel", 72)])
 def test_streaming_kernels_store_four_outputs_at_a_time(src, pattern, count):
     """The streaming GEMMs write a lane's four outputs in one store at any alignment of the rows: every site of it comes with
     the three element stores of a row's last channels and no others (rows off the alignment stored element by
@@ -227,3 +238,18 @@ def test_block_kernels_of_wide_layers_share_their_compute_unit():
     for pattern, budget in (("17wush_block_kernelILi4E", 168), ("19wush_block16_kernelILi4E", 96)):
         counts = [int(c) for name, c in re.findall(r"\.name:\s+(\S+)\n(?:.*\n)*?\s+\.vgpr_count:\s+(\d+)", text) if pattern in name]
         assert len(counts) == 1 and counts[0] <= budget, (pattern, counts)
+
+
+@pytest.mark.parametrize("src,pattern,count", [("layer_decode.hip", r"gemm_skinny_kernelILi\d", 6), ("layer_decode.hip", r"gemm_skinny16_kernelILi\dELi2E", 4),
+                                                ("mxfp4_gemm_canon_stream.hip", r"gemm_canon_stream16_kernelILi\dELi[23]E", 6)])
+def test_rings_of_tiles_are_never_drained(src, pattern, count):
+    """The streaming GEMMs that keep several K tiles in flight: no wait in the K loop for all of them (a first load under a branch, or a scale
+    shifted where it is loaded, makes the compiler put one there), and nothing spills."""
+    parts = re.split(rf"^(_ZN4wush\S*{pattern}\S*):.*$", _compile(src), flags=re.M)
+    kernels = {parts[i]: parts[i + 1].split(".Lfunc_end")[0] for i in range(1, len(parts) - 1, 2)}
+    assert len(kernels) == count, list(kernels)
+    for name, body in kernels.items():
+        assert "scratch_" not in body, f"{name}: spills to scratch"
+        loop = _loop_of(body)
+        assert "v_mfma_scale" in loop and "global_load" in loop, name
+        assert "vmcnt(0)" not in loop, name

@@ -120,3 +120,31 @@ def test_int4_infinite_scale_in_the_last_step(P, layout, M, K):
     ref = torch.full((M, N), float(K))
     ref[:, 5] = float("inf")
     assert torch.equal(Y.cpu(), ref)
+
+
+@pytest.mark.parametrize("layout,M", [(0, 1), (1, 3), (1, 20), (1, 40)])
+def test_more_blocks_than_a_grid_is_wide(P, layout, M):
+    """2^20 blocks of 32 channels and three more, the last one partial: the grid goes on along z.  The channels on either side of the line and the
+    last ones against a call of those alone, bit for bit."""
+    import torch
+    K, N, C = 256, (1 << 25) + 77, 8
+    g = torch.Generator(device="cuda").manual_seed(M)
+    rows = N + -N % 32
+    X, W = (torch.randint(0, 256, (r, K // 2), dtype=torch.uint8, device="cuda", generator=g) for r in (M + -M % 32, rows))
+    xs, ws = (torch.randint(110, 140, (r, C), dtype=torch.uint8, device="cuda", generator=g) for r in (M + -M % 32, rows))
+    fmt = P.default_fmt(out_dtype=0, layout=layout)          # random bytes are an operand in either layout; a block of 32 rows is contiguous
+
+    def call(first, n):
+        Y = torch.full((M, n + 3), 7.0, dtype=torch.bfloat16, device="cuda")
+        last = first + n + -n % 32
+        w = W[first:last] if layout else W[first:first + n]
+        s = ws[first:last] if layout else ws[first:first + n]
+        x, t = (X, xs) if layout else (X[:M], xs[:M])
+        P.wush_linear(x, t, w, s, Y[:, :n], fmt, K=K)
+        assert (Y[:, n:] == 7.0).all()
+        return Y[:, :n]
+    Y = call(0, N)
+    for first in (0, (1 << 25) - 64):
+        part = Y[:, first:first + 141]
+        assert torch.equal(part, call(first, 141)[:, :part.shape[1]])
+    assert torch.isfinite(Y).all()
