@@ -129,22 +129,26 @@ def test_more_blocks_than_a_grid_is_wide(P, layout, M):
     import torch
     K, N, C = 256, (1 << 25) + 77, 8
     g = torch.Generator(device="cuda").manual_seed(M)
-    rows = N + -N % 32
-    X, W = (torch.randint(0, 256, (r, K // 2), dtype=torch.uint8, device="cuda", generator=g) for r in (M + -M % 32, rows))
-    xs, ws = (torch.randint(110, 140, (r, C), dtype=torch.uint8, device="cuda", generator=g) for r in (M + -M % 32, rows))
+    rows, tokens = N + -N % 256, M + -M % 256                # as many as a tiled operand has
+    X, W = (torch.randint(0, 256, (r, K // 2), dtype=torch.uint8, device="cuda", generator=g) for r in (tokens, rows))
+    xs, ws = (torch.randint(110, 140, (r, C), dtype=torch.uint8, device="cuda", generator=g) for r in (tokens, rows))
     fmt = P.default_fmt(out_dtype=0, layout=layout)          # random bytes are an operand in either layout; a block of 32 rows is contiguous
 
     def call(first, n):
         Y = torch.full((M, n + 3), 7.0, dtype=torch.bfloat16, device="cuda")
-        last = first + n + -n % 32
+        last = first + n + -n % 256
         w = W[first:last] if layout else W[first:first + n]
         s = ws[first:last] if layout else ws[first:first + n]
         x, t = (X, xs) if layout else (X[:M], xs[:M])
         P.wush_linear(x, t, w, s, Y[:, :n], fmt, K=K)
         assert (Y[:, n:] == 7.0).all()
         return Y[:, :n]
-    Y = call(0, N)
-    for first in (0, (1 << 25) - 64):
-        part = Y[:, first:first + 141]
-        assert torch.equal(part, call(first, 141)[:, :part.shape[1]])
+    P.wush_debug_set(P.WUSH_DEBUG_GEMM_SKINNY, 1)            # 40 tokens of so many channels take the tiles by themselves
+    try:
+        Y = call(0, N)
+        for first in (0, (1 << 25) - 64):
+            part = Y[:, first:first + 141]
+            assert torch.equal(part, call(first, 141)[:, :part.shape[1]])
+    finally:
+        P.wush_debug_set(P.WUSH_DEBUG_GEMM_SKINNY, -1)
     assert torch.isfinite(Y).all()
