@@ -276,3 +276,25 @@ def test_gptq_block_that_turns_by_many_angles_at_once(P, G, tangent):
     T, c, s = _run_gpu(P, G, W, Xc, 0.0)
     Tr, cr, sr = Q.gptq_wush_layer(W, Xc, 0.0)
     _compare(T, c, s, Tr, cr, sr, W, Xc, f"tangent {tangent}")
+
+
+@pytest.mark.parametrize("spread", [60, 120])
+def test_gptq_given_transform_whose_inverse_needs_elimination(P, G, spread):
+    """inv(T) comes from the factor of T T^T and Newton steps from X near it.  With rows of T that are 2^0 to 2^-spread of one size, T X - I is 2^spread
+    times rounding in some entries, too far for the steps, and T is inverted by elimination.  H = I exactly and lambda = 0, so the
+    group scales are those of W inv(T): FP64 throughout, and no AbsMax within 1e-4 of a power of two."""
+    import torch
+    N, K = 1024, 32
+    rng = np.random.default_rng(3)
+    W = O.round_to_bf16(rng.standard_normal((N, K)))
+    T = O.round_to_bf16(rng.standard_normal((K, K)) + 4.0 * np.eye(K)) * np.exp2(-np.round(np.linspace(0, spread, K)))[:, None]
+    amax = np.abs(np.linalg.solve(T.T, W.T)).max(axis=0)
+    assert np.abs(T @ np.linalg.inv(T) - np.eye(K)).max() > 1.0            # whichever way it is computed
+    assert np.abs(amax / np.exp2(np.round(np.log2(amax))) - 1.0).min() > 1e-4
+    Xc = O.hadamard(K) * np.sqrt(K)
+    Wd, Xd, Td = (G.bf16_dev(O.bf16_values_to_bits(np.ascontiguousarray(O.round_to_bf16(a)))) for a in (W, Xc, T[None]))
+    q, s = G.empty_u8(N, K // 2), G.empty_u8(N, K // 32)
+    ws = torch.full((P.wush_prepare_weight_gptq_workspace(N, K),), 255, dtype=torch.uint8, device="cuda")     # NaN, should nothing be written
+    P.wush_prepare_weight_gptq(Wd, Xd, 0.0, Td, q, s, ws, P.default_fmt(), transform_given=True)
+    P.wush_prepare_weight_gptq_status(ws, N, K)
+    assert np.array_equal(G.host(s)[:, 0], O.scale_bytes(amax, "nosat"))

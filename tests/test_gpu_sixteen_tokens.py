@@ -81,12 +81,13 @@ def test_sixteen_tokens(P, fmt, layout, M, K, N):
     assert torch.equal(_outputs(call, M, N, 0), y.bfloat16())
 
 
-# canonical MXFP4 layers of more blocks of 32 channels than the 256 compute units, on either side of the lines
-@pytest.mark.parametrize("M,K,N,streams", [(4, 2560, 16416, True), (4, 2816, 16416, False), (4, 2816, 16384, True), (5, 2560, 8224, False),
-                                           (16, 12288, 8224, True), (16, 12032, 8224, False), (1, 12288, 16416, False)])
-def test_wide_canonical_layers(P, M, K, N, streams):
+# canonical MXFP4 layers of more blocks of 32 channels than compute units, on either side of the lines: (tokens, K, blocks a compute unit, channels
+# past them, streams)
+@pytest.mark.parametrize("M,K,rounds,more,streams", [(4, 2560, 2, 32, True), (4, 2816, 2, 32, False), (4, 2816, 2, 0, True), (5, 2560, 1, 32, False),
+                                                     (16, 12288, 1, 32, True), (16, 12032, 1, 32, False), (1, 12288, 2, 32, False)])
+def test_wide_canonical_layers(P, M, K, rounds, more, streams):
     import torch
-    assert torch.cuda.get_device_properties(0).multi_processor_count == 256
+    N = 32 * torch.cuda.get_device_properties(0).multi_processor_count * rounds + more
     call, ref, cols = _operands(P, "mxfp4", 0, M, K, N)
     y = _outputs(call, M, N, 1)
     P.wush_debug_set(P.WUSH_DEBUG_GEMM_SKINNY, 0)
@@ -96,7 +97,8 @@ def test_wide_canonical_layers(P, M, K, N, streams):
         P.wush_debug_set(P.WUSH_DEBUG_GEMM_SKINNY, -1)
     for out in (y, tiles):
         assert O.rel_fro(out.double().numpy()[:, cols], ref) <= 1e-6
-    assert torch.equal(y, tiles) != streams        # the kernels add K in different orders
+    # the kernels add K in different orders: of the 30000 outputs and more some differ in their last bits, and none where both are the tiles
+    assert torch.equal(y, tiles) != streams
 
 
 @pytest.mark.parametrize("layout", [0, 1])
@@ -151,4 +153,42 @@ def test_more_blocks_than_a_grid_is_wide(P, layout, M):
             assert torch.equal(part, call(first, 141)[:, :part.shape[1]])
     finally:
         P.wush_debug_set(P.WUSH_DEBUG_GEMM_SKINNY, -1)
+    assert torch.isfinite(Y).all()
+
+
+@pytest.mark.parametrize("schedule", [2, 3, 4, 6])
+@pytest.mark.parametrize("fmt", ["nvfp4", "int4"])
+@pytest.mark.parametrize("layout,M", [(0, 1), (1, 3), (1, 16), (0, 17), (1, 40), (1, 70)])
+def test_w4_more_blocks_than_workgroups(P, fmt, layout, M, schedule):
+    """The streaming kernels of these formats launch 4096 workgroups side by side at most, each of which goes on to further blocks: one weight block
+    at a time (schedule 3), two (4, 6) or, shared activations, four (2).  The channels on either side of the lines and the last ones against a
+    call of those alone, bit for bit."""
+    import torch
+    K, N = 64, 4096 * 4 * 32 + 101
+    g = torch.Generator(device="cuda").manual_seed(M)
+
+    def operand(rows):
+        q, s = (torch.randint(lo, hi, (rows + -rows % 32, n), dtype=torch.uint8, device="cuda", generator=g) for lo, hi, n in ((0, 256, K // 2), (30, 100, K // 16)))
+        if fmt == "int4":
+            s = (torch.rand((s.shape[0], K // 32), device="cuda", generator=g) + 0.5).bfloat16().view(torch.uint8)
+        return q, s
+    x, w = operand(M), operand(N)                            # random bytes are an operand in either layout; a block of 32 rows is contiguous
+    ts = [torch.tensor([v], dtype=torch.float32, device="cuda") for v in (0.5, 0.25)]
+
+    def call(first, n):
+        Y = torch.full((M, n + 3), 7.0, dtype=torch.bfloat16, device="cuda")
+        wq, ws = (t[first:first + n + -n % 32] for t in w)
+        if fmt == "nvfp4":
+            P.wush_linear_nvfp4(*x, ts[0], wq, ws, ts[1], Y[:, :n], layout, 0, K=K)
+        else:
+            P.wush_linear_int4(*x, wq, ws, Y[:, :n], layout, 0, K=K)
+        assert (Y[:, n:] == 7.0).all()
+        return Y[:, :n]
+    P.wush_debug_set(P.WUSH_DEBUG_W4_SKINNY, schedule)
+    try:
+        Y = call(0, N)
+        for first in (0, 4096 * 32 - 64, 4096 * 64 - 64, 4096 * 128 - 64):
+            assert torch.equal(Y[:, first:first + 165], call(first, min(165, N - first))), first
+    finally:
+        P.wush_debug_set(P.WUSH_DEBUG_W4_SKINNY, -1)
     assert torch.isfinite(Y).all()

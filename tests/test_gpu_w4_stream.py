@@ -23,9 +23,11 @@ def P():
 
 
 # (tokens, K, output channels, layout, the default streams; None: K too short to tell by the bits)
+# At most 16 tokens take 16-row kernels of one token block, whatever blocks of tokens are forced: two of them need 17.
 SIZES = [(129, 1088, 70, 1, True), (160, 64, 512, 1, None), (300, 512, 130, 1, True), (321, 256, 4100, 1, True),
          (1, 64, 1, 0, None), (1, 1088, 70, 0, True), (31, 512, 2048, 0, True), (33, 192, 8200, 0, None), (100, 256, 130, 0, True),
          (16, 512, 8224, 0, True), (48, 512, 4128, 0, True), (33, 512, 8200, 0, True), (300, 512, 1030, 0, True),
+         (17, 64, 1, 0, None), (17, 64, 1, 1, None), (17, 1088, 70, 0, True), (20, 512, 8224, 0, True), (17, 8128, 70, 1, True),
          (130, 1024, 300, 0, True), (1, 8128, 70, 1, True), (33, 8192, 70, 1, True), (70, 8256, 33, 1, True), (2048, 256, 8192, 1, False), (2048, 256, 8192, 0, False)]
 
 
