@@ -450,11 +450,13 @@ __global__ __launch_bounds__(kWaves * 64, 2) void w4_shared_x_kernel(
 // units, and with many two weight blocks share the conversion (us, NVFP4 | INT4, a workgroup with all tokens and one weight
 // block before: 100 x 14336 -> 4096 33.8 -> 23.4 | 46.0 -> 30.3; 64 x 14336 -> 4096 21.1 -> 17.0 | 28.1 -> 21.4; 100 x 2048 ->
 // 2048 8.5 -> 4.9 | 10.2 -> 5.5; 128 x 8192 -> 28672 81 -> 77 | 119 -> 93; 128 x 4096 -> 24576 34.6 -> 33.0 | 50.4 -> 39.0). Up
-// to 64 tokens two weight blocks pay from where the coarser grid takes no round more: 64 x 8192 -> 28672, 3.5 blocks per
-// compute unit, 49.3 -> 43.1 | 61.9 -> 51.2, 16 tokens INT4 44.1 -> 40.1, but 16 x 8192 -> 20480 (2.5 blocks) NVFP4 25.1
-// against 27.2.  NVFP4 between three and four blocks (replayed graphs, from HBM | weights in the last-level cache, one -> two
-// weight blocks): 16 x 8192 -> 28672 35.2 -> 33.7 | 28.8 -> 28.3, 16 x 8192 -> 25088 33.1 -> 31.4 | 27.9 -> 27.0, 32 x 4096 ->
-// 28672 21.4 -> 21.2 | 17.9 -> 17.4, 1 x 16384 -> 28672 64.6 -> 60.3 | 53.9 -> 51.5.
+// to 64 tokens two weight blocks pay from where the coarser grid takes no round more, one -> two (replayed graphs, four sets of operands): 64 x 8192 ->
+// 28672, 3.5 blocks per compute unit, 46.0 -> 41.3 | 54.8 -> 45.0, 32 x 4096 -> 28672 16.7 -> 15.4 | 19.7 -> 17.5.
+// Up to 16 tokens the line is the 32-row kernel's (NVFP4 16 x 8192 -> 28672 35.2 -> 33.7, INT4 44.1 -> 40.1); the 16-row kernel, which runs there,
+// has half the activations to convert and little to share: 16 x 8192 -> 28672 28.1 -> 28.3 | 32.6 -> 31.3, 25088 27.0 -> 26.6 | 30.4 -> 29.9,
+// 1 x 16384 -> 28672 51.5 -> 51.8 | 56.7 -> 56.2, and below the line, 16 x 8192 -> 20480, 21.0 -> 23.6 | 24.4 -> 28.8; but short K and many blocks
+// are faster with one weight block on this side of it too: 1 x 192 -> 28672 3.1 -> 3.6 | 3.2 -> 3.7, 16 x 8192 -> 57344 50.0 -> 54.1 |
+// 54.9 -> 58.3, 1 x 8192 -> 57344 46.2 -> 52.7 | 53.7 -> 57.4.
 void few_token_blocks(int64_t M, int64_t N, int& rb, int& cbw) {
   const int64_t NB = (N + 31) / 32;
   const int64_t cus = device_cu_count(), tokens = (M + 31) / 32;
@@ -487,11 +489,11 @@ hipError_t launch_split_k(const void* Xq, const void* Xs, const float* tsx, cons
   }
   if (M <= 16) {
     const int64_t per_wave = (K + 511) / 512;   // pairs of K steps
-    const bool single = tiled ? cbw == 2 || per_wave <= 4 : per_wave <= 2;
-#define WUSH_W4S16(CBW, U)                                                                                                  \
-  (out_f32 ? (tiled ? w4_skinny16_kernel<CBW, U, FMT, true, true> : w4_skinny16_kernel<CBW, U, FMT, true, false>)           \
-           : (tiled ? w4_skinny16_kernel<CBW, U, FMT, false, true> : w4_skinny16_kernel<CBW, U, FMT, false, false>))
-    auto kernel = cbw == 2 ? (single ? WUSH_W4S16(2, 1) : WUSH_W4S16(2, 2)) : (single ? WUSH_W4S16(1, 1) : WUSH_W4S16(1, 2));
+    const bool single = tiled ? per_wave <= 4 : per_wave <= 2;   // with two weight blocks of the tiled layout always
+#define WUSH_W4S16(CBW, U, TILED) (out_f32 ? w4_skinny16_kernel<CBW, U, FMT, true, TILED> : w4_skinny16_kernel<CBW, U, FMT, false, TILED>)
+    auto kernel = cbw == 2 ? (tiled ? WUSH_W4S16(2, 1, true) : single ? WUSH_W4S16(2, 1, false) : WUSH_W4S16(2, 2, false))
+                           : (tiled ? (single ? WUSH_W4S16(1, 1, true) : WUSH_W4S16(1, 2, true))
+                                    : (single ? WUSH_W4S16(1, 1, false) : WUSH_W4S16(1, 2, false)));
 #undef WUSH_W4S16
     kernel<<<grid, block, 0, stream>>>((const uint8_t*)Xq, (const uint8_t*)Xs, tsx, (const uint8_t*)Wq, (const uint8_t*)Ws, tsw,
                                        (int)M, (int)N, (int)K, Y, ldy);
@@ -564,9 +566,13 @@ constexpr StreamCost kStreamCost[2][2][5] = {
 // estimate, if that is below the estimate for the 256-row tiles (tile_us, which the caller has): those leave compute units idle until
 // tokens / 256 x channels / 128 reaches their number (us, tiles | streaming: NVFP4 224 x 16384 -> 1024 182 | 20, 320 x 14336 ->
 // 4096 160 | 54, 1024 x 4096 -> 4096 52 | 40, 2048 x 4096 -> 4096 61 | 71; canonical INT4 16 x 8192 -> 28672 134 | 60).
-// With every schedule forced on eleven layers from 704 -> 512 to 8192 -> 28672, 8 to 4096 tokens, the choice is within 7 % of the fastest; the
+// With every schedule forced on eleven layers from 704 -> 512 to 8192 -> 28672, 17 to 4096 tokens, the choice is within 7 % of the fastest; the
 // canonical INT4 costs, taken from NVFP4's, hold as well as those.  On 640 drawn layers of K from 64 on, 25 lose 8 % or more, 13 of them
 // with K <= 192, where a wave's K range is a step or none.
+// The costs are the 32-row kernel's also up to 16 tokens, where canonical operands take the 16-row one.  There the choice is the fastest or within 3 % of it
+// on most of 300 drawn layers (geomean 1.026), but estimates are too high for short K, where streaming is the faster throughout: 1 x 64 -> 10240
+// 5.0 (tiles) | 2.5, 4 x 192 -> 24576 7.5 | 3.0; beyond that the worst is the number of weight blocks, 12 x 1152 -> 39424 two 11.4, one 10.1,
+// 4 x 22912 -> 8844 one 57, two 52.
 W4StreamPlan w4_stream_plan(int fmt, int64_t M, int64_t N, int64_t K, int tiled, double tile_us) {
   const int forced = debug_option(kDbgW4Skinny);
   W4StreamPlan plan;
@@ -588,7 +594,8 @@ W4StreamPlan w4_stream_plan(int fmt, int64_t M, int64_t N, int64_t K, int tiled,
     const int rb = shared ? 4 : 1 + c / 2, cbw = shared ? 4 : 1 + c % 2;   // shared X: one weight block for each of four waves
     if ((forced == 1 && shared) || (forced == 2 && !shared)) continue;
     // a second row block needs more than 32 tokens; canonical rows: so few tokens that the lanes of an activation load share
-    // lines make the conversion cheap, and one weight block is the faster
+    // lines make the conversion cheap, and one weight block is the faster (16-row kernel, one | two: 1 x 8192 -> 28672 NVFP4 41.7 | 45.3, INT4 43.9 | 49.0,
+    // 4 x 4096 -> 4096 7.8 | 11.9, 8.7 | 13.2; 16 tokens 8192 -> 28672 52.0 | 48.2, 52.8 | 51.2)
     if (!shared && ((rb == 2 && M <= 32) || (cbw == 2 && !tiled && M <= 8))) continue;
     const double us = stream_us(cost[c], ((NB + cbw - 1) / cbw) * ((T + rb - 1) / rb), KT, cus);
     if (us >= best) continue;
