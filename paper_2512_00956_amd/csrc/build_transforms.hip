@@ -153,10 +153,9 @@ __global__ __launch_bounds__(128) void wush_block16_kernel(const double* __restr
                                           T_f64 ? T_f64 + (int64_t)b * 256 : nullptr, nullptr, status);
 }
 
-// Splits of the rows, for about four workgroups of each moment per compute unit.  Every split costs a partial moment of 8 KiB per
-// block, written and read back (both kernels together, us, 2048 / C | 1024 / C | 512 / C: c2 layer 168.6 | 164.6 | 163.4,
-// 8192 x 8192 -> 57344 626 | 616 | 640, 512 x 1024 -> 1024 146 | 132 | 126); partials of splits without rows are not read
-// (the last shape 132 -> 121).
+// Splits of the rows, for about four workgroups of each moment per compute unit.  Every split costs a partial moment of 4.1 KiB per
+// block, written and read back (both kernels together, us, 2048 / C | 1024 / C | 512 / C: c2 layer 107.3 | 104.6 | 102.9,
+// 8192 x 8192 -> 57344 495 | 502 | 539, 512 x 1024 -> 1024 70.2 | 70.2 | 70.1); partials of splits without rows are not read.
 int splits_for(int64_t C) {
   int64_t s = 1024 / C;
   if (s < 1) s = 1;

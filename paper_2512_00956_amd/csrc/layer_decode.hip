@@ -1,9 +1,10 @@
 // Decode-sized layer forward (at most 64 tokens) for gfx950:
 //   Y = sum_i Wq(i)^T q(T(i) X(i))      (layer forward-pass equation)
-// with the weights already transformed and quantized, in two forms:
-//   * gemm_skinny_kernel and its variants: the MXFP4 GEMM alone for few tokens, or few output channels (wush_linear);
-//   * layer_decode_kernel: activation transform + quantization + GEMM in ONE
-//     launch (wush_layer_decode).
+// with the weights already transformed and quantized:
+//   * gemm_skinny_kernel and its variants: the MXFP4 GEMM alone for few tokens, or few output channels (wush_linear, and
+//     wush_layer_decode behind the activation quantizer);
+//   * layer_decode_kernel: activation transform + quantization + GEMM in ONE launch, the slower form on this part: only where
+//     a test or measurement asks wush_layer_decode for it (kDbgDecodeFused).
 // At these sizes the layer is bound by streaming the weights once (K/2 + K/32
 // bytes per output channel); the activations are a few hundred KiB.
 //
@@ -393,9 +394,9 @@ hipError_t resident_limit(Kern kern, int* limit) {
 // Row blocks of 32 tokens a workgroup takes.  A workgroup reads all of its tokens' activations for every 32 output
 // channels, so beyond 32 tokens it is bound by that traffic into its compute unit: while the layer has too few blocks of
 // output channels for all of them, the tokens are dealt out as well, as finely as one workgroup per compute unit allows
-// (us, all tokens in one workgroup | two groups | one group per 32 tokens: 100 x 14336 -> 4096 16.4 | 12.8 | 15.2;
-// 64 x 14336 -> 4096 12.3 | - | 10.2; 128 x 4096 -> 4096 7.7 | 6.1 | 6.2; 100 x 8192 -> 1024 8.8 | 6.7 | 5.2; with more
-// groups than compute units the weights' second trip costs more than it saves: 128 x 28672 -> 8192 43.7 | 49.6 | 73.7).
+// (us, all tokens in one workgroup | two groups | one group per 32 tokens: 100 x 14336 -> 4096 14.9 | 10.2 | 12.7;
+// 64 x 14336 -> 4096 10.1 | - | 7.9; 128 x 4096 -> 4096 6.8 | 5.1 | 5.4; 100 x 8192 -> 1024 8.2 | 5.5 | 4.2; with more
+// groups than compute units the weights' second trip costs more than it saves: 128 x 28672 -> 8192 40.6 | 46.1 | 70.9).
 // Eight waves per workgroup instead of four (deeper split of K) gave nothing.
 int skinny_row_blocks(int64_t M, int64_t N) {
   const int64_t blocks = (N + 31) / 32, tokens = (M + 31) / 32, cus = device_cu_count();
@@ -406,7 +407,8 @@ int skinny_row_blocks(int64_t M, int64_t N) {
 
 // Workgroups side by side where they take four row blocks each: a multiple of 8, the last few finding no block.  Workgroups go round the 8
 // XCDs, so the row groups of a block of output channels, one grid row after the other, then run on one XCD and read its weights into one
-// L2 (us, tiles | as many workgroups as blocks | this: 512 x 1024 -> 1984 4.89 | 5.86 | 4.76, 384 x 1536 -> 1984 5.59 | 6.27 | 5.48).
+// L2 (us, tiles | as many workgroups as blocks | this: 512 x 1024 -> 1984 4.65 | 4.22 | 4.18, 384 x 1536 -> 1984 5.37 | 4.60 | 4.58; before the ring, with
+// less in flight, 4.89 | 5.86 | 4.76 and 5.59 | 6.27 | 5.48).
 int64_t skinny_grid_width(int64_t N) { return ((N + 31) / 32 + 7) & ~(int64_t)7; }
 
 hipError_t launch_mxfp4_gemm_skinny(const void* Xq, const void* Xs, const void* Wq, const void* Ws, int64_t M,

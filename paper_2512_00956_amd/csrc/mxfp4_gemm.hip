@@ -72,8 +72,12 @@ __global__ __launch_bounds__(256) void gemm_simple_kernel(
 // prologue and on turning the outputs in LDS, which one or two steps of K do not hide; what that costs depends on the outputs'
 // width, on their rows' alignment and, once they no longer fit the L2s, on their number.  Ratio of times, one wave per tile : the other kernel
 // (graph replays, 1 to 8192 tokens, 512 to 65536 channels), on either side of the lines:
-//   Against the streaming kernel: one token, K <= 128 0.91 to 1.03, two 0.95 to 1.01, K = 288 to 480 1.16 to 1.4; from four tokens 0.92 to 1.8
-//   (16 x 480 -> 8192 4.5 us : 3.2).
+//   Against the streaming kernel (its 16-row form up to 16 tokens): two tokens and fewer, K = 32 1.01 to 1.11, 64 0.95 to 1.08, 96 and 128 1.02 to 1.20,
+//   with 2.2 to 2.8 us in all; K = 160 to 224 1.10 to 1.30, 288 to 480 1.4 to 1.6; more tokens 1.0 to 1.9 (16 x 480 -> 8192 4.3 us : 2.6).  (Against the 32-row
+//   kernel, by which the line at two tokens was drawn: K <= 128 0.91 to 1.03.)
+//   More blocks of channels than compute units, up to 16 tokens, against the 16-row kernel: K <= 128 1.0 to 1.1 up to four blocks per unit,
+//   0.6 to 1.0 beyond; K = 160 to 224 1.05 to 1.2 up to four, 0.7 to 1.07 beyond; K = 288 to 480 1.1 to 1.5 (4 x 480 -> 16384 4.3 us : 3.0),
+//   where the lines below, drawn against the tiles, still take this kernel for rows at multiples of 16 bytes.
 //   Against the pipelined kernel ("aligned": rows at multiples of 16 bytes):
 //   * BF16, aligned: up to 16 tokens, K <= 128 0.78 to 0.99.  More: K = 32 and 64 0.82 to 1.19; 96 and 128 0.89 to 1.15, from 2^24 outputs on
 //     1.06 to 1.36 (2048 x 96 -> 8192 12.9 us : 10.1).  K = 160 to 224 0.85 to 1.62 (2048 x 192 -> 32768 54.7 : 43.7).
@@ -111,14 +115,17 @@ hipError_t launch_mxfp4_gemm(const void* Xq, const void* Xs, const void* Wq, con
     // Small batches: the streaming kernel (one workgroup per 32 output channels, the whole K) or
     // the tiled kernel with one row of 128-row tiles.  Up to 32 tokens the streaming kernel always
     // wins or ties.  Beyond, whichever the timing models below put first; they are fits to
-    // measurements on ten layer shapes (4096 x 4096 .. 8192 x 57344 and 28672 x 8192), in us:
+    // measurements on ten layer shapes (4096 x 4096 .. 8192 x 57344 and 28672 x 8192), of the streaming kernel before its
+    // ring, which took 4 to 30 % off, in us:
     //   streaming, by the row blocks of 32 tokens a workgroup takes (skinny_row_blocks):
     //     1: 0.6 K/1024 + 1.8, 2: 0.75 K/1024 + 2.3, and at least MiB of weights / 5.5 + 3
     //     4: rounds of (N/32 workgroups over the CUs) x (1.05 K/1024 + 2.5)
     //   tiled                    : max(4.3 + 0.3 x K/256 x rounds of (N/128 tiles over the CUs),
     //                                  MiB of weights / 6.4 + 4)
-    // (100 x 14336 -> 4096 12.8 against 22.3; 8192 x 57344, 64 tokens: 45.6 against 38.0; 128 tokens: 78.5 against 39.3;
-    //  4096 x 24576, 128 tokens: 21.8 against 11.3; 28672 x 8192, 128 tokens: 31.1 against 41.4).
+    // (with the ring, replayed graphs, four sets of operands, 100 x 14336 -> 4096 10.4 against 21.6; 64 x 8192 -> 57344 59.7 against 46.8; 128 tokens
+    //  83.9 against 47.8; 128 x 4096 -> 24576 16.8 against 11.7; 128 x 28672 -> 8192 41.3 against 69.6.  On 250 drawn layers of 33 to 128
+    //  tokens the choice is 1.2 % off the faster in the mean; 12 lose 5 % or more, of them long K with one to two blocks of channels per compute
+    //  unit, up to 64 tokens, 33 % (46 x 28672 -> 14569 54.7 streaming against 73.4) and K up to 768 with little more than one 10 to 17 %.)
     bool skinny = M <= 32;
     if (!skinny && M <= 128) {
       const double cus = (double)device_cu_count();
@@ -132,11 +139,11 @@ hipError_t launch_mxfp4_gemm(const void* Xq, const void* Xs, const void* Wq, con
       skinny = skinny_us < tiled_us;
     }
     // Up to 1024 tokens the streaming kernel also takes the layers of so few output channels that it needs no more than one workgroup
-    // per compute unit, where 128-row tiles leave most of them idle (us, tiles | streaming: 256 x 4096 -> 1024 8.7 | 5.0, 1024 x 4096 ->
-    // 1024 10.2 | 9.3, 256 x 16384 -> 1024 24.3 | 10.2, 448 x 28672 -> 512 40 | 16, 256 x 14336 -> 4096 22.6 | 18.8, 256 x 4096 -> 4096
-    // 8.9 | 7.8; with more workgroups 448 x 4096 -> 4096 10.1 | 12.2, 448 x 14336 -> 4096 23.4 | 29).  One or two row blocks per
+    // per compute unit, where 128-row tiles leave most of them idle (us, tiles | streaming: 256 x 4096 -> 1024 7.8 | 3.5, 1024 x 4096 ->
+    // 1024 8.5 | 7.0, 256 x 16384 -> 1024 22.0 | 7.7, 448 x 28672 -> 512 39 | 13, 256 x 14336 -> 4096 21.7 | 15.6, 256 x 4096 -> 4096
+    // 8.7 | 7.1; with more workgroups 448 x 4096 -> 4096 8.9 | 10.6, 448 x 14336 -> 4096 22.3 | 28.6).  One or two row blocks per
     // workgroup take 0.3 to 0.9 of the tiles' time at any K from 256 to 28672; four 0.75 to 1.02 from K = 512, but 0.9 to 1.09 with the
-    // one K tile of 256 (512 x 256 -> 1984 3.85 | 4.12), and 1.3 to 1.6 where the grid's spare workgroups start a second round.
+    // one K tile of 256 (512 x 256 -> 1984 3.85 | 4.12; with the ring 3.67 | 3.46), and 1.3 to 1.6 where the grid's spare workgroups start a second round.
     if (M > 128 && M <= 1024 && debug_option(kDbgGemmTile) < 0) {
       const int rb = skinny_row_blocks(M, N);
       const int64_t groups = (M + 32 * rb - 1) / (32 * rb), blocks = rb < 4 ? (N + 31) / 32 : skinny_grid_width(N);

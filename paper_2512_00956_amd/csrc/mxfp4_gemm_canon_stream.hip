@@ -191,17 +191,20 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_canon_stream16_kernel(
 
 }  // namespace
 
-// One workgroup per compute unit at the most (us, tiles | this kernel: 1376 -> 3000, 16 tokens 6.3 | 4.2; 4096 -> 4096, 48 tokens 8.6 |
-// 8.1; 14336 -> 4096, 1 token 26.8 | 14.5; 16384 -> 1024, 256 tokens 31 | 21.6; 28672 -> 512, 448 tokens 53 | 36; with more: 4096 ->
-// 4096, 100 tokens 8.8 | 12.4; 1024 -> 16384, 1 token 4.6 | 4.6; 8192 -> 28672, 1 token 22.4 | 30.6).
+// One workgroup per compute unit at the most (us, tiles | this kernel: 48 x 4096 -> 4096 9.2 | 7.5, 256 x 16384 -> 1024 29 | 20.8, 448 x 28672 -> 512
+// 52 | 34; with more: 100 x 4096 -> 4096 8.8 | 12.4; 16-row kernel 16 x 1376 -> 3000 4.6 | 2.6, 1 x 4096 -> 4096 9.0 | 3.9, 1 x 14336 -> 4096
+// 25.5 | 7.9).
 bool canon_streams(int64_t M, int64_t N) {
   return M <= 8192 && N <= 8192 && ((M + 31) / 32) * ((N + 31) / 32) <= device_cu_count();
 }
 
 // More blocks of output channels than compute units, at most 16 tokens: where the 16-row kernel is ahead of the tiles, which read a layer's
-// weights in larger pieces (us, tiles | 16 rows: 1 x 1024 -> 16384 4.4 | 4.0, 4 x 1024 -> 40000 7.0 | 6.8, 4 x 4096 -> 12288 9.8 | 9.2, 4 x 6144 -> 16384
-// 14.2 | 12.8, 1 x 14336 -> 16384 36.9 | 28.3, 16 tokens 38.8 | 34.8; but 1 x 4096 -> 20000 11.5 | 12.4, 4 x 8192 -> 28672 32.5 | 33.1, 8 x 2048
-// -> 20000 7.4 | 7.8, 16 x 8192 -> 12000 16.6 | 18.6).
+// weights in larger pieces (us, tiles | 16 rows: 1 x 1024 -> 16384 4.6 | 3.9, 4 x 4096 -> 12288 9.7 | 8.9, 4 x 6144 -> 16384 13.8 | 12.0, 1 x 14336 ->
+// 16384 36.7 | 26.4, 16 tokens 38.8 | 34.9; but 8 x 2048 -> 20000 7.3 | 7.8, 16 x 8192 -> 12000 16.6 | 18.2, 16 x 8192 -> 28672 32.8 | 36.9,
+// 16 x 4096 -> 57344 25.7 | 32.8, 1 x 28672 -> 57344 151 | 173).  The lines were drawn with an earlier ring, 5 to 30 % slower, and the 16-row kernel is now
+// ahead of the tiles on most layers beyond them too (1 x 8192 -> 28672 32.1 | 27.7, 8 x 832 -> 34416 8.4 | 5.3, 1 x 9088 -> 16789 33.8 | 24.3): on 629
+// drawn layers of K from 512 on these lines are 10 % off the faster kernel in the mean; 16 rows up to 8 tokens until 6 blocks per compute unit or
+// K = 12288, more tokens until 3 or K = 4096, would be 0.5 %.
 bool canon_streams16(int64_t M, int64_t N, int64_t K) {
   const bool few = (N + 31) / 32 <= 2 * device_cu_count();
   return M <= 16 && ((M <= 4 && (K <= 2560 || few)) || (K >= 12288 && few));
